@@ -205,6 +205,76 @@ int validate_reg_pass(int n, int dtype, const Compiled &c, size_t i) {
     return QSIM_OK;
 }
 
+// A span pass: the load vectors and the rest bits generate the index space,
+// the store vectors span the same tile, every layout is a bijection onto the
+// tile's LDS slots, and masks and coefficients lie inside their ranges.
+int validate_span_pass(int n, int dtype, const Compiled &c, size_t i) {
+    const PackedPlan &p = c.plan;
+    const qk::SpanArgs &sa = c.passes[i].sa;
+    const int t = sa.t, logt = t - kSpanRegs;
+    const uint64_t all = (uint64_t(1) << n) - 1;
+    if (!span_tile_ok(t) || sa.n != n || t > n || n - t > 31 || (sa.rest_mask & ~all) ||
+        __builtin_popcountll(sa.rest_mask) != n - t)
+        return QSIM_E_ARG;
+    // rank of vectors by elimination; `room`: 64 entries, empty at first
+    auto add = [](uint64_t *room, uint64_t x) {
+        while (x) {
+            const int b = 63 - __builtin_clzll(x);
+            if (!room[b]) {
+                room[b] = x;
+                return true;
+            }
+            x ^= room[b];
+        }
+        return false;
+    };
+    uint64_t load[64] = {0}, tile[64] = {0};
+    for (int q = 0; q < n; q++)
+        if ((sa.rest_mask >> q) & 1) add(load, uint64_t(1) << q);
+    for (int j = 0; j < t; j++) {
+        if ((sa.load_v[j] & ~all) || (sa.store_v[j] & ~all)) return QSIM_E_ARG;
+        if (!add(load, sa.load_v[j]) || !add(tile, sa.load_v[j])) return QSIM_E_ARG;
+    }
+    uint64_t store[64] = {0};
+    for (int j = 0; j < t; j++) {
+        if (!add(store, sa.store_v[j])) return QSIM_E_ARG;
+        if (add(tile, sa.store_v[j])) return QSIM_E_ARG;   // outside the tile
+    }
+    const uint32_t rb = p.pass_begin[i], re = p.pass_begin[i + 1];
+    if (rb >= re || re > p.ops.size() || p.coef_begin[i] > p.coef_begin[i + 1] || p.coef_begin[i + 1] > p.coefs.size())
+        return QSIM_E_ARG;
+    uint32_t stages = 0, cf = p.coef_begin[i];
+    for (uint32_t j = rb; j < re; j++) {
+        const DevOp &o = p.ops[j];
+        if (o.kind == DEVOP_STAGE) {
+            const uint8_t *raw = reinterpret_cast<const uint8_t *>(&o);
+            uint64_t slots[64] = {0};
+            if (o.kx != t) return QSIM_E_ARG;
+            for (int x = 0; x < t; x++) {
+                uint16_t s;
+                std::memcpy(&s, raw + (x < 7 ? 2 * x : 16 + 2 * (x - 7)), 2);
+                if ((s >> t) || !add(slots, s)) return QSIM_E_ARG;
+            }
+            stages++;
+        } else if (o.kind == DEVOP_PAULI) {
+            const size_t need = size_t(2) << p.op_np[j];
+            if (!stages || o.k > 2 * kSpanRegs || (o.slot[0] >> logt) ||
+                (o.present >> (1 << kSpanRegs)) || p.op_np[j] < 0 || p.op_np[j] > 1)
+                return QSIM_E_ARG;
+            // the kernel takes the coefficients in order
+            if (o.coef != cf || o.coef + need > p.coef_begin[i + 1]) return QSIM_E_ARG;
+            cf += uint32_t(need);
+        } else {
+            return QSIM_E_ARG;
+        }
+    }
+    if (p.ops[rb].kind != DEVOP_STAGE || sa.tile_bytes != (stages > 1 ? uint32_t(elem_bytes(dtype) << t) : 0u) ||
+        qk::span_lds_bytes(elem_bytes(dtype), sa.tile_bytes, re - rb, p.coef_begin[i + 1] - p.coef_begin[i]) >
+            qk::max_lds_bytes())
+        return QSIM_E_ARG;
+    return QSIM_OK;
+}
+
 // Check, before anything is launched, that every device record stays inside
 // the buffers and tiles the kernels will index: tile qubits partition the n
 // qubits, operator positions are ascending and inside the tile (or the
@@ -217,8 +287,8 @@ int validate_plan(int n, int dtype, const Compiled &c) {
     for (size_t i = 0; i < c.passes.size(); i++) {
         const PassInfo &pi = c.passes[i];
         int width = n;
-        if (pi.reg) {
-            const int rc = validate_reg_pass(n, dtype, c, i);
+        if (pi.reg || pi.span) {
+            const int rc = pi.reg ? validate_reg_pass(n, dtype, c, i) : validate_span_pass(n, dtype, c, i);
             if (rc) return rc;
             continue;
         }
@@ -312,6 +382,84 @@ int validate_plan(int n, int dtype, const Compiled &c) {
     return QSIM_OK;
 }
 
+// Whether a circuit may run as a Pauli program (QSIM_SPAN=0 turns it off): in
+// tiled passes, with level-5 fusion and no option that asks for another form
+// of operator or pass, or that keeps commuting operators in order.
+static bool spans_wanted(int n, const FuseConfig &fc, const PlanConfig &pc) {
+    return fc.level == 5 && fc.sparse && !pc.one_op_per_pass && !pc.reg_engine &&
+           pc.tile_qubits < n && span_tile_ok(pc.tile_qubits) && n - pc.tile_qubits <= 31 &&
+           env_int("QSIM_SPAN", 1) != 0 && env_int("QSIM_PLAN_COMMUTE", 1) != 0;
+}
+
+// The plan of a Pauli program, with the measurement records of L.
+static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered &L, const PlanConfig &pc,
+                         Compiled *out) {
+    TraceRange range("qsim.plan");
+    const size_t elem = elem_bytes(dtype);
+    std::vector<Pass> passes;
+    const int t = pc.tile_qubits;
+    size_t at = 0, m = 0;
+    for (int e = 0; e < L.n_epochs; e++) {
+        size_t end = at;
+        while (end < P.ops.size() && P.op_epoch[end] == e) end++;
+        plan_spans(n, P, t, pc.low_qubits, kSpanRegs, uint32_t(sizeof(DevOp) + 2 * elem), pc.meta_budget, pc.window,
+                   pc.full_support, int(at), int(end), &passes);
+        at = end;
+        for (; m < L.meas.size() && L.meas[m].epoch == e; m++) {
+            Pass p;
+            p.kind = Pass::MEASURE;
+            p.meas = L.meas[m];
+            passes.push_back(std::move(p));
+        }
+    }
+    PackedPlan &pl = out->plan;
+    const uint64_t all = (uint64_t(1) << n) - 1;
+    bool phased = P.phase == 0.0;
+    for (const Pass &p : passes) {
+        pl.pass_begin.push_back(uint32_t(pl.ops.size()));
+        pl.coef_begin.push_back(uint32_t(pl.coefs.size()));
+        PassInfo pi;
+        pi.kind = p.kind;
+        pi.meas = p.meas;
+        if (p.span) {
+            const int rc = pack_span_pass(P, p, kSpanRegs, dtype == QSIM_C64, &pl);
+            if (rc) return rc;
+            pi.span = true;
+            pi.ta.n = n;
+            qk::SpanArgs &sa = pi.sa;
+            sa.n = n;
+            sa.t = p.t;
+            sa.rest_mask = all & ~p.tile_mask;
+            for (int j = 0; j < p.t; j++) {
+                sa.load_v[j] = span_vector(p, p.stages.front().layout[j]);
+                sa.store_v[j] = span_vector(p, p.stages.back().layout[j]);
+            }
+            sa.tile_bytes = p.stages.size() > 1 ? uint32_t(elem << p.t) : 0u;
+            sa.phase_re = 1.0;
+            if (!phased) {
+                sa.phase_re = std::cos(P.phase);
+                sa.phase_im = std::sin(P.phase);
+                phased = true;
+            }
+        }
+        out->passes.push_back(pi);
+    }
+    pl.pass_begin.push_back(uint32_t(pl.ops.size()));
+    pl.coef_begin.push_back(uint32_t(pl.coefs.size()));
+    out->records = int64_t(L.meas.size());
+    qsim_apply_stats &s = out->stats;
+    std::memset(&s, 0, sizeof(s));
+    s.input_gates = L.input_gates;
+    for (int l = 1; l < 5; l++) s.ops_after[l] = -1;   // the paper's fusion steps are not taken
+    s.ops_after[0] = L.input_gates;
+    s.ops_after[5] = s.fused_ops = int64_t(P.ops.size());
+    s.passes = int64_t(passes.size());
+    s.terms = pl.terms;
+    s.bytes_moved = s.passes * 2 * (int64_t(1) << n) * int64_t(elem);
+    s.tile_qubits = t;
+    return QSIM_OK;
+}
+
 int compile_circuit(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
                     const qsim_fuse_opts *opt, Compiled *out) {
     return compile_program(n, dtype, g, ng, in, false, false, 0, opt, out);
@@ -331,7 +479,23 @@ int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
     int rc;
     {
         TraceRange r("qsim.lower");
-        rc = lower(n, g, ng, in, keep_params, allow_meas, &L);
+        std::vector<size_t> op_gate;
+        size_t first_at;
+        split_records(n, g, ng, allow_meas, &L, &op_gate, &rc, &first_at);
+        if (!rc && spans_wanted(n, fc, pc)) {
+            PauliProgram P;
+            bool fits = pauli_lower(n, g, op_gate, L.op_epoch, in, keep_params, &P);
+            if (pc.full_support)
+                for (const PauliOp &o : P.ops)
+                    fits = fits && __builtin_popcountll(o.x | o.z) <= pc.tile_qubits - pc.low_qubits;
+            if (fits) {
+                rc = compile_spans(n, dtype, P, L, pc, out);
+                out->stats.max_width = fc.max_width;
+                out->stats.compile_seconds = now_seconds() - t0;
+                return rc || keep_params ? rc : validate_plan(n, dtype, *out);
+            }
+        }
+        rc = lower_gates(n, g, ng, in, keep_params, op_gate, rc, first_at, &L);
     }
     if (rc) return rc;
     int64_t counts[6];
@@ -524,30 +688,39 @@ void free_tables(DeviceTables *dt) {
     *dt = DeviceTables{};
 }
 
-int enqueue_passes(const Compiled &c, const DeviceTables &dt, int dtype, void *state,
-                   hipStream_t st, bool init_zero_first, uint64_t sstride, uint32_t nstates) {
+int enqueue_pass(const Compiled &c, size_t i, const DevOp *d_ops, const void *d_coefs, uint64_t cstride, int dtype,
+                 void *state, uint64_t sstride, uint32_t nstates, const qk::MeasArgs *ma, uint32_t flags,
+                 hipStream_t st) {
     const PackedPlan &p = c.plan;
-    for (size_t i = 0; i < c.passes.size(); i++) {
-        const PassInfo &pi = c.passes[i];
-        const uint32_t ob = p.pass_begin[i], oe = p.pass_begin[i + 1];
-        int rc;
-        if (pi.kind == Pass::MEASURE) return QSIM_E_UNSUPPORTED;
-        if (pi.strided) {
-            for (uint32_t j = ob; j < oe; j++) {
-                rc = qk::launch_sweep(dtype, state, sstride, nstates, pi.ta.n, p.ops[j], dt.d_coefs, st);
-                if (rc) return rc;
-            }
-        } else if (pi.reg) {
-            uint32_t flags = (init_zero_first && i == 0) ? qk::TF_INIT_ZERO : 0u;
-            rc = qk::launch_reg(dtype, state, sstride, nstates, pi.ra, dt.d_ops, ob, oe, dt.d_coefs,
-                                p.coef_begin[i], p.coef_begin[i + 1], 0, nullptr, flags, st);
-            if (rc) return rc;
-        } else {
-            uint32_t flags = (init_zero_first && i == 0) ? qk::TF_INIT_ZERO : 0u;
-            rc = qk::launch_tile(dtype, state, sstride, nstates, pi.ta, dt.d_ops, ob, oe, dt.d_coefs,
-                                 p.coef_begin[i], p.coef_begin[i + 1], 0, nullptr, flags, st);
+    const PassInfo &pi = c.passes[i];
+    const uint32_t ob = p.pass_begin[i], oe = p.pass_begin[i + 1], cb = p.coef_begin[i], ce = p.coef_begin[i + 1];
+    const int32_t *status = ma ? ma->status : nullptr;
+    if (pi.kind == Pass::MEASURE) return QSIM_E_UNSUPPORTED;
+    if (pi.strided) {
+        for (uint32_t j = ob; j < oe; j++) {
+            const int rc =
+                qk::launch_sweep(dtype, state, sstride, nstates, pi.ta.n, p.ops[j], d_coefs, st, cstride, status);
             if (rc) return rc;
         }
+        return QSIM_OK;
+    }
+    if (pi.span)
+        return qk::launch_span(dtype, state, sstride, nstates, pi.sa, d_ops, ob, oe, d_coefs, cb, ce, cstride, status,
+                               flags, st);
+    if (pi.reg)
+        return qk::launch_reg(dtype, state, sstride, nstates, pi.ra, d_ops, ob, oe, d_coefs, cb, ce, cstride, status,
+                              flags, st);
+    return qk::launch_tile(dtype, state, sstride, nstates, pi.ta, d_ops, ob, oe, d_coefs, cb, ce, cstride, ma, flags,
+                           st);
+}
+
+int enqueue_passes(const Compiled &c, const DeviceTables &dt, int dtype, void *state,
+                   hipStream_t st, bool init_zero_first, uint64_t sstride, uint32_t nstates) {
+    for (size_t i = 0; i < c.passes.size(); i++) {
+        const uint32_t flags = (init_zero_first && i == 0) ? qk::TF_INIT_ZERO : 0u;
+        const int rc =
+            enqueue_pass(c, i, dt.d_ops, dt.d_coefs, 0, dtype, state, sstride, nstates, nullptr, flags, st);
+        if (rc) return rc;
     }
     return QSIM_OK;
 }
@@ -807,23 +980,10 @@ int qsim_run_timed(qsim_h h, qsim_prog p) {
             p->events.push_back(e);
         }
     }
-    const PackedPlan &pl = p->c.plan;
     for (size_t i = 0; i < np; i++) {
-        const PassInfo &pi = p->c.passes[i];
         if (hipEventRecord(p->events[2 * i], h->stream) != hipSuccess) return QSIM_E_HIP;
-        int rc;
-        if (pi.strided) {
-            rc = QSIM_OK;
-            for (uint32_t j = pl.pass_begin[i]; j < pl.pass_begin[i + 1] && !rc; j++)
-                rc = qk::launch_sweep(p->dtype, h->buf, 0, 1, p->n, pl.ops[j], p->dt.d_coefs, h->stream);
-        } else if (pi.reg) {
-            rc = qk::launch_reg(p->dtype, h->buf, 0, 1, pi.ra, p->dt.d_ops, pl.pass_begin[i], pl.pass_begin[i + 1],
-                                p->dt.d_coefs, pl.coef_begin[i], pl.coef_begin[i + 1], 0, nullptr, 0, h->stream);
-        } else {
-            rc = qk::launch_tile(p->dtype, h->buf, 0, 1, pi.ta, p->dt.d_ops, pl.pass_begin[i],
-                                 pl.pass_begin[i + 1], p->dt.d_coefs, pl.coef_begin[i],
-                                 pl.coef_begin[i + 1], 0, nullptr, 0, h->stream);
-        }
+        const int rc = enqueue_pass(p->c, i, p->dt.d_ops, p->dt.d_coefs, 0, p->dtype, h->buf, 0, 1, nullptr, 0,
+                                    h->stream);
         if (rc) return rc;
         if (hipEventRecord(p->events[2 * i + 1], h->stream) != hipSuccess) return QSIM_E_HIP;
     }
@@ -1419,6 +1579,71 @@ int qsim_debug_emulate(int n, int dtype, const qsim_gate *g, size_t ng, const do
                 }
                 if (std::memcmp(cur, ra.store_pos, size_t(t)) != 0) return QSIM_E_ARG;
                 for (uint64_t P = 0; P < v.size(); P++) st[addr(P, ra.store_pos)] = v[P];
+            }
+            continue;
+        }
+        if (pi.span) {
+            // elements at positions (thread bits, then register bits), moved
+            // through the slots of each stage's layout
+            const qk::SpanArgs &sa = pi.sa;
+            const int t = sa.t, logt = t - kSpanRegs;
+            auto combine = [&](uint64_t P, auto &&vec) {
+                uint64_t a = 0;
+                for (int b = 0; b < t; b++)
+                    if ((P >> b) & 1) a ^= uint64_t(vec(b));
+                return a;
+            };
+            std::vector<cd> v(size_t(1) << t), w(v.size());
+            const cd turn(sa.phase_re, sa.phase_im);
+            for (uint64_t tile = 0; tile < (uint64_t(1) << (n - t)); tile++) {
+                const uint64_t base = qk::span_base(tile, sa);
+                for (uint64_t P = 0; P < v.size(); P++) v[P] = st[base ^ combine(P, [&](int b) { return sa.load_v[b]; })];
+                const uint8_t *cur = nullptr;
+                cd scale = turn;
+                for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i + 1]; j++) {
+                    const DevOp &o = p.ops[j];
+                    if (o.kind == DEVOP_STAGE) {
+                        const uint8_t *raw = reinterpret_cast<const uint8_t *>(&o);
+                        auto slots = [](const uint8_t *at) {
+                            return [at](int x) {
+                                uint16_t s;
+                                std::memcpy(&s, at + (x < 7 ? 2 * x : 16 + 2 * (x - 7)), 2);
+                                return s;
+                            };
+                        };
+                        if (cur) {
+                            for (uint64_t P = 0; P < v.size(); P++) w[combine(P, slots(cur))] = v[P];
+                            for (uint64_t P = 0; P < v.size(); P++) v[P] = w[combine(P, slots(raw))];
+                        }
+                        cur = raw;
+                        continue;
+                    }
+                    const cd e0 = p.coefs[o.coef], e1 = p.coefs[o.coef + 1];
+                    scale *= e0.real() + e0.imag();
+                    // the sign of each register, from those of the pairs
+                    const bool diag = o.k == 2 * kSpanRegs, real = !diag && (o.k & 1);
+                    const uint32_t m = diag ? 0u : 1u << (o.k >> 1);
+                    uint32_t rsign = 0;
+                    for (uint32_t r = 0, k = 0, last = 0; r < (1u << kSpanRegs); r++) {
+                        const uint32_t q = r ^ m;
+                        if (m && r > q) continue;
+                        last ^= (o.present >> k++) & 1;
+                        rsign |= last << r;
+                        if (m) rsign |= (last ^ uint32_t(real)) << q;
+                    }
+                    const uint64_t zb = uint64_t(o.slot[1]) | uint64_t(o.slot[2]) << 16 | uint64_t(o.slot[3]) << 32;
+                    for (uint64_t P = 0; P < v.size(); P++) {
+                        const uint64_t tid = P & ((uint64_t(1) << logt) - 1), r = P >> logt;
+                        const int s = (__builtin_popcountll(tid & o.slot[0]) + __builtin_popcountll(base & zb) +
+                                       int((rsign >> r) & 1)) & 1;
+                        const cd b = (real ? cd(1.0) : cd(0.0, 1.0)) * (s ? -e1.imag() : e1.imag());
+                        w[P] = v[P] + b * v[P ^ (uint64_t(m) << logt)];
+                        if (e1.real() != 0.0) w[P] *= e1.real();
+                    }
+                    std::swap(v, w);
+                }
+                for (uint64_t P = 0; P < v.size(); P++)
+                    st[base ^ combine(P, [&](int b) { return sa.store_v[b]; })] = v[P] * scale;
             }
             continue;
         }

@@ -129,7 +129,7 @@ size_t bind_layout(Compiled *c, std::vector<qk::BindEntry> *ents, uint32_t *max_
         e.bound_off = uint32_t(bound);
         e.count = count;
         e.tmpl_off = o.coef;
-        e.np = p.op_np[j];
+        e.np = o.kind == DEVOP_PAULI && p.op_np[j] == 1 ? -1 : p.op_np[j];
         for (int s = 0; s < 3; s++) e.slot[s] = p.op_slots[3 * j + s];
         ents->push_back(e);
         *max_count = std::max(*max_count, count);
@@ -314,7 +314,6 @@ int enqueue_group(const Group &G, int dtype, hipStream_t st) {
                              G.cstride, uint32_t(G.nstates), G.max_count, st);
         if (rc) return rc;
     }
-    const PackedPlan &p = G.c.plan;
     qk::MeasArgs ma{};
     ma.uniforms = G.d_uniforms;
     ma.forced = G.d_forced;
@@ -336,21 +335,10 @@ int enqueue_group(const Group &G, int dtype, hipStream_t st) {
             if (!rc)
                 rc = qk::launch_decide(dtype, G.d_states, G.sstride, uint32_t(G.nstates), G.n, q,
                                        pi.meas.kind, pi.meas.slot, G.d_p01, ma, st);
-        } else if (pi.strided) {
-            rc = QSIM_OK;
-            for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i + 1] && !rc; j++)
-                rc = qk::launch_sweep(dtype, G.d_states, G.sstride, uint32_t(G.nstates), G.n, p.ops[j],
-                                      G.d_coefs, st, G.cstride, G.d_status);
-        } else if (pi.reg) {
-            const uint32_t flags = (i == 0 && first_tile) ? qk::TF_INIT_ZERO : 0u;
-            rc = qk::launch_reg(dtype, G.d_states, G.sstride, uint32_t(G.nstates), pi.ra, G.d_ops,
-                                p.pass_begin[i], p.pass_begin[i + 1], G.d_coefs, p.coef_begin[i],
-                                p.coef_begin[i + 1], G.cstride, G.d_status, flags, st);
         } else {
             const uint32_t flags = (i == 0 && first_tile) ? qk::TF_INIT_ZERO : 0u;
-            rc = qk::launch_tile(dtype, G.d_states, G.sstride, uint32_t(G.nstates), pi.ta, G.d_ops,
-                                 p.pass_begin[i], p.pass_begin[i + 1], G.d_coefs, p.coef_begin[i],
-                                 p.coef_begin[i + 1], G.cstride, &ma, flags, st);
+            rc = enqueue_pass(G.c, i, G.d_ops, G.d_coefs, G.cstride, dtype, G.d_states, G.sstride,
+                              uint32_t(G.nstates), &ma, flags, st);
         }
         if (rc) return rc;
     }

@@ -337,8 +337,8 @@ int lower_gate(int n, const qsim_gate &gi, const GateInputs &in, bool keep_param
 
 }  // namespace
 
-int lower(int n, const qsim_gate *g, size_t ng, const GateInputs &in, bool keep_params,
-          bool allow_meas, Lowered *out) {
+void split_records(int n, const qsim_gate *g, size_t ng, bool allow_meas, Lowered *out,
+                   std::vector<size_t> *op_gate_out, int *first_rc_out, size_t *first_at_out) {
     out->ops.clear();
     out->op_epoch.clear();
     out->meas.clear();
@@ -347,11 +347,14 @@ int lower(int n, const qsim_gate *g, size_t ng, const GateInputs &in, bool keep_
     // record of every operator.  Then the operators themselves, which are
     // independent, on several threads.  The first failing record in
     // program order decides the error.
-    std::vector<size_t> op_gate;
+    std::vector<size_t> &op_gate = *op_gate_out;
+    op_gate.clear();
     op_gate.reserve(ng);
     int epoch = 0;
-    int first_rc = QSIM_OK;
-    size_t first_at = ng;
+    int &first_rc = *first_rc_out;
+    size_t &first_at = *first_at_out;
+    first_rc = QSIM_OK;
+    first_at = ng;
     // Records out->meas[run_begin ..] follow each other with no operator or
     // barrier between them.  Non-unitary steps on different qubits commute,
     // and after a measurement, an assertion or a reset the qubit is definite,
@@ -406,6 +409,12 @@ int lower(int n, const qsim_gate *g, size_t ng, const GateInputs &in, bool keep_
         out->op_epoch.push_back(epoch);
         run_begin = out->meas.size();
     }
+    out->input_gates = int64_t(op_gate.size());
+    out->n_epochs = epoch + 1;
+}
+
+int lower_gates(int n, const qsim_gate *g, size_t ng, const GateInputs &in, bool keep_params,
+                const std::vector<size_t> &op_gate, int first_rc, size_t first_at, Lowered *out) {
     // the operators, in contiguous ranges; each range keeps its first error
     const size_t nops = op_gate.size();
     out->ops.resize(nops);
@@ -445,10 +454,16 @@ int lower(int n, const qsim_gate *g, size_t ng, const GateInputs &in, bool keep_
             first_at = at[w];
             first_rc = rcs[w];
         }
-    if (first_rc) return first_rc;
-    out->input_gates = int64_t(nops);
-    out->n_epochs = epoch + 1;
-    return QSIM_OK;
+    return first_rc;
+}
+
+int lower(int n, const qsim_gate *g, size_t ng, const GateInputs &in, bool keep_params,
+          bool allow_meas, Lowered *out) {
+    std::vector<size_t> op_gate;
+    int first_rc = QSIM_OK;
+    size_t first_at = ng;
+    split_records(n, g, ng, allow_meas, out, &op_gate, &first_rc, &first_at);
+    return lower_gates(n, g, ng, in, keep_params, op_gate, first_rc, first_at, out);
 }
 
 }  // namespace qs

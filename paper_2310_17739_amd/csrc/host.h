@@ -2,6 +2,7 @@
 // operators, pass plans and the packed device tables.
 #pragma once
 
+#include <cmath>
 #include <complex>
 #include <cstdint>
 #include <string>
@@ -61,6 +62,24 @@ struct Lowered {
     int64_t input_gates = 0;
 };
 
+// A rotation exp(-i phi P) of a Pauli program, P|b> = sign i^|x & z| (-1)^|b & z|
+// |b ^ x>; with slot >= 0, phi is half the angle of that slot of the parameter
+// vector.
+struct PauliOp {
+    uint64_t x = 0, z = 0;
+    double phi = 0.0;
+    double sign = 1.0;
+    int32_t slot = -1;
+};
+
+// A circuit as rotations in order, each with its epoch; `phase` is the angle
+// of the global phase that the rotations leave out.
+struct PauliProgram {
+    std::vector<PauliOp> ops;
+    std::vector<int> op_epoch;
+    double phase = 0.0;
+};
+
 struct FuseConfig {
     int level = 5;
     int max_width = 4;
@@ -87,6 +106,14 @@ struct GateInputs {
     const double *params = nullptr;
     size_t n_params = 0;
 };
+// split_records makes the epochs and the measurement records of *out and lists
+// the records that are gates (op_gate); it stops at the first bad measurement
+// record, *first_rc at *first_at (ng if none).  lower_gates builds their
+// operators; it takes what split_records found.
+void split_records(int n, const qsim_gate *g, size_t ng, bool allow_meas, Lowered *out,
+                   std::vector<size_t> *op_gate, int *first_rc, size_t *first_at);
+int lower_gates(int n, const qsim_gate *g, size_t ng, const GateInputs &in, bool keep_params,
+                const std::vector<size_t> &op_gate, int first_rc, size_t first_at, Lowered *out);
 int lower(int n, const qsim_gate *g, size_t ng, const GateInputs &in, bool keep_params,
           bool allow_meas, Lowered *out);
 // Dense matrix of one gate record on its own qubits in record order.
@@ -100,6 +127,38 @@ void fuse(int n, Lowered *L, const FuseConfig &cfg, int64_t counts[6]);
 void embed(const Op &a, const int *uq, int uk, std::vector<cd> *out, int basis);
 int xor_terms(const cd *m, int k, double tol, uint32_t *present);
 double max_abs(const cd *m, size_t n);
+
+// ---- Pauli programs (span.cpp)
+// The gates op_gate (epochs op_epoch) as rotations.  Returns false, and leaves
+// the circuit to lower_gates, for records that are not rotations, Clifford
+// gates or products of few rotations, for records that it refuses, and for
+// circuits whose Clifford gates mostly do not cancel.
+bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, const std::vector<int> &op_epoch,
+                 const GateInputs &in, bool keep_params, PauliProgram *out);
+
+// Coefficients of a rotation record, from a = cos phi and b = +-sin phi:
+// y = a (x + t x') with t = b / a = e[1].im.  The factor a goes into the scale
+// of the pass (e[0].re + e[0].im: in single precision a and what rounding
+// leaves of it) while |t| <= 1, which bounds what an amplitude grows by before
+// the scale is applied; beyond, the result is multiplied by e[1].re = a at
+// once.  (A cosine below 1e-25 is none: t stays finite in single precision.)
+inline void pauli_coefs(double a, double b, bool single, cd e[2]) {
+    if (std::fabs(a) < 1e-25) a = 1e-25;
+    if (std::fabs(b) <= std::fabs(a)) {
+        e[0] = single ? cd(double(float(a)), a - double(float(a))) : cd(a, 0.0);
+        e[1] = cd(0.0, b / a);
+    } else {
+        e[0] = cd(1.0, 0.0);
+        e[1] = cd(a, b / a);
+    }
+}
+
+// A stage of a span pass: position j of an element (thread bits, then register
+// bits) moves it by layout[j], in coordinates of the tile's basis.
+struct SpanStage {
+    uint16_t layout[14] = {0};
+    std::vector<int> ops;         // rotations, in order
+};
 
 // ---- planning (plan.cpp)
 struct Pass {
@@ -131,6 +190,11 @@ struct Pass {
     int reg_swaps = 0, reg_xposes = 0;
     int nxcd = 0;                 // XCD-aware tile order (see qk::TileArgs)
     uint8_t xcd_q[4] = {0};
+    // passes of rotations (span.cpp): the tile is a coset of the space spanned
+    // by span_v[0..t-1], in reduced echelon form with the pivot bits tile_mask
+    bool span = false;
+    uint64_t span_v[14] = {0};
+    std::vector<SpanStage> stages;
 };
 
 struct PlanConfig {
@@ -202,7 +266,7 @@ static_assert(sizeof(DevOp) == 32, "DevOp layout");
 
 // Coefficients of one record: for each of the 2^kx blocks, each present
 // shift's 2^k diagonal entries.
-inline uint32_t devop_coefs(const DevOp &o) { return uint32_t(__builtin_popcount(o.present)) << (o.k + o.kx); }
+inline uint32_t devop_coefs(const DevOp &o);
 
 enum { DEVOP_MAT = 0, DEVOP_MEASURE = 1, DEVOP_ASSERT0 = 2, DEVOP_RESET = 3,
        // register-resident passes:
@@ -211,11 +275,23 @@ enum { DEVOP_MAT = 0, DEVOP_MEASURE = 1, DEVOP_ASSERT0 = 2, DEVOP_RESET = 3,
        DEVOP_SWAP = 5,    // pos[0] = lane bit (4 or 5), pos[1] = register bit: exchange them
        DEVOP_XPOSE = 6,   // LDS re-layout; bytes 0..13 = canonical bit per position before,
        DEVOP_XPOSE2 = 7,  // and, in the record that follows, after
-       DEVOP_MEASURE_RESET = 8   // a measurement followed by a reset of the same qubit
+       DEVOP_MEASURE_RESET = 8,  // a measurement followed by a reset of the same qubit
+       // span passes:
+       DEVOP_STAGE = 9,   // the LDS slots of the layout's positions, 16 bits each, in bytes 0..13
+                          // and 16..29; kx = their number
+       DEVOP_PAULI = 10   // rotation: k = 2 b + 1 for a real t and 2 b for an imaginary one on
+                          // register bit b, 2 kSpanRegs for a diagonal; bit j of present = whether the sign of register pair j
+                          // (in ascending order of the smaller register) differs from that of
+                          // pair j - 1; slot[0], slot[1..3] = the sign masks of the thread bits
+                          // and of the tile's base index; two coefficients (see pauli_coefs)
 };
-inline bool devop_is_mat(int kind) { return kind == DEVOP_MAT || kind == DEVOP_RMAT; }
+inline bool devop_is_mat(int kind) { return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI; }
 inline bool devop_is_record(int kind) {
     return kind == DEVOP_MEASURE || kind == DEVOP_ASSERT0 || kind == DEVOP_RESET || kind == DEVOP_MEASURE_RESET;
+}
+
+inline uint32_t devop_coefs(const DevOp &o) {
+    return o.kind == DEVOP_PAULI ? 2u : uint32_t(__builtin_popcount(o.present)) << (o.k + o.kx);
 }
 
 struct PackedPlan {
@@ -252,6 +328,21 @@ int pack_plan(const std::vector<Op> &ops, const std::vector<uint32_t> &present,
 // QSIM_E_ARG for an operator the pass cannot hold.
 int pack_reg_pass(const std::vector<Op> &ops, const std::vector<uint32_t> &present, Pass &p,
                   bool coalesce, PackedPlan *out);
+
+// Register bits of a span pass: each thread holds 2^kSpanRegs amplitudes.
+constexpr int kSpanRegs = 4;
+inline bool span_tile_ok(int t) { return t >= 6 + kSpanRegs && t <= 14; }
+
+// Span passes of the rotations [first, last) of P: tiles of t dimensions that
+// hold the low c qubits.  op_bytes: LDS bytes of a rotation (record and
+// coefficients); full: a tile holds every qubit of its rotations (each string has
+// at most t - c of them).
+void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, uint32_t op_bytes, size_t meta_budget, int window,
+                bool full, int first, int last, std::vector<Pass> *passes);
+// Appends the pass's records and coefficients.
+int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, PackedPlan *out);
+// The vector of the state's index that tile coordinates stand for.
+uint64_t span_vector(const Pass &p, uint32_t coords);
 
 double now_seconds();
 

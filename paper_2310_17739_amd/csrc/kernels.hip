@@ -28,6 +28,7 @@
 #include <mutex>
 #include <vector>
 
+#include "device.h"
 #include "launch.h"
 #include "swizzle.h"
 
@@ -37,11 +38,6 @@ using qs::DevOp;
 
 constexpr int NT = 256;            // threads per workgroup (4 waves of 64)
 constexpr int NWAVES = NT / 64;
-
-template <typename T>
-struct alignas(2 * sizeof(T)) Cx {
-    T re, im;
-};
 
 template <typename T>
 __device__ __forceinline__ void cmac(Cx<T> &acc, const Cx<T> c, const Cx<T> x) {
@@ -63,18 +59,6 @@ __device__ __forceinline__ Cx<T> cmul(const Cx<T> c, const Cx<T> x) {
 #ifndef APPLY_CHUNK_C128
 #define APPLY_CHUNK_C128 2
 #endif
-
-template <int V>
-struct IntC {
-    static constexpr int value = V;
-};
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (B < E) {
-        f(IntC<B>{});
-        static_for<B + 1, E>(f);
-    }
-}
 
 // y[r] = sum over present shifts m of d_m[r] * x[r ^ m]; cf holds the present
 // diagonals in ascending m, 2^K entries each.  Outputs R0 .. R0+RC-1 only, so
@@ -149,37 +133,6 @@ __device__ __forceinline__ double norm2(const Cx<T> a) {
     const double re = double(a.re), im = double(a.im);
     return re * re + im * im;
 }
-
-// LDS slot of tile element j (the fold defined with the pass packer).
-template <typename T>
-__device__ __forceinline__ int sw(int j) {
-    return qs::lds_slot(int(sizeof(Cx<T>)), j);
-}
-
-// The tile of k_tile sits at LDS byte 0 of its workgroup (the kernel has no
-// static LDS, which init_kernels checks), slot i at byte i * sizeof(Cx<T>),
-// and is addressed by byte offsets, so that an access costs one XOR; the FP64
-// reduction scratch of in-tile measurements follows the tile.
-template <typename T>
-struct LdsTile {
-    static constexpr int LOGE = sizeof(Cx<T>) == 8 ? 3 : 4;
-    typedef T V2 __attribute__((ext_vector_type(2)));
-    static __device__ __forceinline__ Cx<T> ld(uint32_t byte) {
-        const V2 v = *reinterpret_cast<const __attribute__((address_space(3))) V2 *>(uintptr_t(byte));
-        return Cx<T>{v.x, v.y};
-    }
-    static __device__ __forceinline__ void st(uint32_t byte, Cx<T> c) {
-        V2 v;
-        v.x = c.re;
-        v.y = c.im;
-        *reinterpret_cast<__attribute__((address_space(3))) V2 *>(uintptr_t(byte)) = v;
-    }
-    static __device__ __forceinline__ Cx<T> at(int j) { return ld(uint32_t(sw<T>(j)) << LOGE); }
-    static __device__ __forceinline__ void set(int j, Cx<T> v) { st(uint32_t(sw<T>(j)) << LOGE, v); }
-    static __device__ __forceinline__ __attribute__((address_space(3))) double *red(int t) {
-        return reinterpret_cast<__attribute__((address_space(3))) double *>(uintptr_t(uint32_t(sizeof(Cx<T>)) << t));
-    }
-};
 
 // ------------------------------------------------------------ tile kernel
 // Operator record fields, read as eight scalar words (see qs::DevOp).
@@ -599,24 +552,6 @@ __device__ int lds_measure(int t, const OpRec &op, const MeasArgs &ma, uint32_t 
         }
     }
     return 0;
-}
-
-// Tile loads and stores of the state stream past the caches (non-temporal):
-// each pass touches every amplitude once, and the operator records and
-// coefficients read through the scalar cache then stay resident in L2.
-template <typename T>
-__device__ __forceinline__ Cx<T> ld_stream(const Cx<T> *p) {
-    typedef T V2 __attribute__((ext_vector_type(2)));
-    const V2 v = __builtin_nontemporal_load(reinterpret_cast<const V2 *>(p));
-    return Cx<T>{v.x, v.y};
-}
-template <typename T>
-__device__ __forceinline__ void st_stream(Cx<T> *p, Cx<T> c) {
-    typedef T V2 __attribute__((ext_vector_type(2)));
-    V2 v;
-    v.x = c.re;
-    v.y = c.im;
-    __builtin_nontemporal_store(v, reinterpret_cast<V2 *>(p));
 }
 
 // One tile of 2^t amplitudes per workgroup of TNT threads (blockIdx.x:
@@ -1398,6 +1333,24 @@ __global__ void __launch_bounds__(NT) k_bind(const double *__restrict__ tmpl,
     for (uint64_t idx = uint64_t(blockIdx.y) * NT + threadIdx.x; idx < total;
          idx += uint64_t(gridDim.y) * NT) {
         const uint32_t b = uint32_t(idx / e.count), c = uint32_t(idx % e.count);
+        if (e.np < 0) {
+            // a rotation's two coefficients (the host's pauli_coefs)
+            const double th = params[size_t(b) * nparams + e.slot[0]];
+            double a = cos(0.5 * th);
+            const double s = tmpl[2 * size_t(e.tmpl_off)] * sin(0.5 * th);
+            if (fabs(a) < 1e-25) a = 1e-25;
+            const bool out_a = fabs(s) <= fabs(a);
+            double x, y;
+            if (c == 0) {
+                x = out_a ? a : 1.0;
+                y = (out_a && sizeof(T) == 4) ? a - double(float(a)) : 0.0;
+            } else {
+                x = out_a ? 0.0 : a;
+                y = s / a;
+            }
+            out[size_t(b) * cstride + e.bound_off + c] = Cx<T>{T(x), T(y)};
+            continue;
+        }
         double cs[3], sn[3];
         for (int j = 0; j < e.np; j++) {
             const double th = params[size_t(b) * nparams + e.slot[j]];
@@ -1559,8 +1512,9 @@ int init_kernels() {
     lds_attr<double, 5, 512>();
     lds_attr<double, 6, 512>();
     (void)hipGetLastError();
+    if (!init_span_kernels()) tile_static_lds = 1;
     if (tile_static_lds) {
-        note_hip(hipErrorInvalidKernelFile, "k_tile declares static LDS (its tile must start at LDS byte 0)");
+        note_hip(hipErrorInvalidKernelFile, "a tile kernel declares static LDS (its tile must start at LDS byte 0)");
         return QSIM_E_UNSUPPORTED;
     }
     done = 1;

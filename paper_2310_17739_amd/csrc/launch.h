@@ -100,6 +100,46 @@ int launch_reg(int dtype, void *state, uint64_t sstride, uint32_t nstates, const
                const qs::DevOp *ops, uint32_t ob, uint32_t oe, const void *coefs, uint32_t cb, uint32_t ce,
                uint64_t cstride, const int32_t *status, uint32_t flags, hipStream_t st);
 
+// Pass of rotations (records DEVOP_STAGE / DEVOP_PAULI): the tile of workgroup
+// b is the coset of span_base(b) under the space of the load vectors (and of
+// the store vectors: the same space).  Position j of an element (thread bits,
+// then register bits) moves its index by load_v[j] as loaded and by store_v[j]
+// as stored.  The result is multiplied by the phase and the rotations' scales.
+struct SpanArgs {
+    uint64_t rest_mask;      // the index bits that tell cosets apart
+    uint64_t load_v[14];
+    uint64_t store_v[14];
+    double phase_re, phase_im;
+    int32_t n, t;
+    uint32_t tile_bytes;     // LDS bytes of the tile: 0 for a pass with one stage
+    int32_t pad;
+};
+
+// Base index of the tile of workgroup bx: its bits in the rest bits, ascending.
+__host__ __device__ inline uint64_t span_base(uint64_t bx, const SpanArgs &sa) {
+    uint64_t m = sa.rest_mask, x = bx, r = 0;
+    while (m && x) {
+        const uint64_t low = m & (~m + 1);
+        if (x & 1) r |= low;
+        x >>= 1;
+        m &= m - 1;
+    }
+    return r;
+}
+
+// LDS bytes of a span pass (the padding covers the kernel's read-ahead of a
+// record and its coefficients).
+inline size_t span_lds_bytes(size_t elem, size_t tile_bytes, uint32_t nrec, uint32_t ncoef) {
+    return tile_bytes + size_t(nrec) * sizeof(qs::DevOp) + size_t(ncoef) * elem + sizeof(qs::DevOp) + 2 * elem;
+}
+
+// Sets the kernels' LDS limit; false if one declares static LDS (its tile must
+// start at LDS byte 0).
+bool init_span_kernels();
+int launch_span(int dtype, void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa,
+                const qs::DevOp *ops, uint32_t ob, uint32_t oe, const void *coefs, uint32_t cb, uint32_t ce,
+                uint64_t cstride, const int32_t *status, uint32_t flags, hipStream_t st);
+
 // Enable > 64 KiB of dynamic LDS for the tile kernels.  Idempotent.
 int init_kernels();
 size_t max_lds_bytes();
@@ -142,7 +182,8 @@ struct BindEntry {
     uint32_t bound_off;   // offset in a state's bound coefficient array (elements)
     uint32_t count;       // coefficients of the operator (terms * 2^k)
     uint32_t tmpl_off;    // offset of block 0 in the FP64 template (complex elements)
-    int32_t np;           // angle slots (0..3)
+    int32_t np;           // angle slots (0..3); -1: a rotation of angle slot[0], the sign of its
+                          // t in block 0
     int32_t slot[3];
     int32_t pad;
 };

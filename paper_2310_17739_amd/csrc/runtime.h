@@ -17,6 +17,8 @@ struct PassInfo {
     qk::TileArgs ta{};
     bool reg = false;           // register-resident tiled pass (k_reg)
     qk::RegArgs ra{};
+    bool span = false;          // pass of rotations (k_span)
+    qk::SpanArgs sa{};
     MeasRec meas;               // MEASURE passes
 };
 
@@ -67,6 +69,11 @@ int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs
 // width for groups whose states fit one tile, which are not timed).
 int tune_tile_batch(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
                     const qsim_fuse_opts &base, uint32_t nstates, int *best_t);
+// Enqueue pass i of a plan (not a MEASURE pass) over nstates states spaced
+// sstride elements apart, state b's coefficients at coefs + b * cstride.
+int enqueue_pass(const Compiled &c, size_t i, const DevOp *d_ops, const void *d_coefs, uint64_t cstride, int dtype,
+                 void *state, uint64_t sstride, uint32_t nstates, const qk::MeasArgs *ma, uint32_t flags,
+                 hipStream_t st);
 int upload_plan(DeviceTables *dt, int dtype, const PackedPlan &plan, hipStream_t st);
 void free_tables(DeviceTables *dt);
 // (sstride, nstates: the same passes over nstates states laid out every

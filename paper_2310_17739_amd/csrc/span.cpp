@@ -1,0 +1,656 @@
+// Pauli programs: circuits run as sequences of Pauli rotations.
+//
+// Lowering.  Most gates of the deep circuits of Section 5.1 are Clifford gates
+// that cancel again: the basis changes and CNOT ladders around each Rz.  They
+// are not applied to the state at all.  Going through the circuit, the state
+// is psi = C phi with a Clifford frame C, and a rotation exp(-i phi P) on psi
+// is the rotation exp(-i phi C^dagger P C) on phi, again a Pauli string (of
+// any weight).  C is kept as the images C^dagger X_q C and C^dagger Z_q C of
+// the generators.  Gates of the frame cancel structurally: a gate that undoes
+// the last one on all of its wires removes it, so that what is left at the end
+// of an epoch is an explicit gate list (empty for Pauli exponentials), emitted
+// as rotations.  A circuit with gates that are no product of few rotations
+// (dense matrices, Toffolis) is not lowered this way.
+//
+// Passes.  A rotation mixes the amplitudes i and i ^ x only, x the string's X
+// mask.  A pass therefore needs no tile of whole qubits: a tile is a coset of
+// a t-dimensional subspace of GF(2)^n that holds the X masks of its rotations
+// (and the low qubits, for contiguous chunks), so each rotation costs at most
+// one dimension, whatever its weight, and its Z mask costs none: it is a sign,
+// linear in the index.  Inside a pass, stages do the same for a thread's
+// registers: with 2^r amplitudes per thread, a stage runs every rotation whose
+// X mask is one of r independent ones, the bits of the register index, without
+// any exchange, and only between stages the tile is re-laid out through LDS.
+// (Sums of the r masks could run as well, but then the kernel has 2^r forms of
+// a rotation in place of r, which outgrow the instruction cache.)  Rotations commute iff
+// their strings do, so both levels may take a rotation past skipped ones that
+// it commutes with.
+#include <algorithm>
+#include <cmath>
+#include <cstdlib>
+#include <cstring>
+
+#include "host.h"
+
+namespace qs {
+
+namespace {
+
+// i^k times the Hermitian string i^|x & z| X^x Z^z
+struct Pauli {
+    uint64_t x = 0, z = 0;
+    int k = 0;
+};
+
+Pauli mul(const Pauli &a, const Pauli &b) {
+    Pauli r;
+    r.x = a.x ^ b.x;
+    r.z = a.z ^ b.z;
+    r.k = (a.k + b.k + __builtin_popcountll(a.x & a.z) + __builtin_popcountll(b.x & b.z) +
+           2 * __builtin_popcountll(a.z & b.x) - __builtin_popcountll(r.x & r.z)) & 3;
+    return r;
+}
+
+bool anticommute(uint64_t ax, uint64_t az, uint64_t bx, uint64_t bz) {
+    return __builtin_popcountll((ax & bz) ^ (az & bx)) & 1;
+}
+
+// A string on up to two qubits, as gates name it.
+struct Axis {
+    char l[2];
+    int q[2];
+    int k;
+};
+
+// The quarter turns of a rotation by theta: 1, 2 or 3 if theta is that many
+// times pi/2 modulo 2 pi, to rounding, and 0 otherwise (whole turns included).
+int quarter_turns(double theta) {
+    const double t = theta / (M_PI / 2), r = std::nearbyint(t);
+    if (std::fabs(r) > 3.0 || std::fabs(t - r) > 1e-15 * std::fabs(t)) return 0;
+    return int(r) & 3;
+}
+
+struct Frame {
+    struct Node {
+        int kind, q0, q1;
+        double theta;
+        bool alive;
+    };
+    std::vector<Pauli> X, Z;
+    std::vector<Node> nodes;
+    std::vector<std::vector<int>> wire;   // live nodes on each qubit, in order
+    size_t live = 0;
+
+    explicit Frame(int n) : X(size_t(n)), Z(size_t(n)), wire(size_t(n)) { reset(); }
+    void reset() {
+        for (size_t q = 0; q < X.size(); q++) {
+            X[q] = Pauli{uint64_t(1) << q, 0, 0};
+            Z[q] = Pauli{0, uint64_t(1) << q, 0};
+            wire[q].clear();
+        }
+        nodes.clear();
+        live = 0;
+    }
+    // C^dagger P C
+    Pauli image(const Axis &a) const {
+        Pauli r;
+        for (int j = 0; j < a.k; j++) {
+            const size_t q = size_t(a.q[j]);
+            if (a.l[j] == 'X') r = mul(r, X[q]);
+            else if (a.l[j] == 'Z') r = mul(r, Z[q]);
+            else {
+                r = mul(r, mul(X[q], Z[q]));
+                r.k = (r.k + 1) & 3;   // Y = i X Z
+            }
+        }
+        return r;
+    }
+    // images after a turn of `turns` quarters about the axis joins the frame
+    void turn(const Axis &a, int turns) {
+        const Pauli p = image(a);
+        for (int j = 0; j < a.k; j++) {
+            const size_t q = size_t(a.q[j]);
+            for (int s = 0; s < 2; s++) {
+                if ((a.l[j] == 'X' && s == 0) || (a.l[j] == 'Z' && s == 1)) continue;   // commutes
+                Pauli &row = s == 0 ? X[q] : Z[q];
+                if (turns == 2) row.k = (row.k + 2) & 3;
+                else {
+                    row = mul(row, p);
+                    row.k = (row.k + (turns == 1 ? 3 : 1)) & 3;
+                }
+            }
+        }
+    }
+    // Record a gate of the frame: it removes the last live node of all of its
+    // wires if that is its inverse, else it becomes one.
+    void push(int kind, int q0, int q1, double theta) {
+        const int nq = q1 >= 0 ? 2 : 1;
+        std::vector<int> &w0 = wire[size_t(q0)];
+        if (!w0.empty() && (nq == 1 || (!wire[size_t(q1)].empty() && wire[size_t(q1)].back() == w0.back()))) {
+            Node &h = nodes[size_t(w0.back())];
+            const bool same_q = (h.q0 == q0 && h.q1 == q1) ||
+                                ((kind == QSIM_G_CZ || kind == QSIM_G_SWAP || kind == QSIM_G_RXX || kind == QSIM_G_RZZ) &&
+                                 h.q0 == q1 && h.q1 == q0);
+            bool inverse = same_q && h.kind == kind && h.theta == -theta;
+            if (kind == QSIM_G_S || kind == QSIM_G_SDG)
+                inverse = same_q && h.kind == (kind == QSIM_G_S ? QSIM_G_SDG : QSIM_G_S);
+            if (kind == QSIM_G_SX) inverse = false;
+            if (inverse) {
+                h.alive = false;
+                live--;
+                w0.pop_back();
+                if (nq == 2) wire[size_t(q1)].pop_back();
+                return;
+            }
+        }
+        w0.push_back(int(nodes.size()));
+        if (nq == 2) wire[size_t(q1)].push_back(int(nodes.size()));
+        nodes.push_back({kind, q0, q1, theta, true});
+        live++;
+    }
+};
+
+}  // namespace
+
+bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, const std::vector<int> &op_epoch,
+                 const GateInputs &in, bool keep_params, PauliProgram *out) {
+    out->ops.clear();
+    out->op_epoch.clear();
+    out->phase = 0.0;
+    if (n > 48) return false;   // the device record keeps 48 bits of a Z mask
+    Frame f(n);
+    size_t extra = 0;
+    int epoch = 0;
+    out->ops.reserve(op_gate.size() / 4 + 16);
+    // a rotation exp(-i phi P) about an axis seen through the frame
+    auto emit = [&](const Pauli &p, double phi, int slot) {
+        PauliOp o;
+        o.x = p.x;
+        o.z = p.z;
+        o.sign = (p.k & 2) ? -1.0 : 1.0;
+        o.phi = phi;
+        o.slot = slot;
+        out->ops.push_back(o);
+        out->op_epoch.push_back(epoch);
+    };
+    auto one = [](char l, int q) { return Axis{{l, 'I'}, {q, -1}, 1}; };
+    auto two = [](char a, int qa, char b, int qb) { return Axis{{a, b}, {qa, qb}, 2}; };
+    // the live gates of the frame, as rotations of phi
+    auto flush = [&]() {
+        if (f.live) {
+            std::vector<Frame::Node> nodes;
+            for (const Frame::Node &h : f.nodes)
+                if (h.alive) nodes.push_back(h);
+            f.reset();
+            const size_t before = out->ops.size();
+            auto rot = [&](const Axis &a, double theta) { emit(f.image(a), theta / 2, -1); };
+            const double h2 = M_PI / 2;
+            auto cx = [&](int c, int t) {
+                rot(one('Z', c), h2);
+                rot(one('X', t), h2);
+                rot(two('Z', c, 'X', t), -h2);
+                out->phase += M_PI / 4;
+            };
+            for (const Frame::Node &h : nodes) {
+                switch (h.kind) {
+                case QSIM_G_H:
+                    rot(one('Z', h.q0), h2);
+                    rot(one('X', h.q0), h2);
+                    rot(one('Z', h.q0), h2);
+                    out->phase += h2;
+                    break;
+                case QSIM_G_X: rot(one('X', h.q0), M_PI); out->phase += h2; break;
+                case QSIM_G_Y: rot(one('Y', h.q0), M_PI); out->phase += h2; break;
+                case QSIM_G_Z: rot(one('Z', h.q0), M_PI); out->phase += h2; break;
+                case QSIM_G_S: rot(one('Z', h.q0), h2); out->phase += M_PI / 4; break;
+                case QSIM_G_SDG: rot(one('Z', h.q0), -h2); out->phase -= M_PI / 4; break;
+                case QSIM_G_SX: rot(one('X', h.q0), h2); out->phase += M_PI / 4; break;
+                case QSIM_G_RX: rot(one('X', h.q0), h.theta); break;
+                case QSIM_G_RY: rot(one('Y', h.q0), h.theta); break;
+                case QSIM_G_RZ: rot(one('Z', h.q0), h.theta); break;
+                case QSIM_G_RXX: rot(two('X', h.q0, 'X', h.q1), h.theta); break;
+                case QSIM_G_RZZ: rot(two('Z', h.q0, 'Z', h.q1), h.theta); break;
+                case QSIM_G_CX: cx(h.q0, h.q1); break;
+                case QSIM_G_CY:
+                    rot(one('Z', h.q0), h2);
+                    rot(one('Y', h.q1), h2);
+                    rot(two('Z', h.q0, 'Y', h.q1), -h2);
+                    out->phase += M_PI / 4;
+                    break;
+                case QSIM_G_CZ:
+                    rot(one('Z', h.q0), h2);
+                    rot(one('Z', h.q1), h2);
+                    rot(two('Z', h.q0, 'Z', h.q1), -h2);
+                    out->phase += M_PI / 4;
+                    break;
+                default:   // SWAP
+                    cx(h.q0, h.q1);
+                    cx(h.q1, h.q0);
+                    cx(h.q0, h.q1);
+                    break;
+                }
+            }
+            extra += out->ops.size() - before;
+        }
+        f.reset();
+    };
+    for (size_t j = 0; j < op_gate.size(); j++) {
+        const qsim_gate &gi = g[op_gate[j]];
+        if (op_epoch[j] != epoch) {
+            flush();
+            epoch = op_epoch[j];
+        }
+        // records that the matrix lowering refuses are left to it
+        const int k = gi.nq;
+        const int kind = gi.kind;
+        const bool wide = kind >= QSIM_G_CX && kind <= QSIM_G_RZZ;
+        if (k != (wide ? 2 : 1) || (!wide && (kind > QSIM_G_U3 || kind < QSIM_G_ID))) return false;
+        const int q0 = gi.q[0], q1 = wide ? gi.q[1] : -1;
+        if (q0 < 0 || q0 >= n || (wide && (q1 < 0 || q1 >= n || q1 == q0))) return false;
+        for (double v : gi.theta)
+            if (!std::isfinite(v)) return false;
+        double th = gi.theta[0];
+        const bool linear = kind == QSIM_G_RX || kind == QSIM_G_RY || kind == QSIM_G_RZ || kind == QSIM_G_RXX ||
+                            kind == QSIM_G_RZZ;
+        int slot = -1;
+        if (gi.slot >= 0) {
+            if (size_t(gi.slot) >= in.n_params) return false;
+            if (keep_params) {
+                if (!linear) return false;
+                slot = gi.slot;
+            } else {
+                if (!in.params || !std::isfinite(in.params[gi.slot])) return false;
+                th = in.params[gi.slot];
+            }
+        }
+        auto rotation = [&](const Axis &a, double theta) {
+            const int turns = slot < 0 ? quarter_turns(theta) : 0;
+            if (turns) {
+                f.turn(a, turns);
+                f.push(kind, q0, q1, theta);
+            } else {
+                emit(f.image(a), theta / 2, slot);
+            }
+        };
+        switch (kind) {
+        case QSIM_G_ID: break;
+        case QSIM_G_H:
+            std::swap(f.X[size_t(q0)], f.Z[size_t(q0)]);
+            f.push(kind, q0, -1, 0.0);
+            break;
+        case QSIM_G_X: f.turn(one('X', q0), 2); f.push(kind, q0, -1, 0.0); break;
+        case QSIM_G_Y: f.turn(one('Y', q0), 2); f.push(kind, q0, -1, 0.0); break;
+        case QSIM_G_Z: f.turn(one('Z', q0), 2); f.push(kind, q0, -1, 0.0); break;
+        case QSIM_G_S: f.turn(one('Z', q0), 1); f.push(kind, q0, -1, 0.0); break;
+        case QSIM_G_SDG: f.turn(one('Z', q0), 3); f.push(kind, q0, -1, 0.0); break;
+        case QSIM_G_SX: f.turn(one('X', q0), 1); f.push(kind, q0, -1, 0.0); break;
+        case QSIM_G_T: emit(f.image(one('Z', q0)), M_PI / 8, -1); out->phase += M_PI / 8; break;
+        case QSIM_G_TDG: emit(f.image(one('Z', q0)), -M_PI / 8, -1); out->phase -= M_PI / 8; break;
+        case QSIM_G_RX: rotation(one('X', q0), th); break;
+        case QSIM_G_RY: rotation(one('Y', q0), th); break;
+        case QSIM_G_RZ: rotation(one('Z', q0), th); break;
+        case QSIM_G_RXX: rotation(two('X', q0, 'X', q1), th); break;
+        case QSIM_G_RZZ: rotation(two('Z', q0, 'Z', q1), th); break;
+        case QSIM_G_U1: emit(f.image(one('Z', q0)), th / 2, -1); out->phase += th / 2; break;
+        case QSIM_G_U2:
+        case QSIM_G_U3: {
+            // e^{i (ph + la) / 2} Rz(ph) Ry(t) Rz(la)
+            const double t = kind == QSIM_G_U2 ? M_PI / 2 : th;
+            const double ph = kind == QSIM_G_U2 ? th : gi.theta[1];
+            const double la = kind == QSIM_G_U2 ? gi.theta[1] : gi.theta[2];
+            emit(f.image(one('Z', q0)), la / 2, -1);
+            emit(f.image(one('Y', q0)), t / 2, -1);
+            emit(f.image(one('Z', q0)), ph / 2, -1);
+            out->phase += (ph + la) / 2;
+            break;
+        }
+        case QSIM_G_CX: {
+            Pauli &xc = f.X[size_t(q0)], &zt = f.Z[size_t(q1)];
+            xc = mul(xc, f.X[size_t(q1)]);
+            zt = mul(f.Z[size_t(q0)], zt);
+            f.push(kind, q0, q1, 0.0);
+            break;
+        }
+        case QSIM_G_CY: {
+            const Pauli y = f.image(one('Y', q1));
+            f.X[size_t(q0)] = mul(f.X[size_t(q0)], y);
+            f.X[size_t(q1)] = mul(f.Z[size_t(q0)], f.X[size_t(q1)]);
+            f.Z[size_t(q1)] = mul(f.Z[size_t(q0)], f.Z[size_t(q1)]);
+            f.push(kind, q0, q1, 0.0);
+            break;
+        }
+        case QSIM_G_CZ: {
+            const Pauli zc = f.Z[size_t(q0)], zt = f.Z[size_t(q1)];
+            f.X[size_t(q0)] = mul(f.X[size_t(q0)], zt);
+            f.X[size_t(q1)] = mul(f.X[size_t(q1)], zc);
+            f.push(kind, q0, q1, 0.0);
+            break;
+        }
+        case QSIM_G_SWAP:
+            std::swap(f.X[size_t(q0)], f.X[size_t(q1)]);
+            std::swap(f.Z[size_t(q0)], f.Z[size_t(q1)]);
+            f.push(kind, q0, q1, 0.0);
+            break;
+        case QSIM_G_CRX:
+        case QSIM_G_CRY:
+        case QSIM_G_CRZ: {
+            // exp(-i theta/2 (1 - Z_c)/2 P)
+            const char l = kind == QSIM_G_CRX ? 'X' : kind == QSIM_G_CRY ? 'Y' : 'Z';
+            emit(f.image(one(l, q1)), th / 4, -1);
+            emit(f.image(two('Z', q0, l, q1)), -th / 4, -1);
+            break;
+        }
+        case QSIM_G_CU1:
+            // exp(i theta (1 - Z_c)(1 - Z_t) / 4)
+            emit(f.image(one('Z', q0)), th / 4, -1);
+            emit(f.image(one('Z', q1)), th / 4, -1);
+            emit(f.image(two('Z', q0, 'Z', q1)), -th / 4, -1);
+            out->phase += th / 4;
+            break;
+        default: return false;   // CH, CU3: no product of few rotations
+        }
+    }
+    flush();
+    // gates left in the frame are emitted at up to nine rotations each: with
+    // many of them the fused operators of the matrix lowering do less
+    return 4 * extra <= out->ops.size();
+}
+
+// -------------------------------------------------------------- planning
+namespace {
+
+// A subspace of GF(2)^n in reduced echelon form: vector v[j] is the only one
+// with bit piv[j].
+struct Span {
+    uint64_t v[16];
+    int piv[16];
+    int d = 0;
+    uint64_t pm = 0;                 // pivot bits
+    int8_t at[64];                   // vector of each pivot bit
+
+    uint64_t reduce(uint64_t x) const {
+        for (uint64_t m = x & pm; m; m &= m - 1) x ^= v[at[__builtin_ctzll(m)]];
+        return x;
+    }
+    // adds x, already reduced and not 0
+    void add(uint64_t x) {
+        const int p = 63 - __builtin_clzll(x);
+        for (int j = 0; j < d; j++)
+            if ((v[j] >> p) & 1) v[j] ^= x;
+        v[d] = x;
+        piv[d] = p;
+        at[p] = int8_t(d);
+        pm |= uint64_t(1) << p;
+        d++;
+    }
+    // the coordinates of a member: its pivot bits
+    uint32_t coords(uint64_t x) const {
+        uint32_t c = 0;
+        for (int j = 0; j < d; j++) c |= uint32_t((x >> piv[j]) & 1) << j;
+        return c;
+    }
+};
+
+// The same for small masks, for tests of independence only.
+struct Rank {
+    uint32_t v[32];
+    uint32_t have = 0;
+    // whether x is independent of what was added (and adds it)
+    bool add(uint32_t x) {
+        while (x) {
+            const int p = 31 - __builtin_clz(x);
+            if (!((have >> p) & 1)) {
+                v[p] = x;
+                have |= 1u << p;
+                return true;
+            }
+            x ^= v[p];
+        }
+        return false;
+    }
+};
+
+// LDS slot of tile coordinates c: the coordinates from 5 up are folded into
+// the low 5 bits (the banks: 32 elements of 8 bytes or 16 of 16), so that a
+// layout finds lanes on distinct banks whichever coordinates its registers
+// take.  Linear and a bijection.
+constexpr uint32_t kBank[9] = {1, 2, 4, 8, 19, 22, 5, 10, 31};
+uint32_t span_slot(uint32_t c) {
+    uint32_t s = c;
+    for (int j = 5; j < 14; j++)
+        if ((c >> j) & 1) s ^= kBank[j - 5];
+    return s;
+}
+
+// Rotations skipped by one pass after which it is closed: a later one has to
+// commute with all of them, and a longer list finds hardly any on the
+// benchmark circuits.
+constexpr size_t kSkipMax = 64;
+// Rotations of one pass: each may grow an amplitude by sqrt 2 before the pass
+// scales its result.
+constexpr size_t kPassMax = 96;
+
+}  // namespace
+
+void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, uint32_t op_bytes, size_t meta_budget, int window,
+                bool full, int first, int last, std::vector<Pass> *passes) {
+    const size_t N = size_t(last - first);
+    std::vector<int> nxt(N + 1), prv(N + 1);
+    const int head = int(N);
+    for (size_t i = 0; i <= N; i++) {
+        nxt[i] = i < N ? int(i) + 1 : 0;
+        prv[i] = i > 0 ? int(i) - 1 : int(N);
+    }
+    if (N == 0) return;
+    const PauliOp *ops = P.ops.data() + first;
+    struct Mask {
+        uint64_t x, z;
+    };
+    std::vector<Mask> skipped;
+    skipped.reserve(kSkipMax + 1);
+    // may o run before every skipped rotation?
+    auto passes_by = [&](const PauliOp &o) {
+        for (const Mask &s : skipped)
+            if (anticommute(s.x, s.z, o.x, o.z)) return false;
+        return true;
+    };
+    while (nxt[size_t(head)] != head) {
+        Span T;
+        for (int q = 0; q < c; q++) T.add(uint64_t(1) << q);
+        // the space with o in it; false if it grows beyond t dimensions
+        auto grow = [&](const PauliOp &o) {
+            if (!full) {
+                const uint64_t r = T.reduce(o.x);
+                if (r && T.d >= t) return false;
+                if (r) T.add(r);
+                return true;
+            }
+            Span U = T;
+            for (uint64_t m = o.x | o.z; m; m &= m - 1) {
+                const uint64_t r = U.reduce(m & (~m + 1));
+                if (r && U.d >= t) return false;
+                if (r) U.add(r);
+            }
+            T = U;
+            return true;
+        };
+        std::vector<int> sel;
+        skipped.clear();
+        size_t meta = 0;
+        int scanned = 0;
+        for (int i = nxt[size_t(head)]; i != head && scanned < window && skipped.size() < kSkipMax && sel.size() < kPassMax;
+             i = nxt[size_t(i)], scanned++) {
+            const PauliOp &o = ops[i];
+            // a rotation may open a stage of its own: its record and one more
+            const size_t need = op_bytes + sizeof(DevOp);
+            if ((sel.empty() || meta + need <= meta_budget) && passes_by(o) && grow(o)) {
+                sel.push_back(i);
+                meta += need;
+            } else {
+                skipped.push_back({o.x, o.z});
+            }
+        }
+        for (int i : sel) {
+            nxt[size_t(prv[size_t(i)])] = nxt[size_t(i)];
+            prv[size_t(nxt[size_t(i)])] = prv[size_t(i)];
+        }
+        for (int q = 0; q < n && T.d < t; q++) {
+            const uint64_t r = T.reduce(uint64_t(1) << q);
+            if (r) T.add(r);
+        }
+        Pass p;
+        p.kind = Pass::TILE;
+        p.t = t;
+        p.c = c;
+        p.span = true;
+        p.tile_mask = T.pm;
+        // stages of at most `regs` independent X masks
+        std::vector<int> left = sel, later;
+        while (!left.empty()) {
+            Span R;
+            SpanStage st;
+            std::vector<uint64_t> dirs;   // the masks that opened a dimension
+            skipped.clear();
+            later.clear();
+            for (int i : left) {
+                const PauliOp &o = ops[i];
+                // its X mask is a register bit of its own, or opens one
+                const bool have = !o.x || std::find(dirs.begin(), dirs.end(), o.x) != dirs.end();
+                const uint64_t r = have ? 0 : R.reduce(o.x);
+                if ((have || (r && R.d < regs)) && passes_by(o)) {
+                    if (r) {
+                        R.add(r);
+                        dirs.push_back(o.x);
+                    }
+                    st.ops.push_back(first + i);
+                } else {
+                    skipped.push_back({o.x, o.z});
+                    later.push_back(i);
+                }
+            }
+            left.swap(later);
+            // layout: thread bits, then register bits, as tile coordinates
+            const int logt = t - regs;
+            uint32_t reg[8];
+            int nr = 0;
+            Rank all;
+            for (uint64_t x : dirs) {
+                reg[nr] = T.coords(x);
+                all.add(reg[nr++]);
+            }
+            // spare register bits: the highest coordinates that are free
+            for (int j = t - 1; j >= 0 && nr < regs; j--)
+                if (all.add(1u << j)) reg[nr++] = 1u << j;
+            // lanes: the low qubits first (contiguous chunks in memory), then
+            // coordinates that bring the lanes of an LDS access to distinct
+            // banks, then the others
+            int nt = 0;
+            uint32_t thr[16], taken = 0;
+            Rank bank;
+            auto take = [&](int j) {
+                thr[nt++] = 1u << j;
+                taken |= 1u << j;
+            };
+            for (int j = 0; j < c && nt < logt; j++) {
+                Rank probe = all;
+                if (!probe.add(1u << j)) continue;
+                all = probe;
+                bank.add(span_slot(1u << j) & 31u);
+                take(j);
+            }
+            for (int j = c; j < t && nt < std::min(5, logt); j++) {
+                if ((taken >> j) & 1) continue;
+                Rank probe = all, pb = bank;
+                if (!probe.add(1u << j) || !pb.add(span_slot(1u << j) & 31u)) continue;
+                all = probe;
+                bank = pb;
+                take(j);
+            }
+            for (int j = 0; j < t && nt < logt; j++)
+                if (!((taken >> j) & 1) && all.add(1u << j)) take(j);
+            for (int j = 0; j < logt; j++) st.layout[j] = uint16_t(thr[j]);
+            for (int j = 0; j < regs; j++) st.layout[logt + j] = uint16_t(reg[j]);
+            p.stages.push_back(std::move(st));
+        }
+        for (int j = 0; j < t; j++) p.span_v[j] = T.v[j];
+        passes->push_back(std::move(p));
+    }
+}
+
+uint64_t span_vector(const Pass &p, uint32_t coords) {
+    uint64_t x = 0;
+    for (int j = 0; j < p.t; j++)
+        if ((coords >> j) & 1) x ^= p.span_v[j];
+    return x;
+}
+
+int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, PackedPlan *out) {
+    const int t = p.t, logt = t - regs;
+    for (const SpanStage &st : p.stages) {
+        DevOp h{};
+        h.kind = DEVOP_STAGE;
+        h.kx = uint8_t(t);
+        uint8_t *raw = reinterpret_cast<uint8_t *>(&h);
+        for (int j = 0; j < t; j++) {
+            const uint16_t s = uint16_t(span_slot(st.layout[j]));
+            std::memcpy(raw + (j < 7 ? 2 * j : 16 + 2 * (j - 7)), &s, 2);
+        }
+        out->ops.push_back(h);
+        out->op_np.push_back(0);
+        for (int j = 0; j < 3; j++) out->op_slots.push_back(-1);
+        // the layout's positions as vectors of the state's index
+        uint64_t V[16];
+        for (int j = 0; j < t; j++) V[j] = span_vector(p, st.layout[j]);
+        for (int idx : st.ops) {
+            const PauliOp &o = P.ops[size_t(idx)];
+            // the register bit that the X mask is (none for a diagonal)
+            int bit = -1;
+            for (int r = 0; r < regs; r++)
+                if (V[logt + r] == o.x) bit = r;
+            if (o.x && bit < 0) return QSIM_E_ARG;
+            const uint32_t m = o.x ? 1u << bit : 0u;
+            const int ny = __builtin_popcountll(o.x & o.z) & 3;
+            DevOp d{};
+            d.kind = DEVOP_PAULI;
+            d.coef = uint32_t(out->coefs.size());
+            d.k = uint8_t(o.x ? 2 * bit + (ny & 1) : 2 * regs);
+            uint32_t zr = 0, zt = 0;
+            for (int b = 0; b < regs; b++) zr |= uint32_t(__builtin_popcountll(o.z & V[logt + b]) & 1) << b;
+            for (int b = 0; b < logt; b++) zt |= uint32_t(__builtin_popcountll(o.z & V[b]) & 1) << b;
+            // the signs of the register pairs {r, r ^ m} in ascending order of
+            // r < r ^ m, each against the pair before it
+            for (uint32_t r = 0, k = 0, last = 0; r < (1u << regs); r++) {
+                if (m && r > (r ^ m)) continue;
+                const uint32_t sgn = uint32_t(__builtin_popcount(r & zr) & 1);
+                d.present |= (sgn ^ last) << k++;
+                last = sgn;
+            }
+            d.slot[0] = uint16_t(zt);
+            for (int b = 0; b < 3; b++) d.slot[1 + b] = uint16_t((o.z >> (16 * b)) & 0xffff);
+            // y[i] = a x[i] + b (-1)^(i . z) x[i ^ x] with a = cos phi and
+            // b = -i sin phi (-i)^ny: t is its real or imaginary part
+            const double kappa = (ny & 2) ? 1.0 : -1.0;
+            out->ops.push_back(d);
+            if (o.slot >= 0) {
+                // bound per state: the sign of t (four entries of template)
+                out->coefs.push_back(cd(kappa * o.sign, 0.0));
+                for (int j = 0; j < 3; j++) out->coefs.push_back(cd(0.0, 0.0));
+                out->op_np.push_back(1);
+                out->op_slots.push_back(o.slot);
+            } else {
+                cd e[2];
+                pauli_coefs(std::cos(o.phi), kappa * o.sign * std::sin(o.phi), single, e);
+                out->coefs.push_back(e[0]);
+                out->coefs.push_back(e[1]);
+                out->op_np.push_back(0);
+                out->op_slots.push_back(-1);
+            }
+            out->op_slots.push_back(-1);
+            out->op_slots.push_back(-1);
+            out->terms += m ? 2 : 1;
+        }
+    }
+    return QSIM_OK;
+}
+
+}  // namespace qs

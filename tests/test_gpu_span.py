@@ -1,0 +1,86 @@
+"""Passes of Pauli rotations (k_span) against the oracle: every tile width,
+one and several stages, angles whose cosine vanishes, initial |0...0>, per-state
+angles, and measurements between passes."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from test_host_span import mixed_circuit, norm_error, spanned
+
+pytestmark = pytest.mark.gpu
+# norm of the rounding errors: at most two roundings per rotation and at most
+# nine rotations per gate, each 2^-53 or 2^-24 of an amplitude
+EPS = {"complex128": 1.2e-16, "complex64": 6e-8}
+
+
+def tol(dtype, gates):
+    return 2 * 9 * gates * EPS[dtype]
+
+
+@pytest.fixture(scope="module")
+def Q():
+    from paper_2310_17739_amd import qsim
+    return qsim
+
+
+@pytest.mark.parametrize("dtype,n,tile", [("complex128", 14, 10), ("complex128", 15, 11), ("complex128", 16, 12),
+                                          ("complex128", 17, 13), ("complex64", 15, 10), ("complex64", 16, 11),
+                                          ("complex64", 15, 12), ("complex64", 16, 13), ("complex64", 17, 14)])
+@pytest.mark.parametrize("count", [1, 5, 150])
+def test_tile_widths(Q, dtype, n, tile, count):
+    g = mixed_circuit(n, count, seed=tile + count, p_clifford=0.0 if count < 10 else 0.04)
+    psi0 = W.random_state(n, 7)
+    print(f"span tile dtype={dtype} n={n} tile={tile} gates={count}", flush=True)
+    sv = Q.StateVector(n, dtype)
+    sv.qsim_set_state(psi0)
+    sv.qsim_apply(g, tile_qubits=tile)
+    assert spanned(sv.qsim_last_stats())
+    want, _, _ = oracle.run(n, g, psi=psi0.astype(dtype).astype(np.complex128))
+    assert norm_error(sv.qsim_get_state(), want) < tol(dtype, count)
+    sv.close()
+
+
+@pytest.mark.parametrize("dtype", ["complex128", "complex64"])
+def test_templates_with_any_angles(Q, dtype):
+    """Per-state angles, bound on the device, from 0 to beyond a whole turn."""
+    n, nexp, states = 15, 60, 5
+    rng = np.random.default_rng(2)
+    recs = []
+    for e, (qs, letters) in enumerate(W.pauli_strings(n, nexp, rng)):
+        W.compile_pauli_exponential(qs, letters, 0.0, e, recs)
+    g = W.gates(recs)
+    th = rng.uniform(-7, 7, (states, nexp))
+    th[0] = np.pi
+    th[1, ::2] = 0.0
+    th[2] = np.pi / 2
+    print(f"span template dtype={dtype}", flush=True)
+    b = Q.Batch([{"n": n, "n_states": states, "gates": g, "params": th}], dtype=dtype, tile_qubits=11)
+    assert spanned(b.qsim_batch_group_stats(0))
+    b.qsim_batch_run()
+    assert np.all(b.qsim_batch_results(0)["status"] == 0)
+    for s in range(states):
+        want, _, _ = oracle.run(n, g, params=th[s])
+        assert norm_error(b.qsim_batch_get_state(0, s), want) < tol(dtype, nexp)
+    b.close()
+
+
+@pytest.mark.parametrize("dtype", ["complex128", "complex64"])
+def test_measurements_between_passes(Q, dtype):
+    """The projection filter as a batch: assertions and resets between the
+    passes of rotations."""
+    g, info = W.projection_filter(14, 3, seed=5, delta=0.3)
+    n = info["n"]
+    print(f"span filter dtype={dtype}", flush=True)
+    b = Q.Batch([{"n": n, "n_states": 2, "gates": g, "n_slots": 3}], dtype=dtype, tile_qubits=11)
+    assert spanned(b.qsim_batch_group_stats(0))
+    b.qsim_batch_run()
+    r = b.qsim_batch_results(0)
+    want, _, p = oracle.run(n, g)
+    assert np.all(r["status"] == 0)
+    for s in range(2):
+        # a projection onto a branch of probability p magnifies an error by 1 / sqrt(p)
+        grow = 1 / np.sqrt(np.prod(p))
+        assert np.max(np.abs(r["probs"][s] - p)) < 2 * grow * tol(dtype, 3 * 16)
+        assert norm_error(b.qsim_batch_get_state(0, s), want) < grow * tol(dtype, 3 * 16)
+    b.close()
