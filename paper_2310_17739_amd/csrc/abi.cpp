@@ -243,13 +243,13 @@ int validate_span_pass(int n, int dtype, const Compiled &c, size_t i) {
     const uint32_t rb = p.pass_begin[i], re = p.pass_begin[i + 1];
     if (rb >= re || re > p.ops.size() || p.coef_begin[i] > p.coef_begin[i + 1] || p.coef_begin[i + 1] > p.coefs.size())
         return QSIM_E_ARG;
-    uint32_t stages = 0, cf = p.coef_begin[i];
+    uint32_t stages = 0;
     for (uint32_t j = rb; j < re; j++) {
         const DevOp &o = p.ops[j];
         if (o.kind == DEVOP_STAGE) {
             const uint8_t *raw = reinterpret_cast<const uint8_t *>(&o);
             uint64_t slots[64] = {0};
-            if (o.kx != t) return QSIM_E_ARG;
+            if (o.kx != stages || stages >= 255) return QSIM_E_ARG;
             for (int x = 0; x < t; x++) {
                 uint16_t s;
                 std::memcpy(&s, raw + (x < 7 ? 2 * x : 16 + 2 * (x - 7)), 2);
@@ -257,20 +257,17 @@ int validate_span_pass(int n, int dtype, const Compiled &c, size_t i) {
             }
             stages++;
         } else if (o.kind == DEVOP_PAULI) {
-            const size_t need = size_t(2) << p.op_np[j];
+            const size_t need = 2;
             if (!stages || o.k > 2 * kSpanRegs || (o.slot[0] >> logt) ||
-                (o.present >> (1 << kSpanRegs)) || p.op_np[j] < 0 || p.op_np[j] > 1)
+                (o.present >> (1 << kSpanRegs)) || p.op_np[j] != 0)
                 return QSIM_E_ARG;
-            // the kernel takes the coefficients in order
-            if (o.coef != cf || o.coef + need > p.coef_begin[i + 1]) return QSIM_E_ARG;
-            cf += uint32_t(need);
+            if (o.coef < p.coef_begin[i] || o.coef + need > p.coef_begin[i + 1]) return QSIM_E_ARG;
         } else {
             return QSIM_E_ARG;
         }
     }
     if (p.ops[rb].kind != DEVOP_STAGE || sa.tile_bytes != (stages > 1 ? uint32_t(elem_bytes(dtype) << t) : 0u) ||
-        qk::span_lds_bytes(elem_bytes(dtype), sa.tile_bytes, re - rb, p.coef_begin[i + 1] - p.coef_begin[i]) >
-            qk::max_lds_bytes())
+        sa.nstage != stages || qk::span_lds_bytes(sa.tile_bytes, re - rb, stages) > qk::max_lds_bytes())
         return QSIM_E_ARG;
     return QSIM_OK;
 }
@@ -402,8 +399,7 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
     for (int e = 0; e < L.n_epochs; e++) {
         size_t end = at;
         while (end < P.ops.size() && P.op_epoch[end] == e) end++;
-        plan_spans(n, P, t, pc.low_qubits, kSpanRegs, uint32_t(sizeof(DevOp) + 2 * elem), pc.meta_budget, pc.window,
-                   pc.full_support, int(at), int(end), &passes);
+        plan_spans(n, P, t, pc.low_qubits, kSpanRegs, pc.meta_budget, pc.window, pc.full_support, int(at), int(end), &passes);
         at = end;
         for (; m < L.meas.size() && L.meas[m].epoch == e; m++) {
             Pass p;
@@ -435,6 +431,7 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
                 sa.store_v[j] = span_vector(p, p.stages.back().layout[j]);
             }
             sa.tile_bytes = p.stages.size() > 1 ? uint32_t(elem << p.t) : 0u;
+            sa.nstage = uint32_t(p.stages.size());
             sa.phase_re = 1.0;
             if (!phased) {
                 sa.phase_re = std::cos(P.phase);
@@ -705,8 +702,7 @@ int enqueue_pass(const Compiled &c, size_t i, const DevOp *d_ops, const void *d_
         return QSIM_OK;
     }
     if (pi.span)
-        return qk::launch_span(dtype, state, sstride, nstates, pi.sa, d_ops, ob, oe, d_coefs, cb, ce, cstride, status,
-                               flags, st);
+        return qk::launch_span(dtype, state, sstride, nstates, pi.sa, d_ops, ob, oe, d_coefs, cstride, status, flags, st);
     if (pi.reg)
         return qk::launch_reg(dtype, state, sstride, nstates, pi.ra, d_ops, ob, oe, d_coefs, cb, ce, cstride, status,
                               flags, st);

@@ -278,7 +278,7 @@ enum { DEVOP_MAT = 0, DEVOP_MEASURE = 1, DEVOP_ASSERT0 = 2, DEVOP_RESET = 3,
        DEVOP_MEASURE_RESET = 8,  // a measurement followed by a reset of the same qubit
        // span passes:
        DEVOP_STAGE = 9,   // the LDS slots of the layout's positions, 16 bits each, in bytes 0..13
-                          // and 16..29; kx = their number
+                          // and 16..29; kx = the stage's number
        DEVOP_PAULI = 10   // rotation: k = 2 b + 1 for a real t and 2 b for an imaginary one on
                           // register bit b, 2 kSpanRegs for a diagonal; bit j of present = whether the sign of register pair j
                           // (in ascending order of the smaller register) differs from that of
@@ -334,10 +334,9 @@ constexpr int kSpanRegs = 4;
 inline bool span_tile_ok(int t) { return t >= 6 + kSpanRegs && t <= 14; }
 
 // Span passes of the rotations [first, last) of P: tiles of t dimensions that
-// hold the low c qubits.  op_bytes: LDS bytes of a rotation (record and
-// coefficients); full: a tile holds every qubit of its rotations (each string has
+// hold the low c qubits.  full: a tile holds every qubit of its rotations (each string has
 // at most t - c of them).
-void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, uint32_t op_bytes, size_t meta_budget, int window,
+void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t meta_budget, int window,
                 bool full, int first, int last, std::vector<Pass> *passes);
 // Appends the pass's records and coefficients.
 int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, PackedPlan *out);

@@ -112,7 +112,7 @@ struct SpanArgs {
     double phase_re, phase_im;
     int32_t n, t;
     uint32_t tile_bytes;     // LDS bytes of the tile: 0 for a pass with one stage
-    int32_t pad;
+    uint32_t nstage;         // stages of the pass
 };
 
 // Base index of the tile of workgroup bx: its bits in the rest bits, ascending.
@@ -127,18 +127,18 @@ __host__ __device__ inline uint64_t span_base(uint64_t bx, const SpanArgs &sa) {
     return r;
 }
 
-// LDS bytes of a span pass (the padding covers the kernel's read-ahead of a
-// record and its coefficients).
-inline size_t span_lds_bytes(size_t elem, size_t tile_bytes, uint32_t nrec, uint32_t ncoef) {
-    return tile_bytes + size_t(nrec) * sizeof(qs::DevOp) + size_t(ncoef) * elem + sizeof(qs::DevOp) + 2 * elem;
+// LDS bytes of a span pass: the tile, an entry per record (and one that the
+// kernel reads ahead), a layout per stage and a factor per record.
+inline size_t span_lds_bytes(size_t tile_bytes, uint32_t nrec, uint32_t nstage) {
+    return tile_bytes + 16 * (size_t(nrec) + 1) + 32 * size_t(nstage) + 8 * size_t(nrec);
 }
 
 // Sets the kernels' LDS limit; false if one declares static LDS (its tile must
 // start at LDS byte 0).
 bool init_span_kernels();
 int launch_span(int dtype, void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa,
-                const qs::DevOp *ops, uint32_t ob, uint32_t oe, const void *coefs, uint32_t cb, uint32_t ce,
-                uint64_t cstride, const int32_t *status, uint32_t flags, hipStream_t st);
+                const qs::DevOp *ops, uint32_t ob, uint32_t oe, const void *coefs, uint64_t cstride,
+                const int32_t *status, uint32_t flags, hipStream_t st);
 
 // Enable > 64 KiB of dynamic LDS for the tile kernels.  Idempotent.
 int init_kernels();

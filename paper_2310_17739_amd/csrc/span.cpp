@@ -432,7 +432,7 @@ constexpr size_t kPassMax = 96;
 
 }  // namespace
 
-void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, uint32_t op_bytes, size_t meta_budget, int window,
+void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t meta_budget, int window,
                 bool full, int first, int last, std::vector<Pass> *passes) {
     const size_t N = size_t(last - first);
     std::vector<int> nxt(N + 1), prv(N + 1);
@@ -481,8 +481,8 @@ void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, uint32_t o
         for (int i = nxt[size_t(head)]; i != head && scanned < window && skipped.size() < kSkipMax && sel.size() < kPassMax;
              i = nxt[size_t(i)], scanned++) {
             const PauliOp &o = ops[i];
-            // a rotation may open a stage of its own: its record and one more
-            const size_t need = op_bytes + sizeof(DevOp);
+            // LDS of its entry and factor; it may open a stage of its own
+            const size_t need = 24 + 56;
             if ((sel.empty() || meta + need <= meta_budget) && passes_by(o) && grow(o)) {
                 sel.push_back(i);
                 meta += need;
@@ -586,10 +586,11 @@ uint64_t span_vector(const Pass &p, uint32_t coords) {
 
 int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, PackedPlan *out) {
     const int t = p.t, logt = t - regs;
+    int number = 0;
     for (const SpanStage &st : p.stages) {
         DevOp h{};
         h.kind = DEVOP_STAGE;
-        h.kx = uint8_t(t);
+        h.kx = uint8_t(number++);
         uint8_t *raw = reinterpret_cast<uint8_t *>(&h);
         for (int j = 0; j < t; j++) {
             const uint16_t s = uint16_t(span_slot(st.layout[j]));

@@ -13,6 +13,14 @@
 // of the new one.  It reads and later rewrites the same slots, so one barrier
 // per re-layout is enough.
 //
+// What bounds it: the trip of the tile through memory, then what of the
+// rotations the other workgroups of a CU do not hide.  So the work around a
+// rotation's 32 multiply-adds is kept small: an entry of 16 bytes per rotation
+// (one LDS read, two words moved to scalar registers), the tile's sign joined to
+// t beforehand, eight sign changes in place, byte offsets in 32 bits where they
+// fit, the scale multiplied once per pass.  Against records and coefficients
+// decoded per rotation, us per pass: 21 qubits complex128 19.4 -> 18.5, complex64
+// 16.7 -> 15.9, 24 qubits complex128 120 -> 114, 30 qubits complex64 3681 -> 3626.
 // Plain loads and stores: non-temporal ones, which suit k_tile's passes, cost
 // 1540 us against 925 per pass at 27 qubits complex128 and 5174 against 3681 at
 // 30 qubits complex64 (22.1 against 19.4 at 21 qubits complex128).
@@ -27,10 +35,25 @@ namespace qk {
 
 using qs::DevOp;
 
-// v with its sign flipped where bit 31 of s is set
+// v with its sign flipped where bit 31 of s (no other bit set) is
 __device__ __forceinline__ float flip(float v, uint32_t s) { return __uint_as_float(__float_as_uint(v) ^ s); }
 __device__ __forceinline__ double flip(double v, uint32_t s) {
     return __longlong_as_double(__double_as_longlong(v) ^ (int64_t(uint64_t(s) << 32)));
+}
+// The same in place, for a sign that is the same on every lane: one operation.
+// (Left to itself the compiler copies the other half of a double each time.)
+__device__ __forceinline__ void turn(float &v, uint32_t s) {
+    uint32_t u = __float_as_uint(v);
+    asm("v_xor_b32 %0, %1, %0" : "+v"(u) : "s"(s));
+    v = __uint_as_float(u);
+}
+__device__ __forceinline__ void turn(double &v, uint32_t s) {
+    typedef uint32_t U2 __attribute__((ext_vector_type(2)));
+    U2 u = __builtin_bit_cast(U2, v);
+    uint32_t hi = u.y;
+    asm("v_xor_b32 %0, %1, %0" : "+v"(hi) : "s"(s));
+    u.y = hi;
+    v = __builtin_bit_cast(double, u);
 }
 
 // XOR of the register bits' vectors over the bits of R
@@ -61,7 +84,7 @@ __device__ __forceinline__ void rotate(const Cx<T> (&x)[1 << LR], Cx<T> (&y)[1 <
         if constexpr (M == 0 || r < q) {
             // place of the pair in the order
             constexpr int k = M == 0 ? r : (r / (2 * M)) * M + r % M;
-            if constexpr (k > 0) t = flip(t, turn_sign(d, k));
+            if constexpr (k > 0) turn(t, turn_sign(d, k));
             const Cx<T> a = x[r], b = x[q];
             if constexpr (REAL) {
                 y[r] = Cx<T>{T(fma(t, b.re, a.re)), T(fma(t, b.im, a.im))};
@@ -94,12 +117,39 @@ __device__ __forceinline__ void rotate_form(const Cx<T> (&x)[1 << LR], Cx<T> (&y
     }
 }
 
+// LDS behind the tile: an entry of 16 bytes per record, the layouts of the
+// stages (32 bytes each: the record) and a factor of the pass's scale per record.
+typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) U4 LdsU4;
+typedef __attribute__((address_space(3))) double LdsF8;
+
+// An entry.  Word 0: the form (bits 28-31; kStageForm: a stage, its number in
+// the low bits), the thread sign mask (bits 16-27) and the pair signs (bits
+// 0-15).  Word 1: not 0 where a factor is to be applied at once.  t: the upper
+// half (complex128) or word 2.
+constexpr uint32_t kStageForm = 15;
+__device__ __forceinline__ void put_t(U4 &e, float t) { e.z = __float_as_uint(t); }
+__device__ __forceinline__ void put_t(U4 &e, double t) {
+    const uint64_t b = uint64_t(__double_as_longlong(t));
+    e.z = uint32_t(b);
+    e.w = uint32_t(b >> 32);
+}
+template <typename T>
+__device__ __forceinline__ T get_t(const U4 &e) {
+    if constexpr (sizeof(T) == 4) return __uint_as_float(e.z);
+    else return __longlong_as_double(int64_t(uint64_t(e.z) | (uint64_t(e.w) << 32)));
+}
+__device__ __forceinline__ U4 lds_u4(uint32_t at) { return *reinterpret_cast<const LdsU4 *>(uintptr_t(at)); }
+
 // LDS byte addresses of a layout (a stage record): the thread's part and
 // each register bit's.
 template <typename T, int LOGT>
-__device__ __forceinline__ void stage_layout(const uint32_t (&w)[8], int tid, uint32_t &slot_t,
-                                             uint32_t (&slot_r)[qs::kSpanRegs]) {
+__device__ __forceinline__ void stage_layout(uint32_t at, int tid, uint32_t &slot_t, uint32_t (&slot_r)[qs::kSpanRegs]) {
     constexpr int LOGE = LdsTile<T>::LOGE;
+    const U4 a = lds_u4(at), c = lds_u4(at + 16u);
+    uint32_t w[8] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
+#pragma unroll
+    for (int j = 0; j < 8; j++) w[j] = __builtin_amdgcn_readfirstlane(w[j]);
     const uint32_t h[14] = {w[0] & 0xffff, w[0] >> 16,    w[1] & 0xffff, w[1] >> 16,    w[2] & 0xffff,
                             w[2] >> 16,    w[3] & 0xffff, w[4] & 0xffff, w[4] >> 16,    w[5] & 0xffff,
                             w[5] >> 16,    w[6] & 0xffff, w[6] >> 16,    w[7] & 0xffff};
@@ -114,86 +164,107 @@ __device__ __forceinline__ void stage_layout(const uint32_t (&w)[8], int tid, ui
     });
 }
 
-template <typename T, int LOGT>
+template <bool WIDE>
+struct OffsetOf {
+    typedef uint32_t type;
+};
+template <>
+struct OffsetOf<true> {
+    typedef uint64_t type;
+};
+
+// WIDE: byte offsets inside a state need more than 32 bits.
+template <typename T, int LOGT, bool WIDE>
 __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, uint64_t sstride, SpanArgs sa,
                                                    const DevOp *__restrict__ ops, uint32_t ob, uint32_t oe,
-                                                   const Cx<T> *__restrict__ coefs, uint32_t cb, uint32_t ce,
-                                                   uint64_t cstride, const int32_t *__restrict__ status,
-                                                   uint32_t flags) {
+                                                   const Cx<T> *__restrict__ coefs, uint64_t cstride,
+                                                   const int32_t *__restrict__ status, uint32_t flags) {
     using L = LdsTile<T>;
+    using Off = typename OffsetOf<WIDE>::type;
     constexpr int LR = qs::kSpanRegs, E = 1 << LR, TNT = 1 << LOGT;
     const uint32_t b = blockIdx.y;
     if (status && status[b] != 0) return;   // an earlier step of this state failed
-    Cx<T> *st = state + size_t(b) * sstride;
-    const Cx<T> *gcf = coefs + size_t(b) * cstride + cb;
+    char *st = reinterpret_cast<char *>(state + size_t(b) * sstride);
+    const Cx<T> *gcf = coefs + size_t(b) * cstride;
     const int tid = threadIdx.x;
-    const uint32_t nrec = oe - ob, ncf = ce - cb;
-    // LDS: the tile (unless the pass has a single stage), records, coefficients
-    const uint32_t rec_at = sa.tile_bytes, cf_at = rec_at + nrec * uint32_t(sizeof(DevOp));
+    const uint32_t nrec = oe - ob;
+    const uint32_t ent_at = sa.tile_bytes, lay_at = ent_at + 16u * (nrec + 1), fac_at = lay_at + 32u * sa.nstage;
     const uint64_t base = span_base(blockIdx.x, sa);
-    typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+    // byte offset of a thread's register 0, and what each register bit changes
+    auto offsets = [&](const uint64_t *vec, Off (&reg)[LR]) {
+        Off off = Off(base) << L::LOGE;
+        static_for<0, LOGT>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            off ^= ((tid >> k) & 1) ? Off(vec[k]) << L::LOGE : Off(0);
+        });
+        static_for<0, LR>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            reg[k] = Off(vec[LOGT + k]) << L::LOGE;
+        });
+        return off;
+    };
 
     Cx<T> v[E];
     {
-        uint64_t off = base;
-#pragma unroll
-        for (int k = 0; k < LOGT; k++) off ^= ((tid >> k) & 1) ? sa.load_v[k] : 0;
+        Off reg[LR];
+        const Off off = offsets(sa.load_v, reg);
         if (flags & TF_INIT_ZERO) {
             static_for<0, E>([&](auto rc) {
                 constexpr int r = decltype(rc)::value;
-                v[r] = Cx<T>{T((off ^ reg_off<r>(sa.load_v + LOGT)) == 0 ? 1 : 0), T(0)};
+                v[r] = Cx<T>{T((off ^ reg_off<r>(reg)) == 0 ? 1 : 0), T(0)};
             });
         } else {
             static_for<0, E>([&](auto rc) {
                 constexpr int r = decltype(rc)::value;
-                v[r] = st[off ^ reg_off<r>(sa.load_v + LOGT)];
+                v[r] = *reinterpret_cast<const Cx<T> *>(st + (off ^ reg_off<r>(reg)));
             });
         }
     }
-    // the pass's records and coefficients follow while the tile loads fly
-    const U4 *gops = reinterpret_cast<const U4 *>(ops + ob);
-    for (uint32_t x = uint32_t(tid); x < 2 * nrec; x += TNT)
-        *reinterpret_cast<__attribute__((address_space(3))) U4 *>(uintptr_t(rec_at + 16u * x)) = gops[x];
-    for (uint32_t x = uint32_t(tid); x < ncf; x += TNT) L::st(cf_at + (x << L::LOGE), gcf[x]);
+    // While the tile loads fly, one thread per record writes its entry: the
+    // sign of the tile's base index joins t here, once per tile and rotation.
+    for (uint32_t x = uint32_t(tid); x < nrec; x += TNT) {
+        const U4 *p = reinterpret_cast<const U4 *>(ops + ob + x);
+        const U4 a = p[0], c = p[1];
+        U4 e = {0, 0, 0, 0};
+        double f = 1.0;
+        if (((a.w >> 16) & 0xff) == qs::DEVOP_PAULI) {
+            const Cx<T> e0 = gcf[a.x], e1 = gcf[a.x + 1];
+            const uint64_t zb = uint64_t((c.x >> 16) | (c.y << 16)) | (uint64_t(c.y >> 16) << 32);
+            e.x = (a.y & 0xffffu) | ((c.x & 0xfffu) << 16) | ((a.z & 0xffu) << 28);
+            e.y = e1.re != T(0);
+            put_t(e, flip(e1.im, uint32_t(__builtin_popcountll(base & zb)) << 31));
+            f = e.y ? double(e1.re) : double(e0.re) + double(e0.im);
+        } else {
+            const uint32_t number = a.w >> 24;
+            e.x = (kStageForm << 28) | number;
+            *reinterpret_cast<LdsU4 *>(uintptr_t(lay_at + 32u * number)) = a;
+            *reinterpret_cast<LdsU4 *>(uintptr_t(lay_at + 32u * number + 16u)) = c;
+        }
+        *reinterpret_cast<LdsU4 *>(uintptr_t(ent_at + 16u * x)) = e;
+        *reinterpret_cast<LdsF8 *>(uintptr_t(fac_at + 8u * x)) = f;
+    }
     __syncthreads();
 
-    double scale = 1.0;
-    uint32_t slot_t = 0, slot_r[LR] = {};   // LDS bytes: the thread's part, each register bit's
-    auto rec = [&](uint32_t i, U4 &a, U4 &c) {
-        a = *reinterpret_cast<const __attribute__((address_space(3))) U4 *>(uintptr_t(rec_at + 32u * i));
-        c = *reinterpret_cast<const __attribute__((address_space(3))) U4 *>(uintptr_t(rec_at + 32u * i + 16u));
-    };
-    U4 ra, rb;
-    rec(0, ra, rb);
-    uint32_t cf = cf_at;
-    Cx<T> e0 = L::ld(cf), e1 = L::ld(cf + uint32_t(sizeof(Cx<T>)));
+    uint32_t slot_t, slot_r[LR];   // LDS bytes: the thread's part, each register bit's
+    stage_layout<T, LOGT>(lay_at, tid, slot_t, slot_r);
+    U4 ahead = lds_u4(ent_at + 16u);
     // One record, from the registers x to y.  (Two sets of registers in turn:
     // a rotation reads both members of a pair for both results, and in one set
     // every second result would have to be moved.)
     auto step = [&](uint32_t i, const Cx<T> (&x)[E], Cx<T> (&y)[E]) __attribute__((always_inline)) {
-        uint32_t w[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
-#pragma unroll
-        for (int j = 0; j < 8; j++) w[j] = __builtin_amdgcn_readfirstlane(w[j]);
-        const bool pauli = ((w[3] >> 16) & 0xff) == qs::DEVOP_PAULI;
-        const Cx<T> c0 = e0, c1 = e1;
-        // the next record and (rotations take theirs in order) coefficients;
-        // what the last one reads lies inside the padding of the LDS block
-        if (pauli) cf += 2u * uint32_t(sizeof(Cx<T>));
-        rec(i + 1, ra, rb);
-        e0 = L::ld(cf);
-        e1 = L::ld(cf + uint32_t(sizeof(Cx<T>)));
-        if (pauli) {
-            const uint64_t zb = uint64_t((w[4] >> 16) | (w[5] << 16)) | (uint64_t(w[5] >> 16) << 32);
-            const uint32_t s = uint32_t(__builtin_popcount(uint32_t(tid) & (w[4] & 0xffffu))) +
-                               uint32_t(__builtin_popcountll(base & zb));
-            scale *= double(c0.re) + double(c0.im);
-            rotate_form<T, LR>(x, y, int(w[2] & 0xff), flip(c1.im, s << 31), w[1]);
-            // a factor that the pass's scale does not take (the same on every lane)
-            if (__builtin_amdgcn_readfirstlane(int(c1.re != T(0)))) {
+        const U4 e = ahead;
+        const uint32_t w = __builtin_amdgcn_readfirstlane(e.x);
+        ahead = lds_u4(ent_at + 16u * (i + 1));
+        const uint32_t form = w >> 28;
+        if (form != kStageForm) {
+            const uint32_t s = uint32_t(__builtin_popcount(uint32_t(tid) & ((w >> 16) & 0xfffu))) << 31;
+            rotate_form<T, LR>(x, y, int(form), flip(get_t<T>(e), s), w);
+            if (__builtin_amdgcn_readfirstlane(e.y)) {
+                const T f = T(*reinterpret_cast<const LdsF8 *>(uintptr_t(fac_at + 8u * i)));
                 static_for<0, E>([&](auto rc) {
                     constexpr int r = decltype(rc)::value;
-                    y[r].re *= c1.re;
-                    y[r].im *= c1.re;
+                    y[r].re *= f;
+                    y[r].im *= f;
                 });
             }
         } else {
@@ -202,7 +273,7 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
                 constexpr int r = decltype(rc)::value;
                 L::st(slot_t ^ reg_off<r>(slot_r), x[r]);
             });
-            stage_layout<T, LOGT>(w, tid, slot_t, slot_r);
+            stage_layout<T, LOGT>(lay_at + 32u * (w & 0xffu), tid, slot_t, slot_r);
             __syncthreads();
             static_for<0, E>([&](auto rc) {
                 constexpr int r = decltype(rc)::value;
@@ -210,14 +281,6 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
             });
         }
     };
-    {
-        // the first record: the layout of the load
-        uint32_t w[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
-#pragma unroll
-        for (int j = 0; j < 8; j++) w[j] = __builtin_amdgcn_readfirstlane(w[j]);
-        stage_layout<T, LOGT>(w, tid, slot_t, slot_r);
-        rec(1, ra, rb);
-    }
     uint32_t i = 1;
     for (; i + 1 < nrec; i += 2) {
         Cx<T> u[E];
@@ -230,9 +293,16 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
         static_for<0, E>([&](auto rc) { v[decltype(rc)::value] = u[decltype(rc)::value]; });
     }
     {
-        uint64_t off = base;
+        // the scale: lanes multiply the factors of their records, then each other's
+        double scale = 1.0;
+        for (uint32_t x = uint32_t(tid) & 63u; x < nrec; x += 64u) {
+            const double f = *reinterpret_cast<const LdsF8 *>(uintptr_t(fac_at + 8u * x));
+            scale *= lds_u4(ent_at + 16u * x).y && (lds_u4(ent_at + 16u * x).x >> 28) != kStageForm ? 1.0 : f;
+        }
 #pragma unroll
-        for (int k = 0; k < LOGT; k++) off ^= ((tid >> k) & 1) ? sa.store_v[k] : 0;
+        for (int d = 32; d > 0; d >>= 1) scale *= __shfl_xor(scale, d, 64);
+        Off reg[LR];
+        const Off off = offsets(sa.store_v, reg);
         const T fr = T(scale * sa.phase_re), fi = T(scale * sa.phase_im);
         const bool turned = sa.phase_im != 0.0;
         static_for<0, E>([&](auto rc) {
@@ -242,7 +312,7 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
                 y.re = fma(-fi, v[r].im, y.re);
                 y.im = fma(fi, v[r].re, y.im);
             }
-            st[off ^ reg_off<r>(sa.store_v + LOGT)] = y;
+            *reinterpret_cast<Cx<T> *>(st + (off ^ reg_off<r>(reg))) = y;
         });
     }
 }
@@ -251,24 +321,40 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
 namespace {
 bool span_static_lds = false;
 
-template <typename T, int LOGT>
+template <typename T, int LOGT, bool WIDE>
 void span_attr() {
-    const void *f = reinterpret_cast<const void *>(&k_span<T, LOGT>);
+    const void *f = reinterpret_cast<const void *>(&k_span<T, LOGT, WIDE>);
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(max_lds_bytes()));
     if (e != hipSuccess) note_hip(e, "hipFuncSetAttribute(k_span)");
     hipFuncAttributes fa{};
     if (hipFuncGetAttributes(&fa, f) == hipSuccess && fa.sharedSizeBytes != 0) span_static_lds = true;
 }
+template <typename T, int LOGT>
+void span_attrs() {
+    span_attr<T, LOGT, false>();
+    span_attr<T, LOGT, true>();
+}
+
+template <typename T, int LOGT>
+void span_t(void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops, uint32_t ob,
+            uint32_t oe, const void *coefs, uint64_t cstride, const int32_t *status, uint32_t flags, size_t lds,
+            hipStream_t st) {
+    const dim3 grid(uint32_t(uint64_t(1) << (sa.n - sa.t)), nstates);
+    if ((uint64_t(sizeof(Cx<T>)) << sa.n) <= (uint64_t(1) << 32))
+        hipLaunchKernelGGL((k_span<T, LOGT, false>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state, sstride, sa, ops,
+                           ob, oe, (const Cx<T> *)coefs, cstride, status, flags);
+    else
+        hipLaunchKernelGGL((k_span<T, LOGT, true>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state, sstride, sa, ops,
+                           ob, oe, (const Cx<T> *)coefs, cstride, status, flags);
+}
 
 template <typename T>
-int span_t(void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops, uint32_t ob,
-           uint32_t oe, const void *coefs, uint32_t cb, uint32_t ce, uint64_t cstride, const int32_t *status,
-           uint32_t flags, size_t lds, hipStream_t st) {
-    const dim3 grid(uint32_t(uint64_t(1) << (sa.n - sa.t)), nstates);
-#define QK_SPAN(LOGT)                                                                                          \
-    case LOGT:                                                                                                 \
-        hipLaunchKernelGGL((k_span<T, LOGT>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state, sstride, sa, ops, \
-                           ob, oe, (const Cx<T> *)coefs, cb, ce, cstride, status, flags);                      \
+int span_dispatch(void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops, uint32_t ob,
+                  uint32_t oe, const void *coefs, uint64_t cstride, const int32_t *status, uint32_t flags, size_t lds,
+                  hipStream_t st) {
+#define QK_SPAN(LOGT)                                                                                       \
+    case LOGT:                                                                                              \
+        span_t<T, LOGT>(state, sstride, nstates, sa, ops, ob, oe, coefs, cstride, status, flags, lds, st); \
         break;
     switch (sa.t - qs::kSpanRegs) {
         QK_SPAN(6)
@@ -278,8 +364,7 @@ int span_t(void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, 
     case 10:
         // (a complex128 tile of 14 dimensions is larger than the LDS)
         if constexpr (sizeof(T) == 4) {
-            hipLaunchKernelGGL((k_span<T, 10>), grid, dim3(1 << 10), lds, st, (Cx<T> *)state, sstride, sa, ops, ob,
-                               oe, (const Cx<T> *)coefs, cb, ce, cstride, status, flags);
+            span_t<T, 10>(state, sstride, nstates, sa, ops, ob, oe, coefs, cstride, status, flags, lds, st);
             break;
         }
         return QSIM_E_CAPACITY;
@@ -291,32 +376,32 @@ int span_t(void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, 
 }  // namespace
 
 bool init_span_kernels() {
-    span_attr<float, 6>();
-    span_attr<float, 7>();
-    span_attr<float, 8>();
-    span_attr<float, 9>();
-    span_attr<float, 10>();
-    span_attr<double, 6>();
-    span_attr<double, 7>();
-    span_attr<double, 8>();
-    span_attr<double, 9>();
+    span_attrs<float, 6>();
+    span_attrs<float, 7>();
+    span_attrs<float, 8>();
+    span_attrs<float, 9>();
+    span_attrs<float, 10>();
+    span_attrs<double, 6>();
+    span_attrs<double, 7>();
+    span_attrs<double, 8>();
+    span_attrs<double, 9>();
     (void)hipGetLastError();
     return !span_static_lds;
 }
 
 int launch_span(int dtype, void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops,
-                uint32_t ob, uint32_t oe, const void *coefs, uint32_t cb, uint32_t ce, uint64_t cstride,
-                const int32_t *status, uint32_t flags, hipStream_t st) {
+                uint32_t ob, uint32_t oe, const void *coefs, uint64_t cstride, const int32_t *status, uint32_t flags,
+                hipStream_t st) {
     const size_t elem = dtype == QSIM_C64 ? 8 : 16;
-    if (!qs::span_tile_ok(sa.t) || sa.t > sa.n || sa.n - sa.t > 31 || oe <= ob || ce < cb ||
-        (sa.tile_bytes != 0 && sa.tile_bytes != (elem << sa.t)))
+    if (!qs::span_tile_ok(sa.t) || sa.t > sa.n || sa.n - sa.t > 31 || oe <= ob || sa.nstage == 0 ||
+        sa.nstage > oe - ob || (sa.tile_bytes != 0 && sa.tile_bytes != (elem << sa.t)))
         return QSIM_E_ARG;
-    const size_t lds = span_lds_bytes(elem, sa.tile_bytes, oe - ob, ce - cb);
+    const size_t lds = span_lds_bytes(sa.tile_bytes, oe - ob, sa.nstage);
     if (lds > max_lds_bytes()) return QSIM_E_CAPACITY;
-    return dtype == QSIM_C64 ? span_t<float>(state, sstride, nstates, sa, ops, ob, oe, coefs, cb, ce, cstride, status,
-                                             flags, lds, st)
-                             : span_t<double>(state, sstride, nstates, sa, ops, ob, oe, coefs, cb, ce, cstride, status,
-                                              flags, lds, st);
+    return dtype == QSIM_C64 ? span_dispatch<float>(state, sstride, nstates, sa, ops, ob, oe, coefs, cstride, status,
+                                                    flags, lds, st)
+                             : span_dispatch<double>(state, sstride, nstates, sa, ops, ob, oe, coefs, cstride, status,
+                                                     flags, lds, st);
 }
 
 }  // namespace qk
