@@ -422,7 +422,7 @@ uint32_t span_slot(uint32_t c) {
     return s;
 }
 
-// Rotations skipped by one pass after which it is closed: a later one has to
+// Rotations skipped by one pass (or stage) after which it is closed: a later one has to
 // commute with all of them, and a longer list finds hardly any on the
 // benchmark circuits.
 constexpr size_t kSkipMax = 64;
@@ -514,6 +514,10 @@ void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t met
             later.clear();
             for (int i : left) {
                 const PauliOp &o = ops[i];
+                if (skipped.size() >= kSkipMax) {
+                    later.push_back(i);
+                    continue;
+                }
                 // its X mask is a register bit of its own, or opens one
                 const bool have = !o.x || std::find(dirs.begin(), dirs.end(), o.x) != dirs.end();
                 const uint64_t r = have ? 0 : R.reduce(o.x);
