@@ -413,6 +413,7 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
             passes.push_back(std::move(p));
         }
     }
+    out->pauli = true;
     PackedPlan &pl = out->plan;
     const uint64_t all = (uint64_t(1) << n) - 1;
     bool phased = P.phase == 0.0;
@@ -738,11 +739,13 @@ struct qsim_state {
     size_t cap_red = 0;
     void *d_small = nullptr;   // constant coefficients (the X operator)
     size_t cap_small = 0;
-    void *d_masks = nullptr;   // Pauli masks of qsim_expval
+    void *d_masks = nullptr;   // tables of qsim_expval
     size_t cap_masks = 0;
+    void *h_table = nullptr;   // their pinned staging
+    size_t cap_table = 0;
     void *d_scan = nullptr;    // sampling: prefix sums, block sums, shots
     size_t cap_scan = 0;
-    double *h_out = nullptr;   // pinned readback
+    double *h_out = nullptr;   // pinned readback, written by the reduction kernels
     size_t cap_out = 0;
     qsim_apply_stats last{};
 };
@@ -779,17 +782,26 @@ int reduce_buffers(qsim_h h, size_t partial_doubles, size_t out_doubles, double 
     return QSIM_OK;
 }
 
+// Two parts of a table into h->d_masks, through pinned memory: the copy is
+// asynchronous and the call that makes it synchronises before it returns.
+int upload_table(qsim_h h, const void *a, size_t na, const void *b, size_t nb) {
+    int rc = grow(&h->d_masks, &h->cap_masks, na + nb, h->stream);
+    if (!rc) rc = grow_host(&h->h_table, &h->cap_table, na + nb);
+    if (rc) return rc;
+    std::memcpy(h->h_table, a, na);
+    if (nb) std::memcpy((char *)h->h_table + na, b, nb);
+    return hip_rc(hipMemcpyAsync(h->d_masks, h->h_table, na + nb, hipMemcpyHostToDevice, h->stream));
+}
+
 // Marginal weights of qubits qs (unnormalised), into h->h_out[0 .. 2^nqs).
 int marginal(qsim_h h, const int *qs, int nqs) {
     const uint32_t nch = qk::marginal_chunks(h->n, nqs);
     double *part, *out;
     int rc = reduce_buffers(h, size_t(nch) << nqs, size_t(1) << nqs, &part, &out);
     if (rc) return rc;
-    rc = qk::launch_marginal(h->dtype, h->buf, 0, 1, h->n, qs, nqs, part, out, h->stream);
+    // the sums go straight to the pinned read-back buffer
+    rc = qk::launch_marginal(h->dtype, h->buf, 0, 1, h->n, qs, nqs, part, h->h_out, h->stream);
     if (rc) return rc;
-    if (hipMemcpyAsync(h->h_out, out, (size_t(1) << nqs) * sizeof(double), hipMemcpyDeviceToHost,
-                       h->stream) != hipSuccess)
-        return QSIM_E_HIP;
     return hip_rc(hipStreamSynchronize(h->stream));
 }
 
@@ -868,6 +880,7 @@ int qsim_destroy(qsim_h h) {
     if (h->d_masks) (void)hipFree(h->d_masks);
     if (h->d_scan) (void)hipFree(h->d_scan);
     if (h->h_out) (void)hipHostFree(h->h_out);
+    if (h->h_table) (void)hipHostFree(h->h_table);
     delete h;
     return QSIM_OK;
 }
@@ -1123,31 +1136,54 @@ int qsim_expval(qsim_h h, const qsim_pauli *t, size_t nt, double *out) {
         if ((t[k].xmask & ~lim) || (t[k].zmask & ~lim) || !std::isfinite(t[k].coeff)) return QSIM_E_ARG;
     }
     TraceRange range("qsim_expval");
-    double nrm;
-    int rc = qsim_norm(h, &nrm);
+    if (nt == 0) {
+        double nrm;
+        const int rc = qsim_norm(h, &nrm);
+        if (rc) return rc;
+        if (!(nrm > 0)) return QSIM_E_ZERO_PROB;
+        *out = 0.0;
+        return QSIM_OK;
+    }
+    double nrm = 0.0, total = 0.0;
+    int rc;
+    try {
+        ExpectPlan plan;
+        if (plan_expect(h->n, h->dtype == QSIM_C64 ? 4 : 3, t, nt, &plan)) {
+            // every term and the norm from one set of readings, one round trip
+            const uint32_t nterms = uint32_t(nt) + 1;
+            const uint32_t nch = qk::expect_chunks(h->n, plan.t, nterms, 1);
+            double *part, *dout;
+            rc = reduce_buffers(h, size_t(nch) * nterms, nterms, &part, &dout);
+            if (!rc) rc = upload_table(h, plan.groups.data(), plan.groups.size() * sizeof(ExpectGroup),
+                                       plan.recs.data(), plan.recs.size() * sizeof(DevOp));
+            if (!rc) rc = qk::launch_expect(h->dtype, h->buf, 0, 1, h->n, plan, h->d_masks, nterms, nch, part,
+                                            h->h_out, h->stream);
+            if (!rc) rc = hip_rc(hipStreamSynchronize(h->stream));
+            if (rc) return rc;
+            nrm = h->h_out[nt];
+            if (!(nrm > 0)) return QSIM_E_ZERO_PROB;
+            for (size_t k = 0; k < nt; k++) total += t[k].coeff * expect_value(t[k], h->h_out[k]);
+            *out = total / nrm;
+            return QSIM_OK;
+        }
+        rc = qsim_norm(h, &nrm);
+        if (rc) return rc;
+        if (!(nrm > 0)) return QSIM_E_ZERO_PROB;
+        std::vector<uint64_t> table;
+        const qk::PauliRows nrows = qk::pauli_rows(t, nt, &table);
+        rc = upload_table(h, table.data(), 8 * table.size(), nullptr, 0);
+        if (rc) return rc;
+        const uint32_t nch = qk::pauli_chunks(h->n);
+        double *part, *dout;
+        rc = reduce_buffers(h, size_t(nch) * 2 * nt, 2 * nt, &part, &dout);
+        if (rc) return rc;
+        rc = qk::launch_pauli(h->dtype, h->buf, 0, 1, h->n, (const uint64_t *)h->d_masks, int(nt), nrows, part,
+                              h->h_out, h->stream);
+    } catch (const std::bad_alloc &) {
+        return QSIM_E_NOMEM;
+    }
+    if (!rc) rc = hip_rc(hipStreamSynchronize(h->stream));
     if (rc) return rc;
-    if (!(nrm > 0)) return QSIM_E_ZERO_PROB;
-    if (nt == 0) { *out = 0.0; return QSIM_OK; }
-    std::vector<uint64_t> table;
-    const qk::PauliRows nrows = qk::pauli_rows(t, nt, &table);
-    rc = grow(&h->d_masks, &h->cap_masks, 8 * table.size(), h->stream);
-    if (rc) return rc;
-    uint64_t *dm = (uint64_t *)h->d_masks;
-    // pageable source: the copy has left `table` when the call returns
-    if (hipMemcpyAsync(dm, table.data(), 8 * table.size(), hipMemcpyHostToDevice, h->stream) != hipSuccess)
-        return QSIM_E_HIP;
-    const uint32_t nch = qk::pauli_chunks(h->n);
-    double *part, *dout;
-    rc = reduce_buffers(h, size_t(nch) * 2 * nt, 2 * nt, &part, &dout);
-    if (rc) return rc;
-    rc = qk::launch_pauli(h->dtype, h->buf, 0, 1, h->n, dm, int(nt), nrows, part, dout, h->stream);
-    if (rc) return rc;
-    if (hipMemcpyAsync(h->h_out, dout, 2 * nt * sizeof(double), hipMemcpyDeviceToHost, h->stream) !=
-        hipSuccess)
-        return QSIM_E_HIP;
-    rc = hip_rc(hipStreamSynchronize(h->stream));
-    if (rc) return rc;
-    double total = 0;
     for (size_t k = 0; k < nt; k++) {
         const double re = h->h_out[2 * k], im = h->h_out[2 * k + 1];
         // <P> = Re(i^{#Y} S), S = sum_x (-1)^{popcount(x & z)} conj(a[x ^ x_mask]) a[x]
@@ -1248,6 +1284,8 @@ int qsim_autotune(qsim_h h, const qsim_gate *g, size_t ng, const double *mats, s
         }
         if (rc) break;
         if (c.plan.ops.empty()) continue;
+        // fusion options change nothing: one candidate of each tile
+        if (c.pauli && (o.max_width != 4 || o.op_cost != 4.0f)) continue;
         if ((rc = upload_plan(&dt, h->dtype, c.plan, h->stream))) break;
         // warm, then time one run
         if ((rc = enqueue_passes(c, dt, h->dtype, h->buf, h->stream, false))) break;
@@ -1291,7 +1329,8 @@ int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs
     DeviceTables dt;
     *best_w = 0;
     *best_ns = 1e300;
-    for (int w = 2; w <= wmax && !rc; w++) {
+    for (int w : {4, 2, 3, 5}) {
+        if (w > wmax || rc) break;
         qsim_fuse_opts o{};
         if (base) o = *base;
         o.level = 5;
@@ -1326,6 +1365,7 @@ int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs
             *best_ns = ns;
             *best_w = w;
         }
+        if (c.pauli) break;   // the same plan at every width
     }
     if (st) (void)hipStreamSynchronize(st);
     free_tables(&dt);

@@ -70,6 +70,8 @@ struct Group {
     double *d_pauli = nullptr;     // [nstates][nterms][2]
     uint32_t pauli_chunks = 0, norm_chunks = 0;
     qk::PauliRows pauli_rows;
+    ExpectPlan expect;             // of the terms, from 10 qubits: d_masks then holds its table and
+                                   // d_pauli [nstates][nterms + 1], the norm last
     int64_t coef_bytes = 0;
     int tuned_width = 0;           // fusion width the autotuner chose (0: not tuned)
     double tune_seconds = 0.0;
@@ -285,18 +287,33 @@ int setup_group(Group &G, const qsim_batch_group &in, int dtype, const qsim_batc
                                                            pow2_floor((1u << 22) / uint64_t(G.nstates) / 2)));
     size_t part = size_t(G.nstates) * 2 * G.norm_chunks;
     if (G.nterms) {
-        G.pauli_chunks = std::max<uint32_t>(1, std::min<uint32_t>(qk::pauli_chunks(G.n),
-                                                                pow2_floor((1u << 22) / (uint64_t(G.nstates) * G.nterms * 2))));
-        part = std::max(part, size_t(G.nstates) * G.nterms * 2 * G.pauli_chunks);
         G.terms.assign(in.terms, in.terms + G.nterms);
         const uint64_t lim = (uint64_t(1) << G.n) - 1;
         for (size_t k = 0; k < G.nterms; k++)
             if ((in.terms[k].xmask & ~lim) || (in.terms[k].zmask & ~lim)) return QSIM_E_ARG;
-        std::vector<uint64_t> masks;
-        G.pauli_rows = qk::pauli_rows(in.terms, G.nterms, &masks);
-        if ((rc = dalloc(&G.d_masks, masks.size() * 8))) return rc;
-        if ((rc = hip_ok(hipMemcpy(G.d_masks, masks.data(), masks.size() * 8, hipMemcpyHostToDevice), "masks"))) return rc;
-        if ((rc = dalloc(&G.d_pauli, size_t(G.nstates) * G.nterms * 2 * 8))) return rc;
+        if (plan_expect(G.n, dtype == QSIM_C64 ? 4 : 3, in.terms, G.nterms, &G.expect)) {
+            const ExpectPlan &plan = G.expect;
+            const uint32_t nterms = uint32_t(G.nterms) + 1;
+            G.pauli_chunks = qk::expect_chunks(G.n, plan.t, nterms, uint32_t(G.nstates));
+            part = std::max(part, size_t(G.nstates) * nterms * G.pauli_chunks);
+            const size_t ga = plan.groups.size() * sizeof(ExpectGroup);
+            if ((rc = dalloc(&G.d_masks, plan.table_bytes()))) return rc;
+            if ((rc = hip_ok(hipMemcpy(G.d_masks, plan.groups.data(), ga, hipMemcpyHostToDevice), "terms"))) return rc;
+            if ((rc = hip_ok(hipMemcpy((char *)G.d_masks + ga, plan.recs.data(), plan.table_bytes() - ga,
+                                       hipMemcpyHostToDevice), "terms")))
+                return rc;
+            if ((rc = dalloc(&G.d_pauli, size_t(G.nstates) * nterms * 8))) return rc;
+        } else {
+            G.expect = ExpectPlan{};
+            G.pauli_chunks = std::max<uint32_t>(1, std::min<uint32_t>(qk::pauli_chunks(G.n),
+                                                                    pow2_floor((1u << 22) / (uint64_t(G.nstates) * G.nterms * 2))));
+            part = std::max(part, size_t(G.nstates) * G.nterms * 2 * G.pauli_chunks);
+            std::vector<uint64_t> masks;
+            G.pauli_rows = qk::pauli_rows(in.terms, G.nterms, &masks);
+            if ((rc = dalloc(&G.d_masks, masks.size() * 8))) return rc;
+            if ((rc = hip_ok(hipMemcpy(G.d_masks, masks.data(), masks.size() * 8, hipMemcpyHostToDevice), "masks"))) return rc;
+            if ((rc = dalloc(&G.d_pauli, size_t(G.nstates) * G.nterms * 2 * 8))) return rc;
+        }
     }
     G.part_doubles = part;
     if ((rc = dalloc(&G.d_part, part * 8))) return rc;
@@ -345,6 +362,9 @@ int enqueue_group(const Group &G, int dtype, hipStream_t st) {
     if (G.c.passes.empty()) {
         if ((rc = qk::launch_init_zero(dtype, G.d_states, G.sstride, uint32_t(G.nstates), G.n, st))) return rc;
     }
+    if (!G.expect.groups.empty())
+        return qk::launch_expect(dtype, G.d_states, G.sstride, uint32_t(G.nstates), G.n, G.expect, G.d_masks,
+                                 uint32_t(G.nterms) + 1, G.pauli_chunks, G.d_part, G.d_pauli, st);
     rc = qk::launch_marginal(dtype, G.d_states, G.sstride, uint32_t(G.nstates), G.n, nullptr, 0, G.d_part,
                              G.d_norm, st, G.norm_chunks);
     if (rc) return rc;
@@ -456,19 +476,31 @@ int qsim_batch_results(qsim_batch_h b, int group, int32_t *outcomes, double *pro
         return rc;
     if (status && (rc = hip_ok(hipMemcpy(status, G.d_status, size_t(G.nstates) * 4, hipMemcpyDeviceToHost), "status")))
         return rc;
-    std::vector<double> nrm(size_t(G.nstates));
-    if ((rc = hip_ok(hipMemcpy(nrm.data(), G.d_norm, nrm.size() * 8, hipMemcpyDeviceToHost), "norms"))) return rc;
+    std::vector<double> nrm(size_t(G.nstates)), sums;
+    const bool planned = !G.expect.groups.empty();
+    const size_t per = planned ? G.nterms + 1 : 2 * G.nterms;   // d_pauli's values per state
+    if (planned || (expvals && G.nterms)) {
+        sums.resize(size_t(G.nstates) * per);
+        if ((rc = hip_ok(hipMemcpy(sums.data(), G.d_pauli, sums.size() * 8, hipMemcpyDeviceToHost), "pauli"))) return rc;
+    }
+    if (planned) {
+        for (size_t bb = 0; bb < nrm.size(); bb++) nrm[bb] = sums[bb * per + G.nterms];
+    } else if ((rc = hip_ok(hipMemcpy(nrm.data(), G.d_norm, nrm.size() * 8, hipMemcpyDeviceToHost), "norms"))) {
+        return rc;
+    }
     if (norms) std::copy(nrm.begin(), nrm.end(), norms);
     if (expvals) {
         if (!G.nterms) {
             std::fill(expvals, expvals + G.nstates, 0.0);
         } else {
-            std::vector<double> s(size_t(G.nstates) * G.nterms * 2);
-            if ((rc = hip_ok(hipMemcpy(s.data(), G.d_pauli, s.size() * 8, hipMemcpyDeviceToHost), "pauli"))) return rc;
             for (int bb = 0; bb < G.nstates; bb++) {
                 double total = 0;
                 for (size_t k = 0; k < G.nterms; k++) {
-                    const double re = s[(size_t(bb) * G.nterms + k) * 2], im = s[(size_t(bb) * G.nterms + k) * 2 + 1];
+                    if (planned) {
+                        total += G.terms[k].coeff * expect_value(G.terms[k], sums[size_t(bb) * per + k]);
+                        continue;
+                    }
+                    const double re = sums[size_t(bb) * per + 2 * k], im = sums[size_t(bb) * per + 2 * k + 1];
                     double v;
                     switch (__builtin_popcountll(G.terms[k].xmask & G.terms[k].zmask) & 3) {
                     case 0: v = re; break;

@@ -279,11 +279,13 @@ enum { DEVOP_MAT = 0, DEVOP_MEASURE = 1, DEVOP_ASSERT0 = 2, DEVOP_RESET = 3,
        // span passes:
        DEVOP_STAGE = 9,   // the LDS slots of the layout's positions, 16 bits each, in bytes 0..13
                           // and 16..29; kx = the stage's number
-       DEVOP_PAULI = 10   // rotation: k = 2 b + 1 for a real t and 2 b for an imaginary one on
+       DEVOP_PAULI = 10,  // rotation: k = 2 b + 1 for a real t and 2 b for an imaginary one on
                           // register bit b, 2 kSpanRegs for a diagonal; bit j of present = whether the sign of register pair j
                           // (in ascending order of the smaller register) differs from that of
                           // pair j - 1; slot[0], slot[1..3] = the sign masks of the thread bits
                           // and of the tile's base index; two coefficients (see pauli_coefs)
+       DEVOP_EXPECT = 11  // a term of a Pauli sum: its form and signs as a rotation's; coef = its
+                          // number
 };
 inline bool devop_is_mat(int kind) { return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI; }
 inline bool devop_is_record(int kind) {
@@ -342,6 +344,28 @@ void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t met
 int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, PackedPlan *out);
 // The vector of the state's index that tile coordinates stand for.
 uint64_t span_vector(const Pass &p, uint32_t coords);
+
+// The terms of a Pauli sum in groups, each evaluated on one reading of the state
+// in tiles that are cosets of a space holding its X masks.  The identity is
+// term number nt.
+constexpr size_t kExpectGroup = 64;   // terms of a group
+struct ExpectGroup {
+    uint64_t rest_mask = 0;        // the index bits that tell cosets apart
+    uint64_t load_v[14] = {0};     // what position j of an element moves the index by, as loaded
+    uint32_t rec_begin = 0, rec_end = 0, stages = 0, pad = 0;
+};
+struct ExpectPlan {
+    int t = 0;
+    std::vector<DevOp> recs;
+    std::vector<ExpectGroup> groups;
+    uint32_t max_rec = 0, max_stage = 0;   // of a group
+    bool relaid = false;                   // a group has several stages
+    size_t table_bytes() const { return groups.size() * sizeof(ExpectGroup) + recs.size() * sizeof(DevOp); }
+};
+// c: contiguous low qubits.  False for states too small for a tile.
+bool plan_expect(int n, int c, const qsim_pauli *terms, size_t nt, ExpectPlan *out);
+// <P> of a term (not normalised) from its sum over the state.
+double expect_value(const qsim_pauli &t, double sum);
 
 double now_seconds();
 

@@ -1785,6 +1785,10 @@ int launch_probs_noalloc(int dtype, const void *state, int n, const int *qs, int
     return check(hipGetLastError());
 }
 
+void launch_finish(const double *partials, uint32_t nchunks, uint32_t count, double *out, hipStream_t st) {
+    hipLaunchKernelGGL(k_finish, dim3(count), dim3(NT), 0, st, partials, nchunks, out);
+}
+
 uint32_t pauli_chunks(int n) {
     uint64_t c = (uint64_t(1) << n) / 4096;
     if (c < 1) c = 1;

@@ -115,9 +115,9 @@ struct SpanArgs {
     uint32_t nstage;         // stages of the pass
 };
 
-// Base index of the tile of workgroup bx: its bits in the rest bits, ascending.
-__host__ __device__ inline uint64_t span_base(uint64_t bx, const SpanArgs &sa) {
-    uint64_t m = sa.rest_mask, x = bx, r = 0;
+// The bits of bx in the bits of `rest`, ascending.
+__host__ __device__ inline uint64_t rest_base(uint64_t bx, uint64_t rest) {
+    uint64_t m = rest, x = bx, r = 0;
     while (m && x) {
         const uint64_t low = m & (~m + 1);
         if (x & 1) r |= low;
@@ -125,6 +125,11 @@ __host__ __device__ inline uint64_t span_base(uint64_t bx, const SpanArgs &sa) {
         m &= m - 1;
     }
     return r;
+}
+
+// Base index of the tile of workgroup bx.
+__host__ __device__ inline uint64_t span_base(uint64_t bx, const SpanArgs &sa) {
+    return rest_base(bx, sa.rest_mask);
 }
 
 // LDS bytes of a span pass: the tile, an entry per record (and one that the
@@ -139,6 +144,17 @@ bool init_span_kernels();
 int launch_span(int dtype, void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa,
                 const qs::DevOp *ops, uint32_t ob, uint32_t oe, const void *coefs, uint64_t cstride,
                 const int32_t *status, uint32_t flags, hipStream_t st);
+
+// Sums of a planned Pauli sum (qs::ExpectPlan) over nstates states: out[b * nterms
+// + k] for term k (nterms counts the identity).  `table`: the plan's groups, then
+// its records, in device memory; partials: nstates * nterms * chunks doubles.
+// out may be host memory that the device can write.
+uint32_t expect_chunks(int n, int t, uint32_t nterms, uint32_t nstates);
+int launch_expect(int dtype, const void *state, uint64_t sstride, uint32_t nstates, int n, const qs::ExpectPlan &plan,
+                  const void *table, uint32_t nterms, uint32_t chunks, double *partials, double *out,
+                  hipStream_t st);
+// out[i] = sum over c of partials[i * nchunks + c], for i < count
+void launch_finish(const double *partials, uint32_t nchunks, uint32_t count, double *out, hipStream_t st);
 
 // Enable > 64 KiB of dynamic LDS for the tile kernels.  Idempotent.
 int init_kernels();

@@ -23,6 +23,7 @@ struct PassInfo {
 };
 
 struct Compiled {
+    bool pauli = false;   // a Pauli program: its plan does not depend on fusion options
     PackedPlan plan;
     std::vector<PassInfo> passes;
     qsim_apply_stats stats{};

@@ -91,6 +91,7 @@ struct Request {
     std::vector<qsim_pauli> terms;
     void *host_state_out = nullptr;
     Compiled c;
+    ExpectPlan expect;            // of the terms (none planned for states of few qubits)
     bool compiled = false;
     int status = QSIM_OK;
     size_t bytes = 0, off = 0;
@@ -106,8 +107,10 @@ struct Slot {
     size_t cap_red = 0;
     uint64_t *d_masks = nullptr;
     size_t cap_masks = 0;
-    double *h_out = nullptr;      // pinned: [norm][2 * nterms]
+    double *h_out = nullptr;      // pinned results, written by the reduction kernels
     size_t cap_out = 0;
+    void *h_table = nullptr;      // pinned staging of the terms' table
+    size_t cap_table = 0;
 };
 
 int grow_dev(void **p, size_t *cap, size_t need) {
@@ -196,6 +199,9 @@ void worker_loop(qsim_server *s) {
                                  GateInputs{r->mats.empty() ? nullptr : r->mats.data(),
                                             r->mats.size() / 2, nullptr, 0},
                                  fo, &r->c);
+            if (!rc && !r->terms.empty() &&
+                !plan_expect(r->n, s->opt.dtype == QSIM_C64 ? 4 : 3, r->terms.data(), r->terms.size(), &r->expect))
+                r->expect = ExpectPlan{};
         } catch (const std::bad_alloc &) {
             rc = QSIM_E_NOMEM;
         }
@@ -218,27 +224,46 @@ int launch_request(qsim_server *s, Slot &sl, Request *r) {
     const bool first_tile = !c.passes.empty() && c.passes[0].kind == Pass::TILE;
     if (!first_tile && (rc = qk::launch_init_zero(dtype, state, 0, 1, r->n, sl.st))) return rc;
     if (!c.passes.empty() && (rc = enqueue_passes(c, sl.dt, dtype, state, sl.st, first_tile))) return rc;
+    // the reductions write their results to the slot's pinned buffer
     const size_t nt = r->terms.size();
-    const uint32_t nch = qk::marginal_chunks(r->n, 0);
-    const uint32_t pch = qk::pauli_chunks(r->n);
-    const size_t part = std::max<size_t>(nch, size_t(pch) * 2 * nt);
-    if ((rc = grow_dev((void **)&sl.d_red, &sl.cap_red, (part + 1 + 2 * nt + 64) * 8))) return rc;
-    double *d_part = sl.d_red, *d_out = sl.d_red + part + 32;
-    if ((rc = grow_pinned((void **)&sl.h_out, &sl.cap_out, (1 + 2 * nt) * 8))) return rc;
-    if ((rc = qk::launch_marginal(dtype, state, 0, 1, r->n, nullptr, 0, d_part, d_out, sl.st))) return rc;
-    if (nt) {
-        std::vector<uint64_t> m;
-        const qk::PauliRows nrows = qk::pauli_rows(r->terms.data(), nt, &m);
-        if ((rc = grow_dev((void **)&sl.d_masks, &sl.cap_masks, 8 * m.size()))) return rc;
-        // synchronous copy: the slot's previous request has completed
-        if ((rc = qk::note_hip(hipMemcpy(sl.d_masks, m.data(), 8 * m.size(), hipMemcpyHostToDevice), "masks")))
+    if (!r->expect.groups.empty()) {
+        // [terms][norm], from one set of readings of the state
+        const ExpectPlan &plan = r->expect;
+        const uint32_t nterms = uint32_t(nt) + 1, nch = qk::expect_chunks(r->n, plan.t, nterms, 1);
+        const size_t ga = plan.groups.size() * sizeof(ExpectGroup), bytes = plan.table_bytes();
+        if ((rc = grow_dev((void **)&sl.d_red, &sl.cap_red, size_t(nch) * nterms * 8))) return rc;
+        if ((rc = grow_pinned((void **)&sl.h_out, &sl.cap_out, nterms * 8))) return rc;
+        if ((rc = grow_dev((void **)&sl.d_masks, &sl.cap_masks, bytes))) return rc;
+        // (the slot's previous request has completed: its table is free)
+        if ((rc = grow_pinned(&sl.h_table, &sl.cap_table, bytes))) return rc;
+        std::memcpy(sl.h_table, plan.groups.data(), ga);
+        std::memcpy((char *)sl.h_table + ga, plan.recs.data(), bytes - ga);
+        if ((rc = qk::note_hip(hipMemcpyAsync(sl.d_masks, sl.h_table, bytes, hipMemcpyHostToDevice, sl.st), "terms")))
             return rc;
-        if ((rc = qk::launch_pauli(dtype, state, 0, 1, r->n, sl.d_masks, int(nt), nrows, d_part, d_out + 1, sl.st)))
+        if ((rc = qk::launch_expect(dtype, state, 0, 1, r->n, plan, sl.d_masks, nterms, nch, sl.d_red, sl.h_out,
+                                    sl.st)))
             return rc;
+    } else {
+        // [terms, re and im][norm]
+        const uint32_t nch = qk::marginal_chunks(r->n, 0);
+        const uint32_t pch = qk::pauli_chunks(r->n);
+        const size_t part = std::max<size_t>(nch, size_t(pch) * 2 * nt);
+        if ((rc = grow_dev((void **)&sl.d_red, &sl.cap_red, part * 8))) return rc;
+        if ((rc = grow_pinned((void **)&sl.h_out, &sl.cap_out, (1 + 2 * nt) * 8))) return rc;
+        if ((rc = qk::launch_marginal(dtype, state, 0, 1, r->n, nullptr, 0, sl.d_red, sl.h_out + 2 * nt, sl.st)))
+            return rc;
+        if (nt) {
+            std::vector<uint64_t> m;
+            const qk::PauliRows nrows = qk::pauli_rows(r->terms.data(), nt, &m);
+            if ((rc = grow_dev((void **)&sl.d_masks, &sl.cap_masks, 8 * m.size()))) return rc;
+            // synchronous copy: the slot's previous request has completed
+            if ((rc = qk::note_hip(hipMemcpy(sl.d_masks, m.data(), 8 * m.size(), hipMemcpyHostToDevice), "masks")))
+                return rc;
+            if ((rc = qk::launch_pauli(dtype, state, 0, 1, r->n, sl.d_masks, int(nt), nrows, sl.d_red, sl.h_out,
+                                       sl.st)))
+                return rc;
+        }
     }
-    if ((rc = qk::note_hip(hipMemcpyAsync(sl.h_out, d_out, (1 + 2 * nt) * 8, hipMemcpyDeviceToHost, sl.st),
-                           "results")))
-        return rc;
     if (r->host_state_out &&
         (rc = qk::note_hip(hipMemcpyAsync(r->host_state_out, state, (size_t(1) << r->n) * elem_bytes(dtype),
                                           hipMemcpyDeviceToHost, sl.st),
@@ -251,10 +276,15 @@ void retire(qsim_server *s, Slot &sl) {
     Request *r = sl.req;
     sl.req = nullptr;
     const size_t nt = r->terms.size();
-    const double norm = sl.h_out[0];
+    const bool planned = !r->expect.groups.empty();
+    const double norm = sl.h_out[planned ? nt : 2 * nt];
     double total = 0;
     for (size_t k = 0; k < nt; k++) {
-        const double re = sl.h_out[1 + 2 * k], im = sl.h_out[2 + 2 * k];
+        if (planned) {
+            total += r->terms[k].coeff * expect_value(r->terms[k], sl.h_out[k]);
+            continue;
+        }
+        const double re = sl.h_out[2 * k], im = sl.h_out[2 * k + 1];
         double v;
         switch (__builtin_popcountll(r->terms[k].xmask & r->terms[k].zmask) & 3) {
         case 0: v = re; break;
@@ -459,6 +489,7 @@ int qsim_server_destroy(qsim_server_h s) {
         if (sl.d_red) (void)hipFree(sl.d_red);
         if (sl.d_masks) (void)hipFree(sl.d_masks);
         if (sl.h_out) (void)hipHostFree(sl.h_out);
+        if (sl.h_table) (void)hipHostFree(sl.h_table);
         if (sl.done) (void)hipEventDestroy(sl.done);
         if (sl.st) (void)hipStreamDestroy(sl.st);
     }

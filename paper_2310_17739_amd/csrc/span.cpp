@@ -430,6 +430,90 @@ constexpr size_t kSkipMax = 64;
 // scales its result.
 constexpr size_t kPassMax = 96;
 
+// The layout of a stage whose registers run the directions `dirs` (at most
+// `regs` independent vectors of T), as tile coordinates.
+void stage_layout(const Span &T, const std::vector<uint64_t> &dirs, int t, int c, int regs, SpanStage *st) {
+    const int logt = t - regs;
+    uint32_t reg[8];
+    int nr = 0;
+    Rank all;
+    for (uint64_t x : dirs) {
+        reg[nr] = T.coords(x);
+        all.add(reg[nr++]);
+    }
+    // spare register bits: the highest coordinates that are free
+    for (int j = t - 1; j >= 0 && nr < regs; j--)
+        if (all.add(1u << j)) reg[nr++] = 1u << j;
+    // lanes: the low qubits first (contiguous chunks in memory), then
+    // coordinates that bring the lanes of an LDS access to distinct banks,
+    // then the others
+    int nt = 0;
+    uint32_t thr[16], taken = 0;
+    Rank bank;
+    auto take = [&](int j) {
+        thr[nt++] = 1u << j;
+        taken |= 1u << j;
+    };
+    for (int j = 0; j < c && nt < logt; j++) {
+        Rank probe = all;
+        if (!probe.add(1u << j)) continue;
+        all = probe;
+        bank.add(span_slot(1u << j) & 31u);
+        take(j);
+    }
+    for (int j = c; j < t && nt < std::min(5, logt); j++) {
+        if ((taken >> j) & 1) continue;
+        Rank probe = all, pb = bank;
+        if (!probe.add(1u << j) || !pb.add(span_slot(1u << j) & 31u)) continue;
+        all = probe;
+        bank = pb;
+        take(j);
+    }
+    for (int j = 0; j < t && nt < logt; j++)
+        if (!((taken >> j) & 1) && all.add(1u << j)) take(j);
+    for (int j = 0; j < logt; j++) st->layout[j] = uint16_t(thr[j]);
+    for (int j = 0; j < regs; j++) st->layout[logt + j] = uint16_t(reg[j]);
+}
+
+// A stage record: the LDS slots of the layout's positions.
+DevOp stage_record(const SpanStage &st, int t, int number) {
+    DevOp h{};
+    h.kind = DEVOP_STAGE;
+    h.kx = uint8_t(number);
+    uint8_t *raw = reinterpret_cast<uint8_t *>(&h);
+    for (int j = 0; j < t; j++) {
+        const uint16_t s = uint16_t(span_slot(st.layout[j]));
+        std::memcpy(raw + (j < 7 ? 2 * j : 16 + 2 * (j - 7)), &s, 2);
+    }
+    return h;
+}
+
+// The form and the sign masks of the string (x, z) in a layout whose positions
+// move the state's index by V; false if x is none of its register bits.
+bool string_record(uint64_t x, uint64_t z, const uint64_t *V, int t, int regs, DevOp *d) {
+    const int logt = t - regs;
+    int bit = -1;
+    for (int r = 0; r < regs; r++)
+        if (V[logt + r] == x) bit = r;
+    if (x && bit < 0) return false;
+    const uint32_t m = x ? 1u << bit : 0u;
+    d->k = uint8_t(x ? 2 * bit + (__builtin_popcountll(x & z) & 1) : 2 * regs);
+    uint32_t zr = 0, zt = 0;
+    for (int b = 0; b < regs; b++) zr |= uint32_t(__builtin_popcountll(z & V[logt + b]) & 1) << b;
+    for (int b = 0; b < logt; b++) zt |= uint32_t(__builtin_popcountll(z & V[b]) & 1) << b;
+    // the signs of the register pairs {r, r ^ m} in ascending order of
+    // r < r ^ m, each against the pair before it
+    for (uint32_t r = 0, k = 0, last = 0; r < (1u << regs); r++) {
+        if (m && r > (r ^ m)) continue;
+        const uint32_t sgn = uint32_t(__builtin_popcount(r & zr) & 1);
+        d->present |= (sgn ^ last) << k++;
+        last = sgn;
+    }
+    d->slot[0] = uint16_t(zt);
+    for (int b = 0; b < 3; b++) d->slot[1 + b] = uint16_t((z >> (16 * b)) & 0xffff);
+    return true;
+}
+
 }  // namespace
 
 void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t meta_budget, int window,
@@ -533,47 +617,7 @@ void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t met
                 }
             }
             left.swap(later);
-            // layout: thread bits, then register bits, as tile coordinates
-            const int logt = t - regs;
-            uint32_t reg[8];
-            int nr = 0;
-            Rank all;
-            for (uint64_t x : dirs) {
-                reg[nr] = T.coords(x);
-                all.add(reg[nr++]);
-            }
-            // spare register bits: the highest coordinates that are free
-            for (int j = t - 1; j >= 0 && nr < regs; j--)
-                if (all.add(1u << j)) reg[nr++] = 1u << j;
-            // lanes: the low qubits first (contiguous chunks in memory), then
-            // coordinates that bring the lanes of an LDS access to distinct
-            // banks, then the others
-            int nt = 0;
-            uint32_t thr[16], taken = 0;
-            Rank bank;
-            auto take = [&](int j) {
-                thr[nt++] = 1u << j;
-                taken |= 1u << j;
-            };
-            for (int j = 0; j < c && nt < logt; j++) {
-                Rank probe = all;
-                if (!probe.add(1u << j)) continue;
-                all = probe;
-                bank.add(span_slot(1u << j) & 31u);
-                take(j);
-            }
-            for (int j = c; j < t && nt < std::min(5, logt); j++) {
-                if ((taken >> j) & 1) continue;
-                Rank probe = all, pb = bank;
-                if (!probe.add(1u << j) || !pb.add(span_slot(1u << j) & 31u)) continue;
-                all = probe;
-                bank = pb;
-                take(j);
-            }
-            for (int j = 0; j < t && nt < logt; j++)
-                if (!((taken >> j) & 1) && all.add(1u << j)) take(j);
-            for (int j = 0; j < logt; j++) st.layout[j] = uint16_t(thr[j]);
-            for (int j = 0; j < regs; j++) st.layout[logt + j] = uint16_t(reg[j]);
+            stage_layout(T, dirs, t, c, regs, &st);
             p.stages.push_back(std::move(st));
         }
         for (int j = 0; j < t; j++) p.span_v[j] = T.v[j];
@@ -589,18 +633,10 @@ uint64_t span_vector(const Pass &p, uint32_t coords) {
 }
 
 int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, PackedPlan *out) {
-    const int t = p.t, logt = t - regs;
+    const int t = p.t;
     int number = 0;
     for (const SpanStage &st : p.stages) {
-        DevOp h{};
-        h.kind = DEVOP_STAGE;
-        h.kx = uint8_t(number++);
-        uint8_t *raw = reinterpret_cast<uint8_t *>(&h);
-        for (int j = 0; j < t; j++) {
-            const uint16_t s = uint16_t(span_slot(st.layout[j]));
-            std::memcpy(raw + (j < 7 ? 2 * j : 16 + 2 * (j - 7)), &s, 2);
-        }
-        out->ops.push_back(h);
+        out->ops.push_back(stage_record(st, t, number++));
         out->op_np.push_back(0);
         for (int j = 0; j < 3; j++) out->op_slots.push_back(-1);
         // the layout's positions as vectors of the state's index
@@ -608,30 +644,11 @@ int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, 
         for (int j = 0; j < t; j++) V[j] = span_vector(p, st.layout[j]);
         for (int idx : st.ops) {
             const PauliOp &o = P.ops[size_t(idx)];
-            // the register bit that the X mask is (none for a diagonal)
-            int bit = -1;
-            for (int r = 0; r < regs; r++)
-                if (V[logt + r] == o.x) bit = r;
-            if (o.x && bit < 0) return QSIM_E_ARG;
-            const uint32_t m = o.x ? 1u << bit : 0u;
-            const int ny = __builtin_popcountll(o.x & o.z) & 3;
             DevOp d{};
             d.kind = DEVOP_PAULI;
             d.coef = uint32_t(out->coefs.size());
-            d.k = uint8_t(o.x ? 2 * bit + (ny & 1) : 2 * regs);
-            uint32_t zr = 0, zt = 0;
-            for (int b = 0; b < regs; b++) zr |= uint32_t(__builtin_popcountll(o.z & V[logt + b]) & 1) << b;
-            for (int b = 0; b < logt; b++) zt |= uint32_t(__builtin_popcountll(o.z & V[b]) & 1) << b;
-            // the signs of the register pairs {r, r ^ m} in ascending order of
-            // r < r ^ m, each against the pair before it
-            for (uint32_t r = 0, k = 0, last = 0; r < (1u << regs); r++) {
-                if (m && r > (r ^ m)) continue;
-                const uint32_t sgn = uint32_t(__builtin_popcount(r & zr) & 1);
-                d.present |= (sgn ^ last) << k++;
-                last = sgn;
-            }
-            d.slot[0] = uint16_t(zt);
-            for (int b = 0; b < 3; b++) d.slot[1 + b] = uint16_t((o.z >> (16 * b)) & 0xffff);
+            if (!string_record(o.x, o.z, V, t, regs, &d)) return QSIM_E_ARG;
+            const int ny = __builtin_popcountll(o.x & o.z) & 3;
             // y[i] = a x[i] + b (-1)^(i . z) x[i ^ x] with a = cos phi and
             // b = -i sin phi (-i)^ny: t is its real or imaginary part
             const double kappa = (ny & 2) ? 1.0 : -1.0;
@@ -652,10 +669,111 @@ int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, 
             }
             out->op_slots.push_back(-1);
             out->op_slots.push_back(-1);
-            out->terms += m ? 2 : 1;
+            out->terms += o.x ? 2 : 1;
         }
     }
     return QSIM_OK;
+}
+
+bool plan_expect(int n, int c, const qsim_pauli *terms, size_t nt, ExpectPlan *out) {
+    const int t = std::min(n, 12), regs = kSpanRegs;
+    out->t = t;
+    out->recs.clear();
+    out->groups.clear();
+    out->max_rec = out->max_stage = 0;
+    out->relaid = false;
+    if (!span_tile_ok(t) || n > 48) return false;
+    const uint64_t all = (uint64_t(1) << n) - 1;
+    // the terms in ascending order of their X masks, and the identity (whose
+    // value is the norm) first
+    std::vector<uint32_t> idx(nt + 1);
+    for (size_t k = 0; k <= nt; k++) idx[k] = uint32_t(k);
+    auto X = [&](uint32_t k) { return k < nt ? terms[k].xmask : 0; };
+    auto Z = [&](uint32_t k) { return k < nt ? terms[k].zmask : 0; };
+    std::stable_sort(idx.begin(), idx.end(), [&](uint32_t a, uint32_t b) { return X(a) < X(b); });
+    // (in blocks, so that planning stays linear in the number of terms)
+    std::vector<uint32_t> left, later, sel, rest;
+    size_t taken = 0;
+    while (taken < idx.size() || !left.empty()) {
+        if (left.empty()) {
+            const size_t end = std::min(idx.size(), taken + 2048);
+            left.assign(idx.begin() + long(taken), idx.begin() + long(end));
+            taken = end;
+        }
+        // a group: terms whose X masks lie in one tile's space
+        Span T;
+        for (int q = 0; q < std::min(c, t); q++) T.add(uint64_t(1) << q);
+        later.clear();
+        sel.clear();
+        for (uint32_t k : left) {
+            const uint64_t r = T.reduce(X(k));
+            if (sel.size() < kExpectGroup && (r == 0 || T.d < t)) {
+                if (r) T.add(r);
+                sel.push_back(k);
+            } else {
+                later.push_back(k);
+            }
+        }
+        left.swap(later);
+        for (int q = 0; q < n && T.d < t; q++) {
+            const uint64_t r = T.reduce(uint64_t(1) << q);
+            if (r) T.add(r);
+        }
+        ExpectGroup g{};
+        g.rest_mask = all & ~T.pm;
+        g.rec_begin = uint32_t(out->recs.size());
+        while (!sel.empty()) {
+            // a stage: at most `regs` independent X masks
+            Span R;
+            std::vector<uint64_t> dirs;
+            std::vector<uint32_t> mine;
+            rest.clear();
+            for (uint32_t k : sel) {
+                const uint64_t x = X(k);
+                const bool have = !x || std::find(dirs.begin(), dirs.end(), x) != dirs.end();
+                const uint64_t r = have ? 0 : R.reduce(x);
+                if (have || (r && R.d < regs)) {
+                    if (r) {
+                        R.add(r);
+                        dirs.push_back(x);
+                    }
+                    mine.push_back(k);
+                } else {
+                    rest.push_back(k);
+                }
+            }
+            sel.swap(rest);
+            SpanStage st;
+            stage_layout(T, dirs, t, c, regs, &st);
+            uint64_t V[16];
+            for (int j = 0; j < t; j++) {
+                V[j] = 0;
+                for (int i = 0; i < t; i++)
+                    if ((st.layout[j] >> i) & 1) V[j] ^= T.v[i];
+                if (g.stages == 0) g.load_v[j] = V[j];
+            }
+            out->recs.push_back(stage_record(st, t, int(g.stages++)));
+            for (uint32_t k : mine) {
+                DevOp d{};
+                d.kind = DEVOP_EXPECT;
+                d.coef = k;
+                if (!string_record(X(k), Z(k), V, t, regs, &d)) return false;
+                out->recs.push_back(d);
+            }
+        }
+        g.rec_end = uint32_t(out->recs.size());
+        out->max_rec = std::max(out->max_rec, g.rec_end - g.rec_begin);
+        out->max_stage = std::max(out->max_stage, g.stages);
+        out->relaid = out->relaid || g.stages > 1;
+        out->groups.push_back(g);
+    }
+    return true;
+}
+
+double expect_value(const qsim_pauli &t, double sum) {
+    // <P> = sum over pairs {i, i ^ x} of 2 (-i)^ny s_i Re or i Im of conj(a_i) a_(i ^ x)
+    if (!t.xmask) return sum;
+    return (__builtin_popcountll(t.xmask & t.zmask) & 2) ? -2.0 * sum : 2.0 * sum;
 }
 
 }  // namespace qs

@@ -26,6 +26,7 @@
 // 30 qubits complex64 (22.1 against 19.4 at 21 qubits complex128).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "device.h"
@@ -317,9 +318,197 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
     }
 }
 
+// ---------------------------------------------------------- Pauli sums
+// Sum over a wave, in lane 63 (fixed order; row shifts and row broadcasts, no LDS).
+__device__ __forceinline__ double wave_total(double v) {
+    auto step = [&](auto ctrl, auto rows) {
+        const int64_t b = __double_as_longlong(v);
+        const int lo = __builtin_amdgcn_update_dpp(0, int(uint32_t(b)), decltype(ctrl)::value, decltype(rows)::value, 0xf, true);
+        const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), decltype(ctrl)::value, decltype(rows)::value, 0xf, true);
+        v += __longlong_as_double((int64_t(hi) << 32) | int64_t(uint32_t(lo)));
+    };
+    step(IntC<0x111>{}, IntC<0xf>{});   // row_shr 1, 2, 4, 8: lane 15 of a row holds its sum
+    step(IntC<0x112>{}, IntC<0xf>{});
+    step(IntC<0x114>{}, IntC<0xf>{});
+    step(IntC<0x118>{}, IntC<0xf>{});
+    step(IntC<0x142>{}, IntC<0xa>{});   // row_bcast 15 into rows 1 and 3, 31 into rows 2 and 3
+    step(IntC<0x143>{}, IntC<0xc>{});
+    return v;
+}
+
+// A term's sum over a thread's registers (see rotate for M, REAL and d): the
+// real parts of conj(v[r]) v[r ^ M] with their signs, the imaginary parts for
+// an odd number of Y letters (REAL), |v[r]|^2 for M = 0.
+template <typename T, int LR, int M, bool REAL>
+__device__ __forceinline__ double term_sum(const Cx<T> (&v)[1 << LR], double one, uint32_t d) {
+    double acc = 0.0;
+    static_for<0, 1 << LR>([&](auto rc) {
+        constexpr int r = decltype(rc)::value, q = r ^ M;
+        if constexpr (M == 0 || r < q) {
+            constexpr int k = M == 0 ? r : (r / (2 * M)) * M + r % M;
+            if constexpr (k > 0) turn(one, turn_sign(d, k));
+            const double ar = v[r].re, ai = v[r].im, br = v[q].re, bi = v[q].im;
+            acc = fma(one, REAL ? fma(ar, bi, -(ai * br)) : fma(ar, br, ai * bi), acc);
+        }
+    });
+    asm volatile("; summed by %0" ::"i"(M * 2 + REAL));
+    return acc;
+}
+
+// One workgroup: the tiles blockIdx.x, blockIdx.x + gridDim.x, ... of group
+// blockIdx.y, state blockIdx.z.  The stages and layouts are those of k_span; a
+// term is read off the registers of the stage that holds its X mask, so a group
+// of about ten masks costs one reading of the state (k_pauli: one per mask).
+// partials[(b * nterms + term) * gridDim.x + blockIdx.x]
+template <typename T, int LOGT, bool WIDE>
+__global__ void __launch_bounds__(1 << LOGT) k_expect(const Cx<T> *__restrict__ state, uint64_t sstride,
+                                                     const qs::ExpectGroup *__restrict__ groups,
+                                                     const DevOp *__restrict__ all_recs,
+                                                     uint32_t nterms, uint32_t ntiles, uint32_t tile_bytes,
+                                                     double *__restrict__ partials) {
+    using L = LdsTile<T>;
+    using Off = typename OffsetOf<WIDE>::type;
+    constexpr int LR = qs::kSpanRegs, E = 1 << LR, TNT = 1 << LOGT, NW = TNT / 64;
+    const qs::ExpectGroup *g = groups + blockIdx.y;
+    const DevOp *recs = all_recs + g->rec_begin;
+    const uint32_t nrec = g->rec_end - g->rec_begin, nstage = g->stages;
+    const char *st = reinterpret_cast<const char *>(state + size_t(blockIdx.z) * sstride);
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const uint32_t ent_at = tile_bytes, lay_at = ent_at + 16u * (nrec + 1), acc_at = lay_at + 32u * nstage;
+    for (uint32_t x = uint32_t(tid); x < nrec; x += TNT) {
+        const U4 *p = reinterpret_cast<const U4 *>(recs + x);
+        const U4 a = p[0], c = p[1];
+        U4 e = {0, 0, 0, 0};
+        if (((a.w >> 16) & 0xff) == qs::DEVOP_EXPECT) {
+            e.x = (a.y & 0xffffu) | ((c.x & 0xfffu) << 16) | ((a.z & 0xffu) << 28);
+            e.y = (c.x >> 16) | (c.y << 16);   // the sign mask of the base index
+            e.z = c.y >> 16;
+        } else {
+            const uint32_t number = a.w >> 24;
+            e.x = (kStageForm << 28) | number;
+            *reinterpret_cast<LdsU4 *>(uintptr_t(lay_at + 32u * number)) = a;
+            *reinterpret_cast<LdsU4 *>(uintptr_t(lay_at + 32u * number + 16u)) = c;
+        }
+        *reinterpret_cast<LdsU4 *>(uintptr_t(ent_at + 16u * x)) = e;
+    }
+    for (uint32_t x = uint32_t(tid); x < nrec * NW; x += TNT) *reinterpret_cast<LdsF8 *>(uintptr_t(acc_at + 8u * x)) = 0.0;
+    __syncthreads();
+    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const uint64_t base = rest_base(tile, g->rest_mask);
+        Cx<T> v[E];
+        {
+            Off off = Off(base) << L::LOGE, reg[LR];
+            static_for<0, LOGT>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                off ^= ((tid >> k) & 1) ? Off(g->load_v[k]) << L::LOGE : Off(0);
+            });
+            static_for<0, LR>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                reg[k] = Off(g->load_v[LOGT + k]) << L::LOGE;
+            });
+            static_for<0, E>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                v[r] = *reinterpret_cast<const Cx<T> *>(st + (off ^ reg_off<r>(reg)));
+            });
+        }
+        uint32_t slot_t, slot_r[LR];
+        stage_layout<T, LOGT>(lay_at, tid, slot_t, slot_r);
+        if (tile != blockIdx.x && nstage > 1) __syncthreads();   // the last tile's slots have been read
+        U4 ahead = lds_u4(ent_at + 16u);
+        for (uint32_t i = 1; i < nrec; i++) {
+            const U4 e = ahead;
+            const uint32_t w = __builtin_amdgcn_readfirstlane(e.x);
+            ahead = lds_u4(ent_at + 16u * (i + 1));
+            const uint32_t form = w >> 28;
+            if (form != kStageForm) {
+                const uint32_t zl = __builtin_amdgcn_readfirstlane(e.y), zh = __builtin_amdgcn_readfirstlane(e.z);
+                const uint32_t s = uint32_t(__builtin_popcount(uint32_t(tid) & ((w >> 16) & 0xfffu))) +
+                                   uint32_t(__builtin_popcount(uint32_t(base) & zl)) +
+                                   uint32_t(__builtin_popcount(uint32_t(base >> 32) & zh));
+                const double one = flip(1.0, s << 31);
+                double acc;
+                switch (form) {
+                case 0: acc = term_sum<T, LR, 1, false>(v, one, w); break;
+                case 1: acc = term_sum<T, LR, 1, true>(v, one, w); break;
+                case 2: acc = term_sum<T, LR, 2, false>(v, one, w); break;
+                case 3: acc = term_sum<T, LR, 2, true>(v, one, w); break;
+                case 4: acc = term_sum<T, LR, 4, false>(v, one, w); break;
+                case 5: acc = term_sum<T, LR, 4, true>(v, one, w); break;
+                case 6: acc = term_sum<T, LR, 8, false>(v, one, w); break;
+                case 7: acc = term_sum<T, LR, 8, true>(v, one, w); break;
+                default: acc = term_sum<T, LR, 0, false>(v, one, w); break;
+                }
+                acc = wave_total(acc);
+                if ((tid & 63) == 63) *reinterpret_cast<LdsF8 *>(uintptr_t(acc_at + 8u * (i * NW + uint32_t(wave)))) += acc;
+            } else {
+                static_for<0, E>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    L::st(slot_t ^ reg_off<r>(slot_r), v[r]);
+                });
+                stage_layout<T, LOGT>(lay_at + 32u * (w & 0xffu), tid, slot_t, slot_r);
+                __syncthreads();
+                static_for<0, E>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    v[r] = L::ld(slot_t ^ reg_off<r>(slot_r));
+                });
+            }
+        }
+    }
+    __syncthreads();
+    for (uint32_t x = uint32_t(tid); x < nrec; x += TNT) {
+        if (((reinterpret_cast<const U4 *>(recs + x)[0].w >> 16) & 0xff) != qs::DEVOP_EXPECT) continue;
+        double s = 0.0;
+        for (int w = 0; w < NW; w++) s += *reinterpret_cast<const LdsF8 *>(uintptr_t(acc_at + 8u * (x * NW + uint32_t(w))));
+        partials[(size_t(blockIdx.z) * nterms + recs[x].coef) * gridDim.x + blockIdx.x] = s;
+    }
+}
+
 // ------------------------------------------------------------- launchers
 namespace {
 bool span_static_lds = false;
+
+template <typename T, int LOGT, bool WIDE>
+void expect_attr() {
+    const void *f = reinterpret_cast<const void *>(&k_expect<T, LOGT, WIDE>);
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(max_lds_bytes()));
+    if (e != hipSuccess) note_hip(e, "hipFuncSetAttribute(k_expect)");
+    hipFuncAttributes fa{};
+    if (hipFuncGetAttributes(&fa, f) == hipSuccess && fa.sharedSizeBytes != 0) span_static_lds = true;
+}
+template <typename T>
+void expect_attrs() {
+    expect_attr<T, 6, false>();
+    expect_attr<T, 7, false>();
+    expect_attr<T, 8, false>();
+    expect_attr<T, 8, true>();
+}
+
+template <typename T>
+int expect_t(const void *state, uint64_t sstride, uint32_t nstates, int n, const qs::ExpectPlan &plan,
+             const void *table, uint32_t nterms, uint32_t chunks, uint32_t tile_bytes, size_t lds, double *partials,
+             hipStream_t st) {
+    const uint32_t ng = uint32_t(plan.groups.size()), ntiles = uint32_t(uint64_t(1) << (n - plan.t));
+    const qs::ExpectGroup *groups = (const qs::ExpectGroup *)table;
+    const DevOp *recs = reinterpret_cast<const DevOp *>(groups + ng);
+    const bool wide = (uint64_t(sizeof(Cx<T>)) << n) > (uint64_t(1) << 32);
+    for (uint32_t g0 = 0; g0 < ng; g0 += 32768) {   // (a grid's y extent is limited)
+        const dim3 grid(chunks, std::min<uint32_t>(ng - g0, 32768), nstates);
+#define QK_EXPECT(LOGT, WIDE)                                                                                   \
+    hipLaunchKernelGGL((k_expect<T, LOGT, WIDE>), grid, dim3(1 << LOGT), lds, st, (const Cx<T> *)state, sstride, \
+                       groups + g0, recs, nterms, ntiles, tile_bytes, partials)
+        switch (plan.t - qs::kSpanRegs) {
+        case 6: QK_EXPECT(6, false); break;
+        case 7: QK_EXPECT(7, false); break;
+        case 8:
+            if (wide) QK_EXPECT(8, true);
+            else QK_EXPECT(8, false);
+            break;
+        default: return QSIM_E_ARG;
+        }
+    }
+#undef QK_EXPECT
+    return note_hip(hipGetLastError(), "k_expect launch");
+}
 
 template <typename T, int LOGT, bool WIDE>
 void span_attr() {
@@ -385,8 +574,38 @@ bool init_span_kernels() {
     span_attrs<double, 7>();
     span_attrs<double, 8>();
     span_attrs<double, 9>();
+    expect_attrs<float>();
+    expect_attrs<double>();
     (void)hipGetLastError();
     return !span_static_lds;
+}
+
+// Workgroups per group and state: up to 1024, fewer for many terms and states,
+// so that the partial sums stay within 32 MiB.
+uint32_t expect_chunks(int n, int t, uint32_t nterms, uint32_t nstates) {
+    uint64_t c = std::min<uint64_t>(uint64_t(1) << (n - t), 1024);
+    while (c > 1 && c * nterms * nstates > (uint64_t(1) << 22)) c /= 2;
+    return uint32_t(c);
+}
+
+int launch_expect(int dtype, const void *state, uint64_t sstride, uint32_t nstates, int n, const qs::ExpectPlan &plan,
+                  const void *table, uint32_t nterms, uint32_t chunks, double *partials, double *out,
+                  hipStream_t st) {
+    const size_t elem = dtype == QSIM_C64 ? 8 : 16;
+    if (!qs::span_tile_ok(plan.t) || plan.t > 12 || plan.t > n || n - plan.t > 31 || plan.groups.empty() ||
+        chunks == 0 || chunks > (uint64_t(1) << (n - plan.t)))
+        return QSIM_E_ARG;
+    const uint32_t tile_bytes = plan.relaid ? uint32_t(elem << plan.t) : 0u;
+    const size_t nw = (size_t(1) << (plan.t - qs::kSpanRegs)) / 64;
+    const size_t lds = tile_bytes + 16 * (size_t(plan.max_rec) + 1) + 32 * size_t(plan.max_stage) + 8 * nw * plan.max_rec;
+    if (lds > max_lds_bytes()) return QSIM_E_CAPACITY;
+    const int rc = dtype == QSIM_C64 ? expect_t<float>(state, sstride, nstates, n, plan, table, nterms, chunks,
+                                                       tile_bytes, lds, partials, st)
+                                     : expect_t<double>(state, sstride, nstates, n, plan, table, nterms, chunks,
+                                                        tile_bytes, lds, partials, st);
+    if (rc) return rc;
+    launch_finish(partials, chunks, nstates * nterms, out, st);
+    return note_hip(hipGetLastError(), "k_finish launch");
 }
 
 int launch_span(int dtype, void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops,

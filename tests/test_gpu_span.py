@@ -84,3 +84,39 @@ def test_measurements_between_passes(Q, dtype):
         assert np.max(np.abs(r["probs"][s] - p)) < 2 * grow * tol(dtype, 3 * 16)
         assert norm_error(b.qsim_batch_get_state(0, s), want) < grow * tol(dtype, 3 * 16)
     b.close()
+
+
+@pytest.mark.parametrize("dtype", ["complex128", "complex64"])
+@pytest.mark.parametrize("n", [9, 10, 11, 12, 13, 18])
+@pytest.mark.parametrize("count", [1, 70, 300])
+def test_pauli_sums(Q, dtype, n, count):
+    """Terms of any weight, several groups and stages, X masks that repeat, the
+    identity and diagonals; one state and a batch of two."""
+    rng = np.random.default_rng(n + count)
+    t = np.zeros(count, dtype=W.PAULI_DTYPE)
+    t["xmask"] = rng.integers(0, 1 << n, count)
+    t["zmask"] = rng.integers(0, 1 << n, count)
+    t["xmask"][::5] = 0
+    t["xmask"][1::7] = t["xmask"][min(1, count - 1)]
+    t["zmask"][::15] = 0
+    t["coeff"] = rng.normal(size=count)
+    psi = (1.5 * W.random_state(n, 4)).astype(dtype)
+    print(f"span pauli sum dtype={dtype} n={n} terms={count}", flush=True)
+    sv = Q.StateVector(n, dtype)
+    sv.qsim_set_state(psi)
+    want = oracle.expval(n, psi.astype(np.complex128), t)
+    # FP64 sums of at most a few hundred partial sums each: 2^-53 of each partial
+    assert abs(sv.qsim_expval(t) - want) < 1e-13 * np.abs(t["coeff"]).sum()
+    for k in range(min(count, 4)):
+        one = t[k:k + 1]
+        assert abs(sv.qsim_expval(one) - oracle.expval(n, psi.astype(np.complex128), one)) < 1e-13 * abs(one["coeff"][0])
+    sv.close()
+    g = mixed_circuit(n, 30, seed=n, p_clifford=0.0)
+    b = Q.Batch([{"n": n, "n_states": 2, "gates": g, "terms": t}], dtype=dtype)
+    b.qsim_batch_run()
+    r = b.qsim_batch_results(0)
+    for s in range(2):
+        psi = b.qsim_batch_get_state(0, s).astype(np.complex128)
+        assert abs(r["expvals"][s] - oracle.expval(n, psi, t)) < 1e-13 * np.abs(t["coeff"]).sum()
+        assert abs(r["norms"][s] - np.vdot(psi, psi).real) < 1e-13
+    b.close()
