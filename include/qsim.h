@@ -418,7 +418,7 @@ int qsim_server_destroy(qsim_server_h s);
  * shots together).  Shot s is the smallest basis index x with
  * C(x) > u[s] * C(2^n - 1), where C is the FP64 inclusive prefix sum of
  * |a_x|^2 in index order; u[s] in [0,1).  out[s] receives x.  Synchronous;
- * uses 8 * 2^n bytes of device scratch, allocated on first use. */
+ * uses 2^n / 2 bytes of device scratch, allocated on first use. */
 int qsim_sample(qsim_h h, const double *uniforms, size_t m, uint64_t *out);
 
 /* ------------------------------------------------------ copy ceiling */

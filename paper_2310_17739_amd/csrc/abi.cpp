@@ -741,9 +741,9 @@ struct qsim_state {
     size_t cap_small = 0;
     void *d_masks = nullptr;   // tables of qsim_expval
     size_t cap_masks = 0;
-    void *h_table = nullptr;   // their pinned staging
+    void *h_table = nullptr;   // their pinned staging; draws and shots of qsim_sample
     size_t cap_table = 0;
-    void *d_scan = nullptr;    // sampling: prefix sums, block sums, shots
+    void *d_scan = nullptr;    // sampling: prefix sums
     size_t cap_scan = 0;
     double *h_out = nullptr;   // pinned readback, written by the reduction kernels
     size_t cap_out = 0;
@@ -1158,8 +1158,8 @@ int qsim_expval(qsim_h h, const qsim_pauli *t, size_t nt, double *out) {
                                        plan.recs.data(), plan.recs.size() * sizeof(DevOp));
             if (!rc) rc = qk::launch_expect(h->dtype, h->buf, 0, 1, h->n, plan, h->d_masks, nterms, nch, part,
                                             h->h_out, h->stream);
-            if (!rc) rc = hip_rc(hipStreamSynchronize(h->stream));
-            if (rc) return rc;
+            const int src = hip_rc(hipStreamSynchronize(h->stream));
+            if (rc || src) return rc ? rc : src;
             nrm = h->h_out[nt];
             if (!(nrm > 0)) return QSIM_E_ZERO_PROB;
             for (size_t k = 0; k < nt; k++) total += t[k].coeff * expect_value(t[k], h->h_out[k]);
@@ -1205,30 +1205,31 @@ int qsim_sample(qsim_h h, const double *u, size_t m, uint64_t *out) {
     for (size_t s = 0; s < m; s++)
         if (!(u[s] >= 0.0 && u[s] < 1.0)) return QSIM_E_ARG;
     TraceRange range("qsim_sample");
-    const uint64_t len = uint64_t(1) << h->n;
-    const uint64_t nb = qk::scan_blocks(h->n);
-    // layout: cum[len] | bsum[nb] | boff[nb] | u[m] | shots[m]
-    const size_t need = (len + 2 * nb + 2 * m) * 8 + 1024;
-    int rc = grow(&h->d_scan, &h->cap_scan, need, h->stream);
+    // device scratch: seg | bsum[nb] | boff[nb + 1]; pinned: draws | shots, in
+    // pieces of at most kPiece shots, read and written by the search itself
+    const uint64_t nb = qk::scan_blocks(h->n), ns = qk::scan_segments(h->n);
+    constexpr size_t kPiece = size_t(1) << 18;
+    int rc = grow(&h->d_scan, &h->cap_scan, (ns + 2 * nb + 1) * 8, h->stream);
+    double *part, *dout;
+    if (!rc) rc = reduce_buffers(h, 0, 1, &part, &dout);
+    if (!rc && m) rc = grow_host(&h->h_table, &h->cap_table, 16 * std::min(m, kPiece));
     if (rc) return rc;
-    double *cum = (double *)h->d_scan, *bsum = cum + len, *boff = bsum + nb, *du = boff + nb;
-    uint64_t *dshot = (uint64_t *)(du + m);
-    if ((rc = qk::launch_blockscan(h->dtype, h->buf, h->n, cum, bsum, h->stream))) return rc;
-    std::vector<double> bs(nb);
-    if ((rc = hip_rc(hipMemcpyAsync(bs.data(), bsum, nb * 8, hipMemcpyDeviceToHost, h->stream)))) return rc;
-    if ((rc = hip_rc(hipStreamSynchronize(h->stream)))) return rc;
-    double acc = 0.0;
-    for (uint64_t b = 0; b < nb; b++) {   // exclusive prefix of block totals, in order
-        const double v = bs[b];
-        bs[b] = acc;
-        acc += v;
+    double *seg = (double *)h->d_scan, *bsum = seg + ns, *boff = bsum + nb;
+    if ((rc = qk::launch_scan(h->dtype, h->buf, h->n, seg, bsum, boff, h->h_out, h->stream))) return rc;
+    for (size_t at = 0; at < m || at == 0; at += kPiece) {
+        const size_t k = std::min(m - at, kPiece);
+        double *hu = (double *)h->h_table;
+        uint64_t *hs = (uint64_t *)(hu + k);
+        if (k) std::memcpy(hu, u + at, k * 8);
+        if ((rc = qk::launch_search(h->dtype, h->buf, h->n, seg, boff, hu, k, hs, h->stream))) {
+            (void)hipStreamSynchronize(h->stream);
+            return rc;
+        }
+        if ((rc = hip_rc(hipStreamSynchronize(h->stream)))) return rc;
+        if (at == 0 && !(h->h_out[0] > 0.0)) return QSIM_E_ZERO_PROB;
+        if (k) std::memcpy(out + at, hs, k * 8);
     }
-    if (!(acc > 0.0)) return QSIM_E_ZERO_PROB;
-    if ((rc = hip_rc(hipMemcpyAsync(boff, bs.data(), nb * 8, hipMemcpyHostToDevice, h->stream)))) return rc;
-    if (m && (rc = hip_rc(hipMemcpyAsync(du, u, m * 8, hipMemcpyHostToDevice, h->stream)))) return rc;
-    if ((rc = qk::launch_addoff_search(cum, h->n, boff, du, m, dshot, h->stream))) return rc;
-    if (m && (rc = hip_rc(hipMemcpyAsync(out, dshot, m * 8, hipMemcpyDeviceToHost, h->stream)))) return rc;
-    return hip_rc(hipStreamSynchronize(h->stream));
+    return QSIM_OK;
 }
 
 int qsim_get_state(qsim_h h, void *dst) {

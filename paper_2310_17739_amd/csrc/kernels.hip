@@ -1374,65 +1374,134 @@ __global__ void __launch_bounds__(NT) k_fill_i32(int32_t *__restrict__ p, int32_
 }
 
 // -------------------------------------------------------------- sampling
-// Inclusive prefix sums of |a_x|^2 in FP64, in three fixed-order steps:
-// per-block local scans (4096 elements per block, 16 per thread), block
-// totals scanned on the host, block offsets added back.
-constexpr int SCAN_PER_THREAD = 16;
-constexpr int SCAN_BLOCK = NT * SCAN_PER_THREAD;
+// Prefix sums of |a_x|^2 in FP64 at two levels, segments of 16 elements within
+// blocks of 4096; a shot finds its block, its segment and then its element, whose
+// sum it forms from the state again.  Only the segments' sums are stored (2^n / 16
+// of them), and the whole call is three launches: at 21 qubits complex128, 4,096
+// shots, 109 us with all 2^n sums stored, block offsets scanned on the host and
+// copies around.
+constexpr int SCAN_SEG = 16;
+constexpr int SCAN_BLOCK = NT * SCAN_SEG;
 
+// seg[b * NT + s]: sum of block b up to and with its segment s; bsum[b]: of all
+// of it.  A segment's elements sit on 16 consecutive lanes.  The prefix sums are
+// sequential, within 16 groups of 16 segments and over the groups, and so never
+// fall: a segment of zeros has the sum of the one before it to the last bit, and
+// no shot finds it.
 template <typename T>
 __global__ void __launch_bounds__(NT) k_blockscan(const Cx<T> *__restrict__ state, uint64_t len,
-                                                  double *__restrict__ cum, double *__restrict__ bsum) {
-    __shared__ double tsum[NT];
-    const uint64_t b0 = uint64_t(blockIdx.x) * SCAN_BLOCK + uint64_t(threadIdx.x) * SCAN_PER_THREAD;
-    double loc[SCAN_PER_THREAD];
-    double run = 0.0;
+                                                  double *__restrict__ seg, double *__restrict__ bsum) {
+    constexpr int G = NT / SCAN_SEG;   // groups of a block, segments of a group
+    __shared__ double part[G][G + 1], goff[G];
+    const uint64_t b0 = uint64_t(blockIdx.x) * SCAN_BLOCK;
+    const int tid = threadIdx.x;
 #pragma unroll
-    for (int i = 0; i < SCAN_PER_THREAD; i++) {
-        const uint64_t x = b0 + i;
-        run += (x < len) ? norm2(state[x]) : 0.0;
-        loc[i] = run;
+    for (int i = 0; i < SCAN_SEG; i++) {
+        const uint64_t x = b0 + uint64_t(i) * NT + uint64_t(tid);
+        double v = x < len ? norm2(state[x]) : 0.0;
+#pragma unroll
+        for (int d = 1; d < SCAN_SEG; d <<= 1) v += __shfl_xor(v, d, SCAN_SEG);
+        if ((tid & (SCAN_SEG - 1)) == 0) part[i][tid / SCAN_SEG] = v;
     }
-    tsum[threadIdx.x] = run;
+    __syncthreads();
+    if (tid < G) {
+        double run = 0.0;
+#pragma unroll
+        for (int j = 0; j < G; j++) {
+            run += part[tid][j];
+            part[tid][j] = run;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double run = 0.0;
+#pragma unroll
+        for (int j = 0; j < G; j++) {
+            goff[j] = run;
+            run += part[j][G - 1];
+        }
+        bsum[blockIdx.x] = run;
+    }
+    __syncthreads();
+    seg[uint64_t(blockIdx.x) * NT + uint64_t(tid)] = goff[tid / G] + part[tid / G][tid % G];
+}
+
+// boff[b]: sum of the blocks before b, for b <= nb (never falling, as above);
+// *out: of all of them.  One workgroup, consecutive blocks on a thread.
+__global__ void __launch_bounds__(NT) k_blockoff(const double *__restrict__ bsum, uint64_t nb,
+                                                 double *__restrict__ boff, double *__restrict__ out) {
+    __shared__ double sum[NT];
+    const uint64_t per = (nb + NT - 1) / NT;
+    const uint64_t lo = uint64_t(threadIdx.x) * per, hi = lo + per < nb ? lo + per : nb;
+    double mine = 0.0;
+    for (uint64_t b = lo; b < hi; b++) mine += bsum[b];
+    sum[threadIdx.x] = mine;
     __syncthreads();
     if (threadIdx.x == 0) {
-        double acc = 0.0;
+        double run = 0.0;
+#pragma unroll 16
         for (int j = 0; j < NT; j++) {
-            const double v = tsum[j];
-            tsum[j] = acc;    // exclusive prefix of thread totals
-            acc += v;
+            const double v = sum[j];
+            sum[j] = run;
+            run += v;
         }
-        bsum[blockIdx.x] = acc;
+        boff[nb] = run;
+        *out = run;
     }
     __syncthreads();
-    const double off = tsum[threadIdx.x];
-#pragma unroll
-    for (int i = 0; i < SCAN_PER_THREAD; i++) {
-        const uint64_t x = b0 + i;
-        if (x < len) cum[x] = off + loc[i];
+    const double off = sum[threadIdx.x];
+    double run = 0.0;
+    for (uint64_t b = lo; b < hi; b++) {
+        boff[b] = off + run;
+        run += bsum[b];
     }
 }
 
-__global__ void __launch_bounds__(NT) k_addoff(double *__restrict__ cum, uint64_t len,
-                                               const double *__restrict__ boff) {
-    for (uint64_t x = uint64_t(blockIdx.x) * NT + threadIdx.x; x < len; x += uint64_t(gridDim.x) * NT)
-        cum[x] += boff[x / SCAN_BLOCK];
-}
-
-// Shot s: smallest x with cum[x] > u[s] * cum[len - 1].
-__global__ void __launch_bounds__(NT) k_search(const double *__restrict__ cum, uint64_t len,
-                                               const double *__restrict__ u, uint64_t m,
+// Shot s: smallest x with C(x) > u[s] * C(2^n - 1), C(x) the sum of the blocks,
+// segments and elements up to x.
+template <typename T>
+__global__ void __launch_bounds__(NT) k_search(const Cx<T> *__restrict__ state, uint64_t len,
+                                               const double *__restrict__ seg, const double *__restrict__ boff,
+                                               uint64_t nb, const double *__restrict__ u, uint64_t m,
                                                uint64_t *__restrict__ out) {
     const uint64_t s = uint64_t(blockIdx.x) * NT + threadIdx.x;
     if (s >= m) return;
-    const double target = u[s] * cum[len - 1];
-    uint64_t lo = 0, hi = len - 1;
+    const double target = u[s] * boff[nb];
+    // the first block whose end lies beyond the target, then its first such
+    // segment; where rounding leaves none, the last one that weighs anything
+    const bool past = !(boff[nb] > target);
+    uint64_t lo = 0, hi = nb - 1;
     while (lo < hi) {
         const uint64_t mid = lo + (hi - lo) / 2;
-        if (cum[mid] > target) hi = mid;
+        if (past ? boff[mid + 1] >= boff[nb] : boff[mid + 1] > target) hi = mid;
         else lo = mid + 1;
     }
-    out[s] = lo;
+    const uint64_t b = lo;
+    const double off = boff[b], end = seg[b * NT + NT - 1];
+    const bool beyond = !(off + end > target);
+    uint64_t sl = 0, sh = NT - 1;
+    while (sl < sh) {
+        const uint64_t mid = (sl + sh) / 2;
+        const double v = seg[b * NT + mid];
+        if (beyond ? v >= end : off + v > target) sh = mid;
+        else sl = mid + 1;
+    }
+    const double before = sl ? seg[b * NT + sl - 1] : 0.0;
+    const uint64_t x0 = b * SCAN_BLOCK + sl * SCAN_SEG;
+    // the element, likewise
+    double run = 0.0;
+    uint64_t pick = len - 1;
+    for (int j = 0; j < SCAN_SEG; j++) {
+        const uint64_t x = x0 + uint64_t(j);
+        if (x >= len) break;
+        const double w = norm2(state[x]);
+        run += w;
+        if (w > 0.0) {
+            pick = x;
+            if (off + (before + run) > target) break;
+        }
+    }
+    out[s] = pick;
 }
 
 // ------------------------------------------------------------- launchers
@@ -1895,22 +1964,28 @@ int launch_fill_i32(int32_t *p, int32_t v, uint64_t n, hipStream_t st) {
 }
 
 uint64_t scan_blocks(int n) { return ((uint64_t(1) << n) + SCAN_BLOCK - 1) / SCAN_BLOCK; }
+uint64_t scan_segments(int n) { return scan_blocks(n) * NT; }
 
-int launch_blockscan(int dtype, const void *state, int n, double *cum, double *bsum, hipStream_t st) {
-    const uint64_t len = uint64_t(1) << n;
-    const dim3 grid(uint32_t(scan_blocks(n)));
+int launch_scan(int dtype, const void *state, int n, double *seg, double *bsum, double *boff, double *total,
+                hipStream_t st) {
+    const uint64_t len = uint64_t(1) << n, nb = scan_blocks(n);
     if (dtype == QSIM_C64)
-        hipLaunchKernelGGL(k_blockscan<float>, grid, dim3(NT), 0, st, (const Cx<float> *)state, len, cum, bsum);
+        hipLaunchKernelGGL(k_blockscan<float>, dim3(uint32_t(nb)), dim3(NT), 0, st, (const Cx<float> *)state, len, seg, bsum);
     else
-        hipLaunchKernelGGL(k_blockscan<double>, grid, dim3(NT), 0, st, (const Cx<double> *)state, len, cum, bsum);
+        hipLaunchKernelGGL(k_blockscan<double>, dim3(uint32_t(nb)), dim3(NT), 0, st, (const Cx<double> *)state, len, seg, bsum);
+    hipLaunchKernelGGL(k_blockoff, dim3(1), dim3(NT), 0, st, bsum, nb, boff, total);
     return check(hipGetLastError());
 }
 
-int launch_addoff_search(double *cum, int n, const double *boff, const double *u, uint64_t m,
-                         uint64_t *out, hipStream_t st) {
-    const uint64_t len = uint64_t(1) << n;
-    hipLaunchKernelGGL(k_addoff, dim3(grid_for(len)), dim3(NT), 0, st, cum, len, boff);
-    if (m) hipLaunchKernelGGL(k_search, dim3(uint32_t((m + NT - 1) / NT)), dim3(NT), 0, st, cum, len, u, m, out);
+int launch_search(int dtype, const void *state, int n, const double *seg, const double *boff, const double *u,
+                  uint64_t m, uint64_t *out, hipStream_t st) {
+    if (m == 0) return QSIM_OK;
+    const uint64_t len = uint64_t(1) << n, nb = scan_blocks(n);
+    const dim3 grid(uint32_t((m + NT - 1) / NT));
+    if (dtype == QSIM_C64)
+        hipLaunchKernelGGL(k_search<float>, grid, dim3(NT), 0, st, (const Cx<float> *)state, len, seg, boff, nb, u, m, out);
+    else
+        hipLaunchKernelGGL(k_search<double>, grid, dim3(NT), 0, st, (const Cx<double> *)state, len, seg, boff, nb, u, m, out);
     return check(hipGetLastError());
 }
 

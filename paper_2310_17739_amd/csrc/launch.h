@@ -209,13 +209,16 @@ int launch_bind(int dtype, const double *tmpl, const BindEntry *ents, uint32_t n
 
 int launch_fill_i32(int32_t *p, int32_t v, uint64_t n, hipStream_t st);
 
-// Sampling: per-block inclusive prefix sums of |a_x|^2 into cum[2^n] and
-// block totals into bsum[scan_blocks(n)]; then, with boff the exclusive
-// prefix of the block totals, finish the sums and search each shot.
+// Sampling: prefix sums of |a_x|^2 over segments of 16 elements within blocks of
+// 4096 (seg[scan_segments(n)]), the blocks' sums (bsum[scan_blocks(n)]) and
+// offsets (boff[scan_blocks(n) + 1]), and their total; then the shots.  total, u
+// and out may be host memory that the device can access.
 uint64_t scan_blocks(int n);
-int launch_blockscan(int dtype, const void *state, int n, double *cum, double *bsum, hipStream_t st);
-int launch_addoff_search(double *cum, int n, const double *boff, const double *u, uint64_t m,
-                         uint64_t *out, hipStream_t st);
+uint64_t scan_segments(int n);
+int launch_scan(int dtype, const void *state, int n, double *seg, double *bsum, double *boff, double *total,
+                hipStream_t st);
+int launch_search(int dtype, const void *state, int n, const double *seg, const double *boff, const double *u,
+                  uint64_t m, uint64_t *out, hipStream_t st);
 
 // Streaming copy of `bytes` (a multiple of 16) from src to dst (dst == src
 // allowed) in 64 KiB blocks, one workgroup each, block b handled by
