@@ -23,7 +23,11 @@ DEVICE_SOURCES = ["kernels.hip", "span.hip"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
           f"-I{os.path.join(ROOT, 'include')}"]
-HIP_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# Uniform branches (the kernels' switches over operator forms) stay branches:
+# structurized, every case is followed by a chain of tests, which cost as much as
+# the operator's arithmetic where few waves share a SIMD.
+HIP_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             "-mllvm", "-structurizecfg-skip-uniform-regions=true"]
 
 
 def _run(cmd):
