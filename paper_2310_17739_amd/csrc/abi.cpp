@@ -241,7 +241,8 @@ int validate_span_pass(int n, int dtype, const Compiled &c, size_t i) {
         if (add(tile, sa.store_v[j])) return QSIM_E_ARG;   // outside the tile
     }
     const uint32_t rb = p.pass_begin[i], re = p.pass_begin[i + 1];
-    if (rb >= re || re > p.ops.size() || p.coef_begin[i] > p.coef_begin[i + 1] || p.coef_begin[i + 1] > p.coefs.size())
+    if (rb >= re || re > p.ops.size() || p.coef_begin[i] > p.coef_begin[i + 1] ||
+        p.coef_begin[i + 1] > p.coefs.size() || p.coef_begin[i + 1] - p.coef_begin[i] < 2 * (re - rb))
         return QSIM_E_ARG;
     uint32_t stages = 0;
     for (uint32_t j = rb; j < re; j++) {
@@ -257,11 +258,11 @@ int validate_span_pass(int n, int dtype, const Compiled &c, size_t i) {
             }
             stages++;
         } else if (o.kind == DEVOP_PAULI) {
-            const size_t need = 2;
             if (!stages || o.k > 2 * kSpanRegs || (o.slot[0] >> logt) ||
                 (o.present >> (1 << kSpanRegs)) || p.op_np[j] != 0)
                 return QSIM_E_ARG;
-            if (o.coef < p.coef_begin[i] || o.coef + need > p.coef_begin[i + 1]) return QSIM_E_ARG;
+            // the kernel finds the coefficients at twice the record's number
+            if (o.coef != p.coef_begin[i] + 2 * (j - rb)) return QSIM_E_ARG;
         } else {
             return QSIM_E_ARG;
         }
@@ -708,7 +709,8 @@ int enqueue_pass(const Compiled &c, size_t i, const DevOp *d_ops, const void *d_
         return QSIM_OK;
     }
     if (pi.span)
-        return qk::launch_span(dtype, state, sstride, nstates, pi.sa, d_ops, ob, oe, d_coefs, cstride, status, flags, st);
+        return qk::launch_span(dtype, state, sstride, nstates, pi.sa, d_ops, ob, oe, d_coefs, cb, cstride, status,
+                               flags, st);
     if (pi.reg)
         return qk::launch_reg(dtype, state, sstride, nstates, pi.ra, d_ops, ob, oe, d_coefs, cb, ce, cstride, status,
                               flags, st);
@@ -1662,22 +1664,13 @@ int qsim_debug_emulate(int n, int dtype, const qsim_gate *g, size_t ng, const do
                     }
                     const cd e0 = p.coefs[o.coef], e1 = p.coefs[o.coef + 1];
                     scale *= e0.real() + e0.imag();
-                    // the sign of each register, from those of the pairs
                     const bool diag = o.k == 2 * kSpanRegs, real = !diag && (o.k & 1);
                     const uint32_t m = diag ? 0u : 1u << (o.k >> 1);
-                    uint32_t rsign = 0;
-                    for (uint32_t r = 0, k = 0, last = 0; r < (1u << kSpanRegs); r++) {
-                        const uint32_t q = r ^ m;
-                        if (m && r > q) continue;
-                        last ^= (o.present >> k++) & 1;
-                        rsign |= last << r;
-                        if (m) rsign |= (last ^ uint32_t(real)) << q;
-                    }
                     const uint64_t zb = uint64_t(o.slot[1]) | uint64_t(o.slot[2]) << 16 | uint64_t(o.slot[3]) << 32;
                     for (uint64_t P = 0; P < v.size(); P++) {
                         const uint64_t tid = P & ((uint64_t(1) << logt) - 1), r = P >> logt;
                         const int s = (__builtin_popcountll(tid & o.slot[0]) + __builtin_popcountll(base & zb) +
-                                       int((rsign >> r) & 1)) & 1;
+                                       __builtin_popcountll(r & o.present)) & 1;
                         const cd b = (real ? cd(1.0) : cd(0.0, 1.0)) * (s ? -e1.imag() : e1.imag());
                         w[P] = v[P] + b * v[P ^ (uint64_t(m) << logt)];
                         if (e1.real() != 0.0) w[P] *= e1.real();

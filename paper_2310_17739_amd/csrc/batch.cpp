@@ -124,7 +124,7 @@ namespace {
 // collect the bind entries.  Returns the bound coefficient count.
 size_t bind_layout(Compiled *c, std::vector<qk::BindEntry> *ents, uint32_t *max_count) {
     PackedPlan &p = c->plan;
-    size_t bound = 0;
+    size_t bound = 0, at = 0;   // at: end of the template coefficients read so far
     *max_count = 0;
     for (size_t j = 0; j < p.ops.size(); j++) {
         DevOp &o = p.ops[j];
@@ -133,12 +133,14 @@ size_t bind_layout(Compiled *c, std::vector<qk::BindEntry> *ents, uint32_t *max_
         qk::BindEntry e{};
         e.bound_off = uint32_t(bound);
         e.count = count;
-        e.tmpl_off = o.coef;
+        e.tmpl_off = o.kind == DEVOP_STAGE ? uint32_t(at) : o.coef;
         e.np = o.kind == DEVOP_PAULI && p.op_np[j] == 1 ? -1 : p.op_np[j];
         for (int s = 0; s < 3; s++) e.slot[s] = p.op_slots[3 * j + s];
         ents->push_back(e);
         *max_count = std::max(*max_count, count);
-        o.coef = uint32_t(bound);
+        // (a stage record's words hold its layout, not the place of its coefficients)
+        at = size_t(e.tmpl_off) + (size_t(count) << p.op_np[j]);
+        if (o.kind != DEVOP_STAGE) o.coef = uint32_t(bound);
         bound += count;
     }
     // pass coefficient ranges in the bound layout

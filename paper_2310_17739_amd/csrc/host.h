@@ -280,20 +280,23 @@ enum { DEVOP_MAT = 0, DEVOP_MEASURE = 1, DEVOP_ASSERT0 = 2, DEVOP_RESET = 3,
        DEVOP_STAGE = 9,   // the LDS slots of the layout's positions, 16 bits each, in bytes 0..13
                           // and 16..29; kx = the stage's number
        DEVOP_PAULI = 10,  // rotation: k = 2 b + 1 for a real t and 2 b for an imaginary one on
-                          // register bit b, 2 kSpanRegs for a diagonal; bit j of present = whether the sign of register pair j
-                          // (in ascending order of the smaller register) differs from that of
-                          // pair j - 1; slot[0], slot[1..3] = the sign masks of the thread bits
-                          // and of the tile's base index; two coefficients (see pauli_coefs)
+                          // register bit b, 2 kSpanRegs for a diagonal; present, slot[0] and
+                          // slot[1..3] = the sign masks of the register index, the thread bits
+                          // and the tile's base index; two coefficients (see pauli_coefs)
        DEVOP_EXPECT = 11  // a term of a Pauli sum: its form and signs as a rotation's; coef = its
                           // number
 };
-inline bool devop_is_mat(int kind) { return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI; }
+// records with coefficients (a stage's two are not used: they keep those of a
+// span pass at twice the record's number)
+inline bool devop_is_mat(int kind) {
+    return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI || kind == DEVOP_STAGE;
+}
 inline bool devop_is_record(int kind) {
     return kind == DEVOP_MEASURE || kind == DEVOP_ASSERT0 || kind == DEVOP_RESET || kind == DEVOP_MEASURE_RESET;
 }
 
 inline uint32_t devop_coefs(const DevOp &o) {
-    return o.kind == DEVOP_PAULI ? 2u : uint32_t(__builtin_popcount(o.present)) << (o.k + o.kx);
+    return o.kind == DEVOP_PAULI || o.kind == DEVOP_STAGE ? 2u : uint32_t(__builtin_popcount(o.present)) << (o.k + o.kx);
 }
 
 struct PackedPlan {

@@ -135,14 +135,14 @@ __host__ __device__ inline uint64_t span_base(uint64_t bx, const SpanArgs &sa) {
 // LDS bytes of a span pass: the tile, an entry per record (and one that the
 // kernel reads ahead), a layout per stage and a factor per record.
 inline size_t span_lds_bytes(size_t tile_bytes, uint32_t nrec, uint32_t nstage) {
-    return tile_bytes + 16 * (size_t(nrec) + 1) + 32 * size_t(nstage) + 8 * size_t(nrec);
+    return tile_bytes + 16 * (size_t(nrec) + 1) + 64 * size_t(nstage) + 8 * size_t(nrec);
 }
 
 // Sets the kernels' LDS limit; false if one declares static LDS (its tile must
 // start at LDS byte 0).
 bool init_span_kernels();
 int launch_span(int dtype, void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa,
-                const qs::DevOp *ops, uint32_t ob, uint32_t oe, const void *coefs, uint64_t cstride,
+                const qs::DevOp *ops, uint32_t ob, uint32_t oe, const void *coefs, uint32_t cb, uint64_t cstride,
                 const int32_t *status, uint32_t flags, hipStream_t st);
 
 // Sums of a planned Pauli sum (qs::ExpectPlan) over nstates states: out[b * nterms

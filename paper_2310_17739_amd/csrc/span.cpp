@@ -496,19 +496,11 @@ bool string_record(uint64_t x, uint64_t z, const uint64_t *V, int t, int regs, D
     for (int r = 0; r < regs; r++)
         if (V[logt + r] == x) bit = r;
     if (x && bit < 0) return false;
-    const uint32_t m = x ? 1u << bit : 0u;
     d->k = uint8_t(x ? 2 * bit + (__builtin_popcountll(x & z) & 1) : 2 * regs);
     uint32_t zr = 0, zt = 0;
     for (int b = 0; b < regs; b++) zr |= uint32_t(__builtin_popcountll(z & V[logt + b]) & 1) << b;
     for (int b = 0; b < logt; b++) zt |= uint32_t(__builtin_popcountll(z & V[b]) & 1) << b;
-    // the signs of the register pairs {r, r ^ m} in ascending order of
-    // r < r ^ m, each against the pair before it
-    for (uint32_t r = 0, k = 0, last = 0; r < (1u << regs); r++) {
-        if (m && r > (r ^ m)) continue;
-        const uint32_t sgn = uint32_t(__builtin_popcount(r & zr) & 1);
-        d->present |= (sgn ^ last) << k++;
-        last = sgn;
-    }
+    d->present = zr;
     d->slot[0] = uint16_t(zt);
     for (int b = 0; b < 3; b++) d->slot[1 + b] = uint16_t((z >> (16 * b)) & 0xffff);
     return true;
@@ -566,7 +558,7 @@ void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t met
              i = nxt[size_t(i)], scanned++) {
             const PauliOp &o = ops[i];
             // LDS of its entry and factor; it may open a stage of its own
-            const size_t need = 24 + 56;
+            const size_t need = 24 + 88;
             if ((sel.empty() || meta + need <= meta_budget) && passes_by(o) && grow(o)) {
                 sel.push_back(i);
                 meta += need;
@@ -639,6 +631,8 @@ int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, 
         out->ops.push_back(stage_record(st, t, number++));
         out->op_np.push_back(0);
         for (int j = 0; j < 3; j++) out->op_slots.push_back(-1);
+        // (the kernel reads two coefficients of every record)
+        for (int j = 0; j < 2; j++) out->coefs.push_back(cd(0.0, 0.0));
         // the layout's positions as vectors of the state's index
         uint64_t V[16];
         for (int j = 0; j < t; j++) V[j] = span_vector(p, st.layout[j]);

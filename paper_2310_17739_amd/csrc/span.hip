@@ -68,32 +68,46 @@ __device__ __forceinline__ V reg_off(const V *vec) {
     return o;
 }
 
-// The sign bit that turns pair k's t into pair k + 1's: bit k + 1 of d.
-__device__ __forceinline__ uint32_t turn_sign(uint32_t d, int k) { return (d << (31 - k)) & 0x80000000u; }
+// Register r of place g in an order of the register index in which neighbours
+// differ in one bit, M left out (its bit 0): a Gray code of the other bits.
+template <int M>
+__device__ constexpr int gray_reg(int g) {
+    const int c = g ^ (g >> 1);
+    return M == 0 ? c : (c / M) * (2 * M) + c % M;
+}
+
+// The signs of the register bits, from the low bits of a record's word: s[b] has
+// bit 31 set where bit b's sign mask is.
+template <int LR>
+struct Signs {
+    uint32_t s[LR];
+    __device__ __forceinline__ explicit Signs(uint32_t w) {
+        static_for<0, LR>([&](auto bc) {
+            constexpr int b = decltype(bc)::value;
+            s[b] = (w << (31 - b)) & 0x80000000u;
+        });
+    }
+};
 
 // One rotation from a thread's registers x to y, y[r] = x[r] + t_r x[r ^ M] with
 // M one register bit or none, t real (REAL) or imaginary.  t has the sign of
-// register 0 (and of the tile and the thread); the pairs {r, r ^ M} follow in
-// ascending order of their smaller register, and bit k of d tells whether pair
-// k's sign differs from that of pair k - 1, so that a sign costs one operation
-// on one register.  Register r ^ M has the sign of r for an imaginary t (an
-// even number of Y letters) and the opposite one for a real t.
+// register 0 (and of the tile and the thread).  The pairs {r, r ^ M} follow in
+// Gray code order, so that the next pair's sign is one operation away, with one
+// of few scalars.  Register r ^ M has the sign of r for an imaginary t (an even
+// number of Y letters) and the opposite one for a real t.
 template <typename T, int LR, int M, bool REAL>
-__device__ __forceinline__ void rotate(const Cx<T> (&x)[1 << LR], Cx<T> (&y)[1 << LR], T t, uint32_t d) {
-    static_for<0, 1 << LR>([&](auto rc) {
-        constexpr int r = decltype(rc)::value, q = r ^ M;
-        if constexpr (M == 0 || r < q) {
-            // place of the pair in the order
-            constexpr int k = M == 0 ? r : (r / (2 * M)) * M + r % M;
-            if constexpr (k > 0) turn(t, turn_sign(d, k));
-            const Cx<T> a = x[r], b = x[q];
-            if constexpr (REAL) {
-                y[r] = Cx<T>{T(fma(t, b.re, a.re)), T(fma(t, b.im, a.im))};
-                y[q] = Cx<T>{T(fma(-t, a.re, b.re)), T(fma(-t, a.im, b.im))};
-            } else {
-                y[r] = Cx<T>{T(fma(-t, b.im, a.re)), T(fma(t, b.re, a.im))};
-                if constexpr (M != 0) y[q] = Cx<T>{T(fma(-t, a.im, b.re)), T(fma(t, a.re, b.im))};
-            }
+__device__ __forceinline__ void rotate(const Cx<T> (&x)[1 << LR], Cx<T> (&y)[1 << LR], T t, uint32_t w) {
+    const Signs<LR> sg(w);
+    static_for<0, (M == 0 ? 1 << LR : 1 << (LR - 1))>([&](auto gc) {
+        constexpr int g = decltype(gc)::value, r = gray_reg<M>(g), q = r ^ M;
+        if constexpr (g > 0) turn(t, sg.s[__builtin_ctz(r ^ gray_reg<M>(g - 1))]);
+        const Cx<T> a = x[r], b = x[q];
+        if constexpr (REAL) {
+            y[r] = Cx<T>{T(fma(t, b.re, a.re)), T(fma(t, b.im, a.im))};
+            y[q] = Cx<T>{T(fma(-t, a.re, b.re)), T(fma(-t, a.im, b.im))};
+        } else {
+            y[r] = Cx<T>{T(fma(-t, b.im, a.re)), T(fma(t, b.re, a.im))};
+            if constexpr (M != 0) y[q] = Cx<T>{T(fma(-t, a.im, b.re)), T(fma(t, a.re, b.im))};
         }
     });
     // Differs from form to form: the compiler would else merge the tails of
@@ -119,14 +133,14 @@ __device__ __forceinline__ void rotate_form(const Cx<T> (&x)[1 << LR], Cx<T> (&y
 }
 
 // LDS behind the tile: an entry of 16 bytes per record, the layouts of the
-// stages (32 bytes each: the record) and a factor of the pass's scale per record.
+// stages (64 bytes each) and a factor of the pass's scale per record.
 typedef uint32_t U4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) U4 LdsU4;
 typedef __attribute__((address_space(3))) double LdsF8;
 
 // An entry.  Word 0: the form (bits 28-31; kStageForm: a stage, its number in
-// the low bits), the thread sign mask (bits 16-27) and the pair signs (bits
-// 0-15).  Word 1: not 0 where a factor is to be applied at once.  t: the upper
+// the low bits), the sign masks of the thread (bits 16-27) and of the register
+// index (bits 0-3).  Word 1: not 0 where a factor is to be applied at once.  t: the upper
 // half (complex128) or word 2.
 constexpr uint32_t kStageForm = 15;
 __device__ __forceinline__ void put_t(U4 &e, float t) { e.z = __float_as_uint(t); }
@@ -142,26 +156,44 @@ __device__ __forceinline__ T get_t(const U4 &e) {
 }
 __device__ __forceinline__ U4 lds_u4(uint32_t at) { return *reinterpret_cast<const LdsU4 *>(uintptr_t(at)); }
 
-// LDS byte addresses of a layout (a stage record): the thread's part and
-// each register bit's.
-template <typename T, int LOGT>
-__device__ __forceinline__ void stage_layout(uint32_t at, int tid, uint32_t &slot_t, uint32_t (&slot_r)[qs::kSpanRegs]) {
+// A layout in LDS: the byte address that each position adds, 32 bits each, from
+// the 16-bit slots of a stage record (words a and c).
+constexpr uint32_t kLayoutBytes = 64;
+template <typename T>
+__device__ __forceinline__ void put_layout(uint32_t at, const U4 &a, const U4 &c) {
     constexpr int LOGE = LdsTile<T>::LOGE;
-    const U4 a = lds_u4(at), c = lds_u4(at + 16u);
-    uint32_t w[8] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
+    auto lo = [](uint32_t w) { return (w & 0xffffu) << LOGE; };
+    auto hi = [](uint32_t w) { return (w >> 16) << LOGE; };
+    const U4 q[4] = {{lo(a.x), hi(a.x), lo(a.y), hi(a.y)},
+                     {lo(a.z), hi(a.z), lo(a.w), lo(c.x)},
+                     {hi(c.x), lo(c.y), hi(c.y), lo(c.z)},
+                     {hi(c.z), lo(c.w), 0u, 0u}};
 #pragma unroll
-    for (int j = 0; j < 8; j++) w[j] = __builtin_amdgcn_readfirstlane(w[j]);
-    const uint32_t h[14] = {w[0] & 0xffff, w[0] >> 16,    w[1] & 0xffff, w[1] >> 16,    w[2] & 0xffff,
-                            w[2] >> 16,    w[3] & 0xffff, w[4] & 0xffff, w[4] >> 16,    w[5] & 0xffff,
-                            w[5] >> 16,    w[6] & 0xffff, w[6] >> 16,    w[7] & 0xffff};
-    slot_t = 0;
+    for (int j = 0; j < 4; j++) *reinterpret_cast<LdsU4 *>(uintptr_t(at + 16u * j)) = q[j];
+}
+
+// The LDS byte addresses of a thread's elements under the layout at `at`.
+template <typename T, int LOGT>
+__device__ __forceinline__ void stage_addr(uint32_t at, int tid, uint32_t (&addr)[1 << qs::kSpanRegs]) {
+    constexpr int LR = qs::kSpanRegs;
+    uint32_t h[16];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const U4 q = lds_u4(at + 16u * j);
+        h[4 * j] = q.x;
+        h[4 * j + 1] = q.y;
+        h[4 * j + 2] = q.z;
+        h[4 * j + 3] = q.w;
+    }
+    uint32_t a = 0;
     static_for<0, LOGT>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
-        slot_t ^= ((tid >> k) & 1) ? h[k] << LOGE : 0;
+        a ^= ((tid >> k) & 1) ? h[k] : 0;
     });
-    static_for<0, qs::kSpanRegs>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        slot_r[k] = h[LOGT + k] << LOGE;
+    addr[0] = a;
+    static_for<1, 1 << LR>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        addr[r] = addr[r & (r - 1)] ^ h[LOGT + __builtin_ctz(r)];
     });
 }
 
@@ -178,7 +210,7 @@ struct OffsetOf<true> {
 template <typename T, int LOGT, bool WIDE>
 __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, uint64_t sstride, SpanArgs sa,
                                                    const DevOp *__restrict__ ops, uint32_t ob, uint32_t oe,
-                                                   const Cx<T> *__restrict__ coefs, uint64_t cstride,
+                                                   const Cx<T> *__restrict__ coefs, uint32_t cb, uint64_t cstride,
                                                    const int32_t *__restrict__ status, uint32_t flags) {
     using L = LdsTile<T>;
     using Off = typename OffsetOf<WIDE>::type;
@@ -186,10 +218,10 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
     const uint32_t b = blockIdx.y;
     if (status && status[b] != 0) return;   // an earlier step of this state failed
     char *st = reinterpret_cast<char *>(state + size_t(b) * sstride);
-    const Cx<T> *gcf = coefs + size_t(b) * cstride;
+    const Cx<T> *gcf = coefs + size_t(b) * cstride + cb;
     const int tid = threadIdx.x;
     const uint32_t nrec = oe - ob;
-    const uint32_t ent_at = sa.tile_bytes, lay_at = ent_at + 16u * (nrec + 1), fac_at = lay_at + 32u * sa.nstage;
+    const uint32_t ent_at = sa.tile_bytes, lay_at = ent_at + 16u * (nrec + 1), fac_at = lay_at + kLayoutBytes * sa.nstage;
     const uint64_t base = span_base(blockIdx.x, sa);
     // byte offset of a thread's register 0, and what each register bit changes
     auto offsets = [&](const uint64_t *vec, Off (&reg)[LR]) {
@@ -225,29 +257,29 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
     // sign of the tile's base index joins t here, once per tile and rotation.
     for (uint32_t x = uint32_t(tid); x < nrec; x += TNT) {
         const U4 *p = reinterpret_cast<const U4 *>(ops + ob + x);
+        // (every record has two coefficients, so that they need not wait for it)
         const U4 a = p[0], c = p[1];
+        const Cx<T> e0 = gcf[2 * x], e1 = gcf[2 * x + 1];
         U4 e = {0, 0, 0, 0};
         double f = 1.0;
         if (((a.w >> 16) & 0xff) == qs::DEVOP_PAULI) {
-            const Cx<T> e0 = gcf[a.x], e1 = gcf[a.x + 1];
             const uint64_t zb = uint64_t((c.x >> 16) | (c.y << 16)) | (uint64_t(c.y >> 16) << 32);
-            e.x = (a.y & 0xffffu) | ((c.x & 0xfffu) << 16) | ((a.z & 0xffu) << 28);
+            e.x = (a.y & 0xfu) | ((c.x & 0xfffu) << 16) | ((a.z & 0xffu) << 28);
             e.y = e1.re != T(0);
             put_t(e, flip(e1.im, uint32_t(__builtin_popcountll(base & zb)) << 31));
             f = e.y ? double(e1.re) : double(e0.re) + double(e0.im);
         } else {
             const uint32_t number = a.w >> 24;
             e.x = (kStageForm << 28) | number;
-            *reinterpret_cast<LdsU4 *>(uintptr_t(lay_at + 32u * number)) = a;
-            *reinterpret_cast<LdsU4 *>(uintptr_t(lay_at + 32u * number + 16u)) = c;
+            put_layout<T>(lay_at + kLayoutBytes * number, a, c);
         }
         *reinterpret_cast<LdsU4 *>(uintptr_t(ent_at + 16u * x)) = e;
         *reinterpret_cast<LdsF8 *>(uintptr_t(fac_at + 8u * x)) = f;
     }
     __syncthreads();
 
-    uint32_t slot_t, slot_r[LR];   // LDS bytes: the thread's part, each register bit's
-    stage_layout<T, LOGT>(lay_at, tid, slot_t, slot_r);
+    uint32_t addr[E];
+    stage_addr<T, LOGT>(lay_at, tid, addr);
     U4 ahead = lds_u4(ent_at + 16u);
     // One record, from the registers x to y.  (Two sets of registers in turn:
     // a rotation reads both members of a pair for both results, and in one set
@@ -272,13 +304,13 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
             // a stage: through LDS into its layout
             static_for<0, E>([&](auto rc) {
                 constexpr int r = decltype(rc)::value;
-                L::st(slot_t ^ reg_off<r>(slot_r), x[r]);
+                L::st(addr[r], x[r]);
             });
-            stage_layout<T, LOGT>(lay_at + 32u * (w & 0xffu), tid, slot_t, slot_r);
+            stage_addr<T, LOGT>(lay_at + kLayoutBytes * (w & 0xffu), tid, addr);
             __syncthreads();
             static_for<0, E>([&](auto rc) {
                 constexpr int r = decltype(rc)::value;
-                y[r] = L::ld(slot_t ^ reg_off<r>(slot_r));
+                y[r] = L::ld(addr[r]);
             });
         }
     };
@@ -336,20 +368,18 @@ __device__ __forceinline__ double wave_total(double v) {
     return v;
 }
 
-// A term's sum over a thread's registers (see rotate for M, REAL and d): the
+// A term's sum over a thread's registers (see rotate for M, REAL and w): the
 // real parts of conj(v[r]) v[r ^ M] with their signs, the imaginary parts for
 // an odd number of Y letters (REAL), |v[r]|^2 for M = 0.
 template <typename T, int LR, int M, bool REAL>
-__device__ __forceinline__ double term_sum(const Cx<T> (&v)[1 << LR], double one, uint32_t d) {
+__device__ __forceinline__ double term_sum(const Cx<T> (&v)[1 << LR], double one, uint32_t w) {
+    const Signs<LR> sg(w);
     double acc = 0.0;
-    static_for<0, 1 << LR>([&](auto rc) {
-        constexpr int r = decltype(rc)::value, q = r ^ M;
-        if constexpr (M == 0 || r < q) {
-            constexpr int k = M == 0 ? r : (r / (2 * M)) * M + r % M;
-            if constexpr (k > 0) turn(one, turn_sign(d, k));
-            const double ar = v[r].re, ai = v[r].im, br = v[q].re, bi = v[q].im;
-            acc = fma(one, REAL ? fma(ar, bi, -(ai * br)) : fma(ar, br, ai * bi), acc);
-        }
+    static_for<0, (M == 0 ? 1 << LR : 1 << (LR - 1))>([&](auto gc) {
+        constexpr int g = decltype(gc)::value, r = gray_reg<M>(g), q = r ^ M;
+        if constexpr (g > 0) turn(one, sg.s[__builtin_ctz(r ^ gray_reg<M>(g - 1))]);
+        const double ar = v[r].re, ai = v[r].im, br = v[q].re, bi = v[q].im;
+        acc = fma(one, REAL ? fma(ar, bi, -(ai * br)) : fma(ar, br, ai * bi), acc);
     });
     asm volatile("; summed by %0" ::"i"(M * 2 + REAL));
     return acc;
@@ -374,20 +404,19 @@ __global__ void __launch_bounds__(1 << LOGT) k_expect(const Cx<T> *__restrict__ 
     const uint32_t nrec = g->rec_end - g->rec_begin, nstage = g->stages;
     const char *st = reinterpret_cast<const char *>(state + size_t(blockIdx.z) * sstride);
     const int tid = threadIdx.x, wave = tid >> 6;
-    const uint32_t ent_at = tile_bytes, lay_at = ent_at + 16u * (nrec + 1), acc_at = lay_at + 32u * nstage;
+    const uint32_t ent_at = tile_bytes, lay_at = ent_at + 16u * (nrec + 1), acc_at = lay_at + kLayoutBytes * nstage;
     for (uint32_t x = uint32_t(tid); x < nrec; x += TNT) {
         const U4 *p = reinterpret_cast<const U4 *>(recs + x);
         const U4 a = p[0], c = p[1];
         U4 e = {0, 0, 0, 0};
         if (((a.w >> 16) & 0xff) == qs::DEVOP_EXPECT) {
-            e.x = (a.y & 0xffffu) | ((c.x & 0xfffu) << 16) | ((a.z & 0xffu) << 28);
+            e.x = (a.y & 0xfu) | ((c.x & 0xfffu) << 16) | ((a.z & 0xffu) << 28);
             e.y = (c.x >> 16) | (c.y << 16);   // the sign mask of the base index
             e.z = c.y >> 16;
         } else {
             const uint32_t number = a.w >> 24;
             e.x = (kStageForm << 28) | number;
-            *reinterpret_cast<LdsU4 *>(uintptr_t(lay_at + 32u * number)) = a;
-            *reinterpret_cast<LdsU4 *>(uintptr_t(lay_at + 32u * number + 16u)) = c;
+            put_layout<T>(lay_at + kLayoutBytes * number, a, c);
         }
         *reinterpret_cast<LdsU4 *>(uintptr_t(ent_at + 16u * x)) = e;
     }
@@ -411,8 +440,8 @@ __global__ void __launch_bounds__(1 << LOGT) k_expect(const Cx<T> *__restrict__ 
                 v[r] = *reinterpret_cast<const Cx<T> *>(st + (off ^ reg_off<r>(reg)));
             });
         }
-        uint32_t slot_t, slot_r[LR];
-        stage_layout<T, LOGT>(lay_at, tid, slot_t, slot_r);
+        uint32_t addr[E];
+        stage_addr<T, LOGT>(lay_at, tid, addr);
         if (tile != blockIdx.x && nstage > 1) __syncthreads();   // the last tile's slots have been read
         U4 ahead = lds_u4(ent_at + 16u);
         for (uint32_t i = 1; i < nrec; i++) {
@@ -443,13 +472,13 @@ __global__ void __launch_bounds__(1 << LOGT) k_expect(const Cx<T> *__restrict__ 
             } else {
                 static_for<0, E>([&](auto rc) {
                     constexpr int r = decltype(rc)::value;
-                    L::st(slot_t ^ reg_off<r>(slot_r), v[r]);
+                    L::st(addr[r], v[r]);
                 });
-                stage_layout<T, LOGT>(lay_at + 32u * (w & 0xffu), tid, slot_t, slot_r);
+                stage_addr<T, LOGT>(lay_at + kLayoutBytes * (w & 0xffu), tid, addr);
                 __syncthreads();
                 static_for<0, E>([&](auto rc) {
                     constexpr int r = decltype(rc)::value;
-                    v[r] = L::ld(slot_t ^ reg_off<r>(slot_r));
+                    v[r] = L::ld(addr[r]);
                 });
             }
         }
@@ -526,24 +555,24 @@ void span_attrs() {
 
 template <typename T, int LOGT>
 void span_t(void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops, uint32_t ob,
-            uint32_t oe, const void *coefs, uint64_t cstride, const int32_t *status, uint32_t flags, size_t lds,
+            uint32_t oe, const void *coefs, uint32_t cb, uint64_t cstride, const int32_t *status, uint32_t flags, size_t lds,
             hipStream_t st) {
     const dim3 grid(uint32_t(uint64_t(1) << (sa.n - sa.t)), nstates);
     if ((uint64_t(sizeof(Cx<T>)) << sa.n) <= (uint64_t(1) << 32))
         hipLaunchKernelGGL((k_span<T, LOGT, false>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state, sstride, sa, ops,
-                           ob, oe, (const Cx<T> *)coefs, cstride, status, flags);
+                           ob, oe, (const Cx<T> *)coefs, cb, cstride, status, flags);
     else
         hipLaunchKernelGGL((k_span<T, LOGT, true>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state, sstride, sa, ops,
-                           ob, oe, (const Cx<T> *)coefs, cstride, status, flags);
+                           ob, oe, (const Cx<T> *)coefs, cb, cstride, status, flags);
 }
 
 template <typename T>
 int span_dispatch(void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops, uint32_t ob,
-                  uint32_t oe, const void *coefs, uint64_t cstride, const int32_t *status, uint32_t flags, size_t lds,
+                  uint32_t oe, const void *coefs, uint32_t cb, uint64_t cstride, const int32_t *status, uint32_t flags, size_t lds,
                   hipStream_t st) {
 #define QK_SPAN(LOGT)                                                                                       \
     case LOGT:                                                                                              \
-        span_t<T, LOGT>(state, sstride, nstates, sa, ops, ob, oe, coefs, cstride, status, flags, lds, st); \
+        span_t<T, LOGT>(state, sstride, nstates, sa, ops, ob, oe, coefs, cb, cstride, status, flags, lds, st); \
         break;
     switch (sa.t - qs::kSpanRegs) {
         QK_SPAN(6)
@@ -553,7 +582,7 @@ int span_dispatch(void *state, uint64_t sstride, uint32_t nstates, const SpanArg
     case 10:
         // (a complex128 tile of 14 dimensions is larger than the LDS)
         if constexpr (sizeof(T) == 4) {
-            span_t<T, 10>(state, sstride, nstates, sa, ops, ob, oe, coefs, cstride, status, flags, lds, st);
+            span_t<T, 10>(state, sstride, nstates, sa, ops, ob, oe, coefs, cb, cstride, status, flags, lds, st);
             break;
         }
         return QSIM_E_CAPACITY;
@@ -597,7 +626,7 @@ int launch_expect(int dtype, const void *state, uint64_t sstride, uint32_t nstat
         return QSIM_E_ARG;
     const uint32_t tile_bytes = plan.relaid ? uint32_t(elem << plan.t) : 0u;
     const size_t nw = (size_t(1) << (plan.t - qs::kSpanRegs)) / 64;
-    const size_t lds = tile_bytes + 16 * (size_t(plan.max_rec) + 1) + 32 * size_t(plan.max_stage) + 8 * nw * plan.max_rec;
+    const size_t lds = tile_bytes + 16 * (size_t(plan.max_rec) + 1) + kLayoutBytes * size_t(plan.max_stage) + 8 * nw * plan.max_rec;
     if (lds > max_lds_bytes()) return QSIM_E_CAPACITY;
     const int rc = dtype == QSIM_C64 ? expect_t<float>(state, sstride, nstates, n, plan, table, nterms, chunks,
                                                        tile_bytes, lds, partials, st)
@@ -609,7 +638,7 @@ int launch_expect(int dtype, const void *state, uint64_t sstride, uint32_t nstat
 }
 
 int launch_span(int dtype, void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops,
-                uint32_t ob, uint32_t oe, const void *coefs, uint64_t cstride, const int32_t *status, uint32_t flags,
+                uint32_t ob, uint32_t oe, const void *coefs, uint32_t cb, uint64_t cstride, const int32_t *status, uint32_t flags,
                 hipStream_t st) {
     const size_t elem = dtype == QSIM_C64 ? 8 : 16;
     if (!qs::span_tile_ok(sa.t) || sa.t > sa.n || sa.n - sa.t > 31 || oe <= ob || sa.nstage == 0 ||
@@ -617,10 +646,10 @@ int launch_span(int dtype, void *state, uint64_t sstride, uint32_t nstates, cons
         return QSIM_E_ARG;
     const size_t lds = span_lds_bytes(sa.tile_bytes, oe - ob, sa.nstage);
     if (lds > max_lds_bytes()) return QSIM_E_CAPACITY;
-    return dtype == QSIM_C64 ? span_dispatch<float>(state, sstride, nstates, sa, ops, ob, oe, coefs, cstride, status,
-                                                    flags, lds, st)
-                             : span_dispatch<double>(state, sstride, nstates, sa, ops, ob, oe, coefs, cstride, status,
-                                                     flags, lds, st);
+    return dtype == QSIM_C64 ? span_dispatch<float>(state, sstride, nstates, sa, ops, ob, oe, coefs, cb, cstride,
+                                                    status, flags, lds, st)
+                             : span_dispatch<double>(state, sstride, nstates, sa, ops, ob, oe, coefs, cb, cstride,
+                                                     status, flags, lds, st);
 }
 
 }  // namespace qk
