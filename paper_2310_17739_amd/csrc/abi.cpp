@@ -244,19 +244,34 @@ int validate_span_pass(int n, int dtype, const Compiled &c, size_t i) {
     if (rb >= re || re > p.ops.size() || p.coef_begin[i] > p.coef_begin[i + 1] ||
         p.coef_begin[i + 1] > p.coefs.size() || p.coef_begin[i + 1] - p.coef_begin[i] < 2 * (re - rb))
         return QSIM_E_ARG;
-    uint32_t stages = 0;
+    if (sa.nrun == 0 || sa.nrun > re - rb || (sa.store_base & ~all) || (sa.store_base && t != n)) return QSIM_E_ARG;
+    uint32_t stages = 0, layouts = 0, records = 0;
     for (uint32_t j = rb; j < re; j++) {
         const DevOp &o = p.ops[j];
-        if (o.kind == DEVOP_STAGE) {
+        // layouts are numbered as the stages, then the records behind them
+        if ((o.kind == DEVOP_LAYOUT) != (j - rb >= sa.nrun)) return QSIM_E_ARG;
+        if (o.kind == DEVOP_STAGE || o.kind == DEVOP_LAYOUT) {
             const uint8_t *raw = reinterpret_cast<const uint8_t *>(&o);
             uint64_t slots[64] = {0};
-            if (o.kx != stages || stages >= 255) return QSIM_E_ARG;
+            if (o.kx != layouts || layouts >= 255 || (o.kind == DEVOP_LAYOUT && t != n)) return QSIM_E_ARG;
             for (int x = 0; x < t; x++) {
                 uint16_t s;
                 std::memcpy(&s, raw + (x < 7 ? 2 * x : 16 + 2 * (x - 7)), 2);
                 if ((s >> t) || !add(slots, s)) return QSIM_E_ARG;
             }
-            stages++;
+            uint16_t c;
+            std::memcpy(&c, raw + 30, 2);
+            if (c >> t || (c && o.kind == DEVOP_STAGE)) return QSIM_E_ARG;
+            layouts++;
+            if (o.kind == DEVOP_STAGE) stages++;
+        } else if (o.kind == DEVOP_SPAN_REC) {
+            // each has a layout of its own, in order, behind the stages
+            if (!stages || t != n || !devop_is_record(o.pos[0]) || (o.slot[0] >> logt) || (o.present >> 8) ||
+                ((o.present >> 4) & 7) > kSpanRegs || p.op_np[j] != 0)
+                return QSIM_E_ARG;
+            const bool moves = o.pos[0] == DEVOP_RESET || o.pos[0] == DEVOP_MEASURE_RESET;
+            if (moves && !((o.present >> 4) & 7)) return QSIM_E_ARG;
+            records++;
         } else if (o.kind == DEVOP_PAULI) {
             if (!stages || o.k > 2 * kSpanRegs || (o.slot[0] >> logt) ||
                 (o.present >> (1 << kSpanRegs)) || p.op_np[j] != 0)
@@ -268,8 +283,12 @@ int validate_span_pass(int n, int dtype, const Compiled &c, size_t i) {
         }
     }
     if (p.ops[rb].kind != DEVOP_STAGE || sa.tile_bytes != (stages > 1 ? uint32_t(elem_bytes(dtype) << t) : 0u) ||
-        sa.nstage != stages || qk::span_lds_bytes(sa.tile_bytes, re - rb, stages) > qk::max_lds_bytes())
+        sa.nlayout != layouts || layouts != stages + records ||
+        qk::span_lds_bytes(sa.tile_bytes, re - rb, layouts) > qk::max_lds_bytes())
         return QSIM_E_ARG;
+    uint32_t at = stages;
+    for (uint32_t j = rb; j < re; j++)
+        if (p.ops[j].kind == DEVOP_SPAN_REC && p.ops[j].kx != at++) return QSIM_E_ARG;
     return QSIM_OK;
 }
 
@@ -382,15 +401,14 @@ int validate_plan(int n, int dtype, const Compiled &c) {
 
 // Whether a circuit may run as a Pauli program (QSIM_SPAN=0 turns it off): with
 // level-5 fusion and no option that asks for another form of operator or pass,
-// or that keeps commuting operators in order.  Measurement records are passes
-// of their own between span passes, so a state that is one tile keeps them
-// inside k_tile's resident passes.  Without records a whole state takes span
-// passes too: against k_tile's resident ones, 120 exponentials on 13 qubits
-// complex128 run in 74 us (284) and 250 on 14 qubits complex64 in 156 us (493);
-// states below 10 qubits have too few amplitudes for a wave's registers.
-static bool spans_wanted(int n, const FuseConfig &fc, const PlanConfig &pc, bool records) {
-    return fc.level == 5 && fc.sparse && !pc.one_op_per_pass && !pc.reg_engine &&
-           (pc.tile_qubits < n || !records) && span_tile_ok(pc.tile_qubits) && n - pc.tile_qubits <= 31 &&
+// or that keeps commuting operators in order.
+// A whole state in one tile is such a pass too, its measurement records inside:
+// against k_tile's resident ones, 120 exponentials on 13 qubits complex128 run in
+// 67 us (284) and 250 on 14 qubits complex64 in 161 us (493); states below 10
+// qubits have too few amplitudes for a wave's registers.
+static bool spans_wanted(int n, const FuseConfig &fc, const PlanConfig &pc) {
+    return fc.level == 5 && fc.sparse && !pc.one_op_per_pass && !pc.reg_engine && span_tile_ok(pc.tile_qubits) &&
+           n - pc.tile_qubits <= 31 &&
            env_int("QSIM_SPAN", 1) != 0 && env_int("QSIM_PLAN_COMMUTE", 1) != 0;
 }
 
@@ -401,17 +419,31 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
     const size_t elem = elem_bytes(dtype);
     std::vector<Pass> passes;
     const int t = pc.tile_qubits;
-    size_t at = 0, m = 0;
-    for (int e = 0; e < L.n_epochs; e++) {
-        size_t end = at;
-        while (end < P.ops.size() && P.op_epoch[end] == e) end++;
-        plan_spans(n, P, t, pc.low_qubits, kSpanRegs, pc.meta_budget, pc.window, pc.full_support, int(at), int(end), &passes);
-        at = end;
-        for (; m < L.meas.size() && L.meas[m].epoch == e; m++) {
-            Pass p;
-            p.kind = Pass::MEASURE;
-            p.meas = L.meas[m];
-            passes.push_back(std::move(p));
+    const bool whole = t == n;
+    if (whole) {
+        plan_whole(n, P, L.n_epochs, pc.low_qubits, kSpanRegs, pc.meta_budget, &passes);
+        if (passes.empty() && !P.map.z.empty()) {
+            // nothing but the frame's permutation: a pass without rotations
+            PauliProgram none;
+            none.ops.push_back(PauliOp{});   // the identity
+            none.op_epoch.push_back(0);
+            plan_whole(n, none, 0, pc.low_qubits, kSpanRegs, pc.meta_budget, &passes);
+            for (SpanStage &st : passes[0].stages) st.ops.clear();
+        }
+    } else {
+        size_t at = 0, m = 0;
+        for (int e = 0; e < L.n_epochs; e++) {
+            size_t end = at;
+            while (end < P.ops.size() && P.op_epoch[end] == e) end++;
+            plan_spans(n, P, t, pc.low_qubits, kSpanRegs, pc.meta_budget, pc.window, pc.full_support, int(at),
+                       int(end), &passes);
+            at = end;
+            for (; m < L.meas.size() && L.meas[m].epoch == e; m++) {
+                Pass p;
+                p.kind = Pass::MEASURE;
+                p.meas = L.meas[m];
+                passes.push_back(std::move(p));
+            }
         }
     }
     out->pauli = true;
@@ -425,20 +457,22 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
         pi.kind = p.kind;
         pi.meas = p.meas;
         if (p.span) {
-            const int rc = pack_span_pass(P, p, kSpanRegs, dtype == QSIM_C64, &pl);
+            qk::SpanArgs &sa = pi.sa;
+            const int rc = pack_span_pass(P, p, kSpanRegs, dtype == QSIM_C64, &pl, &sa.nrun);
             if (rc) return rc;
             pi.span = true;
             pi.ta.n = n;
-            qk::SpanArgs &sa = pi.sa;
             sa.n = n;
             sa.t = p.t;
             sa.rest_mask = all & ~p.tile_mask;
             for (int j = 0; j < p.t; j++) {
                 sa.load_v[j] = span_vector(p, p.stages.front().layout[j]);
                 sa.store_v[j] = span_vector(p, p.stages.back().layout[j]);
+                if (whole && &p == &passes.back()) sa.store_v[j] = map_index(P.map, sa.store_v[j]);
             }
+            if (whole && &p == &passes.back()) sa.store_base = P.map.c;
             sa.tile_bytes = p.stages.size() > 1 ? uint32_t(elem << p.t) : 0u;
-            sa.nstage = uint32_t(p.stages.size());
+            sa.nlayout = uint32_t(p.stages.size() + (pl.ops.size() - pl.pass_begin.back() - sa.nrun));
             sa.phase_re = 1.0;
             if (!phased) {
                 sa.phase_re = std::cos(P.phase);
@@ -486,9 +520,9 @@ int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
         std::vector<size_t> op_gate;
         size_t first_at;
         split_records(n, g, ng, allow_meas, &L, &op_gate, &rc, &first_at);
-        if (!rc && spans_wanted(n, fc, pc, !L.meas.empty())) {
+        if (!rc && spans_wanted(n, fc, pc)) {
             PauliProgram P;
-            bool fits = pauli_lower(n, g, op_gate, L.op_epoch, in, keep_params, &P);
+            bool fits = pauli_lower(n, g, op_gate, L, in, keep_params, pc.tile_qubits == n, &P);
             if (pc.full_support)
                 for (const PauliOp &o : P.ops)
                     fits = fits && __builtin_popcountll(o.x | o.z) <= pc.tile_qubits - pc.low_qubits;
@@ -709,8 +743,8 @@ int enqueue_pass(const Compiled &c, size_t i, const DevOp *d_ops, const void *d_
         return QSIM_OK;
     }
     if (pi.span)
-        return qk::launch_span(dtype, state, sstride, nstates, pi.sa, d_ops, ob, oe, d_coefs, cb, cstride, status,
-                               flags, st);
+        return qk::launch_span(dtype, state, sstride, nstates, pi.sa, d_ops, ob, oe, d_coefs, cb, cstride,
+                               ma ? *ma : qk::MeasArgs{}, flags, st);
     if (pi.reg)
         return qk::launch_reg(dtype, state, sstride, nstates, pi.ra, d_ops, ob, oe, d_coefs, cb, ce, cstride, status,
                               flags, st);
@@ -1643,9 +1677,10 @@ int qsim_debug_emulate(int n, int dtype, const qsim_gate *g, size_t ng, const do
                 const uint64_t base = qk::span_base(tile, sa);
                 for (uint64_t P = 0; P < v.size(); P++) v[P] = st[base ^ combine(P, [&](int b) { return sa.load_v[b]; })];
                 const uint8_t *cur = nullptr;
-                cd scale = turn;
-                for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i + 1]; j++) {
+                cd scale = 1.0;
+                for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i] + sa.nrun; j++) {
                     const DevOp &o = p.ops[j];
+                    if (o.kind == DEVOP_SPAN_REC) return QSIM_E_ARG;
                     if (o.kind == DEVOP_STAGE) {
                         const uint8_t *raw = reinterpret_cast<const uint8_t *>(&o);
                         auto slots = [](const uint8_t *at) {
@@ -1673,12 +1708,14 @@ int qsim_debug_emulate(int n, int dtype, const qsim_gate *g, size_t ng, const do
                                        __builtin_popcountll(r & o.present)) & 1;
                         const cd b = (real ? cd(1.0) : cd(0.0, 1.0)) * (s ? -e1.imag() : e1.imag());
                         w[P] = v[P] + b * v[P ^ (uint64_t(m) << logt)];
-                        if (e1.real() != 0.0) w[P] *= e1.real();
+                        if (e1.real() != 0.0) w[P] *= scale;
                     }
+                    if (e1.real() != 0.0) scale = 1.0;
                     std::swap(v, w);
                 }
+                scale *= turn;
                 for (uint64_t P = 0; P < v.size(); P++)
-                    st[base ^ combine(P, [&](int b) { return sa.store_v[b]; })] = v[P] * scale;
+                    st[base ^ sa.store_base ^ combine(P, [&](int b) { return sa.store_v[b]; })] = v[P] * scale;
             }
             continue;
         }

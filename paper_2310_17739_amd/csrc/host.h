@@ -72,12 +72,33 @@ struct PauliOp {
     int32_t slot = -1;
 };
 
+// The basis states behind a frame of CNOTs, SWAPs and Xs: bit q of the logical
+// index is the parity of the state's index with z[q], flipped where bit q of c
+// is set.
+struct IndexMap {
+    std::vector<uint64_t> z;   // empty: the index itself
+    uint64_t c = 0;
+};
+
+// A measurement record seen through the frame: the qubit's value is the parity
+// of the index with z (flipped: `flip`), and index ^ x changes it alone; `map` is
+// the frame at the record.
+struct PauliRecord {
+    MeasRec rec;
+    uint64_t z = 0, x = 0;
+    bool flip = false;
+    IndexMap map;
+};
+
 // A circuit as rotations in order, each with its epoch; `phase` is the angle
-// of the global phase that the rotations leave out.
+// of the global phase that the rotations leave out.  Of a state that is one
+// tile, also its records and the frame that is left at the end.
 struct PauliProgram {
     std::vector<PauliOp> ops;
     std::vector<int> op_epoch;
     double phase = 0.0;
+    std::vector<PauliRecord> recs;
+    IndexMap map;
 };
 
 struct FuseConfig {
@@ -133,31 +154,31 @@ double max_abs(const cd *m, size_t n);
 // the circuit to lower_gates, for records that are not rotations, Clifford
 // gates or products of few rotations, for records that it refuses, and for
 // circuits whose Clifford gates mostly do not cancel.
-bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, const std::vector<int> &op_epoch,
-                 const GateInputs &in, bool keep_params, PauliProgram *out);
+// whole: the state is one tile, so the frame may last beyond measurement records
+// (L.meas) and, where it only permutes the basis states, to the end: the last
+// pass stores through it.
+bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, const Lowered &L,
+                 const GateInputs &in, bool keep_params, bool whole, PauliProgram *out);
 
 // Coefficients of a rotation record, from a = cos phi and b = +-sin phi:
-// y = a (x + t x') with t = b / a = e[1].im.  The factor a goes into the scale
-// of the pass (e[0].re + e[0].im: in single precision a and what rounding
-// leaves of it) while |t| <= 1, which bounds what an amplitude grows by before
-// the scale is applied; beyond, the result is multiplied by e[1].re = a at
-// once.  (A cosine below 1e-25 is none: t stays finite in single precision.)
+// y = a (x + t x') with t = b / a = e[1].im.  The factor a, e[0].re + e[0].im (in
+// single precision a and what rounding leaves of it), goes into the scale of the
+// pass.  The state grows by sqrt(1 + t^2) before it is scaled: e[1].re = 1 asks
+// for the scale so far to be applied after this rotation.  A cosine below
+// kLeastCos, less than the rounding of a sine of 1, counts as that, so that t
+// leaves room for what the other rotations of the pass grow by (kGrownMost).
+constexpr double kLeastCos[2] = {1e-25, 1e-16};   // double, single precision
 inline void pauli_coefs(double a, double b, bool single, cd e[2]) {
-    if (std::fabs(a) < 1e-25) a = 1e-25;
-    if (std::fabs(b) <= std::fabs(a)) {
-        e[0] = single ? cd(double(float(a)), a - double(float(a))) : cd(a, 0.0);
-        e[1] = cd(0.0, b / a);
-    } else {
-        e[0] = cd(1.0, 0.0);
-        e[1] = cd(a, b / a);
-    }
+    if (std::fabs(a) < kLeastCos[single]) a = kLeastCos[single];
+    e[0] = single ? cd(double(float(a)), a - double(float(a))) : cd(a, 0.0);
+    e[1] = cd(0.0, b / a);
 }
 
 // A stage of a span pass: position j of an element (thread bits, then register
 // bits) moves it by layout[j], in coordinates of the tile's basis.
 struct SpanStage {
     uint16_t layout[14] = {0};
-    std::vector<int> ops;         // rotations, in order
+    std::vector<int> ops;         // rotations in order, and ~i for record i
 };
 
 // ---- planning (plan.cpp)
@@ -283,20 +304,28 @@ enum { DEVOP_MAT = 0, DEVOP_MEASURE = 1, DEVOP_ASSERT0 = 2, DEVOP_RESET = 3,
                           // register bit b, 2 kSpanRegs for a diagonal; present, slot[0] and
                           // slot[1..3] = the sign masks of the register index, the thread bits
                           // and the tile's base index; two coefficients (see pauli_coefs)
+       DEVOP_SPAN_REC = 12,   // measurement record: pos[0] = its kind; slot[0] and bits 0-3 of
+                              // present = the masks of the value's parity (thread bits, register
+                              // index); bits 4-6 of present = 1 + the register bit that flips it (0:
+                              // none is needed), bit 7 = value flipped; slot[1], slot[2] = measurement
+                              // slot; kx = the number of the layout to store in after a failure
+       DEVOP_LAYOUT = 13,     // as a stage: the state's index that each position adds, and in bytes
+                              // 30..31 an index to add to all; behind the records that run
        DEVOP_EXPECT = 11  // a term of a Pauli sum: its form and signs as a rotation's; coef = its
                           // number
 };
 // records with coefficients (a stage's two are not used: they keep those of a
 // span pass at twice the record's number)
 inline bool devop_is_mat(int kind) {
-    return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI || kind == DEVOP_STAGE;
+    return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI || kind == DEVOP_STAGE ||
+           kind == DEVOP_SPAN_REC || kind == DEVOP_LAYOUT;
 }
 inline bool devop_is_record(int kind) {
     return kind == DEVOP_MEASURE || kind == DEVOP_ASSERT0 || kind == DEVOP_RESET || kind == DEVOP_MEASURE_RESET;
 }
 
 inline uint32_t devop_coefs(const DevOp &o) {
-    return o.kind == DEVOP_PAULI || o.kind == DEVOP_STAGE ? 2u : uint32_t(__builtin_popcount(o.present)) << (o.k + o.kx);
+    return o.kind >= DEVOP_STAGE ? 2u : uint32_t(__builtin_popcount(o.present)) << (o.k + o.kx);
 }
 
 struct PackedPlan {
@@ -343,8 +372,13 @@ inline bool span_tile_ok(int t) { return t >= 6 + kSpanRegs && t <= 14; }
 // at most t - c of them).
 void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t meta_budget, int window,
                 bool full, int first, int last, std::vector<Pass> *passes);
-// Appends the pass's records and coefficients.
-int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, PackedPlan *out);
+// The same for a state that is one tile, with its records in their places.
+void plan_whole(int n, const PauliProgram &P, int n_epochs, int c, int regs, size_t meta_budget,
+                std::vector<Pass> *passes);
+// Appends the pass's records and coefficients; *run: records that run, without
+// the layouts behind them.
+int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, PackedPlan *out, uint32_t *run);
+uint64_t map_index(const IndexMap &m, uint64_t i);
 // The vector of the state's index that tile coordinates stand for.
 uint64_t span_vector(const Pass &p, uint32_t coords);
 

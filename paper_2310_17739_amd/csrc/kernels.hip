@@ -1338,14 +1338,15 @@ __global__ void __launch_bounds__(NT) k_bind(const double *__restrict__ tmpl,
             const double th = params[size_t(b) * nparams + e.slot[0]];
             double a = cos(0.5 * th);
             const double s = tmpl[2 * size_t(e.tmpl_off)] * sin(0.5 * th);
-            if (fabs(a) < 1e-25) a = 1e-25;
-            const bool out_a = fabs(s) <= fabs(a);
+            if (fabs(a) < qs::kLeastCos[sizeof(T) == 4]) a = qs::kLeastCos[sizeof(T) == 4];
             double x, y;
             if (c == 0) {
-                x = out_a ? a : 1.0;
-                y = (out_a && sizeof(T) == 4) ? a - double(float(a)) : 0.0;
+                x = a;
+                y = sizeof(T) == 4 ? a - double(float(a)) : 0.0;
             } else {
-                x = out_a ? 0.0 : a;
+                // (its angle is not known to the host: beyond 45 degrees the
+                // scale is applied at once)
+                x = fabs(s) <= fabs(a) ? 0.0 : 1.0;
                 y = s / a;
             }
             out[size_t(b) * cstride + e.bound_off + c] = Cx<T>{T(x), T(y)};

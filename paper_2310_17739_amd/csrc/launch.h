@@ -112,7 +112,9 @@ struct SpanArgs {
     double phase_re, phase_im;
     int32_t n, t;
     uint32_t tile_bytes;     // LDS bytes of the tile: 0 for a pass with one stage
-    uint32_t nstage;         // stages of the pass
+    uint32_t nlayout;        // layouts: a stage's, and one per measurement record
+    uint32_t nrun;           // records that run, the others being layouts
+    uint64_t store_base;     // added (XOR) to the index of every element stored
 };
 
 // The bits of bx in the bits of `rest`, ascending.
@@ -133,9 +135,10 @@ __host__ __device__ inline uint64_t span_base(uint64_t bx, const SpanArgs &sa) {
 }
 
 // LDS bytes of a span pass: the tile, an entry per record (and one that the
-// kernel reads ahead), a layout per stage and a factor per record.
-inline size_t span_lds_bytes(size_t tile_bytes, uint32_t nrec, uint32_t nstage) {
-    return tile_bytes + 16 * (size_t(nrec) + 1) + 64 * size_t(nstage) + 8 * size_t(nrec);
+// kernel reads ahead), the layouts, a factor per record, and the reduction
+// scratch of measurement records (two values of up to 16 waves).
+inline size_t span_lds_bytes(size_t tile_bytes, uint32_t nrec, uint32_t nlayout) {
+    return tile_bytes + 16 * (size_t(nrec) + 1) + 64 * size_t(nlayout) + 8 * size_t(nrec) + 256;
 }
 
 // Sets the kernels' LDS limit; false if one declares static LDS (its tile must
@@ -143,7 +146,7 @@ inline size_t span_lds_bytes(size_t tile_bytes, uint32_t nrec, uint32_t nstage) 
 bool init_span_kernels();
 int launch_span(int dtype, void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa,
                 const qs::DevOp *ops, uint32_t ob, uint32_t oe, const void *coefs, uint32_t cb, uint64_t cstride,
-                const int32_t *status, uint32_t flags, hipStream_t st);
+                const MeasArgs &ma, uint32_t flags, hipStream_t st);
 
 // Sums of a planned Pauli sum (qs::ExpectPlan) over nstates states: out[b * nterms
 // + k] for term k (nterms counts the identity).  `table`: the plan's groups, then

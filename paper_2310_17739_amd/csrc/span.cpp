@@ -152,10 +152,20 @@ struct Frame {
 
 }  // namespace
 
-bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, const std::vector<int> &op_epoch,
-                 const GateInputs &in, bool keep_params, PauliProgram *out) {
+uint64_t map_index(const IndexMap &m, uint64_t i) {
+    if (m.z.empty()) return i;
+    uint64_t r = 0;
+    for (size_t q = 0; q < m.z.size(); q++) r |= uint64_t(__builtin_popcountll(i & m.z[q]) & 1) << q;
+    return r;
+}
+
+bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, const Lowered &L,
+                 const GateInputs &in, bool keep_params, bool whole, PauliProgram *out) {
+    const std::vector<int> &op_epoch = L.op_epoch;
     out->ops.clear();
     out->op_epoch.clear();
+    out->recs.clear();
+    out->map = IndexMap{};
     out->phase = 0.0;
     if (n > 48) return false;   // the device record keeps 48 bits of a Z mask
     Frame f(n);
@@ -234,10 +244,48 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
         }
         f.reset();
     };
+    // the frame as a map of the basis states; false if it is none
+    auto as_map = [&](IndexMap *m) {
+        m->z.resize(size_t(n));
+        m->c = 0;
+        bool same = true;
+        for (int q = 0; q < n; q++) {
+            const Pauli &z = f.Z[size_t(q)];
+            if (z.x) return false;
+            m->z[size_t(q)] = z.z;
+            if (z.k) m->c |= uint64_t(1) << q;
+            same = same && z.z == (uint64_t(1) << q);
+        }
+        if (same && !m->c) m->z.clear();
+        return true;
+    };
+    // the records before epoch e, seen through the frame
+    size_t next_rec = 0;
+    auto records = [&](int e) {
+        for (; next_rec < L.meas.size() && L.meas[next_rec].epoch < e; next_rec++) {
+            PauliRecord r;
+            r.rec = L.meas[next_rec];
+            const Pauli &z = f.Z[size_t(r.rec.q)], &x = f.X[size_t(r.rec.q)];
+            if (z.x) return false;
+            r.z = z.z;
+            r.flip = z.k != 0;
+            if (r.rec.kind == DEVOP_RESET || r.rec.kind == DEVOP_MEASURE_RESET) {
+                if (x.z || x.k) return false;
+                r.x = x.x;
+            }
+            // (gates that are diagonal leave phases behind a map of indices)
+            for (const Frame::Node &h : f.nodes)
+                if (h.alive && h.kind != QSIM_G_CX && h.kind != QSIM_G_SWAP && h.kind != QSIM_G_X) return false;
+            if (!as_map(&r.map)) return false;
+            out->recs.push_back(std::move(r));
+        }
+        return true;
+    };
     for (size_t j = 0; j < op_gate.size(); j++) {
         const qsim_gate &gi = g[op_gate[j]];
         if (op_epoch[j] != epoch) {
-            flush();
+            if (!whole) flush();
+            else if (!records(op_epoch[j])) return false;
             epoch = op_epoch[j];
         }
         // records that the matrix lowering refuses are left to it
@@ -350,6 +398,14 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
         default: return false;   // CH, CU3: no product of few rotations
         }
     }
+    if (whole) {
+        if (!records(L.n_epochs)) return false;
+        bool permutes = true;
+        for (const Frame::Node &h : f.nodes)
+            permutes = permutes && (!h.alive || h.kind == QSIM_G_CX || h.kind == QSIM_G_SWAP || h.kind == QSIM_G_X);
+        if (permutes && as_map(&out->map)) f.reset();
+        else epoch = L.n_epochs;   // what is left follows every record
+    }
     flush();
     // gates left in the frame are emitted at up to nine rotations each: with
     // many of them the fused operators of the matrix lowering do less
@@ -426,9 +482,13 @@ uint32_t span_slot(uint32_t c) {
 // commute with all of them, and a longer list finds hardly any on the
 // benchmark circuits.
 constexpr size_t kSkipMax = 64;
-// Rotations of one pass: each may grow an amplitude by sqrt 2 before the pass
-// scales its result.
+// Rotations of one pass.
 constexpr size_t kPassMax = 96;
+// Bits that the rotations whose angle is known here may grow a state by before
+// the scale is applied, for double and single precision.  Those bound per state
+// grow it by half a bit each at most, kPassMax / 2 in a pass, and one rotation
+// beyond the limit by 1 / kLeastCos: 20 + 48 + 53 of the 127 bits of a float.
+constexpr double kGrownMost[2] = {400.0, 20.0};
 
 // The layout of a stage whose registers run the directions `dirs` (at most
 // `regs` independent vectors of T), as tile coordinates.
@@ -473,6 +533,66 @@ void stage_layout(const Span &T, const std::vector<uint64_t> &dirs, int t, int c
         if (!((taken >> j) & 1) && all.add(1u << j)) take(j);
     for (int j = 0; j < logt; j++) st->layout[j] = uint16_t(thr[j]);
     for (int j = 0; j < regs; j++) st->layout[logt + j] = uint16_t(reg[j]);
+}
+
+// Stages for the items of a pass (rotations i of P, and ~i for its records) in
+// their order: each takes what its registers can run, rotations past skipped
+// ones that they commute with, and ends at a record that it cannot take.
+void make_stages(const PauliProgram &P, const std::vector<int> &items, const Span &T, int t, int c, int regs,
+                 std::vector<SpanStage> *stages) {
+    struct Mask {
+        uint64_t x, z;
+    };
+    std::vector<Mask> skipped;
+    std::vector<int> left = items, later;
+    while (!left.empty()) {
+        Span R;
+        SpanStage st;
+        std::vector<uint64_t> dirs;   // the masks that are register bits
+        skipped.clear();
+        later.clear();
+        bool closed = false;
+        auto fits = [&](uint64_t x) {
+            if (!x || std::find(dirs.begin(), dirs.end(), x) != dirs.end()) return true;
+            const uint64_t r = R.reduce(x);
+            if (!r || R.d >= regs) return false;
+            R.add(r);
+            dirs.push_back(x);
+            return true;
+        };
+        for (int i : left) {
+            if (closed || skipped.size() >= kSkipMax) {
+                later.push_back(i);
+                continue;
+            }
+            if (i < 0) {
+                // nothing passes a record
+                if (later.empty() && fits(P.recs[size_t(~i)].x)) {
+                    st.ops.push_back(i);
+                } else {
+                    later.push_back(i);
+                    closed = true;
+                }
+                continue;
+            }
+            const PauliOp &o = P.ops[size_t(i)];
+            bool free = true;
+            for (const Mask &s : skipped)
+                if (anticommute(s.x, s.z, o.x, o.z)) {
+                    free = false;
+                    break;
+                }
+            if (free && fits(o.x)) {
+                st.ops.push_back(i);
+            } else {
+                skipped.push_back({o.x, o.z});
+                later.push_back(i);
+            }
+        }
+        left.swap(later);
+        stage_layout(T, dirs, t, c, regs, &st);
+        stages->push_back(std::move(st));
+    }
 }
 
 // A stage record: the LDS slots of the layout's positions.
@@ -580,41 +700,45 @@ void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t met
         p.c = c;
         p.span = true;
         p.tile_mask = T.pm;
-        // stages of at most `regs` independent X masks
-        std::vector<int> left = sel, later;
-        while (!left.empty()) {
-            Span R;
-            SpanStage st;
-            std::vector<uint64_t> dirs;   // the masks that opened a dimension
-            skipped.clear();
-            later.clear();
-            for (int i : left) {
-                const PauliOp &o = ops[i];
-                if (skipped.size() >= kSkipMax) {
-                    later.push_back(i);
-                    continue;
-                }
-                // its X mask is a register bit of its own, or opens one
-                const bool have = !o.x || std::find(dirs.begin(), dirs.end(), o.x) != dirs.end();
-                const uint64_t r = have ? 0 : R.reduce(o.x);
-                if ((have || (r && R.d < regs)) && passes_by(o)) {
-                    if (r) {
-                        R.add(r);
-                        dirs.push_back(o.x);
-                    }
-                    st.ops.push_back(first + i);
-                } else {
-                    skipped.push_back({o.x, o.z});
-                    later.push_back(i);
-                }
-            }
-            left.swap(later);
-            stage_layout(T, dirs, t, c, regs, &st);
-            p.stages.push_back(std::move(st));
-        }
+        for (int &i : sel) i += first;
+        make_stages(P, sel, T, t, c, regs, &p.stages);
         for (int j = 0; j < t; j++) p.span_v[j] = T.v[j];
         passes->push_back(std::move(p));
     }
+}
+
+void plan_whole(int n, const PauliProgram &P, int n_epochs, int c, int regs, size_t meta_budget,
+                std::vector<Pass> *passes) {
+    Span T;
+    for (int q = 0; q < n; q++) T.add(uint64_t(1) << q);
+    std::vector<int> items;
+    size_t meta = 0;
+    auto close = [&]() {
+        if (items.empty()) return;
+        Pass p;
+        p.kind = Pass::TILE;
+        p.t = n;
+        p.c = std::min(c, n);
+        p.span = true;
+        p.tile_mask = T.pm;
+        make_stages(P, items, T, n, p.c, regs, &p.stages);
+        for (int j = 0; j < n; j++) p.span_v[j] = T.v[j];
+        passes->push_back(std::move(p));
+        items.clear();
+        meta = 0;
+    };
+    auto take = [&](int i, size_t bytes) {
+        if (!items.empty() && (meta + bytes > meta_budget || items.size() >= kPassMax)) close();
+        items.push_back(i);
+        meta += bytes;
+    };
+    size_t at = 0, r = 0;
+    for (int e = 0; e <= n_epochs; e++) {
+        // LDS of an entry, a factor and a stage of its own; a record's layout
+        for (; at < P.ops.size() && P.op_epoch[at] == e; at++) take(int(at), 24 + 88);
+        for (; r < P.recs.size() && P.recs[r].rec.epoch == e; r++) take(~int(r), 24 + 88 + 88);
+    }
+    close();
 }
 
 uint64_t span_vector(const Pass &p, uint32_t coords) {
@@ -624,19 +748,51 @@ uint64_t span_vector(const Pass &p, uint32_t coords) {
     return x;
 }
 
-int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, PackedPlan *out) {
+int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, PackedPlan *out, uint32_t *run) {
     const int t = p.t;
+    std::vector<DevOp> behind;   // the layouts that failing records store in
+    double grown = 0.0;   // bits that the state may have grown by since the scale was last applied
+    const size_t before = out->ops.size();
+    auto dummy = [&]() {
+        out->op_np.push_back(0);
+        for (int j = 0; j < 3; j++) out->op_slots.push_back(-1);
+        for (int j = 0; j < 2; j++) out->coefs.push_back(cd(0.0, 0.0));
+    };
     int number = 0;
     for (const SpanStage &st : p.stages) {
         out->ops.push_back(stage_record(st, t, number++));
-        out->op_np.push_back(0);
-        for (int j = 0; j < 3; j++) out->op_slots.push_back(-1);
-        // (the kernel reads two coefficients of every record)
-        for (int j = 0; j < 2; j++) out->coefs.push_back(cd(0.0, 0.0));
+        dummy();   // (the kernel reads two coefficients of every record)
         // the layout's positions as vectors of the state's index
         uint64_t V[16];
         for (int j = 0; j < t; j++) V[j] = span_vector(p, st.layout[j]);
         for (int idx : st.ops) {
+            if (idx < 0) {
+                const PauliRecord &r = P.recs[size_t(~idx)];
+                DevOp d{};
+                if (!string_record(r.x, r.z, V, t, regs, &d)) return QSIM_E_ARG;
+                d.kind = DEVOP_SPAN_REC;
+                d.pos[0] = uint8_t(r.rec.kind);
+                d.present |= (r.x ? uint32_t(d.k / 2 + 1) : 0u) << 4 | uint32_t(r.flip) << 7;
+                for (int b = 1; b < 5; b++) d.slot[b] = 0;
+                d.slot[1] = uint16_t(uint32_t(r.rec.slot) & 0xffff);
+                d.slot[2] = uint16_t(uint32_t(r.rec.slot) >> 16);
+                d.k = 0;
+                if (p.stages.size() + behind.size() >= 255) return QSIM_E_ARG;
+                d.kx = uint8_t(p.stages.size() + behind.size());
+                out->ops.push_back(d);
+                dummy();
+                DevOp l{};
+                l.kind = DEVOP_LAYOUT;
+                l.kx = d.kx;
+                uint8_t *raw = reinterpret_cast<uint8_t *>(&l);
+                for (int j = 0; j < 15; j++) {
+                    const uint16_t v = uint16_t(j < t ? map_index(r.map, V[j]) : j < 14 ? 0 : r.map.c);
+                    std::memcpy(raw + (j < 7 ? 2 * j : 16 + 2 * (j - 7)), &v, 2);
+                }
+                behind.push_back(l);
+                if (r.rec.kind != DEVOP_RESET) grown = 0.0;   // scaled to norm 1
+                continue;
+            }
             const PauliOp &o = P.ops[size_t(idx)];
             DevOp d{};
             d.kind = DEVOP_PAULI;
@@ -656,6 +812,11 @@ int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, 
             } else {
                 cd e[2];
                 pauli_coefs(std::cos(o.phi), kappa * o.sign * std::sin(o.phi), single, e);
+                grown += 0.5 * std::log2(1.0 + e[1].imag() * e[1].imag());
+                if (grown > kGrownMost[single]) {
+                    e[1] = cd(1.0, e[1].imag());
+                    grown = 0.0;
+                }
                 out->coefs.push_back(e[0]);
                 out->coefs.push_back(e[1]);
                 out->op_np.push_back(0);
@@ -665,6 +826,11 @@ int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, 
             out->op_slots.push_back(-1);
             out->terms += o.x ? 2 : 1;
         }
+    }
+    *run = uint32_t(out->ops.size() - before);
+    for (const DevOp &l : behind) {
+        out->ops.push_back(l);
+        dummy();
     }
     return QSIM_OK;
 }

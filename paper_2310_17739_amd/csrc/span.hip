@@ -140,9 +140,12 @@ typedef __attribute__((address_space(3))) double LdsF8;
 
 // An entry.  Word 0: the form (bits 28-31; kStageForm: a stage, its number in
 // the low bits), the sign masks of the thread (bits 16-27) and of the register
-// index (bits 0-3).  Word 1: not 0 where a factor is to be applied at once.  t: the upper
+// index (bits 0-3).  Word 1: not 0 where the scale so far is to be applied.  t: the upper
 // half (complex128) or word 2.
-constexpr uint32_t kStageForm = 15;
+// A measurement record: form kRecForm, its masks, dimension and value as in the
+// device record (bits 16-27, 0-7), its kind (bits 8-11), its slot in word 1 and
+// the layout of a failing state in word 2.
+constexpr uint32_t kStageForm = 15, kRecForm = 14;
 __device__ __forceinline__ void put_t(U4 &e, float t) { e.z = __float_as_uint(t); }
 __device__ __forceinline__ void put_t(U4 &e, double t) {
     const uint64_t b = uint64_t(__double_as_longlong(t));
@@ -167,12 +170,12 @@ __device__ __forceinline__ void put_layout(uint32_t at, const U4 &a, const U4 &c
     const U4 q[4] = {{lo(a.x), hi(a.x), lo(a.y), hi(a.y)},
                      {lo(a.z), hi(a.z), lo(a.w), lo(c.x)},
                      {hi(c.x), lo(c.y), hi(c.y), lo(c.z)},
-                     {hi(c.z), lo(c.w), 0u, 0u}};
+                     {hi(c.z), lo(c.w), 0u, hi(c.w)}};
 #pragma unroll
     for (int j = 0; j < 4; j++) *reinterpret_cast<LdsU4 *>(uintptr_t(at + 16u * j)) = q[j];
 }
 
-// The LDS byte addresses of a thread's elements under the layout at `at`.
+// The byte addresses of a thread's elements under the layout at `at`.
 template <typename T, int LOGT>
 __device__ __forceinline__ void stage_addr(uint32_t at, int tid, uint32_t (&addr)[1 << qs::kSpanRegs]) {
     constexpr int LR = qs::kSpanRegs;
@@ -185,7 +188,7 @@ __device__ __forceinline__ void stage_addr(uint32_t at, int tid, uint32_t (&addr
         h[4 * j + 2] = q.z;
         h[4 * j + 3] = q.w;
     }
-    uint32_t a = 0;
+    uint32_t a = h[15];   // (0 but for the layout of a failing state)
     static_for<0, LOGT>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
         a ^= ((tid >> k) & 1) ? h[k] : 0;
@@ -206,22 +209,127 @@ struct OffsetOf<true> {
     typedef uint64_t type;
 };
 
-// WIDE: byte offsets inside a state need more than 32 bits.
-template <typename T, int LOGT, bool WIDE>
+// Sum over a wave, in lane 63 (fixed order; row shifts and row broadcasts, no LDS).
+__device__ __forceinline__ double wave_total(double v) {
+    auto step = [&](auto ctrl, auto rows) {
+        const int64_t b = __double_as_longlong(v);
+        const int lo = __builtin_amdgcn_update_dpp(0, int(uint32_t(b)), decltype(ctrl)::value, decltype(rows)::value, 0xf, true);
+        const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), decltype(ctrl)::value, decltype(rows)::value, 0xf, true);
+        v += __longlong_as_double((int64_t(hi) << 32) | int64_t(uint32_t(lo)));
+    };
+    step(IntC<0x111>{}, IntC<0xf>{});   // row_shr 1, 2, 4, 8: lane 15 of a row holds its sum
+    step(IntC<0x112>{}, IntC<0xf>{});
+    step(IntC<0x114>{}, IntC<0xf>{});
+    step(IntC<0x118>{}, IntC<0xf>{});
+    step(IntC<0x142>{}, IntC<0xa>{});   // row_bcast 15 into rows 1 and 3, 31 into rows 2 and 3
+    step(IntC<0x143>{}, IntC<0xc>{});
+    return v;
+}
+
+// A measurement record on a tile that is the whole state: the weights of both
+// values in FP64 (each thread's in order, its wave's, the waves' in order), the
+// decision as in k_tile's records, and the collapse.  Returns 0 or a negative
+// status, the registers then untouched.  *collapsed: the state was scaled to
+// norm 1, `sign` being that of the scale that the rotations before left out.
+template <typename T, int LOGT>
+__device__ __forceinline__ int span_record(Cx<T> (&v)[1 << qs::kSpanRegs], uint32_t w, uint32_t slot, int tid,
+                                           uint32_t red_at, double sign, const MeasArgs &ma, uint32_t b,
+                                           bool *collapsed) {
+    constexpr int E = 1 << qs::kSpanRegs, NW = (1 << LOGT) / 64;
+    const uint32_t fr = w & 15u, dir = (w >> 4) & 7u;
+    const int kind = int((w >> 8) & 15u);
+    const bool tb = ((__builtin_popcount(uint32_t(tid) & ((w >> 16) & 0xfffu)) + int((w >> 7) & 1u)) & 1) != 0;
+    auto reg_bit = [&](int r) { return ((0x6996u >> (uint32_t(r) & fr)) & 1u) != 0; };
+    double w0 = 0.0, w1 = 0.0;
+    static_for<0, E>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        const double re = double(v[r].re), im = double(v[r].im), n2 = re * re + im * im;
+        w0 += reg_bit(r) ? 0.0 : n2;
+        w1 += reg_bit(r) ? n2 : 0.0;
+    });
+    const double a0 = wave_total(tb ? w1 : w0), a1 = wave_total(tb ? w0 : w1);
+    if ((tid & 63) == 63) {
+        *reinterpret_cast<LdsF8 *>(uintptr_t(red_at + 16u * uint32_t(tid >> 6))) = a0;
+        *reinterpret_cast<LdsF8 *>(uintptr_t(red_at + 16u * uint32_t(tid >> 6) + 8u)) = a1;
+    }
+    __syncthreads();
+    double P0 = 0.0, P1 = 0.0;
+    for (int j = 0; j < NW; j++) {
+        P0 += *reinterpret_cast<const LdsF8 *>(uintptr_t(red_at + 16u * uint32_t(j)));
+        P1 += *reinterpret_cast<const LdsF8 *>(uintptr_t(red_at + 16u * uint32_t(j) + 8u));
+    }
+    __syncthreads();   // the next record may write the scratch
+    // registers exchanged along the direction that flips the value
+    auto move = [&]() {
+        auto along = [&](auto mc) {
+            constexpr int M = decltype(mc)::value;
+            static_for<0, E>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                if constexpr (!(r & M)) {
+                    const Cx<T> a = v[r];
+                    v[r] = v[r | M];
+                    v[r | M] = a;
+                }
+            });
+            asm volatile("; moved along %0" ::"i"(M));   // (as in rotate)
+        };
+        if (dir == 1) along(IntC<1>{});
+        else if (dir == 2) along(IntC<2>{});
+        else if (dir == 3) along(IntC<4>{});
+        else along(IntC<8>{});
+    };
+    if (kind == qs::DEVOP_RESET) {
+        if (P1 == 0.0) return 0;
+        if (P0 != 0.0) return QSIM_E_NOT_DEFINITE;
+        move();
+        return 0;
+    }
+    int o;
+    const size_t idx = size_t(b) * ma.nslots + slot;
+    if (kind == qs::DEVOP_ASSERT0) {
+        if (!(P0 > 0.0)) return QSIM_E_ZERO_PROB;
+        o = 0;
+    } else if (ma.forced && ma.forced[idx] >= 0) {
+        o = ma.forced[idx];
+        if (!((o ? P1 : P0) > 0.0)) return QSIM_E_ZERO_PROB;
+    } else {
+        o = ma.uniforms[idx] < P0 / (P0 + P1) ? 0 : 1;
+    }
+    o = __builtin_amdgcn_readfirstlane(o);
+    const double kept = o ? P1 : P0;
+    if (tid == 0) {
+        ma.outcomes[idx] = o;
+        ma.probs[idx] = kept / (P0 + P1);
+    }
+    const T f = T((sign < 0.0 ? -1.0 : 1.0) / sqrt(kept));
+    static_for<0, E>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        const bool keep = (tb != reg_bit(r)) == (o != 0);
+        v[r] = keep ? Cx<T>{v[r].re * f, v[r].im * f} : Cx<T>{T(0), T(0)};
+    });
+    if (kind == qs::DEVOP_MEASURE_RESET && o) move();
+    *collapsed = true;
+    return 0;
+}
+
+// WIDE: byte offsets inside a state need more than 32 bits.  MEAS: the pass holds
+// measurement records.
+template <typename T, int LOGT, bool WIDE, bool MEAS>
 __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, uint64_t sstride, SpanArgs sa,
                                                    const DevOp *__restrict__ ops, uint32_t ob, uint32_t oe,
                                                    const Cx<T> *__restrict__ coefs, uint32_t cb, uint64_t cstride,
-                                                   const int32_t *__restrict__ status, uint32_t flags) {
+                                                   MeasArgs ma, uint32_t flags) {
     using L = LdsTile<T>;
     using Off = typename OffsetOf<WIDE>::type;
     constexpr int LR = qs::kSpanRegs, E = 1 << LR, TNT = 1 << LOGT;
     const uint32_t b = blockIdx.y;
-    if (status && status[b] != 0) return;   // an earlier step of this state failed
+    if (ma.status && ma.status[b] != 0) return;   // an earlier step of this state failed
     char *st = reinterpret_cast<char *>(state + size_t(b) * sstride);
     const Cx<T> *gcf = coefs + size_t(b) * cstride + cb;
     const int tid = threadIdx.x;
     const uint32_t nrec = oe - ob;
-    const uint32_t ent_at = sa.tile_bytes, lay_at = ent_at + 16u * (nrec + 1), fac_at = lay_at + kLayoutBytes * sa.nstage;
+    const uint32_t ent_at = sa.tile_bytes, lay_at = ent_at + 16u * (nrec + 1), fac_at = lay_at + kLayoutBytes * sa.nlayout;
+    const uint32_t red_at = fac_at + 8u * nrec, nrun = sa.nrun;
     const uint64_t base = span_base(blockIdx.x, sa);
     // byte offset of a thread's register 0, and what each register bit changes
     auto offsets = [&](const uint64_t *vec, Off (&reg)[LR]) {
@@ -267,7 +375,11 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
             e.x = (a.y & 0xfu) | ((c.x & 0xfffu) << 16) | ((a.z & 0xffu) << 28);
             e.y = e1.re != T(0);
             put_t(e, flip(e1.im, uint32_t(__builtin_popcountll(base & zb)) << 31));
-            f = e.y ? double(e1.re) : double(e0.re) + double(e0.im);
+            f = double(e0.re) + double(e0.im);
+        } else if (MEAS && ((a.w >> 16) & 0xff) == qs::DEVOP_SPAN_REC) {
+            e.x = (kRecForm << 28) | ((c.x & 0xfffu) << 16) | (((a.z >> 8) & 0xfu) << 8) | (a.y & 0xffu);
+            e.y = (c.x >> 16) | (c.y << 16);
+            e.z = a.w >> 24;
         } else {
             const uint32_t number = a.w >> 24;
             e.x = (kStageForm << 28) | number;
@@ -278,9 +390,22 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
     }
     __syncthreads();
 
+    // the scale of records [lo, hi): lanes multiply the factors of theirs, then
+    // each other's
+    auto scale_of = [&](uint32_t lo, uint32_t hi) {
+        double s = 1.0;
+        for (uint32_t x = lo + (uint32_t(tid) & 63u); x < hi; x += 64u) {
+            s *= *reinterpret_cast<const LdsF8 *>(uintptr_t(fac_at + 8u * x));
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) s *= __shfl_xor(s, d, 64);
+        return s;
+    };
     uint32_t addr[E];
     stage_addr<T, LOGT>(lay_at, tid, addr);
     U4 ahead = lds_u4(ent_at + 16u);
+    uint32_t scaled = 0;   // the first record whose factor the state does not have yet
+    int failed = 0;
     // One record, from the registers x to y.  (Two sets of registers in turn:
     // a rotation reads both members of a pair for both results, and in one set
     // every second result would have to be moved.)
@@ -289,11 +414,28 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
         const uint32_t w = __builtin_amdgcn_readfirstlane(e.x);
         ahead = lds_u4(ent_at + 16u * (i + 1));
         const uint32_t form = w >> 28;
-        if (form != kStageForm) {
+        if (MEAS && form == kRecForm) {
+            static_for<0, E>([&](auto rc) { y[decltype(rc)::value] = x[decltype(rc)::value]; });
+            bool collapsed = false;
+            failed = span_record<T, LOGT>(y, w, __builtin_amdgcn_readfirstlane(e.y), tid, red_at,
+                                          scale_of(scaled, i), ma, b, &collapsed);
+            failed = __builtin_amdgcn_readfirstlane(failed);
+            if (collapsed) scaled = i + 1;
+            if (failed) {
+                // the state stays as it was before the record, in the order that
+                // the frame had there
+                if (tid == 0) {
+                    ma.status[b] = failed;
+                    if (ma.fail_at) ma.fail_at[b] = int(ob + i);
+                }
+                stage_addr<T, LOGT>(lay_at + kLayoutBytes * __builtin_amdgcn_readfirstlane(e.z), tid, addr);
+            }
+        } else if (form != kStageForm) {
             const uint32_t s = uint32_t(__builtin_popcount(uint32_t(tid) & ((w >> 16) & 0xfffu))) << 31;
             rotate_form<T, LR>(x, y, int(form), flip(get_t<T>(e), s), w);
             if (__builtin_amdgcn_readfirstlane(e.y)) {
-                const T f = T(*reinterpret_cast<const LdsF8 *>(uintptr_t(fac_at + 8u * i)));
+                const T f = T(scale_of(scaled, i + 1));
+                scaled = i + 1;
                 static_for<0, E>([&](auto rc) {
                     constexpr int r = decltype(rc)::value;
                     y[r].re *= f;
@@ -315,59 +457,52 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
         }
     };
     uint32_t i = 1;
-    for (; i + 1 < nrec; i += 2) {
+    for (; i + 1 < nrun; i += 2) {
         Cx<T> u[E];
         step(i, v, u);
+        if (MEAS && failed) {
+            static_for<0, E>([&](auto rc) { v[decltype(rc)::value] = u[decltype(rc)::value]; });
+            break;
+        }
         step(i + 1, u, v);
+        if (MEAS && failed) {
+            i++;
+            break;
+        }
     }
-    if (i < nrec) {
+    if (i < nrun && !failed) {
         Cx<T> u[E];
         step(i, v, u);
         static_for<0, E>([&](auto rc) { v[decltype(rc)::value] = u[decltype(rc)::value]; });
+        if (!(MEAS && failed)) i++;
     }
-    {
-        // the scale: lanes multiply the factors of their records, then each other's
-        double scale = 1.0;
-        for (uint32_t x = uint32_t(tid) & 63u; x < nrec; x += 64u) {
-            const double f = *reinterpret_cast<const LdsF8 *>(uintptr_t(fac_at + 8u * x));
-            scale *= lds_u4(ent_at + 16u * x).y && (lds_u4(ent_at + 16u * x).x >> 28) != kStageForm ? 1.0 : f;
+    const double scale = scale_of(scaled, MEAS && failed ? i : nrun);
+    const T fr = T(scale * sa.phase_re), fi = T(scale * sa.phase_im);
+    const bool turned = sa.phase_im != 0.0;
+    auto result = [&](const Cx<T> a) {
+        Cx<T> y{a.re * fr, a.im * fr};
+        if (turned) {
+            y.re = fma(-fi, a.im, y.re);
+            y.im = fma(fi, a.re, y.im);
         }
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) scale *= __shfl_xor(scale, d, 64);
-        Off reg[LR];
-        const Off off = offsets(sa.store_v, reg);
-        const T fr = T(scale * sa.phase_re), fi = T(scale * sa.phase_im);
-        const bool turned = sa.phase_im != 0.0;
+        return y;
+    };
+    if (MEAS && failed) {
         static_for<0, E>([&](auto rc) {
             constexpr int r = decltype(rc)::value;
-            Cx<T> y{v[r].re * fr, v[r].im * fr};
-            if (turned) {
-                y.re = fma(-fi, v[r].im, y.re);
-                y.im = fma(fi, v[r].re, y.im);
-            }
-            *reinterpret_cast<Cx<T> *>(st + (off ^ reg_off<r>(reg))) = y;
+            *reinterpret_cast<Cx<T> *>(st + addr[r]) = result(v[r]);
+        });
+    } else {
+        Off reg[LR];
+        const Off off = offsets(sa.store_v, reg) ^ (Off(sa.store_base) << L::LOGE);
+        static_for<0, E>([&](auto rc) {
+            constexpr int r = decltype(rc)::value;
+            *reinterpret_cast<Cx<T> *>(st + (off ^ reg_off<r>(reg))) = result(v[r]);
         });
     }
 }
 
 // ---------------------------------------------------------- Pauli sums
-// Sum over a wave, in lane 63 (fixed order; row shifts and row broadcasts, no LDS).
-__device__ __forceinline__ double wave_total(double v) {
-    auto step = [&](auto ctrl, auto rows) {
-        const int64_t b = __double_as_longlong(v);
-        const int lo = __builtin_amdgcn_update_dpp(0, int(uint32_t(b)), decltype(ctrl)::value, decltype(rows)::value, 0xf, true);
-        const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), decltype(ctrl)::value, decltype(rows)::value, 0xf, true);
-        v += __longlong_as_double((int64_t(hi) << 32) | int64_t(uint32_t(lo)));
-    };
-    step(IntC<0x111>{}, IntC<0xf>{});   // row_shr 1, 2, 4, 8: lane 15 of a row holds its sum
-    step(IntC<0x112>{}, IntC<0xf>{});
-    step(IntC<0x114>{}, IntC<0xf>{});
-    step(IntC<0x118>{}, IntC<0xf>{});
-    step(IntC<0x142>{}, IntC<0xa>{});   // row_bcast 15 into rows 1 and 3, 31 into rows 2 and 3
-    step(IntC<0x143>{}, IntC<0xc>{});
-    return v;
-}
-
 // A term's sum over a thread's registers (see rotate for M, REAL and w): the
 // real parts of conj(v[r]) v[r ^ M] with their signs, the imaginary parts for
 // an odd number of Y letters (REAL), |v[r]|^2 for M = 0.
@@ -539,9 +674,9 @@ int expect_t(const void *state, uint64_t sstride, uint32_t nstates, int n, const
     return note_hip(hipGetLastError(), "k_expect launch");
 }
 
-template <typename T, int LOGT, bool WIDE>
+template <typename T, int LOGT, bool WIDE, bool MEAS>
 void span_attr() {
-    const void *f = reinterpret_cast<const void *>(&k_span<T, LOGT, WIDE>);
+    const void *f = reinterpret_cast<const void *>(&k_span<T, LOGT, WIDE, MEAS>);
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(max_lds_bytes()));
     if (e != hipSuccess) note_hip(e, "hipFuncSetAttribute(k_span)");
     hipFuncAttributes fa{};
@@ -549,48 +684,58 @@ void span_attr() {
 }
 template <typename T, int LOGT>
 void span_attrs() {
-    span_attr<T, LOGT, false>();
-    span_attr<T, LOGT, true>();
+    span_attr<T, LOGT, false, false>();
+    span_attr<T, LOGT, true, false>();
+    span_attr<T, LOGT, false, true>();
 }
 
-template <typename T, int LOGT>
-void span_t(void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops, uint32_t ob,
-            uint32_t oe, const void *coefs, uint32_t cb, uint64_t cstride, const int32_t *status, uint32_t flags, size_t lds,
-            hipStream_t st) {
-    const dim3 grid(uint32_t(uint64_t(1) << (sa.n - sa.t)), nstates);
-    if ((uint64_t(sizeof(Cx<T>)) << sa.n) <= (uint64_t(1) << 32))
-        hipLaunchKernelGGL((k_span<T, LOGT, false>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state, sstride, sa, ops,
-                           ob, oe, (const Cx<T> *)coefs, cb, cstride, status, flags);
-    else
-        hipLaunchKernelGGL((k_span<T, LOGT, true>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state, sstride, sa, ops,
-                           ob, oe, (const Cx<T> *)coefs, cb, cstride, status, flags);
-}
+struct SpanLaunch {
+    void *state;
+    uint64_t sstride;
+    uint32_t nstates;
+    const SpanArgs &sa;
+    const DevOp *ops;
+    uint32_t ob, oe;
+    const void *coefs;
+    uint32_t cb;
+    uint64_t cstride;
+    const MeasArgs &ma;
+    uint32_t flags;
+    size_t lds;
+    hipStream_t st;
 
-template <typename T>
-int span_dispatch(void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops, uint32_t ob,
-                  uint32_t oe, const void *coefs, uint32_t cb, uint64_t cstride, const int32_t *status, uint32_t flags, size_t lds,
-                  hipStream_t st) {
-#define QK_SPAN(LOGT)                                                                                       \
-    case LOGT:                                                                                              \
-        span_t<T, LOGT>(state, sstride, nstates, sa, ops, ob, oe, coefs, cb, cstride, status, flags, lds, st); \
-        break;
-    switch (sa.t - qs::kSpanRegs) {
-        QK_SPAN(6)
-        QK_SPAN(7)
-        QK_SPAN(8)
-        QK_SPAN(9)
-    case 10:
-        // (a complex128 tile of 14 dimensions is larger than the LDS)
-        if constexpr (sizeof(T) == 4) {
-            span_t<T, 10>(state, sstride, nstates, sa, ops, ob, oe, coefs, cb, cstride, status, flags, lds, st);
-            break;
-        }
-        return QSIM_E_CAPACITY;
-    default: return QSIM_E_ARG;
+    template <typename T, int LOGT, bool WIDE, bool MEAS>
+    void kernel() const {
+        const dim3 grid(uint32_t(uint64_t(1) << (sa.n - sa.t)), nstates);
+        hipLaunchKernelGGL((k_span<T, LOGT, WIDE, MEAS>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state, sstride, sa,
+                           ops, ob, oe, (const Cx<T> *)coefs, cb, cstride, ma, flags);
     }
-#undef QK_SPAN
-    return note_hip(hipGetLastError(), "k_span launch");
-}
+    template <typename T, int LOGT>
+    void tile() const {
+        // (a whole state in one tile, the place of measurement records, is narrow)
+        if ((uint64_t(sizeof(Cx<T>)) << sa.n) > (uint64_t(1) << 32)) kernel<T, LOGT, true, false>();
+        else if (sa.nrun < oe - ob) kernel<T, LOGT, false, true>();
+        else kernel<T, LOGT, false, false>();
+    }
+    template <typename T>
+    int run() const {
+        switch (sa.t - qs::kSpanRegs) {
+        case 6: tile<T, 6>(); break;
+        case 7: tile<T, 7>(); break;
+        case 8: tile<T, 8>(); break;
+        case 9: tile<T, 9>(); break;
+        case 10:
+            // (a complex128 tile of 14 dimensions is larger than the LDS)
+            if constexpr (sizeof(T) == 4) {
+                tile<T, 10>();
+                break;
+            }
+            return QSIM_E_CAPACITY;
+        default: return QSIM_E_ARG;
+        }
+        return note_hip(hipGetLastError(), "k_span launch");
+    }
+};
 }  // namespace
 
 bool init_span_kernels() {
@@ -638,18 +783,19 @@ int launch_expect(int dtype, const void *state, uint64_t sstride, uint32_t nstat
 }
 
 int launch_span(int dtype, void *state, uint64_t sstride, uint32_t nstates, const SpanArgs &sa, const DevOp *ops,
-                uint32_t ob, uint32_t oe, const void *coefs, uint32_t cb, uint64_t cstride, const int32_t *status, uint32_t flags,
-                hipStream_t st) {
+                uint32_t ob, uint32_t oe, const void *coefs, uint32_t cb, uint64_t cstride, const MeasArgs &ma,
+                uint32_t flags, hipStream_t st) {
     const size_t elem = dtype == QSIM_C64 ? 8 : 16;
-    if (!qs::span_tile_ok(sa.t) || sa.t > sa.n || sa.n - sa.t > 31 || oe <= ob || sa.nstage == 0 ||
-        sa.nstage > oe - ob || (sa.tile_bytes != 0 && sa.tile_bytes != (elem << sa.t)))
+    if (!qs::span_tile_ok(sa.t) || sa.t > sa.n || sa.n - sa.t > 31 || oe <= ob || sa.nlayout == 0 ||
+        sa.nlayout > oe - ob || sa.nrun == 0 || sa.nrun > oe - ob || (sa.nrun < oe - ob && sa.t != sa.n) ||
+        (sa.tile_bytes != 0 && sa.tile_bytes != (elem << sa.t)))
         return QSIM_E_ARG;
-    const size_t lds = span_lds_bytes(sa.tile_bytes, oe - ob, sa.nstage);
+    // records write the states' status, and their outcomes where there are slots
+    if (sa.nrun < oe - ob && (!ma.status || (ma.nslots > 0 && (!ma.outcomes || !ma.probs)))) return QSIM_E_ARG;
+    const size_t lds = span_lds_bytes(sa.tile_bytes, oe - ob, sa.nlayout);
     if (lds > max_lds_bytes()) return QSIM_E_CAPACITY;
-    return dtype == QSIM_C64 ? span_dispatch<float>(state, sstride, nstates, sa, ops, ob, oe, coefs, cb, cstride,
-                                                    status, flags, lds, st)
-                             : span_dispatch<double>(state, sstride, nstates, sa, ops, ob, oe, coefs, cb, cstride,
-                                                     status, flags, lds, st);
+    const SpanLaunch l{state, sstride, nstates, sa, ops, ob, oe, coefs, cb, cstride, ma, flags, lds, st};
+    return dtype == QSIM_C64 ? l.run<float>() : l.run<double>();
 }
 
 }  // namespace qk

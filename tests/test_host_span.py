@@ -101,3 +101,23 @@ def test_left_to_the_matrix_lowering():
         with pytest.raises(qsim.QsimError) as e:
             qsim.qsim_debug_plan(n, np.concatenate([p, W.gates([bad])]), "complex128")
         assert e.value.code == code
+
+
+@pytest.mark.parametrize("dtype,n", [("complex64", 10), ("complex128", 11), ("complex128", 13), ("complex64", 14)])
+def test_whole_states_keep_a_permuting_frame(dtype, n):
+    """A state that is one tile is stored through what CX, SWAP and X leave in
+    the frame, whatever their number; a circuit of nothing else is one pass."""
+    rng = np.random.default_rng(n)
+    recs, perm = [], []
+    for i in range(120):
+        a, b = (int(q) for q in rng.choice(n, 2, replace=False))
+        kind = [W.KIND_CX, W.KIND_SWAP, W.KIND_X][rng.integers(3)]
+        perm.append((kind, (a, b)[:W.KIND_QUBITS[kind]], ()))
+        recs += [perm[-1], (W.KIND_RY, (a,), (float(rng.normal()),)), (W.KIND_CRZ, (a, b), (float(rng.normal()),))]
+    psi0 = W.random_state(n, 3)
+    for g in (W.gates(recs), W.gates(perm)):
+        st = qsim.qsim_debug_plan(n, g, dtype)
+        assert spanned(st)
+        want, _, _ = oracle.run(n, g, psi=psi0)
+        assert norm_error(qsim.qsim_debug_emulate(n, g, dtype, psi=psi0), want) < 1e-12
+    assert st["passes"] == 1 and st["fused_ops"] == 0
