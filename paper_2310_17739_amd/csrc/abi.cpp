@@ -367,6 +367,25 @@ int validate_plan(int n, int dtype, const Compiled &c) {
             return QSIM_E_ARG;
         for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i + 1]; j++) {
             const DevOp &o = p.ops[j];
+            if (o.kind == DEVOP_RUN) {
+                // 2-qubit operators on four positions, none of them one of those
+                // that run on registers at the ends of the pass
+                const uint32_t end = p.pass_begin[i + 1] - ((pi.ta.regs >> 1) & 1);
+                if (pi.strided || !run_tile(elem_bytes(dtype), width) || o.k != 4 || o.present < 2 || o.present >= end - j ||
+                    (j == p.pass_begin[i] && (pi.ta.regs & 1)))
+                    return QSIM_E_ARG;
+                for (int a = 0; a < 4; a++)
+                    if (o.pos[a] >= width || (a && o.pos[a] <= o.pos[a - 1]) ||
+                        o.slot[a] != lds_slot(int(elem_bytes(dtype)), 1 << o.pos[a]))
+                        return QSIM_E_ARG;
+                for (uint32_t x = j + 1; x <= j + o.present; x++) {
+                    const DevOp &m = p.ops[x];
+                    if (m.kind != DEVOP_MAT || m.k != 2 || m.kx || m.xq[0] > 5 ||
+                        m.pos[0] != o.pos[kRunPair[m.xq[0]][0]] || m.pos[1] != o.pos[kRunPair[m.xq[0]][1]])
+                        return QSIM_E_ARG;
+                }
+                continue;
+            }
             if (o.kind != DEVOP_MAT) {
                 // measurement records run only inside resident (whole-state) passes
                 if (pi.strided || pi.ta.t != n || o.pos[0] >= n || !devop_is_record(o.kind)) return QSIM_E_ARG;
@@ -563,12 +582,13 @@ int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
     if (pc.xcd_order) place_xcd_qubits(n, &passes);
     rc = pack_plan(L.ops, present, passes, pc, &out->plan);
     if (rc) return rc;
+    group_runs(passes, elem_bytes(dtype), pc.meta_budget, &out->plan);
     // LDS slot offsets of the tile positions (the tile kernel's layout)
     for (size_t i = 0; i < passes.size(); i++) {
         if (passes[i].strided || passes[i].kind != Pass::TILE) continue;
         for (uint32_t j = out->plan.pass_begin[i]; j < out->plan.pass_begin[i + 1]; j++) {
             DevOp &o = out->plan.ops[j];
-            if (o.kind != DEVOP_MAT) continue;
+            if (o.kind != DEVOP_MAT && o.kind != DEVOP_RUN) continue;
             for (int a = 0; a < o.k; a++) o.slot[a] = uint16_t(lds_slot(int(elem_bytes(dtype)), 1 << o.pos[a]));
         }
     }
@@ -1734,6 +1754,7 @@ int qsim_debug_emulate(int n, int dtype, const qsim_gate *g, size_t ng, const do
             for (uint64_t jpos = 0; jpos < v.size(); jpos++) v[jpos] = st[addr(jpos)];
             for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i + 1]; j++) {
                 const DevOp &o = p.ops[j];
+                if (o.kind == DEVOP_RUN) continue;   // its operators follow
                 if (o.kind != DEVOP_MAT) return QSIM_E_ARG;
                 uint32_t e = 0;
                 for (int x = 0; x < o.kx; x++) e |= uint32_t((base >> o.xq[x]) & 1) << x;

@@ -297,6 +297,10 @@ enum { DEVOP_MAT = 0, DEVOP_MEASURE = 1, DEVOP_ASSERT0 = 2, DEVOP_RESET = 3,
        DEVOP_XPOSE = 6,   // LDS re-layout; bytes 0..13 = canonical bit per position before,
        DEVOP_XPOSE2 = 7,  // and, in the record that follows, after
        DEVOP_MEASURE_RESET = 8,  // a measurement followed by a reset of the same qubit
+       // tiled passes: the `present` records behind it are 2-qubit operators on the k = 4
+       // positions pos[0..3] and run on registers one after another; xq[0] of each = the
+       // bits of that list that it acts on, (0 1) (0 2) (0 3) (1 2) (1 3) (2 3)
+       DEVOP_RUN = 14,
        // span passes:
        DEVOP_STAGE = 9,   // the LDS slots of the layout's positions, 16 bits each, in bytes 0..13
                           // and 16..29; kx = the stage's number
@@ -316,6 +320,13 @@ enum { DEVOP_MAT = 0, DEVOP_MEASURE = 1, DEVOP_ASSERT0 = 2, DEVOP_RESET = 3,
 };
 // records with coefficients (a stage's two are not used: they keep those of a
 // span pass at twice the record's number)
+// The bits that pair c = 0..5 of a run's four positions acts on.
+constexpr uint8_t kRunPair[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
+// Tiles of so many qubits run 2-qubit operators in runs (see group_runs): 16
+// amplitudes per thread leave smaller ones too few wavefronts, and in complex128
+// larger ones (one workgroup per CU) have no registers left for them.
+constexpr bool run_tile(size_t elem, int t) { return t == 12 || (t > 12 && elem == 8); }
+
 inline bool devop_is_mat(int kind) {
     return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI || kind == DEVOP_STAGE ||
            kind == DEVOP_SPAN_REC || kind == DEVOP_LAYOUT;
@@ -360,6 +371,10 @@ int pack_plan(const std::vector<Op> &ops, const std::vector<uint32_t> &present,
 // by an LDS re-layout (DEVOP_XPOSE pair), which also chooses the qubits the
 // next operators need (furthest next use leaves first).  Returns QSIM_OK or
 // QSIM_E_ARG for an operator the pass cannot hold.
+// Runs of 2-qubit operators in the tiled passes of a packed plan; `room` is the
+// LDS, behind a tile, that records and coefficients of a pass may take.
+void group_runs(const std::vector<Pass> &passes, size_t elem, size_t room, PackedPlan *plan);
+
 int pack_reg_pass(const std::vector<Op> &ops, const std::vector<uint32_t> &present, Pass &p,
                   bool coalesce, PackedPlan *out);
 

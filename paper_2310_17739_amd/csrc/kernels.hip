@@ -353,6 +353,80 @@ __device__ __forceinline__ void apply_lds(int t, const OpRec &op, uint32_t cfb, 
     }
 }
 
+// A 2-qubit operator on bits I < J of the register index: four groups of four,
+// NB at a time.
+template <typename T, int NB, int I, int J>
+__device__ __forceinline__ void run_pair(Cx<T> (&x)[16], uint32_t present, uint32_t cfb) {
+    // the bits that are not the operator's
+    constexpr int rest = 15 & ~((1 << I) | (1 << J)), lo = rest & -rest, hi = rest & ~lo;
+    static_for<0, 4 / NB>([&](auto cc) {
+        auto at = [](int i, int r) {
+            const int g = decltype(cc)::value * NB + i;
+            return ((g & 1) ? lo : 0) | ((g & 2) ? hi : 0) | ((r & 1) << I) | ((r >> 1) << J);
+        };
+        Cx<T> a[NB][4], y[NB][4];
+#pragma unroll
+        for (int i = 0; i < NB; i++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) a[i][r] = x[at(i, r)];
+        apply_groups_lds<T, 2, NB>(a, y, present, cfb);
+#pragma unroll
+        for (int i = 0; i < NB; i++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) x[at(i, r)] = y[i][r];
+    });
+    asm volatile("; pair %0 %1" ::"i"(I), "i"(J));   // keeps the cases of run_lds apart
+}
+
+// A run (DEVOP_RUN): its operators on 16 amplitudes per thread, through LDS once.
+// Vector arithmetic bounds it (256 multiply-adds per thread and dense operator);
+// one trip and one barrier serve about three operators.
+// `rec` is the LDS address of its first operator, `cf_at` that of the pass's
+// coefficients, which begin at cb.
+template <typename T, int LE, int TNT>
+__device__ __forceinline__ void run_lds(int t, const OpRec &op, uint32_t rec, uint32_t cf_at, uint32_t cb,
+                                        const uint32_t (&addr0)[16]) {
+    using L = LdsTile<T>;
+    typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+    constexpr int LOGT = (TNT == 512) ? 9 : 8, LG = LE > 4 ? LE - 4 : 0;
+    // (complex128: 16 results at once would take 64 registers more)
+    constexpr int NB = sizeof(T) == 4 ? 4 : TNT == 512 ? 1 : 2;
+    if (LE < 4 && int(threadIdx.x) >= (1 << (t - 4))) return;
+    uint32_t gb[LG > 0 ? LG : 1];
+#pragma unroll
+    for (int b = 0; b < LG; b++) {
+        int g = 1 << (LOGT + b);
+#pragma unroll
+        for (int j = 0; j < 4; j++) g = ((g >> op.pos[j]) << (op.pos[j] + 1)) | (g & ((1 << op.pos[j]) - 1));
+        gb[b] = uint32_t(sw<T>(g)) << L::LOGE;
+    }
+    for (int gi = 0; gi < (1 << LG); gi++) {
+        uint32_t o = 0;
+#pragma unroll
+        for (int b = 0; b < LG; b++)
+            if ((gi >> b) & 1) o ^= gb[b];
+        Cx<T> x[16];
+#pragma unroll
+        for (int r = 0; r < 16; r++) x[r] = L::ld(addr0[r] ^ o);
+        for (uint32_t m = 0; m < op.present; m++) {
+            const U4 a = *reinterpret_cast<const __attribute__((address_space(3))) U4 *>(uintptr_t(rec + 32u * m));
+            const U4 bq = *reinterpret_cast<const __attribute__((address_space(3))) U4 *>(uintptr_t(rec + 32u * m + 16u));
+            const uint32_t c = cf_at + ((__builtin_amdgcn_readfirstlane(a.x) - cb) << L::LOGE);
+            const uint32_t present = __builtin_amdgcn_readfirstlane(a.y);
+            switch ((__builtin_amdgcn_readfirstlane(bq.z) >> 16) & 0xff) {
+            case 0: run_pair<T, NB, 0, 1>(x, present, c); break;
+            case 1: run_pair<T, NB, 0, 2>(x, present, c); break;
+            case 2: run_pair<T, NB, 0, 3>(x, present, c); break;
+            case 3: run_pair<T, NB, 1, 2>(x, present, c); break;
+            case 4: run_pair<T, NB, 1, 3>(x, present, c); break;
+            default: run_pair<T, NB, 2, 3>(x, present, c); break;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; r++) L::st(addr0[r] ^ o, x[r]);
+    }
+}
+
 // An operator applied to a thread's registers: element tid + i * TNT sits at
 // tile position log2(TNT) + b for bit b of the register index i, so an
 // operator whose tile positions are log2(TNT) + OFF + j has the groups
@@ -653,7 +727,7 @@ __global__ void __launch_bounds__(TNT) k_tile(Cx<T> *__restrict__ state, uint64_
     uint32_t addr[16];
     if (i < iend) {
         op = decode_op(rec_at + uint32_t(i) * uint32_t(sizeof(DevOp)));
-        if (op.kind == qs::DEVOP_MAT) prep_addr<T>(op, addr);
+        if (op.kind == qs::DEVOP_MAT || op.kind == qs::DEVOP_RUN) prep_addr<T>(op, addr);
     }
     for (; i < iend; i++) {
         if (op.kind == qs::DEVOP_MAT) {
@@ -680,6 +754,9 @@ __global__ void __launch_bounds__(TNT) k_tile(Cx<T> *__restrict__ state, uint64_
             case 3: apply_lds<T, 3, LE, TNT>(ta.t, op, cf, addr); break;
             default: apply_lds<T, 4, LE, TNT>(ta.t, op, cf, addr); break;
             }
+        } else if (qs::run_tile(sizeof(Cx<T>), LOGT + LE) && op.kind == qs::DEVOP_RUN) {
+            run_lds<T, LE, TNT>(ta.t, op, rec_at + uint32_t(i + 1) * uint32_t(sizeof(DevOp)), cf_at, cb, addr);
+            i += int(op.present);
         } else {
             // the same on every lane: keeps the loop (and the record
             // addresses) uniform
@@ -687,7 +764,7 @@ __global__ void __launch_bounds__(TNT) k_tile(Cx<T> *__restrict__ state, uint64_
         }
         if (i + 1 < iend) {
             op = decode_op(rec_at + uint32_t(i + 1) * uint32_t(sizeof(DevOp)));
-            if (op.kind == qs::DEVOP_MAT) prep_addr<T>(op, addr);
+            if (op.kind == qs::DEVOP_MAT || op.kind == qs::DEVOP_RUN) prep_addr<T>(op, addr);
         }
         __syncthreads();
         if (status) break;
