@@ -42,7 +42,7 @@ MEASURED_TRAFFIC = {
 }
 
 
-KERNEL_SOURCES = ("kernels.hip", "launch.h", "swizzle.h", "host.h")
+KERNEL_SOURCES = ("kernels.hip", "span.hip", "device.h", "launch.h", "swizzle.h", "host.h")
 
 
 def kernel_source_hash():
@@ -191,9 +191,9 @@ def run_trajectories(qsim, W, ntraj=1024, rounds=500):
     terms = b.qsim_batch_group_stats(0)["terms"]
     b.close()
     p = res["probs"]
-    # The 128 KiB state stays in one workgroup's LDS for the whole program, so
-    # LDS bounds this form: every fused operator reads and writes the state
-    # there once, and each measurement or reset record reads it and rewrites
+    # The 128 KiB state stays in one workgroup for the whole pass.  LDS bytes are
+    # counted as if every operator read and wrote the state there once (span
+    # passes run several on registers per trip), and each measurement or reset record reads it and rewrites
     # it (counted as one more read and write; a reset that follows a
     # measurement of its qubit runs inside that measurement's record).
     lds_bytes = ntraj * (info["fused_ops"] + info["records"]) * 2 * 8 * (1 << 14)
@@ -620,8 +620,7 @@ def main():
                                "copy_GBps": copy_gbs, "frac_of_copy": achieved / copy_gbs,
                                "copy_ceilings_GBps": ceil,
                                "frac_of_rotated_copy": achieved / ceil["best_rotated"],
-                               "kernel": f"k_tile<{'double' if elem == 16 else 'float'}, LE, "
-                                         f"{os.environ.get('QSIM_TILE_THREADS') or (256 if elem == 16 else 512)}>",
+                               "kernel": f"k_span<{'double' if elem == 16 else 'float'}, LOGT>",
                                "bytes_per_launch": pass_bytes, "launches_per_step": launches}
             # one more step with an event pair around every pass: pure kernel
             # time per launch (what a kernel trace reports)
@@ -636,8 +635,9 @@ def main():
                           "achieved_TFLOPs": flops / (float(np.mean(prog_ms)) * 1e-3) / 1e12,
                           "peak_TFLOPs": 78.6,
                           "frac": flops / (float(np.mean(prog_ms)) * 1e-3) / 1e12 / 78.6}
-            # LDS traffic of the same launches: every operator reads and
-            # writes the whole tile once (coefficient reads not counted)
+            # LDS traffic of the same launches if every operator read and wrote
+            # the whole tile once, as in k_tile (coefficient reads not counted);
+            # span passes run about three rotations on registers per trip
             lds_bytes = float(st["fused_ops"]) * pass_bytes
             lds_gbs = lds_bytes / (float(np.mean(prog_ms)) * 1e-3) / 1e9
             res["lds"] = {"bytes_per_step": lds_bytes, "achieved_GBps": lds_gbs,
