@@ -685,7 +685,7 @@ int grow_host(void **ptr, size_t *cap, size_t need) {
     if (*ptr) (void)hipHostFree(*ptr);
     *ptr = nullptr;
     *cap = 0;
-    size_t sz = std::max(need, size_t(4096));
+    size_t sz = std::max(need, size_t(1) << 17);   // (freeing one to grow it waits for the device)
     sz = (sz + sz / 4 + 255) & ~size_t(255);
     hipError_t e = hipHostMalloc(ptr, sz, hipHostMallocDefault);
     if (e != hipSuccess) { qk::note_hip(e, "hipHostMalloc"); *ptr = nullptr; return QSIM_E_NOMEM; }
