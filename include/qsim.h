@@ -502,6 +502,24 @@ int qsim_debug_emulate(int n, int dtype, const qsim_gate *g, size_t ng, const do
                        size_t n_mats, const double *params, size_t n_params,
                        const qsim_fuse_opts *opt, double *psi);
 
+/* Host-only: one state of a batch group as qsim_batch_run computes it from the
+ * device tables of its plan, emulated in FP64: the template is compiled and laid
+ * out as qsim_batch_create does, its angles are bound from `params` (n_params
+ * values; NULL: none), and measurement records are decided from `uniforms` and
+ * `forced` (n_slots values each; forced may be NULL, uniforms too if there is no
+ * MEASURE record).  max_params as in qsim_batch_opts.  For tests without a GPU.
+ *
+ * psi: 2^n interleaved complex128 values, written (the state starts as
+ * |0...0>); outcomes, probs: n_slots values, written where a record ran (may be
+ * NULL); *status: 0, or the failed record's code, psi then being the state as it
+ * was before that record.  Errors: as qsim_batch_create, and QSIM_E_ARG for
+ * n > 24, psi == NULL or status == NULL. */
+int qsim_debug_emulate_batch(int n, int dtype, const qsim_gate *g, size_t ng, const double *mats,
+                             size_t n_mats, const double *params, size_t n_params,
+                             const double *uniforms, const int32_t *forced, int n_slots,
+                             int max_params, const qsim_fuse_opts *opt, double *psi,
+                             int32_t *outcomes, double *probs, int32_t *status);
+
 /* Host-only: number of full-state passes the planner makes for the fused
  * circuit (same inputs as qsim_debug_fuse), for n qubits and dtype. */
 int qsim_debug_plan(int n, int dtype, const qsim_gate *g, size_t ng,

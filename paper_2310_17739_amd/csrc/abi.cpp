@@ -1560,213 +1560,6 @@ int qsim_parse_qasm(const char *text, size_t len, qsim_gate *out, size_t cap, si
     return QSIM_OK;
 }
 
-int qsim_debug_emulate(int n, int dtype, const qsim_gate *g, size_t ng, const double *mats,
-                       size_t n_mats, const double *params, size_t n_params,
-                       const qsim_fuse_opts *opt, double *psi) {
-    if (n < 1 || n > 24 || (dtype != QSIM_C64 && dtype != QSIM_C128) || !psi) return QSIM_E_ARG;
-    Compiled c;
-    int rc;
-    try {
-        rc = compile_circuit(n, dtype, g, ng, GateInputs{mats, n_mats, params, n_params}, opt, &c);
-    } catch (const std::bad_alloc &) {
-        return QSIM_E_NOMEM;
-    }
-    if (rc) return rc;
-    const PackedPlan &p = c.plan;
-    cd *st = reinterpret_cast<cd *>(psi);
-    // y[r] = sum over present shifts (ascending) of cf[term * 2^k + r] x[r ^ m]
-    // on the 2^k members of every group of a width-w array addressed by pos[]
-    auto apply = [&](cd *v, int w, const DevOp &o, const cd *cf) {
-        const int k = o.k, d = 1 << k;
-        std::vector<cd> x(d), y(d);
-        for (uint64_t grp = 0; grp < (uint64_t(1) << (w - k)); grp++) {
-            uint64_t b0 = grp;
-            for (int j = 0; j < k; j++)
-                b0 = ((b0 >> o.pos[j]) << (o.pos[j] + 1)) | (b0 & ((uint64_t(1) << o.pos[j]) - 1));
-            auto at = [&](int r) {
-                uint64_t a = b0;
-                for (int j = 0; j < k; j++)
-                    if ((r >> j) & 1) a |= uint64_t(1) << o.pos[j];
-                return a;
-            };
-            for (int r = 0; r < d; r++) x[r] = v[at(r)];
-            for (int r = 0; r < d; r++) {
-                cd acc = 0;
-                int term = 0;
-                for (int m = 0; m < d; m++)
-                    if ((o.present >> m) & 1) acc += cf[size_t(term++) * d + r] * x[r ^ m];
-                y[r] = acc;
-            }
-            for (int r = 0; r < d; r++) v[at(r)] = y[r];
-        }
-    };
-    for (size_t i = 0; i < c.passes.size(); i++) {
-        const PassInfo &pi = c.passes[i];
-        if (pi.kind == Pass::MEASURE) return QSIM_E_ARG;
-        if (pi.strided) {
-            for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i + 1]; j++) {
-                const DevOp &o = p.ops[j];
-                if (o.kind != DEVOP_MAT || o.kx) return QSIM_E_ARG;
-                apply(st, n, o, p.coefs.data() + o.coef);
-            }
-            continue;
-        }
-        if (pi.reg) {
-            // register-resident pass: elements indexed by position bits
-            // (thread bits, then register bits), moved as the kernel moves them
-            const qk::RegArgs &ra = pi.ra;
-            const int t = ra.t, logt = t - kRegBits;
-            std::vector<cd> v(size_t(1) << t), w(v.size());
-            for (uint64_t tile = 0; tile < (uint64_t(1) << (n - t)); tile++) {
-                const uint64_t base = qk::tile_base(tile, ra.rest_mask, ra.nxcd, ra.xcd_q);
-                auto addr = [&](uint64_t P, const uint8_t *pos) {
-                    uint64_t a = base;
-                    for (int b = 0; b < t; b++)
-                        if ((P >> b) & 1) a |= uint64_t(1) << ra.tq[pos[b]];
-                    return a;
-                };
-                uint8_t cur[16];
-                std::memcpy(cur, ra.load_pos, 16);
-                for (uint64_t P = 0; P < v.size(); P++) v[P] = st[addr(P, ra.load_pos)];
-                for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i + 1]; j++) {
-                    const DevOp &o = p.ops[j];
-                    if (o.kind == DEVOP_RMAT) {
-                        uint32_t e = 0;
-                        for (int x = 0; x < o.kx; x++) e |= uint32_t((base >> o.xq[x]) & 1) << x;
-                        const cd *cf = p.coefs.data() + o.coef + (size_t(e) * __builtin_popcount(o.present) << 4);
-                        for (uint64_t tid = 0; tid < (uint64_t(1) << logt); tid++) {
-                            cd x[16], y[16];
-                            for (int r = 0; r < 16; r++) x[r] = v[tid | (uint64_t(r) << logt)];
-                            for (int r = 0; r < 16; r++) {
-                                cd acc = 0;
-                                int term = 0;
-                                for (int M = 0; M < 16; M++)
-                                    if ((o.present >> M) & 1) acc += cf[size_t(term++) * 16 + r] * x[r ^ M];
-                                y[r] = acc;
-                            }
-                            for (int r = 0; r < 16; r++) v[tid | (uint64_t(r) << logt)] = y[r];
-                        }
-                    } else if (o.kind == DEVOP_SWAP) {
-                        const int a = o.pos[0], b = logt + o.pos[1];
-                        for (uint64_t P = 0; P < v.size(); P++) {
-                            const uint64_t ba = (P >> a) & 1, bb = (P >> b) & 1;
-                            uint64_t Q = P & ~((uint64_t(1) << a) | (uint64_t(1) << b));
-                            Q |= (ba << b) | (bb << a);
-                            w[Q] = v[P];
-                        }
-                        std::swap(v, w);
-                        std::swap(cur[a], cur[b]);
-                    } else if (o.kind == DEVOP_XPOSE && j + 1 < p.pass_begin[i + 1]) {
-                        const uint8_t *from = reinterpret_cast<const uint8_t *>(&o);
-                        const uint8_t *to = reinterpret_cast<const uint8_t *>(&p.ops[j + 1]);
-                        if (std::memcmp(from, cur, size_t(t)) != 0) return QSIM_E_ARG;
-                        int to_pos[16];
-                        for (int b = 0; b < t; b++) to_pos[to[b]] = b;
-                        for (uint64_t P = 0; P < v.size(); P++) {
-                            uint64_t Q = 0;
-                            for (int b = 0; b < t; b++)
-                                if ((P >> b) & 1) Q |= uint64_t(1) << to_pos[from[b]];
-                            w[Q] = v[P];
-                        }
-                        std::swap(v, w);
-                        std::memcpy(cur, to, size_t(t));
-                        j++;
-                    } else {
-                        return QSIM_E_ARG;
-                    }
-                }
-                if (std::memcmp(cur, ra.store_pos, size_t(t)) != 0) return QSIM_E_ARG;
-                for (uint64_t P = 0; P < v.size(); P++) st[addr(P, ra.store_pos)] = v[P];
-            }
-            continue;
-        }
-        if (pi.span) {
-            // elements at positions (thread bits, then register bits), moved
-            // through the slots of each stage's layout
-            const qk::SpanArgs &sa = pi.sa;
-            const int t = sa.t, logt = t - kSpanRegs;
-            auto combine = [&](uint64_t P, auto &&vec) {
-                uint64_t a = 0;
-                for (int b = 0; b < t; b++)
-                    if ((P >> b) & 1) a ^= uint64_t(vec(b));
-                return a;
-            };
-            std::vector<cd> v(size_t(1) << t), w(v.size());
-            const cd turn(sa.phase_re, sa.phase_im);
-            for (uint64_t tile = 0; tile < (uint64_t(1) << (n - t)); tile++) {
-                const uint64_t base = qk::span_base(tile, sa);
-                for (uint64_t P = 0; P < v.size(); P++) v[P] = st[base ^ combine(P, [&](int b) { return sa.load_v[b]; })];
-                const uint8_t *cur = nullptr;
-                cd scale = 1.0;
-                for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i] + sa.nrun; j++) {
-                    const DevOp &o = p.ops[j];
-                    if (o.kind == DEVOP_SPAN_REC) return QSIM_E_ARG;
-                    if (o.kind == DEVOP_STAGE) {
-                        const uint8_t *raw = reinterpret_cast<const uint8_t *>(&o);
-                        auto slots = [](const uint8_t *at) {
-                            return [at](int x) {
-                                uint16_t s;
-                                std::memcpy(&s, at + (x < 7 ? 2 * x : 16 + 2 * (x - 7)), 2);
-                                return s;
-                            };
-                        };
-                        if (cur) {
-                            for (uint64_t P = 0; P < v.size(); P++) w[combine(P, slots(cur))] = v[P];
-                            for (uint64_t P = 0; P < v.size(); P++) v[P] = w[combine(P, slots(raw))];
-                        }
-                        cur = raw;
-                        continue;
-                    }
-                    const cd e0 = p.coefs[o.coef], e1 = p.coefs[o.coef + 1];
-                    scale *= e0.real() + e0.imag();
-                    const bool diag = o.k == 2 * kSpanRegs, real = !diag && (o.k & 1);
-                    const uint32_t m = diag ? 0u : 1u << (o.k >> 1);
-                    const uint64_t zb = uint64_t(o.slot[1]) | uint64_t(o.slot[2]) << 16 | uint64_t(o.slot[3]) << 32;
-                    for (uint64_t P = 0; P < v.size(); P++) {
-                        const uint64_t tid = P & ((uint64_t(1) << logt) - 1), r = P >> logt;
-                        const int s = (__builtin_popcountll(tid & o.slot[0]) + __builtin_popcountll(base & zb) +
-                                       __builtin_popcountll(r & o.present)) & 1;
-                        const cd b = (real ? cd(1.0) : cd(0.0, 1.0)) * (s ? -e1.imag() : e1.imag());
-                        w[P] = v[P] + b * v[P ^ (uint64_t(m) << logt)];
-                        if (e1.real() != 0.0) w[P] *= scale;
-                    }
-                    if (e1.real() != 0.0) scale = 1.0;
-                    std::swap(v, w);
-                }
-                scale *= turn;
-                for (uint64_t P = 0; P < v.size(); P++)
-                    st[base ^ sa.store_base ^ combine(P, [&](int b) { return sa.store_v[b]; })] = v[P] * scale;
-            }
-            continue;
-        }
-        const qk::TileArgs &ta = pi.ta;
-        const int t = ta.t;
-        std::vector<cd> v(size_t(1) << t);
-        for (uint64_t tile = 0; tile < (uint64_t(1) << (n - t)); tile++) {
-            // the workgroup's tile in the kernel's order
-            const uint64_t base = qk::tile_base(tile, ta.rest_mask, ta.nxcd, ta.xcd_q);
-            auto addr = [&](uint64_t jpos) {
-                uint64_t a = base;
-                for (int b = 0; b < t; b++)
-                    if ((jpos >> b) & 1) a |= uint64_t(1) << ta.tq[b];
-                return a;
-            };
-            for (uint64_t jpos = 0; jpos < v.size(); jpos++) v[jpos] = st[addr(jpos)];
-            for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i + 1]; j++) {
-                const DevOp &o = p.ops[j];
-                if (o.kind == DEVOP_RUN) continue;   // its operators follow
-                if (o.kind != DEVOP_MAT) return QSIM_E_ARG;
-                uint32_t e = 0;
-                for (int x = 0; x < o.kx; x++) e |= uint32_t((base >> o.xq[x]) & 1) << x;
-                apply(v.data(), t, o,
-                      p.coefs.data() + o.coef + size_t(e) * (size_t(__builtin_popcount(o.present)) << o.k));
-            }
-            for (uint64_t jpos = 0; jpos < v.size(); jpos++) st[addr(jpos)] = v[jpos];
-        }
-    }
-    return QSIM_OK;
-}
-
 int qsim_debug_plan(int n, int dtype, const qsim_gate *g, size_t ng, const double *mats,
                     size_t n_mats, const double *params, size_t n_params,
                     const qsim_fuse_opts *opt, qsim_apply_stats *out) {

@@ -18,6 +18,52 @@
 
 using namespace qs;
 
+namespace qs {
+
+// Rewrite a parameterised plan from its template layout (2^np cos/sin blocks
+// per operator) to the bound layout (one block per operator, per state) and
+// collect the bind entries; *ncoef: the bound coefficients.  QSIM_E_ARG if an
+// operator's template coefficients lie outside the template.
+int bind_layout(Compiled *c, std::vector<qk::BindEntry> *ents, size_t *ncoef, uint32_t *max_count) {
+    PackedPlan &p = c->plan;
+    size_t bound = 0, at = 0;   // at: end of the template coefficients read so far
+    *max_count = 0;
+    for (size_t j = 0; j < p.ops.size(); j++) {
+        DevOp &o = p.ops[j];
+        if (!devop_is_mat(o.kind)) continue;
+        const uint32_t count = devop_coefs(o);
+        qk::BindEntry e{};
+        e.bound_off = uint32_t(bound);
+        e.count = count;
+        // (the first word of a stage, a layout or a measurement record of a span
+        // pass is not the place of its coefficients, which follow the last ones)
+        e.tmpl_off = devop_has_place(o.kind) ? o.coef : uint32_t(at);
+        e.np = o.kind == DEVOP_PAULI && p.op_np[j] == 1 ? -1 : p.op_np[j];
+        for (int s = 0; s < 3; s++) e.slot[s] = p.op_slots[3 * j + s];
+        ents->push_back(e);
+        *max_count = std::max(*max_count, count);
+        at = size_t(e.tmpl_off) + (size_t(count) << p.op_np[j]);
+        if (at > p.coefs.size()) return QSIM_E_ARG;
+        if (devop_has_place(o.kind)) o.coef = uint32_t(bound);
+        bound += count;
+    }
+    // pass coefficient ranges in the bound layout
+    std::vector<uint32_t> new_begin(p.coef_begin.size());
+    size_t run = 0;
+    for (size_t i = 0; i + 1 < p.pass_begin.size(); i++) {
+        new_begin[i] = uint32_t(run);
+        for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i + 1]; j++)
+            if (devop_is_mat(p.ops[j].kind)) run += devop_coefs(p.ops[j]);
+    }
+    new_begin.back() = uint32_t(run);
+    p.coef_begin = new_begin;
+    for (auto &x : p.op_np) x = 0;
+    *ncoef = bound;
+    return QSIM_OK;
+}
+
+}  // namespace qs
+
 namespace {
 
 int hip_ok(hipError_t e, const char *where) { return qk::note_hip(e, where); }
@@ -119,44 +165,6 @@ struct qsim_batch {
 
 namespace {
 
-// Rewrite a parameterised plan from its template layout (2^np cos/sin blocks
-// per operator) to the bound layout (one block per operator, per state) and
-// collect the bind entries.  Returns the bound coefficient count.
-size_t bind_layout(Compiled *c, std::vector<qk::BindEntry> *ents, uint32_t *max_count) {
-    PackedPlan &p = c->plan;
-    size_t bound = 0, at = 0;   // at: end of the template coefficients read so far
-    *max_count = 0;
-    for (size_t j = 0; j < p.ops.size(); j++) {
-        DevOp &o = p.ops[j];
-        if (!devop_is_mat(o.kind)) continue;
-        const uint32_t count = devop_coefs(o);
-        qk::BindEntry e{};
-        e.bound_off = uint32_t(bound);
-        e.count = count;
-        e.tmpl_off = o.kind == DEVOP_STAGE ? uint32_t(at) : o.coef;
-        e.np = o.kind == DEVOP_PAULI && p.op_np[j] == 1 ? -1 : p.op_np[j];
-        for (int s = 0; s < 3; s++) e.slot[s] = p.op_slots[3 * j + s];
-        ents->push_back(e);
-        *max_count = std::max(*max_count, count);
-        // (a stage record's words hold its layout, not the place of its coefficients)
-        at = size_t(e.tmpl_off) + (size_t(count) << p.op_np[j]);
-        if (o.kind != DEVOP_STAGE) o.coef = uint32_t(bound);
-        bound += count;
-    }
-    // pass coefficient ranges in the bound layout
-    std::vector<uint32_t> new_begin(p.coef_begin.size());
-    size_t run = 0;
-    for (size_t i = 0; i + 1 < p.pass_begin.size(); i++) {
-        new_begin[i] = uint32_t(run);
-        for (uint32_t j = p.pass_begin[i]; j < p.pass_begin[i + 1]; j++)
-            if (devop_is_mat(p.ops[j].kind)) run += devop_coefs(p.ops[j]);
-    }
-    new_begin.back() = uint32_t(run);
-    p.coef_begin = new_begin;
-    for (auto &x : p.op_np) x = 0;
-    return bound;
-}
-
 int setup_group(Group &G, const qsim_batch_group &in, int dtype, const qsim_batch_opts &opt) {
     G.n = in.n;
     G.nstates = in.n_states;
@@ -226,7 +234,7 @@ int setup_group(Group &G, const qsim_batch_group &in, int dtype, const qsim_batc
     std::vector<qk::BindEntry> ents;
     size_t ncoef = G.c.plan.coefs.size();
     if (param) {
-        ncoef = bind_layout(&G.c, &ents, &G.max_count);
+        if ((rc = bind_layout(&G.c, &ents, &ncoef, &G.max_count))) return rc;
         G.nbind = uint32_t(ents.size());
         G.cstride = ncoef;
     }

@@ -331,6 +331,8 @@ inline bool devop_is_mat(int kind) {
     return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI || kind == DEVOP_STAGE ||
            kind == DEVOP_SPAN_REC || kind == DEVOP_LAYOUT;
 }
+// of those, records whose `coef` is the place of their coefficients
+inline bool devop_has_place(int kind) { return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI; }
 inline bool devop_is_record(int kind) {
     return kind == DEVOP_MEASURE || kind == DEVOP_ASSERT0 || kind == DEVOP_RESET || kind == DEVOP_MEASURE_RESET;
 }

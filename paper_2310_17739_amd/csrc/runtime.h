@@ -70,6 +70,9 @@ int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs
 // width for groups whose states fit one tile, which are not timed).
 int tune_tile_batch(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
                     const qsim_fuse_opts &base, uint32_t nstates, int *best_t);
+// The plan of a template in its bound layout, and the entries that bind it
+// (batch.cpp).
+int bind_layout(Compiled *c, std::vector<qk::BindEntry> *ents, size_t *ncoef, uint32_t *max_count);
 // Enqueue pass i of a plan (not a MEASURE pass) over nstates states spaced
 // sstride elements apart, state b's coefficients at coefs + b * cstride.
 int enqueue_pass(const Compiled &c, size_t i, const DevOp *d_ops, const void *d_coefs, uint64_t cstride, int dtype,

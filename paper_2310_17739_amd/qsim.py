@@ -101,6 +101,7 @@ def _load():
         "qsim_program_destroy": ([P], I),
         "qsim_debug_plan": ([I, I, P, SZ, P, SZ, P, SZ, P, P], I),
         "qsim_debug_emulate": ([I, I, P, SZ, P, SZ, P, SZ, P, P], I),
+        "qsim_debug_emulate_batch": ([I, I, P, SZ, P, SZ, P, SZ, P, P, I, I, P, P, P, P, P], I),
         "qsim_autotune": ([P, P, SZ, P, SZ, P, SZ, SZ, P, P], I),
         "qsim_sample": ([P, P, SZ, P], I),
         "qsim_stream_copy": ([P, P, SZ, I, C.c_uint32, P], I),
@@ -630,6 +631,27 @@ def qsim_debug_emulate(n, gates, dtype="complex128", mats=None, params=None, lev
     check(_lib.qsim_debug_emulate(int(n), QSIM_DTYPES[dtype], _p(g), len(g), _p(m), _n(m), _p(pr), _n(pr),
                                   C.byref(o) if o else None, _p(out)), "qsim_debug_emulate")
     return out
+
+
+def qsim_debug_emulate_batch(n, gates, dtype="complex128", mats=None, params=None, uniforms=None, forced=None,
+                             n_slots=0, max_params=0, level=None, max_width=None, tile_qubits=None, flags=0) -> dict:
+    """Host-only: one state of a batch group (angles `params`, draws `uniforms`,
+    outcomes `forced`) emulated in FP64 from the device tables of its plan."""
+    g = np.ascontiguousarray(gates, dtype=GATE_DTYPE)
+    m = None if mats is None else np.ascontiguousarray(mats, dtype=np.complex128)
+    pr = None if params is None else np.ascontiguousarray(params, dtype=np.float64)
+    u = None if uniforms is None else np.ascontiguousarray(uniforms, dtype=np.float64)
+    f = None if forced is None else np.ascontiguousarray(forced, dtype=np.int32)
+    assert all(a is None or a.size == n_slots for a in (u, f))
+    o = _opts(level, max_width, tile_qubits, flags)
+    psi = np.zeros(1 << int(n), dtype=np.complex128)
+    outcomes = np.zeros(max(n_slots, 1), dtype=np.int32)
+    probs = np.zeros(max(n_slots, 1), dtype=np.float64)
+    status = C.c_int32()
+    check(_lib.qsim_debug_emulate_batch(int(n), QSIM_DTYPES[dtype], _p(g), len(g), _p(m), _n(m), _p(pr), _n(pr), _p(u),
+                                        _p(f), int(n_slots), int(max_params), C.byref(o) if o else None, _p(psi),
+                                        _p(outcomes), _p(probs), C.byref(status)), "qsim_debug_emulate_batch")
+    return {"state": psi, "outcomes": outcomes[:n_slots], "probs": probs[:n_slots], "status": status.value}
 
 
 def qsim_debug_plan(n, gates, dtype="complex128", mats=None, params=None, level=None,
