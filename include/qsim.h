@@ -295,7 +295,9 @@ typedef struct qsim_batch_group {
     size_t n_terms;
     void *dev_states;        /* caller-owned device buffer of n_states * 2^n
                                 elements (state b at offset b * 2^n), or NULL
-                                to let the batch allocate it */
+                                to let the batch allocate it.  Groups may name
+                                the same or overlapping buffers: those run one
+                                after another, in order */
 } qsim_batch_group;
 
 typedef struct qsim_batch_opts {

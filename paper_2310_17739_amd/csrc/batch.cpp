@@ -157,6 +157,7 @@ struct qsim_batch {
     std::vector<Group> groups;
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
+    std::vector<size_t> main, side;       // groups on the caller's stream, and beside it
     static constexpr int kSide = 3;
     hipStream_t side_st[kSide] = {};      // for groups that run beside the others
     hipEvent_t side_ev[kSide] = {}, fork_ev = nullptr;
@@ -391,26 +392,33 @@ int enqueue_group(const Group &G, int dtype, hipStream_t st) {
 
 // Groups whose passes leave most of the chip idle (fewer than two workgroups a
 // CU) run beside the others, on up to kSide streams of the batch that fork from
-// the caller's stream and join it again.  Each group has buffers of its own.
-// Templates of 10, 14 and 18 qubits (64, 64 and 16 states): one after the other
-// 942 us, so 735 us.
-void split_groups(const qsim_batch *b, std::vector<const Group *> *main, std::vector<const Group *> *side) {
-    for (const Group &G : b->groups) {
+// the caller's stream and join it again.  Templates of 10, 14 and 18 qubits (64,
+// 64 and 16 states): one after the other 942 us, so 735 us.  Groups that name
+// overlapping state buffers run one after another, in order, on the caller's
+// stream.
+void split_groups(qsim_batch *b) {
+    const size_t elem = elem_bytes(b->dtype);
+    for (size_t i = 0; i < b->groups.size(); i++) {
+        const Group &G = b->groups[i];
         const int t = G.c.stats.tile_qubits > 0 ? G.c.stats.tile_qubits : G.n;
-        const bool small = (uint64_t(G.nstates) << std::max(0, G.n - t)) < 512;
-        (small ? side : main)->push_back(&G);
+        bool beside = (uint64_t(G.nstates) << std::max(0, G.n - t)) < 512;
+        const uintptr_t lo = uintptr_t(G.d_states), hi = lo + uintptr_t(uint64_t(G.nstates) * G.sstride * elem);
+        for (size_t j = 0; j < b->groups.size() && beside; j++) {
+            const Group &H = b->groups[j];
+            const uintptr_t at = uintptr_t(H.d_states), end = at + uintptr_t(uint64_t(H.nstates) * H.sstride * elem);
+            beside = i == j || hi <= at || end <= lo;
+        }
+        (beside ? b->side : b->main).push_back(i);
     }
-    if (main->empty()) {
-        main->push_back(side->back());
-        side->pop_back();
+    if (b->main.empty()) {
+        b->main.push_back(b->side.back());
+        b->side.pop_back();
     }
 }
 
 // The side streams and their events, made with the batch (a run may be captured).
 int make_side_streams(qsim_batch *b) {
-    std::vector<const Group *> main, side;
-    split_groups(b, &main, &side);
-    const size_t use = std::min(side.size(), size_t(qsim_batch::kSide));
+    const size_t use = std::min(b->side.size(), size_t(qsim_batch::kSide));
     int rc = QSIM_OK;
     for (size_t i = 0; i < use && !rc; i++) {
         rc = hip_ok(hipStreamCreateWithFlags(&b->side_st[i], hipStreamNonBlocking), "side stream");
@@ -421,8 +429,7 @@ int make_side_streams(qsim_batch *b) {
 }
 
 int enqueue_all(qsim_batch *b, hipStream_t st) {
-    std::vector<const Group *> main, side;
-    split_groups(b, &main, &side);
+    const std::vector<size_t> &main = b->main, &side = b->side;
     const size_t use = std::min(side.size(), size_t(qsim_batch::kSide));
     int rc = QSIM_OK;
     if (use && (rc = hip_ok(hipEventRecord(b->fork_ev, st), "fork"))) return rc;
@@ -431,8 +438,8 @@ int enqueue_all(qsim_batch *b, hipStream_t st) {
         rc = hip_ok(hipStreamWaitEvent(b->side_st[i], b->fork_ev, 0), "fork");
         if (!rc) forked++;
     }
-    for (size_t i = 0; i < side.size() && !rc; i++) rc = enqueue_group(*side[i], b->dtype, b->side_st[i % use]);
-    for (size_t i = 0; i < main.size() && !rc; i++) rc = enqueue_group(*main[i], b->dtype, st);
+    for (size_t i = 0; i < side.size() && !rc; i++) rc = enqueue_group(b->groups[side[i]], b->dtype, b->side_st[i % use]);
+    for (size_t i = 0; i < main.size() && !rc; i++) rc = enqueue_group(b->groups[main[i]], b->dtype, st);
     // (joined after an error as well: nothing may run past the call's stream)
     for (size_t i = 0; i < forked; i++) {
         int jrc = hip_ok(hipEventRecord(b->side_ev[i], b->side_st[i]), "join");
@@ -484,6 +491,7 @@ int qsim_batch_create(const qsim_batch_group *groups, int n_groups, const qsim_b
                 b->info.coef_bytes += G.coef_bytes;
             }
         }
+        if (!rc) split_groups(b);
     } catch (const std::bad_alloc &) {
         rc = QSIM_E_NOMEM;
     }
