@@ -431,156 +431,34 @@ static bool spans_wanted(int n, const FuseConfig &fc, const PlanConfig &pc) {
            env_int("QSIM_SPAN", 1) != 0 && env_int("QSIM_PLAN_COMMUTE", 1) != 0;
 }
 
-// The plan of a Pauli program, with the measurement records of L.
-static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered &L, const PlanConfig &pc,
-                         Compiled *out) {
-    TraceRange range("qsim.plan");
-    const size_t elem = elem_bytes(dtype);
-    std::vector<Pass> passes;
-    const int t = pc.tile_qubits;
-    const bool whole = t == n;
-    if (whole) {
-        plan_whole(n, P, L.n_epochs, pc.low_qubits, kSpanRegs, pc.meta_budget, &passes);
-        if (passes.empty() && !P.map.z.empty()) {
-            // nothing but the frame's permutation: a pass without rotations
-            PauliProgram none;
-            none.ops.push_back(PauliOp{});   // the identity
-            none.op_epoch.push_back(0);
-            plan_whole(n, none, 0, pc.low_qubits, kSpanRegs, pc.meta_budget, &passes);
-            for (SpanStage &st : passes[0].stages) st.ops.clear();
-        }
-    } else {
-        size_t at = 0, m = 0;
-        for (int e = 0; e < L.n_epochs; e++) {
-            size_t end = at;
-            while (end < P.ops.size() && P.op_epoch[end] == e) end++;
-            plan_spans(n, P, t, pc.low_qubits, kSpanRegs, pc.meta_budget, pc.window, pc.full_support, int(at),
-                       int(end), &passes);
-            at = end;
-            for (; m < L.meas.size() && L.meas[m].epoch == e; m++) {
-                Pass p;
-                p.kind = Pass::MEASURE;
-                p.meas = L.meas[m];
-                passes.push_back(std::move(p));
-            }
-        }
-    }
-    out->pauli = true;
-    PackedPlan &pl = out->plan;
-    const uint64_t all = (uint64_t(1) << n) - 1;
-    bool phased = P.phase == 0.0;
-    for (const Pass &p : passes) {
-        pl.pass_begin.push_back(uint32_t(pl.ops.size()));
-        pl.coef_begin.push_back(uint32_t(pl.coefs.size()));
-        PassInfo pi;
-        pi.kind = p.kind;
-        pi.meas = p.meas;
-        if (p.span) {
-            qk::SpanArgs &sa = pi.sa;
-            const int rc = pack_span_pass(P, p, kSpanRegs, dtype == QSIM_C64, &pl, &sa.nrun);
-            if (rc) return rc;
-            pi.span = true;
-            pi.ta.n = n;
-            sa.n = n;
-            sa.t = p.t;
-            sa.rest_mask = all & ~p.tile_mask;
-            for (int j = 0; j < p.t; j++) {
-                sa.load_v[j] = span_vector(p, p.stages.front().layout[j]);
-                sa.store_v[j] = span_vector(p, p.stages.back().layout[j]);
-                if (whole && &p == &passes.back()) sa.store_v[j] = map_index(P.map, sa.store_v[j]);
-            }
-            if (whole && &p == &passes.back()) sa.store_base = P.map.c;
-            sa.tile_bytes = p.stages.size() > 1 ? uint32_t(elem << p.t) : 0u;
-            sa.nlayout = uint32_t(p.stages.size() + (pl.ops.size() - pl.pass_begin.back() - sa.nrun));
-            sa.phase_re = 1.0;
-            if (!phased) {
-                sa.phase_re = std::cos(P.phase);
-                sa.phase_im = std::sin(P.phase);
-                phased = true;
-            }
-        }
-        out->passes.push_back(pi);
-    }
-    pl.pass_begin.push_back(uint32_t(pl.ops.size()));
-    pl.coef_begin.push_back(uint32_t(pl.coefs.size()));
-    out->records = int64_t(L.meas.size());
-    qsim_apply_stats &s = out->stats;
-    std::memset(&s, 0, sizeof(s));
-    s.input_gates = L.input_gates;
-    for (int l = 1; l < 5; l++) s.ops_after[l] = -1;   // the paper's fusion steps are not taken
-    s.ops_after[0] = L.input_gates;
-    s.ops_after[5] = s.fused_ops = int64_t(P.ops.size());
-    s.passes = int64_t(passes.size());
-    s.terms = pl.terms;
-    s.bytes_moved = s.passes * 2 * (int64_t(1) << n) * int64_t(elem);
-    s.tile_qubits = t;
-    return QSIM_OK;
-}
-
-int compile_circuit(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
-                    const qsim_fuse_opts *opt, Compiled *out) {
-    return compile_program(n, dtype, g, ng, in, false, false, 0, opt, out);
-}
-
-int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
-                    bool keep_params, bool allow_meas, int max_params,
-                    const qsim_fuse_opts *opt, Compiled *out) {
-    TraceRange range("qsim.compile");
-    double t0 = now_seconds();
-    if (alloc_fault()) throw std::bad_alloc();
-    FuseConfig fc;
-    PlanConfig pc;
-    default_configs(n, dtype, opt, &fc, &pc);
-    fc.max_params = keep_params ? std::max(1, std::min(max_params, 3)) : 0;
-    Lowered L;
-    int rc;
-    {
-        TraceRange r("qsim.lower");
-        std::vector<size_t> op_gate;
-        size_t first_at;
-        split_records(n, g, ng, allow_meas, &L, &op_gate, &rc, &first_at);
-        if (!rc && spans_wanted(n, fc, pc)) {
-            PauliProgram P;
-            bool fits = pauli_lower(n, g, op_gate, L, in, keep_params, pc.tile_qubits == n, &P);
-            if (pc.full_support)
-                for (const PauliOp &o : P.ops)
-                    fits = fits && __builtin_popcountll(o.x | o.z) <= pc.tile_qubits - pc.low_qubits;
-            if (fits) {
-                rc = compile_spans(n, dtype, P, L, pc, out);
-                out->stats.max_width = fc.max_width;
-                out->stats.compile_seconds = now_seconds() - t0;
-                return rc || keep_params ? rc : validate_plan(n, dtype, *out);
-            }
-        }
-        rc = lower_gates(n, g, ng, in, keep_params, op_gate, rc, first_at, &L);
-    }
-    if (rc) return rc;
+// The operators of L, fused, planned and packed into *out.
+static int compile_ops(int n, int dtype, Lowered *L, const FuseConfig &fc, const PlanConfig &pc, Compiled *out) {
     int64_t counts[6];
     {
         TraceRange r("qsim.fuse");
-        fuse(n, &L, fc, counts);
+        fuse(n, L, fc, counts);
     }
     TraceRange plan_range("qsim.plan");
-    std::vector<uint32_t> present(L.ops.size()), meta(L.ops.size());
-    for (size_t i = 0; i < L.ops.size(); i++) {
-        present[i] = op_present(L.ops[i], fc.sparse);
+    std::vector<uint32_t> present(L->ops.size()), meta(L->ops.size());
+    for (size_t i = 0; i < L->ops.size(); i++) {
+        present[i] = op_present(L->ops[i], fc.sparse);
         // LDS holds the bound (per-state) coefficients: no cos/sin blocks
         meta[i] = uint32_t(sizeof(DevOp) + size_t(__builtin_popcount(present[i])) *
-                                               L.ops[i].dim() * elem_bytes(dtype));
+                                               L->ops[i].dim() * elem_bytes(dtype));
     }
-    std::vector<uint64_t> need(L.ops.size());
-    for (size_t i = 0; i < L.ops.size(); i++)
-        need[i] = pc.full_support ? L.ops[i].mask() : op_moved_qubits(L.ops[i], present[i]);
+    std::vector<uint64_t> need(L->ops.size());
+    for (size_t i = 0; i < L->ops.size(); i++)
+        need[i] = pc.full_support ? L->ops[i].mask() : op_moved_qubits(L->ops[i], present[i]);
     std::vector<Pass> passes;
-    plan_passes(n, L, meta, need, pc, &passes);
+    plan_passes(n, *L, meta, need, pc, &passes);
     // tiled passes of 10..13 qubits (not whole-state ones, which may hold
     // measurement records) run register-resident
     for (Pass &p : passes)
         p.reg = pc.reg_engine && p.kind == Pass::TILE && !p.strided && p.t < n && reg_threads_for(p.t) > 0 &&
                 p.c <= 4 && p.inline_meas.empty();
-    place_positions(n, L.ops, pc.threads == 512 ? 9 : 8, first_regs_max_k(dtype), pc.first_in_regs, &passes);
+    place_positions(n, L->ops, pc.threads == 512 ? 9 : 8, first_regs_max_k(dtype), pc.first_in_regs, &passes);
     if (pc.xcd_order) place_xcd_qubits(n, &passes);
-    rc = pack_plan(L.ops, present, passes, pc, &out->plan);
+    const int rc = pack_plan(L->ops, present, passes, pc, &out->plan);
     if (rc) return rc;
     group_runs(passes, elem_bytes(dtype), pc.meta_budget, &out->plan);
     // LDS slot offsets of the tile positions (the tile kernel's layout)
@@ -637,10 +515,10 @@ int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
     }
     qsim_apply_stats &s = out->stats;
     std::memset(&s, 0, sizeof(s));
-    s.input_gates = L.input_gates;
+    s.input_gates = L->input_gates;
     for (int l = 0; l < 6; l++) s.ops_after[l] = counts[l];
-    s.fused_ops = int64_t(L.ops.size());
-    out->records = int64_t(L.meas.size());
+    s.fused_ops = int64_t(L->ops.size());
+    out->records = int64_t(L->meas.size());
     s.passes = int64_t(passes.size());
     s.terms = out->plan.terms;
     s.bytes_moved = int64_t(passes.size()) * 2 * (int64_t(1) << n) * int64_t(elem_bytes(dtype));
@@ -649,6 +527,180 @@ int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
     for (const PassInfo &pi : out->passes) s.reg_passes += pi.reg ? 1 : 0;
     s.reg_swaps = out->stats_reg_swaps;
     s.reg_relayouts = out->stats_reg_xposes;
+    return QSIM_OK;
+}
+
+// The passes of `src` behind those of *out, whose ends are still open.
+static void append_passes(const Compiled &src, Compiled *out) {
+    const PackedPlan &s = src.plan;
+    PackedPlan &p = out->plan;
+    const uint32_t o0 = uint32_t(p.ops.size()), c0 = uint32_t(p.coefs.size());
+    for (size_t i = 0; i < src.passes.size(); i++) {
+        out->passes.push_back(src.passes[i]);
+        p.pass_begin.push_back(o0 + s.pass_begin[i]);
+        p.coef_begin.push_back(c0 + s.coef_begin[i]);
+    }
+    for (DevOp o : s.ops) {
+        if (devop_has_place(o.kind)) o.coef += c0;
+        p.ops.push_back(o);
+    }
+    p.coefs.insert(p.coefs.end(), s.coefs.begin(), s.coefs.end());
+    p.op_np.insert(p.op_np.end(), s.op_np.begin(), s.op_np.end());
+    p.op_slots.insert(p.op_slots.end(), s.op_slots.begin(), s.op_slots.end());
+    p.terms += s.terms;
+}
+
+// The plan of a Pauli program, with the measurement records of L.
+static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered &L, const FuseConfig &fc,
+                         const PlanConfig &pc, Compiled *out) {
+    TraceRange range("qsim.plan");
+    const size_t elem = elem_bytes(dtype);
+    const int t = pc.tile_qubits;
+    const bool whole = t == n;
+    PackedPlan &pl = out->plan;
+    const uint64_t all = (uint64_t(1) << n) - 1;
+    bool phased = P.phase == 0.0;
+    size_t left_ops = 0;
+    auto put = [&](const Pass &p, bool last) -> int {
+        pl.pass_begin.push_back(uint32_t(pl.ops.size()));
+        pl.coef_begin.push_back(uint32_t(pl.coefs.size()));
+        PassInfo pi;
+        pi.kind = p.kind;
+        pi.meas = p.meas;
+        if (p.span) {
+            qk::SpanArgs &sa = pi.sa;
+            const int rc = pack_span_pass(P, p, kSpanRegs, dtype == QSIM_C64, &pl, &sa.nrun);
+            if (rc) return rc;
+            pi.span = true;
+            pi.ta.n = n;
+            sa.n = n;
+            sa.t = p.t;
+            sa.rest_mask = all & ~p.tile_mask;
+            for (int j = 0; j < p.t; j++) {
+                sa.load_v[j] = span_vector(p, p.stages.front().layout[j]);
+                sa.store_v[j] = span_vector(p, p.stages.back().layout[j]);
+                if (last) sa.store_v[j] = map_index(P.map, sa.store_v[j]);
+            }
+            if (last) sa.store_base = P.map.c;
+            sa.tile_bytes = p.stages.size() > 1 ? uint32_t(elem << p.t) : 0u;
+            sa.nlayout = uint32_t(p.stages.size() + (pl.ops.size() - pl.pass_begin.back() - sa.nrun));
+            sa.phase_re = 1.0;
+            if (!phased) {
+                sa.phase_re = std::cos(P.phase);
+                sa.phase_im = std::sin(P.phase);
+                phased = true;
+            }
+        }
+        out->passes.push_back(pi);
+        return QSIM_OK;
+    };
+    // the gates that epoch e leaves in the frame
+    size_t left_at = 0;
+    auto put_left = [&](int e) -> int {
+        size_t end = left_at;
+        while (end < P.left.size() && P.left_epoch[end] == e) end++;
+        if (end == left_at) return QSIM_OK;
+        Lowered T;
+        int rc = lower(n, P.left.data() + left_at, end - left_at, GateInputs{}, false, false, &T);
+        left_at = end;
+        Compiled c;
+        if (!rc) rc = compile_ops(n, dtype, &T, fc, pc, &c);
+        if (!rc) append_passes(c, out);
+        left_ops += T.ops.size();
+        return rc;
+    };
+    std::vector<Pass> passes;
+    int rc = QSIM_OK;
+    if (whole) {
+        plan_whole(n, P, L.n_epochs, pc.low_qubits, kSpanRegs, pc.meta_budget, &passes);
+        if (passes.empty() && !P.map.z.empty()) {
+            // nothing but the frame's permutation: a pass without rotations
+            PauliProgram none;
+            none.ops.push_back(PauliOp{});   // the identity
+            none.op_epoch.push_back(0);
+            plan_whole(n, none, 0, pc.low_qubits, kSpanRegs, pc.meta_budget, &passes);
+            for (SpanStage &st : passes[0].stages) st.ops.clear();
+        }
+        for (size_t i = 0; i < passes.size() && !rc; i++) rc = put(passes[i], i + 1 == passes.size());
+        if (!rc) rc = put_left(L.n_epochs);   // (follows every record)
+    } else {
+        size_t at = 0, m = 0;
+        for (int e = 0; e < L.n_epochs && !rc; e++) {
+            size_t end = at;
+            while (end < P.ops.size() && P.op_epoch[end] == e) end++;
+            passes.clear();
+            plan_spans(n, P, t, pc.low_qubits, kSpanRegs, pc.meta_budget, pc.window, pc.full_support, int(at),
+                       int(end), &passes);
+            at = end;
+            for (size_t i = 0; i < passes.size() && !rc; i++) rc = put(passes[i], false);
+            if (!rc) rc = put_left(e);
+            for (; m < L.meas.size() && L.meas[m].epoch == e && !rc; m++) {
+                Pass p;
+                p.kind = Pass::MEASURE;
+                p.meas = L.meas[m];
+                rc = put(p, false);
+            }
+        }
+    }
+    if (rc) return rc;
+    out->pauli = true;
+    pl.pass_begin.push_back(uint32_t(pl.ops.size()));
+    pl.coef_begin.push_back(uint32_t(pl.coefs.size()));
+    out->records = int64_t(L.meas.size());
+    qsim_apply_stats &s = out->stats;
+    std::memset(&s, 0, sizeof(s));
+    s.input_gates = L.input_gates;
+    for (int l = 1; l < 5; l++) s.ops_after[l] = -1;   // the paper's fusion steps are not taken
+    s.ops_after[0] = L.input_gates;
+    s.ops_after[5] = s.fused_ops = int64_t(P.ops.size() + left_ops);
+    s.passes = int64_t(out->passes.size());
+    s.terms = pl.terms;
+    s.bytes_moved = s.passes * 2 * (int64_t(1) << n) * int64_t(elem);
+    s.tile_qubits = t;
+    return QSIM_OK;
+}
+
+int compile_circuit(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
+                    const qsim_fuse_opts *opt, Compiled *out) {
+    return compile_program(n, dtype, g, ng, in, false, false, 0, opt, out);
+}
+
+int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
+                    bool keep_params, bool allow_meas, int max_params,
+                    const qsim_fuse_opts *opt, Compiled *out) {
+    TraceRange range("qsim.compile");
+    double t0 = now_seconds();
+    if (alloc_fault()) throw std::bad_alloc();
+    FuseConfig fc;
+    PlanConfig pc;
+    default_configs(n, dtype, opt, &fc, &pc);
+    fc.max_params = keep_params ? std::max(1, std::min(max_params, 3)) : 0;
+    Lowered L;
+    int rc;
+    {
+        TraceRange r("qsim.lower");
+        std::vector<size_t> op_gate;
+        size_t first_at;
+        split_records(n, g, ng, allow_meas, &L, &op_gate, &rc, &first_at);
+        if (!rc && spans_wanted(n, fc, pc)) {
+            PauliProgram P;
+            bool fits = pauli_lower(n, g, op_gate, L, in, keep_params, pc.tile_qubits == n, &P);
+            if (pc.full_support)
+                for (const PauliOp &o : P.ops)
+                    fits = fits && __builtin_popcountll(o.x | o.z) <= pc.tile_qubits - pc.low_qubits;
+            if (fits) {
+                rc = compile_spans(n, dtype, P, L, fc, pc, out);
+                out->stats.max_width = fc.max_width;
+                out->stats.compile_seconds = now_seconds() - t0;
+                return rc || keep_params ? rc : validate_plan(n, dtype, *out);
+            }
+        }
+        rc = lower_gates(n, g, ng, in, keep_params, op_gate, rc, first_at, &L);
+    }
+    if (rc) return rc;
+    rc = compile_ops(n, dtype, &L, fc, pc, out);
+    if (rc) return rc;
+    qsim_apply_stats &s = out->stats;
     s.compile_seconds = now_seconds() - t0;
     // parameterised templates are validated after their coefficient layout
     // is bound (qsim_batch_create)

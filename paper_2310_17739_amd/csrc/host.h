@@ -90,12 +90,15 @@ struct PauliRecord {
     IndexMap map;
 };
 
-// A circuit as rotations in order, each with its epoch; `phase` is the angle
-// of the global phase that the rotations leave out.  Of a state that is one
-// tile, also its records and the frame that is left at the end.
+// A circuit as rotations in order, each with its epoch, and the gates that are
+// left in the frame, which follow the rotations of their epoch; `phase` is the
+// angle of the global phase that the rotations leave out.  Of a state that is
+// one tile, also its records and the frame that is left at the end.
 struct PauliProgram {
     std::vector<PauliOp> ops;
     std::vector<int> op_epoch;
+    std::vector<qsim_gate> left;
+    std::vector<int> left_epoch;
     double phase = 0.0;
     std::vector<PauliRecord> recs;
     IndexMap map;

@@ -8,8 +8,10 @@
 // any weight).  C is kept as the images C^dagger X_q C and C^dagger Z_q C of
 // the generators.  Gates of the frame cancel structurally: a gate that undoes
 // the last one on all of its wires removes it, so that what is left at the end
-// of an epoch is an explicit gate list (empty for Pauli exponentials), emitted
-// as rotations.  A circuit with gates that are no product of few rotations
+// of an epoch is an explicit gate list (empty for Pauli exponentials).  These
+// gates run as operators of tiled passes after the epoch's rotations: an X or a
+// CX moves amplitudes and leaves those that are 0 at 0, which rotations by a
+// quarter turn would not.  A circuit with gates that are no product of few rotations
 // (dense matrices, Toffolis) is not lowered this way.
 //
 // Passes.  A rotation mixes the amplitudes i and i ^ x only, x the string's X
@@ -165,6 +167,8 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
     out->ops.clear();
     out->op_epoch.clear();
     out->recs.clear();
+    out->left.clear();
+    out->left_epoch.clear();
     out->map = IndexMap{};
     out->phase = 0.0;
     if (n > 48) return false;   // the device record keeps 48 bits of a Z mask
@@ -185,62 +189,22 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
     };
     auto one = [](char l, int q) { return Axis{{l, 'I'}, {q, -1}, 1}; };
     auto two = [](char a, int qa, char b, int qb) { return Axis{{a, b}, {qa, qb}, 2}; };
-    // the live gates of the frame, as rotations of phi
+    // the live gates of the frame, to run after the epoch's rotations
     auto flush = [&]() {
-        if (f.live) {
-            std::vector<Frame::Node> nodes;
-            for (const Frame::Node &h : f.nodes)
-                if (h.alive) nodes.push_back(h);
-            f.reset();
-            const size_t before = out->ops.size();
-            auto rot = [&](const Axis &a, double theta) { emit(f.image(a), theta / 2, -1); };
-            const double h2 = M_PI / 2;
-            auto cx = [&](int c, int t) {
-                rot(one('Z', c), h2);
-                rot(one('X', t), h2);
-                rot(two('Z', c, 'X', t), -h2);
-                out->phase += M_PI / 4;
-            };
-            for (const Frame::Node &h : nodes) {
-                switch (h.kind) {
-                case QSIM_G_H:
-                    rot(one('Z', h.q0), h2);
-                    rot(one('X', h.q0), h2);
-                    rot(one('Z', h.q0), h2);
-                    out->phase += h2;
-                    break;
-                case QSIM_G_X: rot(one('X', h.q0), M_PI); out->phase += h2; break;
-                case QSIM_G_Y: rot(one('Y', h.q0), M_PI); out->phase += h2; break;
-                case QSIM_G_Z: rot(one('Z', h.q0), M_PI); out->phase += h2; break;
-                case QSIM_G_S: rot(one('Z', h.q0), h2); out->phase += M_PI / 4; break;
-                case QSIM_G_SDG: rot(one('Z', h.q0), -h2); out->phase -= M_PI / 4; break;
-                case QSIM_G_SX: rot(one('X', h.q0), h2); out->phase += M_PI / 4; break;
-                case QSIM_G_RX: rot(one('X', h.q0), h.theta); break;
-                case QSIM_G_RY: rot(one('Y', h.q0), h.theta); break;
-                case QSIM_G_RZ: rot(one('Z', h.q0), h.theta); break;
-                case QSIM_G_RXX: rot(two('X', h.q0, 'X', h.q1), h.theta); break;
-                case QSIM_G_RZZ: rot(two('Z', h.q0, 'Z', h.q1), h.theta); break;
-                case QSIM_G_CX: cx(h.q0, h.q1); break;
-                case QSIM_G_CY:
-                    rot(one('Z', h.q0), h2);
-                    rot(one('Y', h.q1), h2);
-                    rot(two('Z', h.q0, 'Y', h.q1), -h2);
-                    out->phase += M_PI / 4;
-                    break;
-                case QSIM_G_CZ:
-                    rot(one('Z', h.q0), h2);
-                    rot(one('Z', h.q1), h2);
-                    rot(two('Z', h.q0, 'Z', h.q1), -h2);
-                    out->phase += M_PI / 4;
-                    break;
-                default:   // SWAP
-                    cx(h.q0, h.q1);
-                    cx(h.q1, h.q0);
-                    cx(h.q0, h.q1);
-                    break;
-                }
-            }
-            extra += out->ops.size() - before;
+        for (const Frame::Node &h : f.nodes) {
+            if (!h.alive) continue;
+            qsim_gate r{};
+            r.kind = uint16_t(h.kind);
+            r.nq = h.q1 >= 0 ? 2 : 1;
+            r.q[0] = h.q0;
+            r.q[1] = std::max(h.q1, 0);
+            r.slot = -1;
+            r.theta[0] = h.theta;
+            out->left.push_back(r);
+            out->left_epoch.push_back(epoch);
+            // what it would take as rotations
+            extra += h.kind == QSIM_G_SWAP ? 9 : h.kind == QSIM_G_H || h.kind == QSIM_G_CX || h.kind == QSIM_G_CY ||
+                     h.kind == QSIM_G_CZ ? 3 : 1;
         }
         f.reset();
     };
@@ -407,9 +371,9 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
         else epoch = L.n_epochs;   // what is left follows every record
     }
     flush();
-    // gates left in the frame are emitted at up to nine rotations each: with
-    // many of them the fused operators of the matrix lowering do less
-    return 4 * extra <= out->ops.size();
+    // with many gates left in the frame, the fused operators of the matrix
+    // lowering do less
+    return 3 * extra <= out->ops.size();
 }
 
 // -------------------------------------------------------------- planning

@@ -1,0 +1,78 @@
+"""Host-only: amplitudes that a circuit leaves at exactly 0.  A reset, an assertion
+and a forced outcome test for them, so a qubit that permutations, controlled gates
+or cancelling rotations leave definite has to be definite to the last bit.  The
+plans are emulated from their device tables, multiply-adds fused as in the kernels."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from paper_2310_17739_amd import qsim
+from test_host_span import norm_error, spanned
+
+A, B, C = 0, 3, 7     # the ancilla that ends up definite, a qubit that is |0>, one in superposition
+
+
+def surroundings(n, seed, rounds=1):
+    """Rotations that leave every qubit but A and B in superposition."""
+    rng = np.random.default_rng(seed)
+    recs = []
+    for _ in range(rounds):
+        for q in range(n):
+            if q not in (A, B):
+                recs.append((W.KIND_RY, (q,), (float(rng.uniform(0.3, 1.2)),)))
+                recs.append((W.KIND_RZ, (q,), (float(rng.normal()),)))
+        for q in range(n - 1):
+            if not {q, q + 1} & {A, B}:
+                recs.append((W.KIND_RZZ, (q, q + 1), (float(rng.normal()),)))
+                recs.append((W.KIND_RXX, (q, q + 1), (float(rng.normal()),)))
+    return recs
+
+
+# gates after which A is definite: (records, its value)
+GADGETS = {
+    # permutations that nothing cancels, between gates that keep the frame from permuting
+    "x": ([(W.KIND_X, (A,), ())], 1),
+    "x_beside_h": ([(W.KIND_X, (A,), ()), (W.KIND_H, (C,), ())], 1),
+    "y": ([(W.KIND_Y, (A,), ())], 1),
+    "rx_pi": ([(W.KIND_RX, (A,), (np.pi,))], 1),
+    "ry_minus_pi": ([(W.KIND_RY, (A,), (-np.pi,))], 1),
+    "cx": ([(W.KIND_X, (B,), ()), (W.KIND_CX, (B, A), ()), (W.KIND_S, (C,), ())], 1),
+    "cx_from_zero": ([(W.KIND_CX, (B, A), ()), (W.KIND_H, (C,), ())], 0),
+    "cy": ([(W.KIND_X, (B,), ()), (W.KIND_CY, (B, A), ())], 1),
+    "cz_between": ([(W.KIND_X, (A,), ()), (W.KIND_CZ, (A, C), ()), (W.KIND_SWAP, (A, B), ())], 0),
+    "swap": ([(W.KIND_X, (B,), ()), (W.KIND_SWAP, (A, B), ()), (W.KIND_SX, (C,), ())], 1),
+    "rxx_pi": ([(W.KIND_RXX, (A, B), (np.pi,)), (W.KIND_H, (C,), ())], 1),
+}
+
+
+def check(n, dtype, recs, value, tile=None):
+    g = W.gates(surroundings(n, 1, 2) + list(recs))
+    psi = np.zeros(1 << n, dtype=np.complex128)
+    psi[0] = 1
+    got = qsim.qsim_debug_emulate(n, g, dtype, psi=psi, tile_qubits=tile)
+    want, _, _ = oracle.run(n, g)
+    assert norm_error(got, want) < 2 * 9 * len(g) * 1.2e-16
+    other = got.reshape(-1, 2)[:, 1 - value]
+    assert np.all(other == 0)
+    # with records: a reset succeeds, the other outcome has probability 0
+    after = W.gates(surroundings(n, 1, 2) + list(recs) + [(W.KIND_RESET, (A,), ())] + surroundings(n, 2))
+    r = qsim.qsim_debug_emulate_batch(n, after, dtype, tile_qubits=tile)
+    want, _, _ = oracle.run(n, W.gates(surroundings(n, 1, 2) + list(recs) + [(W.KIND_X, (A,), ())] * value + surroundings(n, 2)))
+    assert r["status"] == 0 and norm_error(r["state"], want) < 2 * 9 * len(after) * 1.2e-16
+    for forced in (value, 1 - value):
+        m = W.gates(surroundings(n, 1, 2) + list(recs) + [(W.KIND_MEASURE, (A,), (), 0)])
+        r = qsim.qsim_debug_emulate_batch(n, m, dtype, uniforms=[0.5], forced=[forced], n_slots=1, tile_qubits=tile)
+        assert r["status"] == (0 if forced == value else qsim.E_ZERO_PROB)
+        if forced == value:
+            assert r["probs"][0] == 1.0
+    m = W.gates(surroundings(n, 1, 2) + list(recs) + [(W.KIND_ASSERT0, (A,), (), 0)])
+    r = qsim.qsim_debug_emulate_batch(n, m, dtype, n_slots=1, tile_qubits=tile)
+    assert r["status"] == (0 if value == 0 else qsim.E_ZERO_PROB)
+    return qsim.qsim_debug_plan(n, g, dtype, tile_qubits=tile)
+
+
+@pytest.mark.parametrize("dtype,n,tile", [("complex128", 10, None), ("complex64", 14, None), ("complex128", 15, 11)])
+@pytest.mark.parametrize("name", sorted(GADGETS))
+def test_definite_qubits(dtype, n, tile, name):
+    assert spanned(check(n, dtype, *GADGETS[name], tile=tile))
