@@ -245,7 +245,7 @@ int validate_span_pass(int n, int dtype, const Compiled &c, size_t i) {
         p.coef_begin[i + 1] > p.coefs.size() || p.coef_begin[i + 1] - p.coef_begin[i] < 2 * (re - rb))
         return QSIM_E_ARG;
     if (sa.nrun == 0 || sa.nrun > re - rb || (sa.store_base & ~all) || (sa.store_base && t != n)) return QSIM_E_ARG;
-    uint32_t stages = 0, layouts = 0, records = 0;
+    uint32_t stages = 0, layouts = 0, records = 0, pairs = 0;
     for (uint32_t j = rb; j < re; j++) {
         const DevOp &o = p.ops[j];
         // layouts are numbered as the stages, then the records behind them
@@ -278,12 +278,23 @@ int validate_span_pass(int n, int dtype, const Compiled &c, size_t i) {
                 return QSIM_E_ARG;
             // the kernel finds the coefficients at twice the record's number
             if (o.coef != p.coef_begin[i] + 2 * (j - rb)) return QSIM_E_ARG;
+        } else if (o.kind == DEVOP_PAULI2) {
+            // and two records behind it; its branch is that of both members of a pair
+            if (!stages || o.k >= 2 * kSpanRegs || (o.slot[0] >> logt) || (o.present >> kSpanRegs) || p.op_np[j] != 0 ||
+                o.coef != p.coef_begin[i] + 2 * (j - rb) || j - rb + 2 >= sa.nrun)
+                return QSIM_E_ARG;
+            const DevOp &w = p.ops[j + 1];
+            if (w.kind != DEVOP_PAULI2X || p.ops[j + 2].kind != DEVOP_PAULI2X || (w.slot[0] >> logt) ||
+                (w.present >> kSpanRegs) || ((w.present >> (o.k >> 1)) & 1) || p.op_np[j + 1] != 0 || p.op_np[j + 2] != 0)
+                return QSIM_E_ARG;
+            pairs++;
+            j += 2;
         } else {
             return QSIM_E_ARG;
         }
     }
     if (p.ops[rb].kind != DEVOP_STAGE || sa.tile_bytes != (stages > 1 ? uint32_t(elem_bytes(dtype) << t) : 0u) ||
-        sa.nlayout != layouts || layouts != stages + records ||
+        sa.nlayout != layouts || layouts != stages + records || sa.pairs != pairs ||
         qk::span_lds_bytes(sa.tile_bytes, re - rb, layouts) > qk::max_lds_bytes())
         return QSIM_E_ARG;
     uint32_t at = stages;
@@ -584,6 +595,7 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
             if (last) sa.store_base = P.map.c;
             sa.tile_bytes = p.stages.size() > 1 ? uint32_t(elem << p.t) : 0u;
             sa.nlayout = uint32_t(p.stages.size() + (pl.ops.size() - pl.pass_begin.back() - sa.nrun));
+            for (uint32_t j = pl.pass_begin.back(); j < pl.ops.size(); j++) sa.pairs += pl.ops[j].kind == DEVOP_PAULI2;
             sa.phase_re = 1.0;
             if (!phased) {
                 sa.phase_re = std::cos(P.phase);
@@ -591,6 +603,7 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
                 phased = true;
             }
         }
+        if (p.span && getenv("DBG")) { int nr=0; for (auto &st: p.stages) nr+=int(st.ops.size()); fprintf(stderr,"pass stages %zu ops %d pairs %u records %u\n", p.stages.size(), nr, pi.sa.pairs, pi.sa.nrun);}
         out->passes.push_back(pi);
         return QSIM_OK;
     };
@@ -687,7 +700,7 @@ int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
             bool fits = pauli_lower(n, g, op_gate, L, in, keep_params, pc.tile_qubits == n, &P);
             if (pc.full_support)
                 for (const PauliOp &o : P.ops)
-                    fits = fits && __builtin_popcountll(o.x | o.z) <= pc.tile_qubits - pc.low_qubits;
+                    fits = fits && __builtin_popcountll(o.x | o.z | o.z2) <= pc.tile_qubits - pc.low_qubits;
             if (fits) {
                 rc = compile_spans(n, dtype, P, L, fc, pc, out);
                 out->stats.max_width = fc.max_width;

@@ -242,16 +242,32 @@ int emulate(int n, const Compiled &c, cd *st, Records *recs) {
                         cur = raw;
                         continue;
                     }
+                    const uint64_t zb = uint64_t(o.slot[1]) | uint64_t(o.slot[2]) << 16 | uint64_t(o.slot[3]) << 32;
+                    auto parity = [&](uint64_t P, const DevOp &m, uint64_t mb) {
+                        const uint64_t tid = P & ((uint64_t(1) << logt) - 1), r = P >> logt;
+                        return (__builtin_popcountll(tid & m.slot[0]) + __builtin_popcountll(base & mb) +
+                                __builtin_popcountll(r & m.present)) & 1;
+                    };
                     const cd e0 = p.coefs[o.coef], e1 = p.coefs[o.coef + 1];
+                    if (o.kind == DEVOP_PAULI2) {
+                        const DevOp &m = p.ops[j + 1];
+                        const uint64_t wb = uint64_t(m.slot[1]) | uint64_t(m.slot[2]) << 16 | uint64_t(m.slot[3]) << 32;
+                        for (uint64_t P = 0; P < v.size(); P++) {
+                            const cd c = parity(P, m, wb) ? e1 : e0;
+                            const double A = c.real(), B = parity(P, o, zb) ? -c.imag() : c.imag();
+                            const cd a = v[P], b = v[P ^ (uint64_t(1) << (logt + (o.k >> 1)))];
+                            w[P] = (o.k & 1) ? cd(std::fma(B, b.real(), A * a.real()), std::fma(B, b.imag(), A * a.imag()))
+                                             : cd(std::fma(-B, b.imag(), A * a.real()), std::fma(B, b.real(), A * a.imag()));
+                        }
+                        std::swap(v, w);
+                        j += 2;
+                        continue;
+                    }
                     scale *= e0.real() + e0.imag();
                     const bool diag = o.k == 2 * kSpanRegs, real = !diag && (o.k & 1);
                     const uint32_t m = diag ? 0u : 1u << (o.k >> 1);
-                    const uint64_t zb = uint64_t(o.slot[1]) | uint64_t(o.slot[2]) << 16 | uint64_t(o.slot[3]) << 32;
                     for (uint64_t P = 0; P < v.size(); P++) {
-                        const uint64_t tid = P & ((uint64_t(1) << logt) - 1), r = P >> logt;
-                        const int s = (__builtin_popcountll(tid & o.slot[0]) + __builtin_popcountll(base & zb) +
-                                       __builtin_popcountll(r & o.present)) & 1;
-                        const double tt = s ? -e1.imag() : e1.imag();
+                        const double tt = parity(P, o, zb) ? -e1.imag() : e1.imag();
                         const cd a = v[P], b = v[P ^ (uint64_t(m) << logt)];
                         w[P] = real ? cd(std::fma(tt, b.real(), a.real()), std::fma(tt, b.imag(), a.imag()))
                                     : cd(std::fma(-tt, b.imag(), a.real()), std::fma(tt, b.real(), a.imag()));
@@ -310,6 +326,13 @@ void bind_coefs(Compiled *c, const std::vector<qk::BindEntry> &ents, const doubl
     std::vector<cd> out(ncoef);
     const std::vector<cd> &tmpl = c->plan.coefs;
     for (const qk::BindEntry &e : ents) {
+        if (e.np == -2) {
+            const double u = tmpl[e.tmpl_off].real() * (0.5 * params[e.slot[0]]);
+            const double w = tmpl[e.tmpl_off].imag() * (0.5 * params[e.slot[1]]);
+            out[e.bound_off] = cd(std::cos(u + w), std::sin(u + w));
+            out[e.bound_off + 1] = cd(std::cos(u - w), std::sin(u - w));
+            continue;
+        }
         if (e.np < 0) {
             const double th = params[e.slot[0]];
             const double s = tmpl[e.tmpl_off].real() * std::sin(0.5 * th);

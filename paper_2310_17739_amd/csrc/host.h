@@ -64,12 +64,18 @@ struct Lowered {
 
 // A rotation exp(-i phi P) of a Pauli program, P|b> = sign i^|x & z| (-1)^|b & z|
 // |b ^ x>; with slot >= 0, phi is half the angle of that slot of the parameter
-// vector.
+// vector.  two: times exp(-i phi2 P2), P2 another string with the X mask x that
+// commutes with P.  On amplitudes i and i ^ x both turn the same way, so this is
+// one rotation by phi + phi2 or by their difference, as the parity of i with
+// z ^ z2 says; where that is 0, as for a control that is |0>, it is the identity
+// to the last bit.
 struct PauliOp {
-    uint64_t x = 0, z = 0;
-    double phi = 0.0;
-    double sign = 1.0;
-    int32_t slot = -1;
+    uint64_t x = 0, z = 0, z2 = 0;
+    double phi = 0.0, phi2 = 0.0;
+    double sign = 1.0, sign2 = 1.0;
+    int32_t slot = -1, slot2 = -1;
+    bool two = false;
+    int entries() const { return two ? 3 : 1; }   // records of a span pass
 };
 
 // The basis states behind a frame of CNOTs, SWAPs and Xs: bit q of the logical
@@ -175,6 +181,17 @@ inline void pauli_coefs(double a, double b, bool single, cd e[2]) {
     if (std::fabs(a) < kLeastCos[single]) a = kLeastCos[single];
     e[0] = single ? cd(double(float(a)), a - double(float(a))) : cd(a, 0.0);
     e[1] = cd(0.0, b / a);
+}
+
+// Cosine and sine of a branch of a rotation of two angles; angles that are
+// multiples of a quarter turn to rounding (as operators tell a diagonal that is
+// absent) are taken as such.
+constexpr double kTrivial = 1e-14;
+inline cd branch_coefs(double angle) {
+    double a = std::cos(angle), b = std::sin(angle);
+    if (std::fabs(b) <= kTrivial) a = std::copysign(1.0, a), b = 0.0;
+    if (std::fabs(a) <= kTrivial) a = 0.0, b = std::copysign(1.0, b);
+    return cd(a, b);
 }
 
 // A stage of a span pass: position j of an element (thread bits, then register
@@ -318,6 +335,10 @@ enum { DEVOP_MAT = 0, DEVOP_MEASURE = 1, DEVOP_ASSERT0 = 2, DEVOP_RESET = 3,
                               // slot; kx = the number of the layout to store in after a failure
        DEVOP_LAYOUT = 13,     // as a stage: the state's index that each position adds, and in bytes
                               // 30..31 an index to add to all; behind the records that run
+       DEVOP_PAULI2 = 15,     // rotation of two angles: as DEVOP_PAULI, on a register bit; its
+                              // coefficients are the cosine and sine of one branch and the other
+       DEVOP_PAULI2X = 16,    // two follow it; in the first, present, slot[0] and slot[1..3] are the
+                              // masks of the branch's parity, laid out as its sign masks
        DEVOP_EXPECT = 11  // a term of a Pauli sum: its form and signs as a rotation's; coef = its
                           // number
 };
@@ -332,10 +353,12 @@ constexpr bool run_tile(size_t elem, int t) { return t == 12 || (t > 12 && elem 
 
 inline bool devop_is_mat(int kind) {
     return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI || kind == DEVOP_STAGE ||
-           kind == DEVOP_SPAN_REC || kind == DEVOP_LAYOUT;
+           kind == DEVOP_SPAN_REC || kind == DEVOP_LAYOUT || kind == DEVOP_PAULI2 || kind == DEVOP_PAULI2X;
 }
 // of those, records whose `coef` is the place of their coefficients
-inline bool devop_has_place(int kind) { return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI; }
+inline bool devop_has_place(int kind) {
+    return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI || kind == DEVOP_PAULI2;
+}
 inline bool devop_is_record(int kind) {
     return kind == DEVOP_MEASURE || kind == DEVOP_ASSERT0 || kind == DEVOP_RESET || kind == DEVOP_MEASURE_RESET;
 }

@@ -56,6 +56,10 @@ Pauli mul(const Pauli &a, const Pauli &b) {
 bool anticommute(uint64_t ax, uint64_t az, uint64_t bx, uint64_t bz) {
     return __builtin_popcountll((ax & bz) ^ (az & bx)) & 1;
 }
+// Whether a rotation does not commute with the string (x, z).
+bool clash(const PauliOp &o, uint64_t x, uint64_t z) {
+    return anticommute(x, z, o.x, o.z) || (o.two && anticommute(x, z, o.x, o.z2));
+}
 
 // A string on up to two qubits, as gates name it.
 struct Axis {
@@ -186,6 +190,19 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
         o.slot = slot;
         out->ops.push_back(o);
         out->op_epoch.push_back(epoch);
+    };
+    // rotations about two axes of commuting strings, as one where their X masks agree
+    auto emit_pair = [&](const Pauli &p, double phi, const Pauli &p2, double phi2) {
+        emit(p, phi, -1);
+        if (p.x != p2.x || !p.x) {
+            emit(p2, phi2, -1);
+            return;
+        }
+        PauliOp &o = out->ops.back();
+        o.two = true;
+        o.z2 = p2.z;
+        o.sign2 = (p2.k & 2) ? -1.0 : 1.0;
+        o.phi2 = phi2;
     };
     auto one = [](char l, int q) { return Axis{{l, 'I'}, {q, -1}, 1}; };
     auto two = [](char a, int qa, char b, int qb) { return Axis{{a, b}, {qa, qb}, 2}; };
@@ -348,8 +365,7 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
         case QSIM_G_CRZ: {
             // exp(-i theta/2 (1 - Z_c)/2 P)
             const char l = kind == QSIM_G_CRX ? 'X' : kind == QSIM_G_CRY ? 'Y' : 'Z';
-            emit(f.image(one(l, q1)), th / 4, -1);
-            emit(f.image(two('Z', q0, l, q1)), -th / 4, -1);
+            emit_pair(f.image(one(l, q1)), th / 4, f.image(two('Z', q0, l, q1)), -th / 4);
             break;
         }
         case QSIM_G_CU1:
@@ -542,7 +558,7 @@ void make_stages(const PauliProgram &P, const std::vector<int> &items, const Spa
             const PauliOp &o = P.ops[size_t(i)];
             bool free = true;
             for (const Mask &s : skipped)
-                if (anticommute(s.x, s.z, o.x, o.z)) {
+                if (clash(o, s.x, s.z)) {
                     free = false;
                     break;
                 }
@@ -550,6 +566,7 @@ void make_stages(const PauliProgram &P, const std::vector<int> &items, const Spa
                 st.ops.push_back(i);
             } else {
                 skipped.push_back({o.x, o.z});
+                if (o.two) skipped.push_back({o.x, o.z2});
                 later.push_back(i);
             }
         }
@@ -607,11 +624,11 @@ void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t met
         uint64_t x, z;
     };
     std::vector<Mask> skipped;
-    skipped.reserve(kSkipMax + 1);
+    skipped.reserve(kSkipMax + 2);
     // may o run before every skipped rotation?
     auto passes_by = [&](const PauliOp &o) {
         for (const Mask &s : skipped)
-            if (anticommute(s.x, s.z, o.x, o.z)) return false;
+            if (clash(o, s.x, s.z)) return false;
         return true;
     };
     while (nxt[size_t(head)] != head) {
@@ -626,7 +643,7 @@ void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t met
                 return true;
             }
             Span U = T;
-            for (uint64_t m = o.x | o.z; m; m &= m - 1) {
+            for (uint64_t m = o.x | o.z | o.z2; m; m &= m - 1) {
                 const uint64_t r = U.reduce(m & (~m + 1));
                 if (r && U.d >= t) return false;
                 if (r) U.add(r);
@@ -641,13 +658,14 @@ void plan_spans(int n, const PauliProgram &P, int t, int c, int regs, size_t met
         for (int i = nxt[size_t(head)]; i != head && scanned < window && skipped.size() < kSkipMax && sel.size() < kPassMax;
              i = nxt[size_t(i)], scanned++) {
             const PauliOp &o = ops[i];
-            // LDS of its entry and factor; it may open a stage of its own
-            const size_t need = 24 + 88;
+            // LDS of its entries and factors; it may open a stage of its own
+            const size_t need = 24 * size_t(o.entries()) + 88;
             if ((sel.empty() || meta + need <= meta_budget) && passes_by(o) && grow(o)) {
                 sel.push_back(i);
                 meta += need;
             } else {
                 skipped.push_back({o.x, o.z});
+                if (o.two) skipped.push_back({o.x, o.z2});
             }
         }
         for (int i : sel) {
@@ -698,8 +716,8 @@ void plan_whole(int n, const PauliProgram &P, int n_epochs, int c, int regs, siz
     };
     size_t at = 0, r = 0;
     for (int e = 0; e <= n_epochs; e++) {
-        // LDS of an entry, a factor and a stage of its own; a record's layout
-        for (; at < P.ops.size() && P.op_epoch[at] == e; at++) take(int(at), 24 + 88);
+        // LDS of entries, factors and a stage of its own; a record's layout
+        for (; at < P.ops.size() && P.op_epoch[at] == e; at++) take(int(at), 24 * size_t(P.ops[at].entries()) + 88);
         for (; r < P.recs.size() && P.recs[r].rec.epoch == e; r++) take(~int(r), 24 + 88 + 88);
     }
     close();
@@ -762,10 +780,36 @@ int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, 
             d.kind = DEVOP_PAULI;
             d.coef = uint32_t(out->coefs.size());
             if (!string_record(o.x, o.z, V, t, regs, &d)) return QSIM_E_ARG;
-            const int ny = __builtin_popcountll(o.x & o.z) & 3;
+            // (kappa of a string, see below)
+            auto kappa_of = [&](uint64_t z) { return (__builtin_popcountll(o.x & z) & 2) ? 1.0 : -1.0; };
+            if (o.two) {
+                DevOp w{};
+                if (!o.x || __builtin_popcountll(o.x & (o.z ^ o.z2)) & 1) return QSIM_E_ARG;
+                if (!string_record(0, o.z ^ o.z2, V, t, regs, &w)) return QSIM_E_ARG;
+                d.kind = DEVOP_PAULI2;
+                w.kind = DEVOP_PAULI2X;
+                w.k = 0;
+                out->ops.push_back(d);
+                const double s1 = kappa_of(o.z) * o.sign, s2 = kappa_of(o.z2) * o.sign2;
+                if (o.slot >= 0) {
+                    out->coefs.push_back(cd(s1, s2));
+                    for (int j = 0; j < 3; j++) out->coefs.push_back(cd(0.0, 0.0));
+                } else {
+                    out->coefs.push_back(branch_coefs(s1 * o.phi + s2 * o.phi2));
+                    out->coefs.push_back(branch_coefs(s1 * o.phi - s2 * o.phi2));
+                }
+                out->op_np.push_back(o.slot >= 0 ? 1 : 0);
+                for (int32_t slot : {o.slot, o.slot2, -1}) out->op_slots.push_back(slot);
+                for (int j = 0; j < 2; j++) {
+                    out->ops.push_back(w);
+                    dummy();
+                }
+                out->terms += 2;
+                continue;
+            }
             // y[i] = a x[i] + b (-1)^(i . z) x[i ^ x] with a = cos phi and
             // b = -i sin phi (-i)^ny: t is its real or imaginary part
-            const double kappa = (ny & 2) ? 1.0 : -1.0;
+            const double kappa = kappa_of(o.z);
             out->ops.push_back(d);
             if (o.slot >= 0) {
                 // bound per state: the sign of t (four entries of template)

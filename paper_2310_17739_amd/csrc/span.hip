@@ -132,6 +132,69 @@ __device__ __forceinline__ void rotate_form(const Cx<T> (&x)[1 << LR], Cx<T> (&y
     }
 }
 
+// The bits in which two numbers differ, and the change from one to the other where
+// m is all ones (0: none): one operation a word.
+struct Bits1 {
+    uint32_t lo;
+};
+struct Bits2 {
+    uint32_t lo, hi;
+};
+__device__ __forceinline__ Bits1 differ(float u, float v) { return {__float_as_uint(u) ^ __float_as_uint(v)}; }
+__device__ __forceinline__ Bits2 differ(double u, double v) {
+    const uint64_t d = uint64_t(__double_as_longlong(u) ^ __double_as_longlong(v));
+    return {uint32_t(d), uint32_t(d >> 32)};
+}
+__device__ __forceinline__ void change(float &u, Bits1 d, uint32_t m) { u = __uint_as_float(__float_as_uint(u) ^ (d.lo & m)); }
+__device__ __forceinline__ void change(double &u, Bits2 d, uint32_t m) {
+    const uint64_t b = uint64_t(__double_as_longlong(u));
+    u = __longlong_as_double(int64_t(uint64_t(uint32_t(b) ^ (d.lo & m)) | (uint64_t(uint32_t(b >> 32) ^ (d.hi & m)) << 32)));
+}
+
+// A rotation of two angles: as rotate, but y[r] = a x[r] + b x[r ^ M] in full, with
+// (a, b) that of the branch of register r: register 0's is (a, b), the other differs
+// by (da, db), and the branch changes with the parity of r and bits 4-7 of w, which
+// leave out M.  Where an angle is 0 the amplitudes stay as they are to the last bit,
+// and none of it goes into the pass's scale.
+template <typename T, int LR, int M, bool REAL, typename D>
+__device__ __forceinline__ void rotate2(const Cx<T> (&x)[1 << LR], Cx<T> (&y)[1 << LR], T a, T b, D da, D db, uint32_t w) {
+    const Signs<LR> sg(w);
+    static_for<0, (1 << (LR - 1))>([&](auto gc) {
+        constexpr int g = decltype(gc)::value, r = gray_reg<M>(g), q = r ^ M;
+        if constexpr (g > 0) {
+            constexpr int bit = __builtin_ctz(r ^ gray_reg<M>(g - 1));
+            const uint32_t m = uint32_t(int32_t(w << (31 - LR - bit)) >> 31);
+            turn(b, sg.s[bit]);
+            change(a, da, m);
+            change(b, db, m);
+        }
+        const Cx<T> u = x[r], v = x[q];
+        if constexpr (REAL) {
+            y[r] = Cx<T>{T(fma(b, v.re, a * u.re)), T(fma(b, v.im, a * u.im))};
+            y[q] = Cx<T>{T(fma(-b, u.re, a * v.re)), T(fma(-b, u.im, a * v.im))};
+        } else {
+            y[r] = Cx<T>{T(fma(-b, v.im, a * u.re)), T(fma(b, v.re, a * u.im))};
+            y[q] = Cx<T>{T(fma(-b, u.im, a * v.re)), T(fma(b, u.re, a * v.im))};
+        }
+    });
+    asm volatile("; turned by %0" ::"i"(M * 2 + REAL));   // (as in rotate)
+}
+
+template <typename T, int LR, typename D>
+__device__ __forceinline__ void rotate2_form(const Cx<T> (&x)[1 << LR], Cx<T> (&y)[1 << LR], int form, T a, T b, D da,
+                                             D db, uint32_t w) {
+    switch (form) {
+    case 0: rotate2<T, LR, 1, false>(x, y, a, b, da, db, w); break;
+    case 1: rotate2<T, LR, 1, true>(x, y, a, b, da, db, w); break;
+    case 2: rotate2<T, LR, 2, false>(x, y, a, b, da, db, w); break;
+    case 3: rotate2<T, LR, 2, true>(x, y, a, b, da, db, w); break;
+    case 4: rotate2<T, LR, 4, false>(x, y, a, b, da, db, w); break;
+    case 5: rotate2<T, LR, 4, true>(x, y, a, b, da, db, w); break;
+    case 6: rotate2<T, LR, 8, false>(x, y, a, b, da, db, w); break;
+    default: rotate2<T, LR, 8, true>(x, y, a, b, da, db, w); break;
+    }
+}
+
 // LDS behind the tile: an entry of 16 bytes per record, the layouts of the
 // stages (64 bytes each) and a factor of the pass's scale per record.
 typedef uint32_t U4 __attribute__((ext_vector_type(4)));
@@ -145,7 +208,12 @@ typedef __attribute__((address_space(3))) double LdsF8;
 // A measurement record: form kRecForm, its masks, dimension and value as in the
 // device record (bits 16-27, 0-7), its kind (bits 8-11), its slot in word 1 and
 // the layout of a failing state in word 2.
-constexpr uint32_t kStageForm = 15, kRecForm = 14;
+// A rotation of two angles: form kPairForm, the sign masks of the thread and of
+// the register index as above, the branch's masks in word 1 (thread) and bits
+// 4-7, the form of rotate2_form in bits 8-10; the next two entries hold the
+// cosine and sine of the branch of thread 0's register 0, and of the other (both
+// in the first of them in single precision).
+constexpr uint32_t kStageForm = 15, kRecForm = 14, kPairForm = 13;
 __device__ __forceinline__ void put_t(U4 &e, float t) { e.z = __float_as_uint(t); }
 __device__ __forceinline__ void put_t(U4 &e, double t) {
     const uint64_t b = uint64_t(__double_as_longlong(t));
@@ -313,8 +381,9 @@ __device__ __forceinline__ int span_record(Cx<T> (&v)[1 << qs::kSpanRegs], uint3
 }
 
 // WIDE: byte offsets inside a state need more than 32 bits.  MEAS: the pass holds
-// measurement records.
-template <typename T, int LOGT, bool WIDE, bool MEAS>
+// measurement records.  PAIR: it holds rotations of two angles (a kernel of its
+// own: their registers and branches would cost every other pass).
+template <typename T, int LOGT, bool WIDE, bool MEAS, bool PAIR>
 __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, uint64_t sstride, SpanArgs sa,
                                                    const DevOp *__restrict__ ops, uint32_t ob, uint32_t oe,
                                                    const Cx<T> *__restrict__ coefs, uint32_t cb, uint64_t cstride,
@@ -376,6 +445,31 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
             e.y = e1.re != T(0);
             put_t(e, flip(e1.im, uint32_t(__builtin_popcountll(base & zb)) << 31));
             f = double(e0.re) + double(e0.im);
+        } else if (PAIR && ((a.w >> 16) & 0xff) == qs::DEVOP_PAULI2) {
+            // the signs and the branch of the tile's base index join the coefficients
+            const U4 a1 = p[2], c1 = p[3];
+            const uint64_t zb = uint64_t((c.x >> 16) | (c.y << 16)) | (uint64_t(c.y >> 16) << 32);
+            const uint64_t wb = uint64_t((c1.x >> 16) | (c1.y << 16)) | (uint64_t(c1.y >> 16) << 32);
+            const uint32_t s = uint32_t(__builtin_popcountll(base & zb)) << 31;
+            const bool other = (__builtin_popcountll(base & wb) & 1) != 0;
+            const Cx<T> u = other ? e1 : e0, o = other ? e0 : e1;
+            e.x = (kPairForm << 28) | ((c.x & 0xfffu) << 16) | ((a.z & 7u) << 8) | ((a1.y & 0xfu) << 4) | (a.y & 0xfu);
+            e.y = c1.x & 0xfffu;
+            if constexpr (sizeof(T) == 4) {
+                const U4 d = {__float_as_uint(u.re), __float_as_uint(flip(u.im, s)), __float_as_uint(o.re),
+                              __float_as_uint(flip(o.im, s))};
+                *reinterpret_cast<LdsU4 *>(uintptr_t(ent_at + 16u * (x + 1))) = d;
+            } else {
+                auto words = [](double re, double im) {
+                    const uint64_t r = uint64_t(__double_as_longlong(re)), i = uint64_t(__double_as_longlong(im));
+                    return U4{uint32_t(r), uint32_t(r >> 32), uint32_t(i), uint32_t(i >> 32)};
+                };
+                *reinterpret_cast<LdsU4 *>(uintptr_t(ent_at + 16u * (x + 1))) = words(u.re, flip(u.im, s));
+                *reinterpret_cast<LdsU4 *>(uintptr_t(ent_at + 16u * (x + 2))) = words(o.re, flip(o.im, s));
+            }
+        } else if (PAIR && ((a.w >> 16) & 0xff) == qs::DEVOP_PAULI2X) {
+            *reinterpret_cast<LdsF8 *>(uintptr_t(fac_at + 8u * x)) = 1.0;
+            continue;   // (its entry is written with the one before)
         } else if (MEAS && ((a.w >> 16) & 0xff) == qs::DEVOP_SPAN_REC) {
             e.x = (kRecForm << 28) | ((c.x & 0xfffu) << 16) | (((a.z >> 8) & 0xfu) << 8) | (a.y & 0xffu);
             e.y = (c.x >> 16) | (c.y << 16);
@@ -403,17 +497,30 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
     };
     uint32_t addr[E];
     stage_addr<T, LOGT>(lay_at, tid, addr);
-    U4 ahead = lds_u4(ent_at + 16u);
+    // the next entry, and in single precision the one behind it, where a rotation of
+    // two angles has its coefficients (in double precision the registers are short:
+    // 12 qubits, 6 rounds, 222 us with those read ahead, 210 without; complex64 at 14
+    // qubits, 8 rounds, 701 and 720).  LDS has room beyond the last entry.
+    constexpr bool AHEAD2 = PAIR && sizeof(T) == 4;
+    U4 ahead, ahead1 = {0, 0, 0, 0};
+    auto read_ahead = [&](uint32_t i) __attribute__((always_inline)) {
+        ahead = lds_u4(ent_at + 16u * i);
+        if (AHEAD2) ahead1 = lds_u4(ent_at + 16u * (i + 1));
+    };
+    read_ahead(1);
     uint32_t scaled = 0;   // the first record whose factor the state does not have yet
     int failed = 0;
-    // One record, from the registers x to y.  (Two sets of registers in turn:
+    // One record (with those behind it that belong to it: returns how many), from
+    // the registers x to y.  (Two sets of registers in turn:
     // a rotation reads both members of a pair for both results, and in one set
     // every second result would have to be moved.)
-    auto step = [&](uint32_t i, const Cx<T> (&x)[E], Cx<T> (&y)[E]) __attribute__((always_inline)) {
+    auto step = [&](uint32_t i, const Cx<T> (&x)[E], Cx<T> (&y)[E]) __attribute__((always_inline)) -> uint32_t {
         const U4 e = ahead;
+        U4 d = ahead1;
         const uint32_t w = __builtin_amdgcn_readfirstlane(e.x);
-        ahead = lds_u4(ent_at + 16u * (i + 1));
+        if (!AHEAD2) read_ahead(i + 1);
         const uint32_t form = w >> 28;
+        if (AHEAD2) read_ahead(i + (form == kPairForm ? 3u : 1u));
         if (MEAS && form == kRecForm) {
             static_for<0, E>([&](auto rc) { y[decltype(rc)::value] = x[decltype(rc)::value]; });
             bool collapsed = false;
@@ -430,6 +537,27 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
                 }
                 stage_addr<T, LOGT>(lay_at + kLayoutBytes * __builtin_amdgcn_readfirstlane(e.z), tid, addr);
             }
+        } else if (PAIR && form == kPairForm) {
+            U4 d2 = {0, 0, 0, 0};
+            if (!AHEAD2) {
+                d = ahead;
+                d2 = lds_u4(ent_at + 16u * (i + 2));
+                read_ahead(i + 3);
+            }
+            T a0, b0, a1, b1;
+            if constexpr (sizeof(T) == 4) {
+                a0 = __uint_as_float(d.x), b0 = __uint_as_float(d.y);
+                a1 = __uint_as_float(d.z), b1 = __uint_as_float(d.w);
+            } else {
+                auto wide = [](uint32_t lo, uint32_t hi) { return __longlong_as_double(int64_t(uint64_t(lo) | (uint64_t(hi) << 32))); };
+                a0 = wide(d.x, d.y), b0 = wide(d.z, d.w);
+                a1 = wide(d2.x, d2.y), b1 = wide(d2.z, d2.w);
+            }
+            const uint32_t s = uint32_t(__builtin_popcount(uint32_t(tid) & ((w >> 16) & 0xfffu))) << 31;
+            const bool other = (__builtin_popcount(uint32_t(tid) & e.y) & 1) != 0;
+            rotate2_form<T, LR>(x, y, int((w >> 8) & 7u), other ? a1 : a0, flip(other ? b1 : b0, s), differ(a0, a1),
+                                differ(b0, b1), w);
+            return 3;
         } else if (form != kStageForm) {
             const uint32_t s = uint32_t(__builtin_popcount(uint32_t(tid) & ((w >> 16) & 0xfffu))) << 31;
             rotate_form<T, LR>(x, y, int(form), flip(get_t<T>(e), s), w);
@@ -455,26 +583,29 @@ __global__ void __launch_bounds__(1 << LOGT) k_span(Cx<T> *__restrict__ state, u
                 y[r] = L::ld(addr[r]);
             });
         }
+        return 1;
     };
-    uint32_t i = 1;
-    for (; i + 1 < nrun; i += 2) {
+    // (two steps a turn, between the two sets; a loop that leaves in the middle runs
+    // 9-20% longer)
+    const uint32_t nstep = PAIR ? nrun - 2 * sa.pairs : nrun;
+    uint32_t i = 1, c = 1;   // record, step
+    for (; c + 1 < nstep; c += 2) {
         Cx<T> u[E];
-        step(i, v, u);
+        uint32_t used = step(i, v, u);
         if (MEAS && failed) {
             static_for<0, E>([&](auto rc) { v[decltype(rc)::value] = u[decltype(rc)::value]; });
             break;
         }
-        step(i + 1, u, v);
-        if (MEAS && failed) {
-            i++;
-            break;
-        }
+        i += used;
+        used = step(i, u, v);
+        if (MEAS && failed) break;
+        i += used;
     }
-    if (i < nrun && !failed) {
+    if (c < nstep && !failed) {
         Cx<T> u[E];
-        step(i, v, u);
+        const uint32_t used = step(i, v, u);
         static_for<0, E>([&](auto rc) { v[decltype(rc)::value] = u[decltype(rc)::value]; });
-        if (!(MEAS && failed)) i++;
+        if (!(MEAS && failed)) i += used;
     }
     const double scale = scale_of(scaled, MEAS && failed ? i : nrun);
     const T fr = T(scale * sa.phase_re), fi = T(scale * sa.phase_im);
@@ -674,9 +805,9 @@ int expect_t(const void *state, uint64_t sstride, uint32_t nstates, int n, const
     return note_hip(hipGetLastError(), "k_expect launch");
 }
 
-template <typename T, int LOGT, bool WIDE, bool MEAS>
+template <typename T, int LOGT, bool WIDE, bool MEAS, bool PAIR>
 void span_attr() {
-    const void *f = reinterpret_cast<const void *>(&k_span<T, LOGT, WIDE, MEAS>);
+    const void *f = reinterpret_cast<const void *>(&k_span<T, LOGT, WIDE, MEAS, PAIR>);
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(max_lds_bytes()));
     if (e != hipSuccess) note_hip(e, "hipFuncSetAttribute(k_span)");
     hipFuncAttributes fa{};
@@ -684,9 +815,12 @@ void span_attr() {
 }
 template <typename T, int LOGT>
 void span_attrs() {
-    span_attr<T, LOGT, false, false>();
-    span_attr<T, LOGT, true, false>();
-    span_attr<T, LOGT, false, true>();
+    span_attr<T, LOGT, false, false, false>();
+    span_attr<T, LOGT, true, false, false>();
+    span_attr<T, LOGT, false, true, false>();
+    span_attr<T, LOGT, false, false, true>();
+    span_attr<T, LOGT, true, false, true>();
+    span_attr<T, LOGT, false, true, true>();
 }
 
 struct SpanLaunch {
@@ -707,8 +841,12 @@ struct SpanLaunch {
     template <typename T, int LOGT, bool WIDE, bool MEAS>
     void kernel() const {
         const dim3 grid(uint32_t(uint64_t(1) << (sa.n - sa.t)), nstates);
-        hipLaunchKernelGGL((k_span<T, LOGT, WIDE, MEAS>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state, sstride, sa,
-                           ops, ob, oe, (const Cx<T> *)coefs, cb, cstride, ma, flags);
+        if (sa.pairs)
+            hipLaunchKernelGGL((k_span<T, LOGT, WIDE, MEAS, true>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state,
+                               sstride, sa, ops, ob, oe, (const Cx<T> *)coefs, cb, cstride, ma, flags);
+        else
+            hipLaunchKernelGGL((k_span<T, LOGT, WIDE, MEAS, false>), grid, dim3(1 << LOGT), lds, st, (Cx<T> *)state,
+                               sstride, sa, ops, ob, oe, (const Cx<T> *)coefs, cb, cstride, ma, flags);
     }
     template <typename T, int LOGT>
     void tile() const {

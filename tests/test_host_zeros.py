@@ -42,6 +42,13 @@ GADGETS = {
     "cy": ([(W.KIND_X, (B,), ()), (W.KIND_CY, (B, A), ())], 1),
     "cz_between": ([(W.KIND_X, (A,), ()), (W.KIND_CZ, (A, C), ()), (W.KIND_SWAP, (A, B), ())], 0),
     "swap": ([(W.KIND_X, (B,), ()), (W.KIND_SWAP, (A, B), ()), (W.KIND_SX, (C,), ())], 1),
+    # controlled rotations whose control is |0>
+    "crx": ([(W.KIND_CRX, (B, A), (0.7,))], 0),
+    "cry": ([(W.KIND_CRY, (B, A), (-1.9,))], 0),
+    "cry_after_x": ([(W.KIND_X, (A,), ()), (W.KIND_CRY, (B, A), (2.6,))], 1),
+    "crx_many": ([(W.KIND_CRX, (B, A), (0.1 + 0.3 * i,)) for i in range(5)] + [(W.KIND_CRY, (B, A), (0.9,))], 0),
+    "crz_between_h": ([(W.KIND_H, (A,), ()), (W.KIND_CRZ, (B, A), (1.3,)), (W.KIND_H, (A,), ())], 0),
+    "cry_along_a_frame": ([(W.KIND_CX, (C, A), ()), (W.KIND_CRY, (B, A), (0.8,)), (W.KIND_CX, (C, A), ())], 0),
     "rxx_pi": ([(W.KIND_RXX, (A, B), (np.pi,)), (W.KIND_H, (C,), ())], 1),
 }
 
