@@ -624,20 +624,28 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
     };
     std::vector<Pass> passes;
     int rc = QSIM_OK;
+    // for a pass without rotations, where only a permutation or a phase is left
+    auto identity = [] {
+        PauliProgram none;
+        none.ops.push_back(PauliOp{});
+        none.op_epoch.push_back(0);
+        return none;
+    };
     if (whole) {
         plan_whole(n, P, L.n_epochs, pc.low_qubits, kSpanRegs, pc.meta_budget, &passes);
-        if (passes.empty() && !P.map.z.empty()) {
-            // nothing but the frame's permutation: a pass without rotations
-            PauliProgram none;
-            none.ops.push_back(PauliOp{});   // the identity
-            none.op_epoch.push_back(0);
-            plan_whole(n, none, 0, pc.low_qubits, kSpanRegs, pc.meta_budget, &passes);
-            for (SpanStage &st : passes[0].stages) st.ops.clear();
+        if (passes.empty() && (!P.map.z.empty() || !phased)) {
+            plan_whole(n, identity(), 0, pc.low_qubits, kSpanRegs, pc.meta_budget, &passes);
+            passes[0].stages[0].ops.clear();
         }
         for (size_t i = 0; i < passes.size() && !rc; i++) rc = put(passes[i], i + 1 == passes.size());
         if (!rc) rc = put_left(L.n_epochs);   // (follows every record)
     } else {
         size_t at = 0, m = 0;
+        if (P.ops.empty() && !phased) {
+            plan_spans(n, identity(), t, pc.low_qubits, kSpanRegs, pc.meta_budget, pc.window, false, 0, 1, &passes);
+            passes[0].stages[0].ops.clear();
+            rc = put(passes[0], false);
+        }
         for (int e = 0; e < L.n_epochs && !rc; e++) {
             size_t end = at;
             while (end < P.ops.size() && P.op_epoch[end] == e) end++;

@@ -38,9 +38,7 @@ int bind_layout(Compiled *c, std::vector<qk::BindEntry> *ents, size_t *ncoef, ui
         // (the first word of a stage, a layout or a measurement record of a span
         // pass is not the place of its coefficients, which follow the last ones)
         e.tmpl_off = devop_has_place(o.kind) ? o.coef : uint32_t(at);
-        e.np = p.op_np[j];
-        if (e.np == 1 && o.kind == DEVOP_PAULI) e.np = -1;
-        if (e.np == 1 && o.kind == DEVOP_PAULI2) e.np = -2;
+        e.np = o.kind == DEVOP_PAULI && p.op_np[j] == 1 ? -1 : p.op_np[j];
         for (int s = 0; s < 3; s++) e.slot[s] = p.op_slots[3 * j + s];
         ents->push_back(e);
         *max_count = std::max(*max_count, count);

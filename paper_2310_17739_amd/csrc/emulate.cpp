@@ -326,13 +326,6 @@ void bind_coefs(Compiled *c, const std::vector<qk::BindEntry> &ents, const doubl
     std::vector<cd> out(ncoef);
     const std::vector<cd> &tmpl = c->plan.coefs;
     for (const qk::BindEntry &e : ents) {
-        if (e.np == -2) {
-            const double u = tmpl[e.tmpl_off].real() * (0.5 * params[e.slot[0]]);
-            const double w = tmpl[e.tmpl_off].imag() * (0.5 * params[e.slot[1]]);
-            out[e.bound_off] = cd(std::cos(u + w), std::sin(u + w));
-            out[e.bound_off + 1] = cd(std::cos(u - w), std::sin(u - w));
-            continue;
-        }
         if (e.np < 0) {
             const double th = params[e.slot[0]];
             const double s = tmpl[e.tmpl_off].real() * std::sin(0.5 * th);

@@ -68,12 +68,12 @@ struct Lowered {
 // commutes with P.  On amplitudes i and i ^ x both turn the same way, so this is
 // one rotation by phi + phi2 or by their difference, as the parity of i with
 // z ^ z2 says; where that is 0, as for a control that is |0>, it is the identity
-// to the last bit.
+// to the last bit.  (z2 = z and phi2 = 0: a half turn, which moves amplitudes.)
 struct PauliOp {
     uint64_t x = 0, z = 0, z2 = 0;
     double phi = 0.0, phi2 = 0.0;
-    double sign = 1.0, sign2 = 1.0;
-    int32_t slot = -1, slot2 = -1;
+    double sign = 1.0;   // (1 for an angle known here)
+    int32_t slot = -1;
     bool two = false;
     int entries() const { return two ? 3 : 1; }   // records of a span pass
 };

@@ -1410,15 +1410,6 @@ __global__ void __launch_bounds__(NT) k_bind(const double *__restrict__ tmpl,
     for (uint64_t idx = uint64_t(blockIdx.y) * NT + threadIdx.x; idx < total;
          idx += uint64_t(gridDim.y) * NT) {
         const uint32_t b = uint32_t(idx / e.count), c = uint32_t(idx % e.count);
-        if (e.np == -2) {
-            // a rotation of two angles: their sum for one branch, their difference
-            // for the other (equal angles leave exactly the identity)
-            const double u = tmpl[2 * size_t(e.tmpl_off)] * (0.5 * params[size_t(b) * nparams + e.slot[0]]);
-            const double w = tmpl[2 * size_t(e.tmpl_off) + 1] * (0.5 * params[size_t(b) * nparams + e.slot[1]]);
-            const double angle = c == 0 ? u + w : u - w;
-            out[size_t(b) * cstride + e.bound_off + c] = Cx<T>{T(cos(angle)), T(sin(angle))};
-            continue;
-        }
         if (e.np < 0) {
             // a rotation's two coefficients (the host's pauli_coefs)
             const double th = params[size_t(b) * nparams + e.slot[0]];

@@ -203,7 +203,7 @@ struct BindEntry {
     uint32_t count;       // coefficients of the operator (terms * 2^k)
     uint32_t tmpl_off;    // offset of block 0 in the FP64 template (complex elements)
     int32_t np;           // angle slots (0..3); -1: a rotation of angle slot[0], the sign of its
-                          // t in block 0; -2: of the angles slot[0] and slot[1], both signs there
+                          // t in block 0
     int32_t slot[3];
     int32_t pad;
 };

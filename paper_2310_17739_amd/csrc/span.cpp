@@ -56,10 +56,181 @@ Pauli mul(const Pauli &a, const Pauli &b) {
 bool anticommute(uint64_t ax, uint64_t az, uint64_t bx, uint64_t bz) {
     return __builtin_popcountll((ax & bz) ^ (az & bx)) & 1;
 }
+// The sign of -i (-i)^|x & z|, whose other part is 1 or i.
+double kappa(uint64_t x, uint64_t z) { return (__builtin_popcountll(x & z) & 2) ? 1.0 : -1.0; }
+// Whether exp(-i phi P) is a sign: phi a multiple of pi (sin phi <= kTrivial).
+bool half_turns(double phi) {
+    const double a = std::fabs(phi);
+    return a < 3.0 ? a <= kTrivial : std::fabs(std::sin(phi)) <= kTrivial;
+}
 // Whether a rotation does not commute with the string (x, z).
 bool clash(const PauliOp &o, uint64_t x, uint64_t z) {
     return anticommute(x, z, o.x, o.z) || (o.two && anticommute(x, z, o.x, o.z2));
 }
+
+// The rotations of one epoch as a circuit is lowered.  Rotations about the same
+// string add up past others that both commute with: what undoes each other leaves
+// nothing, as products of matrices would, where one after the other they leave
+// rounding errors.  Two strings of the same X mask whose angles cancel on half of
+// the index space become one rotation of two angles.  `last` finds, by X mask (by
+// string for a diagonal), the latest rotation; `prev` the one before.
+class Rotations {
+public:
+    Rotations(PauliProgram *out, size_t most) : P(out), table(64) {
+        dead.reserve(most);
+        prev.reserve(most);
+    }
+
+    void add(PauliOp o, int epoch) {
+        int pair = -1;
+        if (o.slot < 0) {
+            if (settle(&o)) return;
+            const int at = find(o.x, o.z, o.phi, epoch, &pair);
+            if (at >= 0) return merge(at, o.z, o.phi);
+            if (pair >= 0) {
+                PauliOp &c = P->ops[size_t(pair)];
+                c.two = true;
+                c.z2 = o.z;
+                c.phi2 = o.phi;
+                return;
+            }
+        }
+        append(o, epoch);
+    }
+    // the commuting strings (x, z), (x, z2): as one, unless one of them adds to an
+    // earlier rotation
+    void add_pair(const PauliOp &o, int epoch) {
+        PauliOp a = o, b = o;
+        if (settle(&a)) return;
+        if (!a.two) return add(a, epoch);
+        a.two = b.two = false;
+        b.z = o.z2;
+        b.phi = o.phi2;
+        const int at = find(o.x, o.z, o.phi, epoch, nullptr);
+        const int at2 = at < 0 ? find(o.x, o.z2, o.phi2, epoch, nullptr) : -1;
+        if (at >= 0) {
+            merge(at, o.z, o.phi);
+            add(b, epoch);
+        } else if (at2 >= 0) {
+            merge(at2, o.z2, o.phi2);
+            add(a, epoch);
+        } else {
+            append(o, epoch);
+        }
+    }
+    // takes out what has cancelled; half turns in their exact form
+    void finish() {
+        size_t n = 0;
+        for (size_t i = 0; i < P->ops.size(); i++) {
+            if (dead[i]) continue;
+            PauliOp &o = P->ops[i];
+            // (a half turn is at least pi/2 - 1e-14 away from 0)
+            if (std::fabs(o.phi) > 1.5 && o.x && !o.two && o.slot < 0 && std::fabs(std::cos(o.phi)) <= kTrivial) {
+                o.two = true;
+                o.z2 = o.z;
+                o.phi2 = 0.0;
+            }
+            if (n != i) {
+                P->ops[n] = o;
+                P->op_epoch[n] = P->op_epoch[i];
+            }
+            n++;
+        }
+        P->ops.resize(n);
+        P->op_epoch.resize(n);
+    }
+
+private:
+    PauliProgram *P;
+    std::vector<char> dead;
+    std::vector<int> prev;
+    struct Entry {
+        uint64_t key = 0;
+        int head = -1, epoch = -1;
+    };
+    std::vector<Entry> table;   // open addressing; entries of another epoch are free
+    size_t used = 0;
+    int used_epoch = -1;
+
+    static uint64_t key(uint64_t x, uint64_t z) { return x ? x : z | uint64_t(1) << 63; }
+    size_t place(uint64_t k, int epoch) const {
+        const size_t m = table.size() - 1;
+        size_t i = size_t((k * 0x9e3779b97f4a7c15ull) >> 32) & m;
+        while (table[i].epoch == epoch && table[i].key != k) i = (i + 1) & m;
+        return i;
+    }
+    void append(const PauliOp &o, int epoch) {
+        if (epoch != used_epoch) {
+            used_epoch = epoch;
+            used = 0;
+        }
+        if (2 * (used + 1) > table.size()) {
+            std::vector<Entry> old(4 * table.size());
+            old.swap(table);
+            for (const Entry &e : old)
+                if (e.epoch == epoch) table[place(e.key, epoch)] = e;
+        }
+        Entry &e = table[place(key(o.x, o.z), epoch)];
+        const bool known = e.epoch == epoch;
+        used += known ? 0 : 1;
+        prev.push_back(known ? e.head : -1);
+        e = Entry{key(o.x, o.z), int(P->ops.size()), epoch};
+        dead.push_back(0);
+        P->ops.push_back(o);
+        P->op_epoch.push_back(epoch);
+    }
+    // The rotation that one by phi about (x, z) adds to, if any; else *pair: one that
+    // makes a rotation of two angles with it.  The search ends at a rotation that does
+    // not commute with the string, and after kFar of those that do.
+    int find(uint64_t x, uint64_t z, double phi, int epoch, int *pair) const {
+        const Entry &e = table[place(key(x, z), epoch)];
+        if (e.epoch != epoch) return -1;
+        int from = int(P->ops.size());
+        for (int c = e.head; c >= 0 && int(P->ops.size()) - c <= kFar; c = prev[size_t(c)]) {
+            for (int k = from - 1; k > c; k--)
+                if (!dead[size_t(k)] && clash(P->ops[size_t(k)], x, z)) return -1;
+            from = c;
+            if (dead[size_t(c)]) continue;
+            const PauliOp &o = P->ops[size_t(c)];
+            if (o.slot < 0 && (o.z == z || (o.two && o.z2 == z))) return c;
+            if (clash(o, x, z)) return -1;
+            if (pair && *pair < 0 && x && o.slot < 0 && !o.two) {
+                const double a = kappa(x, o.z) * o.phi, b = kappa(x, z) * phi;
+                if (half_turns(a + b) || half_turns(a - b)) *pair = c;
+            }
+        }
+        return -1;
+    }
+    // Whether the rotation is none (a multiple of a half turn about its string: a sign).
+    bool settle(PauliOp *o) {
+        auto none = [&](double phi) {
+            if (o->x ? !half_turns(phi) : phi != 0.0) return false;
+            if (std::cos(phi) < 0.0) P->phase += M_PI;
+            return true;
+        };
+        if (o->two && none(o->phi2)) o->two = false;
+        if (!none(o->phi)) return false;
+        if (!o->two) return true;
+        o->z = o->z2;
+        o->phi = o->phi2;
+        o->two = false;
+        return false;
+    }
+    void merge(int at, uint64_t z, double phi) {
+        PauliOp &c = P->ops[size_t(at)];
+        (c.z == z ? c.phi : c.phi2) += phi;
+        if (settle(&c)) dead[size_t(at)] = 1;
+        while (!dead.empty() && dead.back()) {
+            const PauliOp &o = P->ops.back();
+            table[place(key(o.x, o.z), P->op_epoch.back())].head = prev.back();
+            P->ops.pop_back();
+            P->op_epoch.pop_back();
+            dead.pop_back();
+            prev.pop_back();
+        }
+    }
+    static constexpr int kFar = 4096;
+};
 
 // A string on up to two qubits, as gates name it.
 struct Axis {
@@ -181,28 +352,35 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
     int epoch = 0;
     out->ops.reserve(op_gate.size() / 4 + 16);
     // a rotation exp(-i phi P) about an axis seen through the frame
+    Rotations rots(out, op_gate.size() / 4 + 16);
+    size_t emitted = 0;
     auto emit = [&](const Pauli &p, double phi, int slot) {
         PauliOp o;
         o.x = p.x;
         o.z = p.z;
-        o.sign = (p.k & 2) ? -1.0 : 1.0;
-        o.phi = phi;
         o.slot = slot;
-        out->ops.push_back(o);
-        out->op_epoch.push_back(epoch);
+        const double sign = (p.k & 2) ? -1.0 : 1.0;
+        if (slot < 0) o.phi = sign * phi;
+        else o.sign = sign;
+        rots.add(o, epoch);
+        emitted++;
     };
     // rotations about two axes of commuting strings, as one where their X masks agree
     auto emit_pair = [&](const Pauli &p, double phi, const Pauli &p2, double phi2) {
-        emit(p, phi, -1);
         if (p.x != p2.x || !p.x) {
+            emit(p, phi, -1);
             emit(p2, phi2, -1);
             return;
         }
-        PauliOp &o = out->ops.back();
+        PauliOp o;
+        o.x = p.x;
+        o.z = p.z;
+        o.phi = (p.k & 2) ? -phi : phi;
         o.two = true;
         o.z2 = p2.z;
-        o.sign2 = (p2.k & 2) ? -1.0 : 1.0;
-        o.phi2 = phi2;
+        o.phi2 = (p2.k & 2) ? -phi2 : phi2;
+        rots.add_pair(o, epoch);
+        emitted += 2;
     };
     auto one = [](char l, int q) { return Axis{{l, 'I'}, {q, -1}, 1}; };
     auto two = [](char a, int qa, char b, int qb) { return Axis{{a, b}, {qa, qb}, 2}; };
@@ -387,9 +565,10 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
         else epoch = L.n_epochs;   // what is left follows every record
     }
     flush();
+    rots.finish();
     // with many gates left in the frame, the fused operators of the matrix
     // lowering do less
-    return 3 * extra <= out->ops.size();
+    return 3 * extra <= emitted;
 }
 
 // -------------------------------------------------------------- planning
@@ -780,8 +959,6 @@ int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, 
             d.kind = DEVOP_PAULI;
             d.coef = uint32_t(out->coefs.size());
             if (!string_record(o.x, o.z, V, t, regs, &d)) return QSIM_E_ARG;
-            // (kappa of a string, see below)
-            auto kappa_of = [&](uint64_t z) { return (__builtin_popcountll(o.x & z) & 2) ? 1.0 : -1.0; };
             if (o.two) {
                 DevOp w{};
                 if (!o.x || __builtin_popcountll(o.x & (o.z ^ o.z2)) & 1) return QSIM_E_ARG;
@@ -790,16 +967,11 @@ int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, 
                 w.kind = DEVOP_PAULI2X;
                 w.k = 0;
                 out->ops.push_back(d);
-                const double s1 = kappa_of(o.z) * o.sign, s2 = kappa_of(o.z2) * o.sign2;
-                if (o.slot >= 0) {
-                    out->coefs.push_back(cd(s1, s2));
-                    for (int j = 0; j < 3; j++) out->coefs.push_back(cd(0.0, 0.0));
-                } else {
-                    out->coefs.push_back(branch_coefs(s1 * o.phi + s2 * o.phi2));
-                    out->coefs.push_back(branch_coefs(s1 * o.phi - s2 * o.phi2));
-                }
-                out->op_np.push_back(o.slot >= 0 ? 1 : 0);
-                for (int32_t slot : {o.slot, o.slot2, -1}) out->op_slots.push_back(slot);
+                const double a1 = kappa(o.x, o.z) * o.phi, a2 = kappa(o.x, o.z2) * o.phi2;
+                out->coefs.push_back(branch_coefs(a1 + a2));
+                out->coefs.push_back(branch_coefs(a1 - a2));
+                out->op_np.push_back(0);
+                for (int j = 0; j < 3; j++) out->op_slots.push_back(-1);
                 for (int j = 0; j < 2; j++) {
                     out->ops.push_back(w);
                     dummy();
@@ -808,18 +980,18 @@ int pack_span_pass(const PauliProgram &P, const Pass &p, int regs, bool single, 
                 continue;
             }
             // y[i] = a x[i] + b (-1)^(i . z) x[i ^ x] with a = cos phi and
-            // b = -i sin phi (-i)^ny: t is its real or imaginary part
-            const double kappa = kappa_of(o.z);
+            // b = -i sin phi (-i)^ny, ny = |x & z|: t is its real or imaginary part
+            const double k = kappa(o.x, o.z) * o.sign;
             out->ops.push_back(d);
             if (o.slot >= 0) {
                 // bound per state: the sign of t (four entries of template)
-                out->coefs.push_back(cd(kappa * o.sign, 0.0));
+                out->coefs.push_back(cd(k, 0.0));
                 for (int j = 0; j < 3; j++) out->coefs.push_back(cd(0.0, 0.0));
                 out->op_np.push_back(1);
                 out->op_slots.push_back(o.slot);
             } else {
                 cd e[2];
-                pauli_coefs(std::cos(o.phi), kappa * o.sign * std::sin(o.phi), single, e);
+                pauli_coefs(std::cos(o.phi), k * std::sin(o.phi), single, e);
                 grown += 0.5 * std::log2(1.0 + e[1].imag() * e[1].imag());
                 if (grown > kGrownMost[single]) {
                     e[1] = cd(1.0, e[1].imag());
