@@ -603,7 +603,6 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
                 phased = true;
             }
         }
-        if (p.span && getenv("DBG")) { int nr=0; for (auto &st: p.stages) nr+=int(st.ops.size()); fprintf(stderr,"pass stages %zu ops %d pairs %u records %u\n", p.stages.size(), nr, pi.sa.pairs, pi.sa.nrun);}
         out->passes.push_back(pi);
         return QSIM_OK;
     };
