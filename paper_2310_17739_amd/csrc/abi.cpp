@@ -680,14 +680,58 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
     return QSIM_OK;
 }
 
+// Modelled run time of a plan, in the time of a rotation in k_span.  Fitted to 12
+// families of circuits (QFT, layers of rotations, Trotter steps, QAOA, random
+// rotations, Pauli exponentials) at 10 to 30 qubits in both types, single states:
+// within 10% of most times, 25% of all; taking the cheaper plan by it costs 1% of
+// the better one's time on average, 23% at worst (53 us for 44).
+static double plan_cost(const Compiled &c, int dtype) {
+    const bool single = dtype == QSIM_C64;
+    double cost = 0.0;
+    for (size_t i = 0; i < c.passes.size(); i++) {
+        if (c.passes[i].kind == Pass::MEASURE) continue;   // the same in every plan
+        // (the passes of gates left in the frame as those of rotations)
+        cost += c.pauli ? (single ? 26.0 : 32.0) : (single ? 14.0 : 18.0);
+        for (uint32_t j = c.plan.pass_begin[i]; j < c.plan.pass_begin[i + 1]; j++) {
+            const DevOp &o = c.plan.ops[j];
+            if (o.kind == DEVOP_STAGE) cost += 1.5;
+            else if (o.kind == DEVOP_PAULI) cost += 1.0;
+            else if (o.kind == DEVOP_PAULI2) cost += 2.0;
+            else if (o.kind == DEVOP_MAT && !c.pauli)
+                cost += (single ? 4.0 : 5.5) + (single ? 0.7 : 1.1) * __builtin_popcount(o.present);
+        }
+    }
+    return cost;
+}
+
+// Whether the tiled plan of a circuit is worth the compile beside its span passes.
+// Fused operators gain where gates share qubits and each is a rotation of its own:
+// Pauli exponentials written with CX are a rotation per 3 gates and more.  A
+// circuit that runs once saves less than half of its span passes' time, about a
+// fifth where it saves any, for at least 100 us + 1.5 us a gate of compile time; a
+// rotation takes 0.3 us, and beyond 16 MiB about 8 ns per MiB of the state.
+// QSIM_SPAN=2 takes span passes wherever they are possible.
+static bool spans_may_lose(int n, int dtype, const PauliProgram &P, const Lowered &L, const PlanConfig &pc, Spans spans,
+                           const Compiled &c) {
+    if (env_int("QSIM_SPAN", 1) >= 2) return false;
+    size_t rots = 0;
+    for (const PauliOp &o : P.ops) rots += o.two ? 2 : 1;
+    if (double(rots) <= 0.35 * double(L.input_gates)) return false;
+    if (spans == Spans::ONCE) {
+        const double us = plan_cost(c, dtype) * (0.3 + 8e-9 * std::ldexp(double(elem_bytes(dtype)), n));
+        return us > 3.0 * (100.0 + 1.5 * double(L.input_gates));
+    }
+    return true;
+}
+
 int compile_circuit(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
-                    const qsim_fuse_opts *opt, Compiled *out) {
-    return compile_program(n, dtype, g, ng, in, false, false, 0, opt, out);
+                    const qsim_fuse_opts *opt, Spans spans, Compiled *out) {
+    return compile_program(n, dtype, g, ng, in, false, false, 0, opt, spans, out);
 }
 
 int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
                     bool keep_params, bool allow_meas, int max_params,
-                    const qsim_fuse_opts *opt, Compiled *out) {
+                    const qsim_fuse_opts *opt, Spans spans, Compiled *out) {
     TraceRange range("qsim.compile");
     double t0 = now_seconds();
     if (alloc_fault()) throw std::bad_alloc();
@@ -697,22 +741,27 @@ int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
     fc.max_params = keep_params ? std::max(1, std::min(max_params, 3)) : 0;
     Lowered L;
     int rc;
+    Compiled rotations;   // the plan of span passes, if there is one
     {
         TraceRange r("qsim.lower");
         std::vector<size_t> op_gate;
         size_t first_at;
         split_records(n, g, ng, allow_meas, &L, &op_gate, &rc, &first_at);
-        if (!rc && spans_wanted(n, fc, pc)) {
+        if (!rc && spans != Spans::OFF && spans_wanted(n, fc, pc)) {
             PauliProgram P;
             bool fits = pauli_lower(n, g, op_gate, L, in, keep_params, pc.tile_qubits == n, &P);
             if (pc.full_support)
                 for (const PauliOp &o : P.ops)
                     fits = fits && __builtin_popcountll(o.x | o.z | o.z2) <= pc.tile_qubits - pc.low_qubits;
             if (fits) {
-                rc = compile_spans(n, dtype, P, L, fc, pc, out);
-                out->stats.max_width = fc.max_width;
-                out->stats.compile_seconds = now_seconds() - t0;
-                return rc || keep_params ? rc : validate_plan(n, dtype, *out);
+                rc = compile_spans(n, dtype, P, L, fc, pc, &rotations);
+                if (rc) return rc;
+                rotations.stats.max_width = fc.max_width;
+                if (!spans_may_lose(n, dtype, P, L, pc, spans, rotations)) {
+                    *out = std::move(rotations);
+                    out->stats.compile_seconds = now_seconds() - t0;
+                    return keep_params ? QSIM_OK : validate_plan(n, dtype, *out);
+                }
             }
         }
         rc = lower_gates(n, g, ng, in, keep_params, op_gate, rc, first_at, &L);
@@ -720,6 +769,7 @@ int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
     if (rc) return rc;
     rc = compile_ops(n, dtype, &L, fc, pc, out);
     if (rc) return rc;
+    if (rotations.pauli && plan_cost(rotations, dtype) < plan_cost(*out, dtype)) *out = std::move(rotations);
     qsim_apply_stats &s = out->stats;
     s.compile_seconds = now_seconds() - t0;
     // parameterised templates are validated after their coefficient layout
@@ -1038,7 +1088,7 @@ int qsim_apply(qsim_h h, const qsim_gate *g, size_t ng, const double *mats, size
     Compiled c;
     int rc;
     try {
-        rc = compile_circuit(h->n, h->dtype, g, ng, GateInputs{mats, n_mats, params, n_params}, opt, &c);
+        rc = compile_circuit(h->n, h->dtype, g, ng, GateInputs{mats, n_mats, params, n_params}, opt, Spans::ONCE, &c);
     } catch (const std::bad_alloc &) {
         return QSIM_E_NOMEM;
     }
@@ -1063,7 +1113,7 @@ int qsim_compile(int n, int dtype, const qsim_gate *g, size_t ng, const double *
     p->n = n;
     p->dtype = dtype;
     try {
-        rc = compile_circuit(n, dtype, g, ng, GateInputs{mats, n_mats, params, n_params}, opt, &p->c);
+        rc = compile_circuit(n, dtype, g, ng, GateInputs{mats, n_mats, params, n_params}, opt, Spans::REPLAY, &p->c);
     } catch (const std::bad_alloc &) {
         rc = QSIM_E_NOMEM;
     }
@@ -1407,7 +1457,7 @@ int qsim_autotune(qsim_h h, const qsim_gate *g, size_t ng, const double *mats, s
     for (const qsim_fuse_opts &o : cands) {
         Compiled c;
         try {
-            rc = compile_circuit(h->n, h->dtype, g, np, GateInputs{mats, n_mats, params, n_params}, &o, &c);
+            rc = compile_circuit(h->n, h->dtype, g, np, GateInputs{mats, n_mats, params, n_params}, &o, Spans::REPLAY, &c);
         } catch (const std::bad_alloc &) {
             rc = QSIM_E_NOMEM;
         }
@@ -1466,7 +1516,7 @@ int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs
         o.max_width = w;
         Compiled c;
         try {
-            rc = compile_circuit(n, dtype, g, ng, in, &o, &c);
+            rc = compile_circuit(n, dtype, g, ng, in, &o, Spans::REPLAY, &c);
         } catch (const std::bad_alloc &) {
             rc = QSIM_E_NOMEM;
         }
@@ -1531,7 +1581,7 @@ int tune_tile_batch(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
         o.tile_qubits = t;
         Compiled c;
         try {
-            rc = compile_circuit(n, dtype, g, ng, in, &o, &c);
+            rc = compile_circuit(n, dtype, g, ng, in, &o, Spans::REPLAY, &c);
         } catch (const std::bad_alloc &) {
             rc = QSIM_E_NOMEM;
         }
@@ -1639,7 +1689,7 @@ int qsim_debug_plan(int n, int dtype, const qsim_gate *g, size_t ng, const doubl
     Compiled c;
     int rc;
     try {
-        rc = compile_circuit(n, dtype, g, ng, GateInputs{mats, n_mats, params, n_params}, opt, &c);
+        rc = compile_circuit(n, dtype, g, ng, GateInputs{mats, n_mats, params, n_params}, opt, Spans::ONCE, &c);
     } catch (const std::bad_alloc &) {
         return QSIM_E_NOMEM;
     }

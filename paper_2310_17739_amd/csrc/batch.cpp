@@ -222,7 +222,7 @@ int setup_group(Group &G, const qsim_batch_group &in, int dtype, const qsim_batc
                              GateInputs{in.mats, in.mats ? in.n_mats : 0, nullptr,
                                         param ? size_t(in.n_params) : 0},
                              param, true,
-                             opt.max_params > 0 ? opt.max_params : 2, fo, &G.c);
+                             opt.max_params > 0 ? opt.max_params : 2, fo, Spans::REPLAY, &G.c);
     if (rc) return rc;
     // every parameter slot and measurement slot must be inside its vector
     for (size_t i = 0; i < in.ng; i++) {

@@ -360,7 +360,7 @@ int qsim_debug_emulate(int n, int dtype, const qsim_gate *g, size_t ng, const do
     if (n < 1 || n > 24 || (dtype != QSIM_C64 && dtype != QSIM_C128) || (ng && !g) || !psi) return QSIM_E_ARG;
     try {
         Compiled c;
-        const int rc = compile_circuit(n, dtype, g, ng, GateInputs{mats, n_mats, params, n_params}, opt, &c);
+        const int rc = compile_circuit(n, dtype, g, ng, GateInputs{mats, n_mats, params, n_params}, opt, Spans::ONCE, &c);
         return rc ? rc : emulate(n, c, reinterpret_cast<cd *>(psi), nullptr);
     } catch (const std::bad_alloc &) {
         return QSIM_E_NOMEM;
@@ -382,7 +382,7 @@ int qsim_debug_emulate_batch(int n, int dtype, const qsim_gate *g, size_t ng, co
         Compiled c;
         const bool param = params && n_params;
         int rc = compile_program(n, dtype, g, ng, GateInputs{mats, n_mats, nullptr, param ? n_params : 0}, param, true,
-                                 max_params > 0 ? max_params : 2, opt, &c);
+                                 max_params > 0 ? max_params : 2, opt, Spans::REPLAY, &c);
         if (rc) return rc;
         std::vector<qk::BindEntry> ents;
         size_t ncoef = c.plan.coefs.size();

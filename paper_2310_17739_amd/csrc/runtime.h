@@ -50,14 +50,19 @@ int resident_max(int dtype);
 // (QSIM_TILE_QUBITS overrides it).
 int default_tile_qubits(int n, int dtype, uint64_t nstates);
 void default_configs(int n, int dtype, const qsim_fuse_opts *opt, FuseConfig *fc, PlanConfig *pc);
+// Whether a circuit that lowers to rotations runs as span passes: never, or
+// where they are modelled to be cheaper than the tiled passes of its fused
+// operators; of a circuit that runs once, only where that can repay compiling it
+// twice.
+enum class Spans { OFF, ONCE, REPLAY };
 int compile_circuit(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
-                    const qsim_fuse_opts *opt, Compiled *out);
+                    const qsim_fuse_opts *opt, Spans spans, Compiled *out);
 // General form: keep_params keeps slot >= 0 angles symbolic (cos/sin basis
 // blocks, at most max_params per fused operator); allow_meas accepts
 // MEASURE / ASSERT0 / RESET records.
 int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
                     bool keep_params, bool allow_meas, int max_params,
-                    const qsim_fuse_opts *opt, Compiled *out);
+                    const qsim_fuse_opts *opt, Spans spans, Compiled *out);
 int validate_plan(int n, int dtype, const Compiled &c);
 // Time fusion widths 2..5 (complex128: 2..4) for this circuit on a scratch
 // state of width n (allocated and freed here), each compiled with `base`

@@ -198,7 +198,7 @@ void worker_loop(qsim_server *s) {
             rc = compile_circuit(r->n, s->opt.dtype, r->g.data(), r->g.size(),
                                  GateInputs{r->mats.empty() ? nullptr : r->mats.data(),
                                             r->mats.size() / 2, nullptr, 0},
-                                 fo, &r->c);
+                                 fo, Spans::ONCE, &r->c);
             if (!rc && !r->terms.empty() &&
                 !plan_expect(r->n, s->opt.dtype == QSIM_C64 ? 4 : 3, r->terms.data(), r->terms.size(), &r->expect))
                 r->expect = ExpectPlan{};

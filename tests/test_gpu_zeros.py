@@ -21,7 +21,8 @@ def Q():
 @pytest.mark.parametrize("dtype,n,tile", [("complex128", 10, None), ("complex64", 14, None), ("complex128", 15, 11),
                                           ("complex64", 16, 12)])
 @pytest.mark.parametrize("name", sorted(GADGETS))
-def test_definite_qubits(Q, dtype, n, tile, name):
+def test_definite_qubits(Q, dtype, n, tile, name, monkeypatch):
+    monkeypatch.setenv("QSIM_SPAN", "2")   # span passes whatever they cost
     recs, value = GADGETS[name]
     head = surroundings(n, 1, 2) + list(recs)
     g = W.gates(head)
