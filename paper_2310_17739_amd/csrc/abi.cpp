@@ -1494,7 +1494,7 @@ int qsim_autotune(qsim_h h, const qsim_gate *g, size_t ng, const double *mats, s
 namespace qs {
 
 int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
-               const qsim_fuse_opts *base, int *best_w, double *best_ns) {
+               const qsim_fuse_opts *base, Spans spans, int *best_w, double *best_ns) {
     const int wmax = dtype == QSIM_C64 ? 5 : 4;
     const size_t bytes = elem_bytes(dtype) << n;
     void *buf = nullptr;
@@ -1516,7 +1516,7 @@ int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs
         o.max_width = w;
         Compiled c;
         try {
-            rc = compile_circuit(n, dtype, g, ng, in, &o, Spans::REPLAY, &c);
+            rc = compile_circuit(n, dtype, g, ng, in, &o, spans, &c);
         } catch (const std::bad_alloc &) {
             rc = QSIM_E_NOMEM;
         }
@@ -1556,7 +1556,7 @@ int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs
 }
 
 int tune_tile_batch(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
-                    const qsim_fuse_opts &base, uint32_t nstates, int *best_t) {
+                    const qsim_fuse_opts &base, Spans spans, uint32_t nstates, int *best_t) {
     *best_t = base.tile_qubits;
     if (n <= resident_max(dtype) || nstates == 0) return QSIM_OK;
     // enough states for 4,096 12-qubit tiles (16 per CU), within 1 GiB
@@ -1581,7 +1581,7 @@ int tune_tile_batch(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
         o.tile_qubits = t;
         Compiled c;
         try {
-            rc = compile_circuit(n, dtype, g, ng, in, &o, Spans::REPLAY, &c);
+            rc = compile_circuit(n, dtype, g, ng, in, &o, spans, &c);
         } catch (const std::bad_alloc &) {
             rc = QSIM_E_NOMEM;
         }

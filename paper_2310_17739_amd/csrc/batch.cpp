@@ -183,12 +183,22 @@ int setup_group(Group &G, const qsim_batch_group &in, int dtype, const qsim_batc
     if (base.tile_qubits <= 0) base.tile_qubits = default_tile_qubits(in.n, dtype, uint64_t(in.n_states));
     const qsim_fuse_opts *fo = &base;
     qsim_fuse_opts tuned{};
+    const auto compile = [&](const qsim_fuse_opts *o) {
+        return compile_program(in.n, dtype, in.g, in.ng,
+                               GateInputs{in.mats, in.mats ? in.n_mats : 0, nullptr, param ? size_t(in.n_params) : 0},
+                               param, true, opt.max_params > 0 ? opt.max_params : 2, o, Spans::REPLAY, &G.c);
+    };
+    int rc = compile(fo);
+    if (rc) return rc;
     if (opt.autotune) {
         // the template's fusion width, timed on its first instance (angles of
         // state 0 bound on the host), then (unless `opt.fuse` fixes it) its
         // tile width, timed over a sample of states run together as the batch
         // runs them; measurement records are left out of the timed circuit,
-        // and the low-qubit choice stays that of `opt.fuse`
+        // and the low-qubit choice stays that of `opt.fuse`.  The timed circuit
+        // may lower to rotations where the program does not (records keep its
+        // frame from cancelling): it runs as the program does.
+        const Spans spans = G.c.pauli ? Spans::REPLAY : Spans::OFF;
         std::vector<qsim_gate> timed;
         timed.reserve(in.ng);
         for (size_t i = 0; i < in.ng; i++)
@@ -197,33 +207,25 @@ int setup_group(Group &G, const qsim_batch_group &in, int dtype, const qsim_batc
         int w = 0;
         double ns = 0.0;
         const double t0 = now_seconds();
-        int rc = tune_width(in.n, dtype, timed.data(), timed.size(),
-                            GateInputs{in.mats, in.mats ? in.n_mats : 0, param ? in.params : nullptr,
-                                       param ? size_t(in.n_params) : 0},
-                            fo, &w, &ns);
+        const GateInputs bound{in.mats, in.mats ? in.n_mats : 0, param ? in.params : nullptr,
+                               param ? size_t(in.n_params) : 0};
+        rc = tune_width(in.n, dtype, timed.data(), timed.size(), bound, fo, spans, &w, &ns);
         if (rc) return rc;
         tuned = *fo;
         tuned.level = 5;
         tuned.max_width = w;
         if (!(opt.fuse.level > 0 && opt.fuse.tile_qubits > 0) && !std::getenv("QSIM_TILE_QUBITS")) {
             int t = tuned.tile_qubits;
-            rc = tune_tile_batch(in.n, dtype, timed.data(), timed.size(),
-                                 GateInputs{in.mats, in.mats ? in.n_mats : 0, param ? in.params : nullptr,
-                                            param ? size_t(in.n_params) : 0},
-                                 tuned, uint32_t(in.n_states), &t);
+            rc = tune_tile_batch(in.n, dtype, timed.data(), timed.size(), bound, tuned, spans, uint32_t(in.n_states), &t);
             if (rc) return rc;
             tuned.tile_qubits = t;
         }
         G.tune_seconds = now_seconds() - t0;
-        fo = &tuned;
         G.tuned_width = w;
+        G.c = Compiled{};
+        rc = compile(&tuned);
+        if (rc) return rc;
     }
-    int rc = compile_program(in.n, dtype, in.g, in.ng,
-                             GateInputs{in.mats, in.mats ? in.n_mats : 0, nullptr,
-                                        param ? size_t(in.n_params) : 0},
-                             param, true,
-                             opt.max_params > 0 ? opt.max_params : 2, fo, Spans::REPLAY, &G.c);
-    if (rc) return rc;
     // every parameter slot and measurement slot must be inside its vector
     for (size_t i = 0; i < in.ng; i++) {
         const qsim_gate &g = in.g[i];

@@ -68,13 +68,13 @@ int validate_plan(int n, int dtype, const Compiled &c);
 // state of width n (allocated and freed here), each compiled with `base`
 // otherwise; writes the fastest width and its time per input gate.
 int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
-               const qsim_fuse_opts *base, int *best_w, double *best_ns);
+               const qsim_fuse_opts *base, Spans spans, int *best_w, double *best_ns);
 // Time tile widths 12 and 13 for a batch group's template (the other options
 // from `base`, fusion width included) over a sample of up to `nstates` states
 // run together, as the batch runs them; writes the faster width (base's tile
 // width for groups whose states fit one tile, which are not timed).
 int tune_tile_batch(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs &in,
-                    const qsim_fuse_opts &base, uint32_t nstates, int *best_t);
+                    const qsim_fuse_opts &base, Spans spans, uint32_t nstates, int *best_t);
 // The plan of a template in its bound layout, and the entries that bind it
 // (batch.cpp).
 int bind_layout(Compiled *c, std::vector<qk::BindEntry> *ents, size_t *ncoef, uint32_t *max_count);

@@ -44,3 +44,43 @@ def test_programs_and_batches(Q, dtype, n, family, spans, monkeypatch):
         b.close()
         p.close()
         sv.close()
+
+
+def attempts(Q, group, **kw):
+    """Allocations and compiles that creating a batch asks for."""
+    for after in range(200):
+        Q.qsim_debug_fail_alloc(after)
+        try:
+            Q.Batch([group], **kw).close()
+            return after
+        except Q.QsimError as e:
+            assert e.code == Q.E_NOMEM
+        finally:
+            Q.qsim_debug_fail_alloc(-1)
+    raise AssertionError("no end")
+
+
+def test_autotuning_times_the_form_that_runs(Q):
+    """A program whose records keep its frame from cancelling runs as fused
+    operators, though its gates alone lower to rotations: every fusion width of
+    them is timed."""
+    n = 12
+    rng = np.random.default_rng(1)
+    recs = []
+    for k in range(3):
+        recs += [(W.KIND_RY, (q,), (float(rng.normal()),)) for q in range(1, n)]
+        recs += [(W.KIND_RXX, (q, q + 1), (float(rng.normal()),)) for q in range(1, n - 1)]
+        recs += [(W.KIND_H, (0,), ()), (W.KIND_MEASURE, (0,), (), k), (W.KIND_H, (0,), ())]
+    g = W.gates(recs)
+    group = {"n": n, "n_states": 2, "gates": g, "uniforms": np.full((2, 3), 0.3), "n_slots": 3}
+    print("autotune with records", flush=True)
+    b = Q.Batch([group], dtype="complex64", autotune=True)
+    assert not spanned(b.qsim_batch_group_stats(0))
+    b.qsim_batch_run()
+    r = b.qsim_batch_results(0)
+    for s in range(2):
+        want, _, _ = oracle.run(n, g, forced=r["outcomes"][s], n_slots=3)
+        assert norm_error(b.qsim_batch_get_state(0, s), want) < 4 * tol("complex64", len(g))
+    b.close()
+    # widths 2 to 5, and the three tables of the timed plans
+    assert attempts(Q, group, dtype="complex64", autotune=True) - attempts(Q, group, dtype="complex64") >= 4 + 3
