@@ -545,43 +545,50 @@ int qsim_batch_results(qsim_batch_h b, int group, int32_t *outcomes, double *pro
         return rc;
     if (status && (rc = hip_ok(hipMemcpy(status, G.d_status, size_t(G.nstates) * 4, hipMemcpyDeviceToHost), "status")))
         return rc;
-    std::vector<double> nrm(size_t(G.nstates)), sums;
+    if (!norms && !expvals) return QSIM_OK;
     const bool planned = !G.expect.groups.empty();
     const size_t per = planned ? G.nterms + 1 : 2 * G.nterms;   // d_pauli's values per state
-    if (planned || (expvals && G.nterms)) {
-        sums.resize(size_t(G.nstates) * per);
-        if ((rc = hip_ok(hipMemcpy(sums.data(), G.d_pauli, sums.size() * 8, hipMemcpyDeviceToHost), "pauli"))) return rc;
-    }
-    if (planned) {
-        for (size_t bb = 0; bb < nrm.size(); bb++) nrm[bb] = sums[bb * per + G.nterms];
-    } else if ((rc = hip_ok(hipMemcpy(nrm.data(), G.d_norm, nrm.size() * 8, hipMemcpyDeviceToHost), "norms"))) {
-        return rc;
-    }
-    if (norms) std::copy(nrm.begin(), nrm.end(), norms);
-    if (expvals) {
+    try {
+        std::vector<double> nrm(size_t(G.nstates)), sums;
+        if (expvals && G.nterms) {
+            sums.resize(size_t(G.nstates) * per);
+            if ((rc = hip_ok(hipMemcpy(sums.data(), G.d_pauli, sums.size() * 8, hipMemcpyDeviceToHost), "pauli"))) return rc;
+        }
+        if (planned && !sums.empty()) {
+            for (size_t bb = 0; bb < nrm.size(); bb++) nrm[bb] = sums[bb * per + G.nterms];
+        } else if ((rc = hip_ok(planned ? hipMemcpy2D(nrm.data(), 8, G.d_pauli + G.nterms, per * 8, 8, nrm.size(),
+                                                      hipMemcpyDeviceToHost)
+                                        : hipMemcpy(nrm.data(), G.d_norm, nrm.size() * 8, hipMemcpyDeviceToHost),
+                                "norms"))) {
+            return rc;
+        }
+        if (norms) std::copy(nrm.begin(), nrm.end(), norms);
+        if (!expvals) return QSIM_OK;
         if (!G.nterms) {
             std::fill(expvals, expvals + G.nstates, 0.0);
-        } else {
-            for (int bb = 0; bb < G.nstates; bb++) {
-                double total = 0;
-                for (size_t k = 0; k < G.nterms; k++) {
-                    if (planned) {
-                        total += G.terms[k].coeff * expect_value(G.terms[k], sums[size_t(bb) * per + k]);
-                        continue;
-                    }
-                    const double re = sums[size_t(bb) * per + 2 * k], im = sums[size_t(bb) * per + 2 * k + 1];
-                    double v;
-                    switch (__builtin_popcountll(G.terms[k].xmask & G.terms[k].zmask) & 3) {
-                    case 0: v = re; break;
-                    case 1: v = -im; break;
-                    case 2: v = -re; break;
-                    default: v = im; break;
-                    }
-                    total += G.terms[k].coeff * v;
-                }
-                expvals[bb] = total / nrm[size_t(bb)];
-            }
+            return QSIM_OK;
         }
+        for (size_t bb = 0; bb < nrm.size(); bb++) {
+            double total = 0;
+            for (size_t k = 0; k < G.nterms; k++) {
+                if (planned) {
+                    total += G.terms[k].coeff * expect_value(G.terms[k], sums[bb * per + k]);
+                    continue;
+                }
+                const double re = sums[bb * per + 2 * k], im = sums[bb * per + 2 * k + 1];
+                double v;
+                switch (__builtin_popcountll(G.terms[k].xmask & G.terms[k].zmask) & 3) {
+                case 0: v = re; break;
+                case 1: v = -im; break;
+                case 2: v = -re; break;
+                default: v = im; break;
+                }
+                total += G.terms[k].coeff * v;
+            }
+            expvals[bb] = total / nrm[bb];
+        }
+    } catch (const std::bad_alloc &) {
+        return QSIM_E_NOMEM;
     }
     return QSIM_OK;
 }

@@ -52,3 +52,33 @@ def test_groups(Q, dtype, graph, shared):
                 for s in range(states[i]):
                     assert norm_error(b.qsim_batch_get_state(i, s), want) < e
     b.close()
+
+
+@pytest.mark.parametrize("n", [9, 11])
+@pytest.mark.parametrize("terms", [0, 1, 7])
+def test_results_one_at_a_time(Q, n, terms):
+    """Outputs that are not asked for (NULL) change nothing in the others."""
+    import ctypes as C
+    states = 5
+    g = mixed_circuit(n, 40, seed=n, p_clifford=0.0)
+    th = np.random.default_rng(1).normal(size=(states, 1))
+    g = np.concatenate([W.gates([(W.KIND_RX, (0,), (0.0,), 0)]), g])
+    group = {"n": n, "n_states": states, "gates": g, "params": th}
+    if terms:
+        group["terms"] = W.pauli_sum(n, terms, seed=3)
+    print(f"results one at a time n={n} terms={terms}", flush=True)
+    b = Q.Batch([group], dtype="complex128")
+    b.qsim_batch_run()
+    r = b.qsim_batch_results(0)
+    for s in range(states):
+        want, _, _ = oracle.run(n, g, params=th[s])
+        assert abs(r["norms"][s] - 1) < 2 * tol("complex128", 41)
+        e = oracle.expval(n, want, group["terms"]) if terms else 0.0
+        assert abs(r["expvals"][s] - e) < 4 * tol("complex128", 41) * max(terms, 1)
+    for name, at, dt in (("expvals", 4, np.float64), ("norms", 5, np.float64), ("status", 6, np.int32)):
+        out = np.full(states, -7, dtype=dt)
+        args = [b.h, 0, None, None, None, None, None]
+        args[at] = C.c_void_p(out.ctypes.data)
+        Q.check(Q.lib().qsim_batch_results(*args))
+        assert np.array_equal(out, r[name])
+    b.close()
