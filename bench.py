@@ -171,6 +171,18 @@ def oracle_distance(W, psi, energy, H):
             "oracle_energy": float(fx["energy"])}
 
 
+def runs_as_rotations(stats):
+    """Passes of rotations take none of the paper's fusion steps."""
+    return stats["ops_after"][1] == -1
+
+
+def flops_per_amplitude(stats):
+    """Arithmetic of one run: in tiled passes a complex multiply-add (8 flops) per
+    XOR-shift term of every operator; in passes of rotations two real multiply-adds
+    per rotation (a controlled one takes four: these are counted low)."""
+    return 4.0 * stats["fused_ops"] if runs_as_rotations(stats) else 8.0 * stats["terms"]
+
+
 def run_trajectories(qsim, W, ntraj=1024, rounds=500):
     """Mid-circuit measurement form: 12 system + 2 ancilla qubits, complex64
     states with FP64 reductions, `rounds` rounds of gates + 2 measurements +
@@ -188,25 +200,25 @@ def run_trajectories(qsim, W, ntraj=1024, rounds=500):
     res = b.qsim_batch_results(0)
     dt = time.perf_counter() - t0
     info = b.qsim_batch_info()
-    terms = b.qsim_batch_group_stats(0)["terms"]
+    gs = b.qsim_batch_group_stats(0)
     b.close()
     p = res["probs"]
-    # The 128 KiB state stays in one workgroup for the whole pass.  LDS bytes are
-    # counted as if every operator read and wrote the state there once (span
-    # passes run several on registers per trip), and each measurement or reset record reads it and rewrites
-    # it (counted as one more read and write; a reset that follows a
-    # measurement of its qubit runs inside that measurement's record).
-    lds_bytes = ntraj * (info["fused_ops"] + info["records"]) * 2 * 8 * (1 << 14)
-    flops = ntraj * terms * 8 * (1 << 14)
+    # The 128 KiB state stays in one workgroup for the whole pass.  In tiled passes
+    # every operator reads and writes the state in LDS once, and so does each
+    # measurement or reset record (a reset that follows a measurement of its qubit
+    # runs inside that measurement's record); passes of rotations do so once per
+    # re-layout and keep it in registers in between.
+    trips = gs["reg_relayouts"] if runs_as_rotations(gs) else info["fused_ops"] + info["records"]
+    lds_bytes = ntraj * trips * 2 * 8 * (1 << 14)
+    flops = ntraj * flops_per_amplitude(gs) * (1 << 14)
     return {"workload": f"{ntraj} trajectories x {rounds} rounds, 14 qubits, complex64",
             "seconds": dt, "trajectory_rounds_per_s": ntraj * rounds / dt,
             "input_gates_per_s": ntraj * len(g) / dt, "passes": info["passes"],
             "fused_ops_per_trajectory": info["fused_ops"], "records_per_trajectory": info["records"],
             "lds": {"bytes": lds_bytes, "achieved_GBps": lds_bytes / dt / 1e9, "peak_GBps": LDS_PEAK_GBS,
                     "frac": lds_bytes / dt / 1e9 / LDS_PEAK_GBS},
-            # every XOR-shift term is one complex multiply-add (8 flops) per
-            # amplitude; vector FP32 without packed instructions peaks at the
-            # FP64 rate, 78.6 TFLOP/s
+            # (see flops_per_amplitude) vector FP32 without packed instructions
+            # peaks at the FP64 rate, 78.6 TFLOP/s
             "alu": {"flops": flops, "achieved_TFLOPs": flops / dt / 1e12, "peak_TFLOPs": 78.6,
                     "frac": flops / dt / 1e12 / 78.6},
             "failed": int((res["status"] != 0).sum()),
@@ -620,7 +632,8 @@ def main():
                                "copy_GBps": copy_gbs, "frac_of_copy": achieved / copy_gbs,
                                "copy_ceilings_GBps": ceil,
                                "frac_of_rotated_copy": achieved / ceil["best_rotated"],
-                               "kernel": f"k_span<{'double' if elem == 16 else 'float'}, LOGT>",
+                               "kernel": f"{'k_span' if runs_as_rotations(st) else 'k_tile'}"
+                                         f"<{'double' if elem == 16 else 'float'}>",
                                "bytes_per_launch": pass_bytes, "launches_per_step": launches}
             # one more step with an event pair around every pass: pure kernel
             # time per launch (what a kernel trace reports)
@@ -628,17 +641,16 @@ def main():
             prog.qsim_run_timed(sv)
             kms, kl = prog.qsim_program_kernel_ms()
             res["per_pass_kernel_us"] = 1e3 * kms / kl
-            # arithmetic of the same launches: 8 flops per complex MAC, one
-            # MAC per amplitude per XOR-shift term
-            flops = 8.0 * st["terms"] * (1 << n)
+            # arithmetic of the same launches
+            flops = flops_per_amplitude(st) * (1 << n)
             res["alu"] = {"flops_per_step": flops,
                           "achieved_TFLOPs": flops / (float(np.mean(prog_ms)) * 1e-3) / 1e12,
                           "peak_TFLOPs": 78.6,
                           "frac": flops / (float(np.mean(prog_ms)) * 1e-3) / 1e12 / 78.6}
-            # LDS traffic of the same launches if every operator read and wrote
-            # the whole tile once, as in k_tile (coefficient reads not counted);
-            # span passes run about three rotations on registers per trip
-            lds_bytes = float(st["fused_ops"]) * pass_bytes
+            # LDS traffic of the same launches: in tiled passes every operator
+            # reads and writes the whole tile once (coefficient reads not
+            # counted), in passes of rotations every re-layout does
+            lds_bytes = float(st["reg_relayouts"] if runs_as_rotations(st) else st["fused_ops"]) * pass_bytes
             lds_gbs = lds_bytes / (float(np.mean(prog_ms)) * 1e-3) / 1e9
             res["lds"] = {"bytes_per_step": lds_bytes, "achieved_GBps": lds_gbs,
                           "peak_GBps": LDS_PEAK_GBS, "frac": lds_gbs / LDS_PEAK_GBS}

@@ -136,7 +136,8 @@ enum {
 /* Counters of the last qsim_apply (host-side compile and device plan). */
 typedef struct qsim_apply_stats {
     int64_t input_gates;      /* gate records, barriers excluded */
-    int64_t ops_after[6];     /* operators after fusion level 0..5 (those computed) */
+    int64_t ops_after[6];     /* operators after fusion level 0..5 (-1: not computed, as levels
+                                 1..4 of a circuit that runs as rotations) */
     int64_t fused_ops;        /* operators executed */
     int64_t passes;           /* full-state read+write passes enqueued */
     int64_t terms;            /* sum over operators of their nonzero XOR diagonals */
@@ -146,7 +147,8 @@ typedef struct qsim_apply_stats {
     int32_t max_width;        /* fusion width used */
     int64_t reg_passes;       /* passes whose tile stays in registers */
     int64_t reg_swaps;        /* lane/register exchanges in those passes */
-    int64_t reg_relayouts;    /* LDS re-layouts in those passes */
+    int64_t reg_relayouts;    /* LDS re-layouts in those passes, and in passes of rotations
+                                 (which keep their tile in registers too) */
 } qsim_apply_stats;
 
 /* ------------------------------------------------------------------ core */
@@ -243,7 +245,9 @@ int qsim_set_state(qsim_h h, const void *host_src);
 
 /* A circuit compiled once (lowering, fusion, pass plan) with its operator
  * tables resident in device memory, replayable on any state of the same
- * width and dtype.  qsim_apply is compile + run + free. */
+ * width and dtype.  qsim_apply is compile + run + free; a circuit that can run
+ * as rotations or as fused operators is compiled both ways for a program, to run
+ * the cheaper form, and for qsim_apply where that can pay in one run. */
 typedef struct qsim_program *qsim_prog;
 
 /* Compile and upload (synchronous).  Same inputs and errors as qsim_apply. */
@@ -492,7 +496,7 @@ int qsim_parse_qasm(const char *text, size_t len, qsim_gate *out, size_t cap, si
 
 /* Host-only: applies the circuit to psi exactly as the device tables of its
  * compiled plan describe (the same lowering, fusion, pass plan and packing as
- * qsim_compile for n and dtype), in FP64 on the host: tiled passes gather each
+ * qsim_apply for n and dtype), in FP64 on the host: tiled passes gather each
  * tile through its position table, apply every operator record with the
  * coefficient block its block qubits select, and scatter the tile back;
  * strided passes apply their operator on global positions.  For tests of the
@@ -522,8 +526,8 @@ int qsim_debug_emulate_batch(int n, int dtype, const qsim_gate *g, size_t ng, co
                              int max_params, const qsim_fuse_opts *opt, double *psi,
                              int32_t *outcomes, double *probs, int32_t *status);
 
-/* Host-only: number of full-state passes the planner makes for the fused
- * circuit (same inputs as qsim_debug_fuse), for n qubits and dtype. */
+/* Host-only: number of full-state passes the planner makes for the circuit
+ * (same inputs as qsim_debug_fuse), for n qubits and dtype, as qsim_apply. */
 int qsim_debug_plan(int n, int dtype, const qsim_gate *g, size_t ng,
                     const double *mats, size_t n_mats, const double *params,
                     size_t n_params, const qsim_fuse_opts *opt, qsim_apply_stats *out);

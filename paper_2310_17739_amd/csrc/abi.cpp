@@ -675,6 +675,8 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
     s.ops_after[5] = s.fused_ops = int64_t(P.ops.size() + left_ops);
     s.passes = int64_t(out->passes.size());
     s.terms = pl.terms;
+    for (const DevOp &o : pl.ops) s.reg_relayouts += o.kind == DEVOP_STAGE ? 1 : 0;
+    for (const PassInfo &pi : out->passes) s.reg_relayouts -= pi.span ? 1 : 0;
     s.bytes_moved = s.passes * 2 * (int64_t(1) << n) * int64_t(elem);
     s.tile_qubits = t;
     return QSIM_OK;
@@ -942,13 +944,12 @@ struct qsim_program {
 
 namespace {
 
-int reduce_buffers(qsim_h h, size_t partial_doubles, size_t out_doubles, double **partials,
-                   double **out) {
-    size_t need = (partial_doubles + out_doubles) * sizeof(double) + 512;
-    int rc = grow(&h->d_red, &h->cap_red, need, h->stream);
+// Device memory for reduction partials, and pinned memory (h->h_out) that the
+// reductions write their results to.
+int reduce_buffers(qsim_h h, size_t partial_doubles, size_t out_doubles, double **partials) {
+    int rc = grow(&h->d_red, &h->cap_red, partial_doubles * sizeof(double), h->stream);
     if (rc) return rc;
     *partials = (double *)h->d_red;
-    *out = (double *)h->d_red + ((partial_doubles + 31) & ~size_t(31));
     if (h->cap_out < out_doubles * sizeof(double)) {
         void *p = h->h_out;
         size_t cap = h->cap_out;
@@ -974,8 +975,8 @@ int upload_table(qsim_h h, const void *a, size_t na, const void *b, size_t nb) {
 // Marginal weights of qubits qs (unnormalised), into h->h_out[0 .. 2^nqs).
 int marginal(qsim_h h, const int *qs, int nqs) {
     const uint32_t nch = qk::marginal_chunks(h->n, nqs);
-    double *part, *out;
-    int rc = reduce_buffers(h, size_t(nch) << nqs, size_t(1) << nqs, &part, &out);
+    double *part;
+    int rc = reduce_buffers(h, size_t(nch) << nqs, size_t(1) << nqs, &part);
     if (rc) return rc;
     // the sums go straight to the pinned read-back buffer
     rc = qk::launch_marginal(h->dtype, h->buf, 0, 1, h->n, qs, nqs, part, h->h_out, h->stream);
@@ -1330,8 +1331,8 @@ int qsim_expval(qsim_h h, const qsim_pauli *t, size_t nt, double *out) {
             // every term and the norm from one set of readings, one round trip
             const uint32_t nterms = uint32_t(nt) + 1;
             const uint32_t nch = qk::expect_chunks(h->n, plan.t, nterms, 1);
-            double *part, *dout;
-            rc = reduce_buffers(h, size_t(nch) * nterms, nterms, &part, &dout);
+            double *part;
+            rc = reduce_buffers(h, size_t(nch) * nterms, nterms, &part);
             if (!rc) rc = upload_table(h, plan.groups.data(), plan.groups.size() * sizeof(ExpectGroup),
                                        plan.recs.data(), plan.recs.size() * sizeof(DevOp));
             if (!rc) rc = qk::launch_expect(h->dtype, h->buf, 0, 1, h->n, plan, h->d_masks, nterms, nch, part,
@@ -1352,8 +1353,8 @@ int qsim_expval(qsim_h h, const qsim_pauli *t, size_t nt, double *out) {
         rc = upload_table(h, table.data(), 8 * table.size(), nullptr, 0);
         if (rc) return rc;
         const uint32_t nch = qk::pauli_chunks(h->n);
-        double *part, *dout;
-        rc = reduce_buffers(h, size_t(nch) * 2 * nt, 2 * nt, &part, &dout);
+        double *part;
+        rc = reduce_buffers(h, size_t(nch) * 2 * nt, 2 * nt, &part);
         if (rc) return rc;
         rc = qk::launch_pauli(h->dtype, h->buf, 0, 1, h->n, (const uint64_t *)h->d_masks, int(nt), nrows, part,
                               h->h_out, h->stream);
@@ -1388,8 +1389,8 @@ int qsim_sample(qsim_h h, const double *u, size_t m, uint64_t *out) {
     const uint64_t nb = qk::scan_blocks(h->n), ns = qk::scan_segments(h->n);
     constexpr size_t kPiece = size_t(1) << 18;
     int rc = grow(&h->d_scan, &h->cap_scan, (ns + 2 * nb + 1) * 8, h->stream);
-    double *part, *dout;
-    if (!rc) rc = reduce_buffers(h, 0, 1, &part, &dout);
+    double *part;
+    if (!rc) rc = reduce_buffers(h, 0, 1, &part);
     if (!rc && m) rc = grow_host(&h->h_table, &h->cap_table, 16 * std::min(m, kPiece));
     if (rc) return rc;
     double *seg = (double *)h->d_scan, *bsum = seg + ns, *boff = bsum + nb;

@@ -342,8 +342,6 @@ enum { DEVOP_MAT = 0, DEVOP_MEASURE = 1, DEVOP_ASSERT0 = 2, DEVOP_RESET = 3,
        DEVOP_EXPECT = 11  // a term of a Pauli sum: its form and signs as a rotation's; coef = its
                           // number
 };
-// records with coefficients (a stage's two are not used: they keep those of a
-// span pass at twice the record's number)
 // The bits that pair c = 0..5 of a run's four positions acts on.
 constexpr uint8_t kRunPair[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
 // Tiles of so many qubits run 2-qubit operators in runs (see group_runs): 16
@@ -351,6 +349,8 @@ constexpr uint8_t kRunPair[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 
 // larger ones (one workgroup per CU) have no registers left for them.
 constexpr bool run_tile(size_t elem, int t) { return t == 12 || (t > 12 && elem == 8); }
 
+// Records with coefficients (of a span pass all have two, so that a rotation's are
+// at twice its record's number; those of the others are not used).
 inline bool devop_is_mat(int kind) {
     return kind == DEVOP_MAT || kind == DEVOP_RMAT || kind == DEVOP_PAULI || kind == DEVOP_STAGE ||
            kind == DEVOP_SPAN_REC || kind == DEVOP_LAYOUT || kind == DEVOP_PAULI2 || kind == DEVOP_PAULI2X;
@@ -399,12 +399,12 @@ int pack_plan(const std::vector<Op> &ops, const std::vector<uint32_t> &present,
 // by an LDS re-layout (DEVOP_XPOSE pair), which also chooses the qubits the
 // next operators need (furthest next use leaves first).  Returns QSIM_OK or
 // QSIM_E_ARG for an operator the pass cannot hold.
+int pack_reg_pass(const std::vector<Op> &ops, const std::vector<uint32_t> &present, Pass &p,
+                  bool coalesce, PackedPlan *out);
+
 // Runs of 2-qubit operators in the tiled passes of a packed plan; `room` is the
 // LDS, behind a tile, that records and coefficients of a pass may take.
 void group_runs(const std::vector<Pass> &passes, size_t elem, size_t room, PackedPlan *plan);
-
-int pack_reg_pass(const std::vector<Op> &ops, const std::vector<uint32_t> &present, Pass &p,
-                  bool coalesce, PackedPlan *out);
 
 // Register bits of a span pass: each thread holds 2^kSpanRegs amplitudes.
 constexpr int kSpanRegs = 4;

@@ -566,8 +566,11 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
     }
     flush();
     rots.finish();
-    // with many gates left in the frame, the fused operators of the matrix
-    // lowering do less
+    // With many gates left in the frame, the fused operators of the matrix lowering
+    // do less.  Span passes against tiled ones, us, random rotations and Clifford
+    // gates with so many left per rotation: 21 qubits complex128 0.1 162 (170), 0.3
+    // 170 (162), 1.6 191 (172), 24 qubits complex64 0.3 630 (603), 1.1 588 (571), 3.2
+    // 674 (527); layers of RY, RZ and CX, 1.4 left, 634 (363) and 2321 (1494).
     return 3 * extra <= emitted;
 }
 

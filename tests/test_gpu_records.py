@@ -5,6 +5,8 @@ import pytest
 
 import oracle
 import workloads as W
+from test_gpu_batch import test_assertion_failure_marks_only_that_state as assertion_failure
+from test_gpu_batch import test_joined_measure_reset_zero_probability as joined_measure_reset
 from test_gpu_span import measured_program, tol
 from test_host_records import as_template, failing_program
 from test_host_span import norm_error
@@ -60,3 +62,13 @@ def test_failing_records_of_templates(Q, dtype, n, bad):
         want, _, _ = oracle.run(n, upto if fails else prog, params=None if fails else th, forced=forced[s], n_slots=2)
         assert norm_error(b.qsim_batch_get_state(0, s), want) < 4 * tol(dtype, len(prog))
     b.close()
+
+
+@pytest.mark.parametrize("dtype", ["complex128", "complex64"])
+@pytest.mark.parametrize("n", [11, 13])
+def test_zero_probability_in_whole_states(Q, dtype, n):
+    """A forced outcome and an assertion of probability 0 in one state of four, its
+    angle bound per state."""
+    joined_measure_reset(Q, dtype, n, None)
+    if dtype == "complex128":
+        assertion_failure(Q, n)
