@@ -252,21 +252,20 @@ struct Frame {
         int kind, q0, q1;
         double theta;
         bool alive;
+        int before[2];   // the live nodes before it on its wires
     };
     std::vector<Pauli> X, Z;
     std::vector<Node> nodes;
-    std::vector<std::vector<int>> wire;   // live nodes on each qubit, in order
-    size_t live = 0;
+    std::vector<int> last;   // the last live node on each qubit's wire, or -1
 
-    explicit Frame(int n) : X(size_t(n)), Z(size_t(n)), wire(size_t(n)) { reset(); }
+    explicit Frame(int n) : X(size_t(n)), Z(size_t(n)), last(size_t(n)) { reset(); }
     void reset() {
         for (size_t q = 0; q < X.size(); q++) {
             X[q] = Pauli{uint64_t(1) << q, 0, 0};
             Z[q] = Pauli{0, uint64_t(1) << q, 0};
-            wire[q].clear();
+            last[q] = -1;
         }
         nodes.clear();
-        live = 0;
     }
     // C^dagger P C
     Pauli image(const Axis &a) const {
@@ -302,9 +301,9 @@ struct Frame {
     // wires if that is its inverse, else it becomes one.
     void push(int kind, int q0, int q1, double theta) {
         const int nq = q1 >= 0 ? 2 : 1;
-        std::vector<int> &w0 = wire[size_t(q0)];
-        if (!w0.empty() && (nq == 1 || (!wire[size_t(q1)].empty() && wire[size_t(q1)].back() == w0.back()))) {
-            Node &h = nodes[size_t(w0.back())];
+        const int at = last[size_t(q0)];
+        if (at >= 0 && (nq == 1 || last[size_t(q1)] == at)) {
+            Node &h = nodes[size_t(at)];
             const bool same_q = (h.q0 == q0 && h.q1 == q1) ||
                                 ((kind == QSIM_G_CZ || kind == QSIM_G_SWAP || kind == QSIM_G_RXX || kind == QSIM_G_RZZ) &&
                                  h.q0 == q1 && h.q1 == q0);
@@ -314,16 +313,14 @@ struct Frame {
             if (kind == QSIM_G_SX) inverse = false;
             if (inverse) {
                 h.alive = false;
-                live--;
-                w0.pop_back();
-                if (nq == 2) wire[size_t(q1)].pop_back();
+                last[size_t(h.q0)] = h.before[0];
+                if (nq == 2) last[size_t(h.q1)] = h.before[1];
                 return;
             }
         }
-        w0.push_back(int(nodes.size()));
-        if (nq == 2) wire[size_t(q1)].push_back(int(nodes.size()));
-        nodes.push_back({kind, q0, q1, theta, true});
-        live++;
+        nodes.push_back({kind, q0, q1, theta, true, {at, nq == 2 ? last[size_t(q1)] : -1}});
+        last[size_t(q0)] = int(nodes.size()) - 1;
+        if (nq == 2) last[size_t(q1)] = int(nodes.size()) - 1;
     }
 };
 
@@ -613,18 +610,26 @@ struct Span {
 struct Rank {
     uint32_t v[32];
     uint32_t have = 0;
-    // whether x is independent of what was added (and adds it)
-    bool add(uint32_t x) {
+    // x without what was added: 0 if it depends on that
+    uint32_t rest(uint32_t x) const {
         while (x) {
             const int p = 31 - __builtin_clz(x);
-            if (!((have >> p) & 1)) {
-                v[p] = x;
-                have |= 1u << p;
-                return true;
-            }
+            if (!((have >> p) & 1)) break;
             x ^= v[p];
         }
-        return false;
+        return x;
+    }
+    // adds a rest that is not 0
+    void put(uint32_t r) {
+        const int p = 31 - __builtin_clz(r);
+        v[p] = r;
+        have |= 1u << p;
+    }
+    // whether x is independent of what was added (and adds it)
+    bool add(uint32_t x) {
+        const uint32_t r = rest(x);
+        if (r) put(r);
+        return r != 0;
     }
 };
 
@@ -677,18 +682,16 @@ void stage_layout(const Span &T, const std::vector<uint64_t> &dirs, int t, int c
         taken |= 1u << j;
     };
     for (int j = 0; j < c && nt < logt; j++) {
-        Rank probe = all;
-        if (!probe.add(1u << j)) continue;
-        all = probe;
+        if (!all.add(1u << j)) continue;
         bank.add(span_slot(1u << j) & 31u);
         take(j);
     }
     for (int j = c; j < t && nt < std::min(5, logt); j++) {
         if ((taken >> j) & 1) continue;
-        Rank probe = all, pb = bank;
-        if (!probe.add(1u << j) || !pb.add(span_slot(1u << j) & 31u)) continue;
-        all = probe;
-        bank = pb;
+        const uint32_t r = all.rest(1u << j), rb = bank.rest(span_slot(1u << j) & 31u);
+        if (!r || !rb) continue;
+        all.put(r);
+        bank.put(rb);
         take(j);
     }
     for (int j = 0; j < t && nt < logt; j++)
@@ -907,8 +910,7 @@ void plan_whole(int n, const PauliProgram &P, int n_epochs, int c, int regs, siz
 
 uint64_t span_vector(const Pass &p, uint32_t coords) {
     uint64_t x = 0;
-    for (int j = 0; j < p.t; j++)
-        if ((coords >> j) & 1) x ^= p.span_v[j];
+    for (; coords; coords &= coords - 1) x ^= p.span_v[__builtin_ctz(coords)];
     return x;
 }
 
@@ -1029,34 +1031,59 @@ bool plan_expect(int n, int c, const qsim_pauli *terms, size_t nt, ExpectPlan *o
     const uint64_t all = (uint64_t(1) << n) - 1;
     // the terms in ascending order of their X masks, and the identity (whose
     // value is the norm) first
-    std::vector<uint32_t> idx(nt + 1);
-    for (size_t k = 0; k <= nt; k++) idx[k] = uint32_t(k);
-    auto X = [&](uint32_t k) { return k < nt ? terms[k].xmask : 0; };
-    auto Z = [&](uint32_t k) { return k < nt ? terms[k].zmask : 0; };
-    std::stable_sort(idx.begin(), idx.end(), [&](uint32_t a, uint32_t b) { return X(a) < X(b); });
+    struct Term {
+        uint64_t x, z;
+        uint32_t k;
+    };
+    std::vector<Term> all_terms(nt + 1);
+    for (size_t k = 0; k < nt; k++) all_terms[k] = {terms[k].xmask, terms[k].zmask, uint32_t(k)};
+    all_terms[nt] = {0, 0, uint32_t(nt)};
+    if (nt < 256) {
+        std::sort(all_terms.begin(), all_terms.end(),
+                  [](const Term &a, const Term &b) { return a.x != b.x ? a.x < b.x : a.k < b.k; });
+    } else {
+        // by digits of 11 bits, lowest first (3,000 terms: 30 us where sorting takes 155)
+        std::vector<Term> by(nt + 1);
+        for (int shift = 0; shift < n; shift += 11) {
+            uint32_t at[2049] = {0};
+            for (const Term &a : all_terms) at[((a.x >> shift) & 2047) + 1]++;
+            for (int d = 0; d < 2048; d++) at[d + 1] += at[d];
+            for (const Term &a : all_terms) by[at[(a.x >> shift) & 2047]++] = a;
+            by.swap(all_terms);
+        }
+    }
+    auto X = [&](uint32_t i) { return all_terms[i].x; };
+    out->recs.reserve(2 * nt + 4);
     // (in blocks, so that planning stays linear in the number of terms)
-    std::vector<uint32_t> left, later, sel, rest;
+    std::vector<uint32_t> left, later, sel, rest, mine;
+    std::vector<uint64_t> dirs;
+    constexpr int kMisses = 64;
     size_t taken = 0;
-    while (taken < idx.size() || !left.empty()) {
+    while (taken < all_terms.size() || !left.empty()) {
         if (left.empty()) {
-            const size_t end = std::min(idx.size(), taken + 2048);
-            left.assign(idx.begin() + long(taken), idx.begin() + long(end));
-            taken = end;
+            const size_t end = std::min(all_terms.size(), taken + 2048);
+            for (; taken < end; taken++) left.push_back(uint32_t(taken));
         }
         // a group: terms whose X masks lie in one tile's space
         Span T;
         for (int q = 0; q < std::min(c, t); q++) T.add(uint64_t(1) << q);
         later.clear();
         sel.clear();
-        for (uint32_t k : left) {
-            const uint64_t r = T.reduce(X(k));
-            if (sel.size() < kExpectGroup && (r == 0 || T.d < t)) {
+        // (once the space is full, few of the others lie in it: the search ends after
+        // kMisses in a row, or planning 3,000 masks would take longer than they do)
+        size_t at = 0;
+        for (int misses = 0; at < left.size() && sel.size() < kExpectGroup && misses < kMisses; at++) {
+            const uint64_t r = T.reduce(X(left[at]));
+            if (r == 0 || T.d < t) {
                 if (r) T.add(r);
-                sel.push_back(k);
+                sel.push_back(left[at]);
+                misses = 0;
             } else {
-                later.push_back(k);
+                later.push_back(left[at]);
+                misses++;
             }
         }
+        later.insert(later.end(), left.begin() + long(at), left.end());
         left.swap(later);
         for (int q = 0; q < n && T.d < t; q++) {
             const uint64_t r = T.reduce(uint64_t(1) << q);
@@ -1068,21 +1095,26 @@ bool plan_expect(int n, int c, const qsim_pauli *terms, size_t nt, ExpectPlan *o
         while (!sel.empty()) {
             // a stage: at most `regs` independent X masks
             Span R;
-            std::vector<uint64_t> dirs;
-            std::vector<uint32_t> mine;
+            dirs.clear();
+            mine.clear();
             rest.clear();
-            for (uint32_t k : sel) {
-                const uint64_t x = X(k);
-                const bool have = !x || std::find(dirs.begin(), dirs.end(), x) != dirs.end();
+            // (equal masks follow each other)
+            for (size_t i = 0; i < sel.size(); i++) {
+                const uint64_t x = X(sel[i]);
+                const bool have = !x || (!dirs.empty() && dirs.back() == x);
+                if (!have && R.d == regs) {
+                    rest.insert(rest.end(), sel.begin() + long(i), sel.end());
+                    break;
+                }
                 const uint64_t r = have ? 0 : R.reduce(x);
-                if (have || (r && R.d < regs)) {
+                if (have || r) {
                     if (r) {
                         R.add(r);
                         dirs.push_back(x);
                     }
-                    mine.push_back(k);
+                    mine.push_back(sel[i]);
                 } else {
-                    rest.push_back(k);
+                    rest.push_back(sel[i]);
                 }
             }
             sel.swap(rest);
@@ -1091,16 +1123,15 @@ bool plan_expect(int n, int c, const qsim_pauli *terms, size_t nt, ExpectPlan *o
             uint64_t V[16];
             for (int j = 0; j < t; j++) {
                 V[j] = 0;
-                for (int i = 0; i < t; i++)
-                    if ((st.layout[j] >> i) & 1) V[j] ^= T.v[i];
+                for (uint32_t m = st.layout[j]; m; m &= m - 1) V[j] ^= T.v[__builtin_ctz(m)];
                 if (g.stages == 0) g.load_v[j] = V[j];
             }
             out->recs.push_back(stage_record(st, t, int(g.stages++)));
-            for (uint32_t k : mine) {
+            for (uint32_t i : mine) {
                 DevOp d{};
                 d.kind = DEVOP_EXPECT;
-                d.coef = k;
-                if (!string_record(X(k), Z(k), V, t, regs, &d)) return false;
+                d.coef = all_terms[i].k;
+                if (!string_record(all_terms[i].x, all_terms[i].z, V, t, regs, &d)) return false;
                 out->recs.push_back(d);
             }
         }
