@@ -761,6 +761,7 @@ int compile_program(int n, int dtype, const qsim_gate *g, size_t ng, const GateI
                 rotations.stats.max_width = fc.max_width;
                 if (!spans_may_lose(n, dtype, P, L, pc, spans, rotations)) {
                     *out = std::move(rotations);
+                    out->fixed = true;
                     out->stats.compile_seconds = now_seconds() - t0;
                     return keep_params ? QSIM_OK : validate_plan(n, dtype, *out);
                 }
@@ -1453,7 +1454,8 @@ int qsim_autotune(qsim_h h, const qsim_gate *g, size_t ng, const double *mats, s
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return QSIM_E_HIP;
     double best_ns = 1e300;
-    int rc = QSIM_OK;
+    int rc = QSIM_OK, spans_tile = 0;
+    uint64_t spans_low = 0;   // of the rotations timed on tiles of spans_tile qubits: a bit each
     DeviceTables dt;
     for (const qsim_fuse_opts &o : cands) {
         Compiled c;
@@ -1464,8 +1466,16 @@ int qsim_autotune(qsim_h h, const qsim_gate *g, size_t ng, const double *mats, s
         }
         if (rc) break;
         if (c.plan.ops.empty()) continue;
-        // fusion options change nothing: one candidate of each tile
-        if (c.pauli && (o.max_width != 4 || o.op_cost != 4.0f)) continue;
+        // fusion options do not change a plan of rotations: one candidate of each
+        // tile (they follow each other) and number of low qubits
+        if (o.tile_qubits != spans_tile) {
+            spans_tile = o.tile_qubits;
+            spans_low = 0;
+        }
+        if (c.pauli) {
+            if ((spans_low >> o.low_qubits) & 1) continue;
+            spans_low |= uint64_t(1) << o.low_qubits;
+        }
         if ((rc = upload_plan(&dt, h->dtype, c.plan, h->stream))) break;
         // warm, then time one run
         if ((rc = enqueue_passes(c, dt, h->dtype, h->buf, h->stream, false))) break;
@@ -1509,6 +1519,7 @@ int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs
     DeviceTables dt;
     *best_w = 0;
     *best_ns = 1e300;
+    bool rotations = false;   // timed: the same plan at every width that takes it
     for (int w : {4, 2, 3, 5}) {
         if (w > wmax || rc) break;
         qsim_fuse_opts o{};
@@ -1527,6 +1538,8 @@ int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs
             *best_ns = 0.0;
             break;
         }
+        if (c.pauli && rotations) continue;
+        rotations = rotations || c.pauli;
         if ((rc = upload_plan(&dt, dtype, c.plan, st))) break;
         // warm, then the best of three timed runs
         if ((rc = enqueue_passes(c, dt, dtype, buf, st, true))) break;
@@ -1545,7 +1558,7 @@ int tune_width(int n, int dtype, const qsim_gate *g, size_t ng, const GateInputs
             *best_ns = ns;
             *best_w = w;
         }
-        if (c.pauli) break;   // the same plan at every width
+        if (c.fixed) break;
     }
     if (st) (void)hipStreamSynchronize(st);
     free_tables(&dt);

@@ -183,12 +183,12 @@ int setup_group(Group &G, const qsim_batch_group &in, int dtype, const qsim_batc
     if (base.tile_qubits <= 0) base.tile_qubits = default_tile_qubits(in.n, dtype, uint64_t(in.n_states));
     const qsim_fuse_opts *fo = &base;
     qsim_fuse_opts tuned{};
-    const auto compile = [&](const qsim_fuse_opts *o) {
+    const auto compile = [&](const qsim_fuse_opts *o, Spans spans) {
         return compile_program(in.n, dtype, in.g, in.ng,
                                GateInputs{in.mats, in.mats ? in.n_mats : 0, nullptr, param ? size_t(in.n_params) : 0},
-                               param, true, opt.max_params > 0 ? opt.max_params : 2, o, Spans::REPLAY, &G.c);
+                               param, true, opt.max_params > 0 ? opt.max_params : 2, o, spans, &G.c);
     };
-    int rc = compile(fo);
+    int rc = compile(fo, Spans::REPLAY);
     if (rc) return rc;
     if (opt.autotune) {
         // the template's fusion width, timed on its first instance (angles of
@@ -223,7 +223,7 @@ int setup_group(Group &G, const qsim_batch_group &in, int dtype, const qsim_batc
         G.tune_seconds = now_seconds() - t0;
         G.tuned_width = w;
         G.c = Compiled{};
-        rc = compile(&tuned);
+        rc = compile(&tuned, spans);
         if (rc) return rc;
     }
     // every parameter slot and measurement slot must be inside its vector

@@ -24,6 +24,7 @@ struct PassInfo {
 
 struct Compiled {
     bool pauli = false;   // a Pauli program: its plan does not depend on fusion options
+    bool fixed = false;   // nor whether it runs: it was not compared with another plan
     PackedPlan plan;
     std::vector<PassInfo> passes;
     qsim_apply_stats stats{};

@@ -6,7 +6,7 @@ import pytest
 import oracle
 import workloads as W
 from test_gpu_span import tol
-from test_host_plan_choice import controlled_layers, exponentials, qft, rotation_layers
+from test_host_plan_choice import controlled_layers, exchange_layers, exponentials, qft, rotation_layers
 from test_host_span import norm_error, spanned
 
 pytestmark = pytest.mark.gpu
@@ -84,3 +84,26 @@ def test_autotuning_times_the_form_that_runs(Q):
     b.close()
     # widths 2 to 5, and the three tables of the timed plans
     assert attempts(Q, group, dtype="complex64", autotune=True) - attempts(Q, group, dtype="complex64") >= 4 + 3
+
+
+def test_autotuning_times_every_width(Q):
+    """At width 2 these layers run as rotations, at 3 to 5 as fused operators: all of
+    them are timed, and the batch runs what the fastest width gave."""
+    n, kw = 20, {"dtype": "complex64", "max_width": 2}
+    g = exchange_layers(n)
+    group = {"n": n, "n_states": 1, "gates": g}
+    print("autotune over widths", flush=True)
+    for w in (2, 3, 4, 5):
+        b = Q.Batch([group], dtype="complex64", max_width=w, tile_qubits=12)
+        assert spanned(b.qsim_batch_group_stats(0)) == (w == 2)
+        b.close()
+    b = Q.Batch([group], autotune=True, tile_qubits=12, **kw)
+    st = b.qsim_batch_group_stats(0)
+    assert spanned(st) == (st["tuned_width"] == 2)
+    b.qsim_batch_run()
+    want, _, _ = oracle.run(n, g)
+    assert norm_error(b.qsim_batch_get_state(0, 0), want) < tol("complex64", len(g))
+    b.close()
+    # widths 2 to 5, the three tables of the timed plans, and the program a second time
+    kw["tile_qubits"] = 12
+    assert attempts(Q, group, autotune=True, **kw) - attempts(Q, group, **kw) >= 4 + 3 + 1
