@@ -9,7 +9,7 @@ The circuit is compiled (fusion + pass plan) once and its operator tables
 are resident in HBM before the timed region, like the state.
 
 Prints one JSON line: input gates/s, the achieved bandwidth of the dominant
-kernel (tiled pass) against HBM peak, and the CPU oracle's rate on a bounded
+kernel (span pass) against HBM peak, and the CPU oracle's rate on a bounded
 prefix of the same circuit.
 """
 from __future__ import annotations
@@ -28,17 +28,16 @@ HBM_PEAK_GBS = 8000.0
 # LDS: 128 bytes per clock per CU (32 banks of 4 bytes), 256 CUs at 2.4 GHz
 LDS_PEAK_GBS = 128 * 256 * 2.4
 
-# HBM bytes per launch of the tile kernel at 21 qubits, from two counter runs
-# of this benchmark (rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE; KiB per
-# dispatch).  A plain device copy dispatch of 128 MiB reads FETCH_SIZE =
-# 65,544 KiB and WRITE_SIZE = 131,073 KiB, so fetches scale by 2.0 and writes
-# by 1.0.
+# HBM bytes per launch of k_span at 21 qubits, from two counter runs of this
+# benchmark (rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE; KiB per dispatch).  A
+# plain device copy dispatch of 256 MiB reads FETCH_SIZE = 131,084 KiB and
+# WRITE_SIZE = 262,144 KiB, so fetches scale by 2.0 and writes by 1.0.
 # The figures hold for the kernel sources with the hash below (see
 # kernel_source_hash); for any other source the traffic is reported as null.
 MEASURED_TRAFFIC = {
-    "kernels_sha256_16": "ba57d9ffd67a8358",
-    "complex128": (16673.0 * 2.0 + 32783.2) * 1024,
-    "complex64": (8387.3 * 2.0 + 16388.1) * 1024,
+    "kernels_sha256_16": "9ac7384a56f951d9",
+    "complex128": (16512.4 * 2.0 + 33698.4) * 1024,
+    "complex64": (8325.2 * 2.0 + 16461.3) * 1024,
 }
 
 

@@ -686,7 +686,10 @@ static int compile_spans(int n, int dtype, const PauliProgram &P, const Lowered 
 // families of circuits (QFT, layers of rotations, Trotter steps, QAOA, random
 // rotations, Pauli exponentials) at 10 to 30 qubits in both types, single states:
 // within 10% of most times, 25% of all; taking the cheaper plan by it costs 1% of
-// the better one's time on average, 23% at worst (53 us for 44).
+// the better one's time on average, 23% at worst (53 us for 44).  184 batches of 8
+// to 512 states, 72 of them with angles per state: 1% on average, at worst 78 us for
+// 65 (exchange layers at 10 qubits complex64) and 385 for 329 (a QFT at 14 qubits
+// complex128).
 static double plan_cost(const Compiled &c, int dtype) {
     const bool single = dtype == QSIM_C64;
     double cost = 0.0;

@@ -14,13 +14,18 @@
 // per re-layout is enough.
 //
 // What bounds it: the trip of the tile through memory, then what of the
-// rotations the other workgroups of a CU do not hide.  So the work around a
-// rotation's 32 multiply-adds is kept small: an entry of 16 bytes per rotation
-// (one LDS read, two words moved to scalar registers), the tile's sign joined to
-// t beforehand, eight sign changes in place, byte offsets in 32 bits where they
-// fit, the scale multiplied once per pass.  Against records and coefficients
-// decoded per rotation, us per pass: 21 qubits complex128 19.4 -> 18.5, complex64
-// 16.7 -> 15.9, 24 qubits complex128 120 -> 114, 30 qubits complex64 3681 -> 3626.
+// rotations the other workgroups of a CU do not hide.  At 21 qubits two
+// workgroups a CU hold every tile and do the same at the same time, so that the
+// parts add up: complex128 17.5 us a pass, of which a copy whose blocks change
+// XCD takes 11.3, vector instructions 3.3 and the LDS 2.0; complex64 15.4 of 7.8,
+// 3.8 and 1.1 (counters of 11 rotations a pass).  At 30 qubits a pass is 88% of
+// the rate of a copy.  So the work around a rotation's 32 multiply-adds is kept
+// small: an entry of 16 bytes per rotation (one LDS read, two words moved to
+// scalar registers), the tile's sign joined to t beforehand, eight sign changes in
+// place, byte offsets in 32 bits where they fit, the scale multiplied once per
+// pass.  Against records and coefficients decoded per rotation, us per pass:
+// 21 qubits complex128 19.4 -> 17.5, complex64 16.7 -> 15.4, 24 qubits complex128
+// 120 -> 114, 30 qubits complex64 3681 -> 3626 to 3710 on several machines.
 // Plain loads and stores: non-temporal ones, which suit k_tile's passes, cost
 // 1540 us against 925 per pass at 27 qubits complex128 and 5174 against 3681 at
 // 30 qubits complex64 (22.1 against 19.4 at 21 qubits complex128).
