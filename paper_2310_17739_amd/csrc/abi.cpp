@@ -1477,6 +1477,8 @@ int qsim_autotune(qsim_h h, const qsim_gate *g, size_t ng, const double *mats, s
         }
         if (c.pauli) {
             if ((spans_low >> o.low_qubits) & 1) continue;
+            // (at the default width and cost, where every one gives it)
+            if (c.fixed && (o.max_width != 4 || o.op_cost != 4.0f)) continue;
             spans_low |= uint64_t(1) << o.low_qubits;
         }
         if ((rc = upload_plan(&dt, h->dtype, c.plan, h->stream))) break;
