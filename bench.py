@@ -35,7 +35,7 @@ LDS_PEAK_GBS = 128 * 256 * 2.4
 # The figures hold for the kernel sources with the hash below (see
 # kernel_source_hash); for any other source the traffic is reported as null.
 MEASURED_TRAFFIC = {
-    "kernels_sha256_16": "9ac7384a56f951d9",
+    "kernels_sha256_16": "39d06d2581eeca87",
     "complex128": (16512.4 * 2.0 + 33698.4) * 1024,
     "complex64": (8325.2 * 2.0 + 16461.3) * 1024,
 }

@@ -75,6 +75,7 @@ struct PauliOp {
     double sign = 1.0;   // (1 for an angle known here)
     int32_t slot = -1;
     bool two = false;
+    bool phases = false;   // of U1, T and CU1 gates (see Rotations)
     int entries() const { return two ? 3 : 1; }   // records of a span pass
 };
 

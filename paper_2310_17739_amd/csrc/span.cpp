@@ -58,10 +58,10 @@ bool anticommute(uint64_t ax, uint64_t az, uint64_t bx, uint64_t bz) {
 }
 // The sign of -i (-i)^|x & z|, whose other part is 1 or i.
 double kappa(uint64_t x, uint64_t z) { return (__builtin_popcountll(x & z) & 2) ? 1.0 : -1.0; }
-// Whether exp(-i phi P) is a sign: phi a multiple of pi (sin phi <= kTrivial).
-bool half_turns(double phi) {
+// Whether exp(-i phi P) is a sign: phi a multiple of pi (sin phi <= least).
+bool half_turns(double phi, double least = kTrivial) {
     const double a = std::fabs(phi);
-    return a < 3.0 ? a <= kTrivial : std::fabs(std::sin(phi)) <= kTrivial;
+    return a < 3.0 ? a <= least : std::fabs(std::sin(phi)) <= least;
 }
 // Whether a rotation does not commute with the string (x, z).
 bool clash(const PauliOp &o, uint64_t x, uint64_t z) {
@@ -72,8 +72,12 @@ bool clash(const PauliOp &o, uint64_t x, uint64_t z) {
 // string add up past others that both commute with: what undoes each other leaves
 // nothing, as products of matrices would, where one after the other they leave
 // rounding errors.  Two strings of the same X mask whose angles cancel on half of
-// the index space become one rotation of two angles.  `last` finds, by X mask (by
-// string for a diagonal), the latest rotation; `prev` the one before.
+// the index space become one rotation of two angles.  It stays one, and only another
+// about the same two strings adds to it, or a rotation that takes one of them
+// away: half of it elsewhere would leave the other half's rounding errors where
+// both are the identity.  (Phases of U1, T and CU1 add up all the same: a QFT has a
+// rotation per controlled phase in place of two.)  `last` finds, by X mask (by string for a diagonal), the
+// latest rotation; `prev` the one before.
 class Rotations {
 public:
     Rotations(PauliProgram *out, size_t most) : P(out), table(64) {
@@ -82,50 +86,88 @@ public:
     }
 
     void add(PauliOp o, int epoch) {
+        if (o.slot >= 0) return append(o, epoch);
+        if (settle(&o)) return;
         int pair = -1;
-        if (o.slot < 0) {
-            if (settle(&o)) return;
-            const int at = find(o.x, o.z, o.phi, epoch, &pair);
-            if (at >= 0) return merge(at, o.z, o.phi);
-            if (pair >= 0) {
-                PauliOp &c = P->ops[size_t(pair)];
-                c.two = true;
-                c.z2 = o.z;
-                c.phi2 = o.phi;
-                return;
+        const int at = find(o.x, o.z, o.phi, o.phases, epoch, &pair);
+        if (at >= 0) return merge(at, o.z, o.phi, o.phases);
+        if (pair < 0) {
+            if (second && spread(o, epoch)) return;
+            return append(o, epoch);
+        }
+        PauliOp &c = P->ops[size_t(pair)];
+        c.two = true;
+        c.z2 = o.z;
+        c.phi2 = o.phi;
+        c.phases = c.phases && o.phases;
+        changed = true;
+        // (the pair may now undo an earlier one)
+        const PauliOp t = c;
+        const int same = find_pair(t, prev[size_t(pair)], pair);
+        if (same < 0) return;
+        dead[size_t(pair)] = 1;
+        merge_pair(same, t);
+    }
+    // the commuting strings (x, z), (x, z2), as one
+    void add_pair(PauliOp o, int epoch) {
+        if (settle(&o)) return;
+        if (!o.two) return add(o, epoch);
+        const Entry &e = table[place(key(o.x, o.z), epoch)];
+        const int same = e.epoch == epoch ? find_pair(o, e.head, int(P->ops.size())) : -1;
+        if (same < 0) return append(o, epoch);
+        merge_pair(same, o);
+    }
+    // Takes out what has cancelled, and gives half turns their exact form.  A half
+    // turn is a string: it moves to the end of its epoch, where they are one, and
+    // turns round the angles of those it does not commute with.  Then, and where
+    // rotations have added up, others may meet that did not before.
+    void finish() {
+        bool again = changed;
+        for (size_t i = 0; i < P->ops.size() && !again; i++) again = !dead[i] && half_turn(P->ops[i]);
+        if (again) {
+            std::vector<PauliOp> ops;
+            std::vector<int> epochs;
+            for (size_t i = 0; i < P->ops.size(); i++) {
+                if (dead[i]) continue;
+                ops.push_back(P->ops[i]);
+                epochs.push_back(P->op_epoch[i]);
+            }
+            P->ops.clear();
+            P->op_epoch.clear();
+            dead.clear();
+            prev.clear();
+            table.assign(64, Entry{});
+            used_epoch = -1;
+            second = true;
+            Pauli turns;   // the half turns so far, behind the rotations of their epoch
+            for (size_t i = 0; i < ops.size(); i++) {
+                PauliOp o = ops[i];
+                if (anticommute(turns.x, turns.z, o.x, o.z)) {
+                    if (o.slot < 0) o.phi = -o.phi;
+                    else o.sign = -o.sign;
+                }
+                if (o.two && anticommute(turns.x, turns.z, o.x, o.z2)) o.phi2 = -o.phi2;
+                if (half_turn(o)) turns = mul(turns, Pauli{o.x, o.z, std::sin(o.phi) > 0.0 ? 3 : 1});   // -i or i times it
+                else if (o.two) add_pair(o, epochs[i]);
+                else add(o, epochs[i]);
+                if (i + 1 < ops.size() && epochs[i + 1] == epochs[i]) continue;
+                P->phase += turns.k * (M_PI / 2);
+                if (turns.x || turns.z) {
+                    o = PauliOp{};
+                    o.x = turns.x;
+                    o.z = turns.z;
+                    o.phi = M_PI / 2;
+                    P->phase += M_PI / 2;
+                    add(o, epochs[i]);
+                }
+                turns = Pauli{};
             }
         }
-        append(o, epoch);
-    }
-    // the commuting strings (x, z), (x, z2): as one, unless one of them adds to an
-    // earlier rotation
-    void add_pair(const PauliOp &o, int epoch) {
-        PauliOp a = o, b = o;
-        if (settle(&a)) return;
-        if (!a.two) return add(a, epoch);
-        a.two = b.two = false;
-        b.z = o.z2;
-        b.phi = o.phi2;
-        const int at = find(o.x, o.z, o.phi, epoch, nullptr);
-        const int at2 = at < 0 ? find(o.x, o.z2, o.phi2, epoch, nullptr) : -1;
-        if (at >= 0) {
-            merge(at, o.z, o.phi);
-            add(b, epoch);
-        } else if (at2 >= 0) {
-            merge(at2, o.z2, o.phi2);
-            add(a, epoch);
-        } else {
-            append(o, epoch);
-        }
-    }
-    // takes out what has cancelled; half turns in their exact form
-    void finish() {
         size_t n = 0;
         for (size_t i = 0; i < P->ops.size(); i++) {
             if (dead[i]) continue;
             PauliOp &o = P->ops[i];
-            // (a half turn is at least pi/2 - 1e-14 away from 0)
-            if (std::fabs(o.phi) > 1.5 && o.x && !o.two && o.slot < 0 && std::fabs(std::cos(o.phi)) <= kTrivial) {
+            if (o.x && half_turn(o)) {
                 o.two = true;
                 o.z2 = o.z;
                 o.phi2 = 0.0;
@@ -144,6 +186,8 @@ private:
     PauliProgram *P;
     std::vector<char> dead;
     std::vector<int> prev;
+    bool changed = false;   // a rotation has been added to another
+    bool second = false;    // the rotations are gone through again
     struct Entry {
         uint64_t key = 0;
         int head = -1, epoch = -1;
@@ -152,6 +196,10 @@ private:
     size_t used = 0;
     int used_epoch = -1;
 
+    // (a half turn is at least pi/2 - 1e-14 away from 0)
+    static bool half_turn(const PauliOp &o) {
+        return o.slot < 0 && !o.two && std::fabs(o.phi) > 1.5 && std::fabs(std::cos(o.phi)) <= (o.x ? kTrivial : 1e-15);
+    }
     static uint64_t key(uint64_t x, uint64_t z) { return x ? x : z | uint64_t(1) << 63; }
     size_t place(uint64_t k, int epoch) const {
         const size_t m = table.size() - 1;
@@ -179,32 +227,95 @@ private:
         P->ops.push_back(o);
         P->op_epoch.push_back(epoch);
     }
+    // Whether the rotations after c and before `from` commute with the string.
+    bool reaches(int c, int from, uint64_t x, uint64_t z) const {
+        for (int k = from - 1; k > c; k--)
+            if (!dead[size_t(k)] && clash(P->ops[size_t(k)], x, z)) return false;
+        return true;
+    }
     // The rotation that one by phi about (x, z) adds to, if any; else *pair: one that
     // makes a rotation of two angles with it.  The search ends at a rotation that does
     // not commute with the string, and after kFar of those that do.
-    int find(uint64_t x, uint64_t z, double phi, int epoch, int *pair) const {
+    int find(uint64_t x, uint64_t z, double phi, bool phase, int epoch, int *pair) const {
         const Entry &e = table[place(key(x, z), epoch)];
         if (e.epoch != epoch) return -1;
         int from = int(P->ops.size());
         for (int c = e.head; c >= 0 && int(P->ops.size()) - c <= kFar; c = prev[size_t(c)]) {
-            for (int k = from - 1; k > c; k--)
-                if (!dead[size_t(k)] && clash(P->ops[size_t(k)], x, z)) return -1;
+            if (!reaches(c, from, x, z)) return -1;
             from = c;
             if (dead[size_t(c)]) continue;
             const PauliOp &o = P->ops[size_t(c)];
-            if (o.slot < 0 && (o.z == z || (o.two && o.z2 == z))) return c;
+            if (o.slot < 0 && (!o.two || (phase && o.phases)) && (o.z == z || (o.two && o.z2 == z))) return c;
+            if (o.two && ((o.z == z && half_turns(o.phi + phi)) || (o.z2 == z && half_turns(o.phi2 + phi)))) return c;
             if (clash(o, x, z)) return -1;
-            if (pair && *pair < 0 && x && o.slot < 0 && !o.two) {
+            if (*pair < 0 && x && o.slot < 0 && !o.two) {
                 const double a = kappa(x, o.z) * o.phi, b = kappa(x, z) * phi;
                 if (half_turns(a + b) || half_turns(a - b)) *pair = c;
             }
         }
         return -1;
     }
-    // Whether the rotation is none (a multiple of a half turn about its string: a sign).
+    // The rotation of two angles about the strings of t before `from`, on the chain
+    // from c, that t can be moved to.
+    int find_pair(const PauliOp &t, int c, int from) const {
+        for (; c >= 0 && int(P->ops.size()) - c <= kFar; c = prev[size_t(c)]) {
+            if (!reaches(c, from, t.x, t.z) || !reaches(c, from, t.x, t.z2)) return -1;
+            from = c;
+            if (dead[size_t(c)]) continue;
+            const PauliOp &o = P->ops[size_t(c)];
+            if (o.two && ((o.z == t.z && o.z2 == t.z2) || (o.z == t.z2 && o.z2 == t.z))) return c;
+            if (clash(o, t.x, t.z) || clash(o, t.x, t.z2)) return -1;
+        }
+        return -1;
+    }
+    // Several controlled rotations of one target, written with CX, may have been added
+    // up: one string then has the angles of all others.  Takes that rotation and its
+    // partners (o is the last of them) as rotations of two angles each, at the end.
+    bool spread(const PauliOp &o, int epoch) {
+        if (!o.x || o.phases) return false;
+        const Entry &e = table[place(key(o.x, o.z), epoch)];
+        if (e.epoch != epoch) return false;
+        const int end = int(P->ops.size());
+        std::vector<PauliOp> all{o};
+        std::vector<int> at;
+        for (int c = e.head; c >= 0 && end - c <= kFar && all.size() <= kSpread; c = prev[size_t(c)]) {
+            const PauliOp &m = P->ops[size_t(c)];
+            if (dead[size_t(c)] || m.slot >= 0 || m.two || m.phases) continue;
+            bool free = reaches(c, end, m.x, m.z);
+            for (const PauliOp &a : all) free = free && !clash(m, a.x, a.z);
+            if (!free) break;
+            all.push_back(m);
+            at.push_back(c);
+        }
+        if (all.size() < 3) return false;
+        // what the others take away from the largest, in the sign of either branch
+        size_t h = 0;
+        for (size_t j = 1; j < all.size(); j++)
+            if (std::fabs(all[j].phi) > std::fabs(all[h].phi)) h = j;
+        double rest = 0.0;
+        for (size_t j = 0; j < all.size(); j++) rest += j == h ? 0.0 : kappa(all[j].x, all[j].z) * all[j].phi;
+        const PauliOp hub = all[h];
+        const double k = kappa(hub.x, hub.z), mine = k * hub.phi;
+        const double sign = half_turns(mine + rest) ? -1.0 : 1.0;
+        if (!half_turns(mine - sign * rest)) return false;
+        P->phase += M_PI * std::nearbyint((mine - sign * rest) / M_PI);
+        for (int c : at) dead[size_t(c)] = 1;
+        for (size_t j = 0; j < all.size(); j++) {
+            if (j == h) continue;
+            PauliOp t = all[j];
+            t.two = true;
+            t.z2 = hub.z;
+            t.phi2 = sign * k * kappa(t.x, t.z) * t.phi;
+            append(t, epoch);
+        }
+        return true;
+    }
+    // Whether the rotation is none (a multiple of a half turn about its string: a
+    // sign).  A diagonal leaves no amplitude out: it is none to the rounding of its
+    // angle only.
     bool settle(PauliOp *o) {
         auto none = [&](double phi) {
-            if (o->x ? !half_turns(phi) : phi != 0.0) return false;
+            if (!half_turns(phi, o->x ? kTrivial : 5e-16)) return false;
             if (std::cos(phi) < 0.0) P->phase += M_PI;
             return true;
         };
@@ -216,10 +327,23 @@ private:
         o->two = false;
         return false;
     }
-    void merge(int at, uint64_t z, double phi) {
+    void merge(int at, uint64_t z, double phi, bool phase) {
         PauliOp &c = P->ops[size_t(at)];
+        c.phases = c.phases && phase;
         (c.z == z ? c.phi : c.phi2) += phi;
-        if (settle(&c)) dead[size_t(at)] = 1;
+        settled(at);
+    }
+    void merge_pair(int at, const PauliOp &t) {
+        PauliOp &c = P->ops[size_t(at)];
+        c.phases = c.phases && t.phases;
+        c.phi += c.z == t.z ? t.phi : t.phi2;
+        c.phi2 += c.z == t.z ? t.phi2 : t.phi;
+        settled(at);
+    }
+    // after the angles of rotation `at` have changed
+    void settled(int at) {
+        changed = true;
+        if (settle(&P->ops[size_t(at)])) dead[size_t(at)] = 1;
         while (!dead.empty() && dead.back()) {
             const PauliOp &o = P->ops.back();
             table[place(key(o.x, o.z), P->op_epoch.back())].head = prev.back();
@@ -230,6 +354,7 @@ private:
         }
     }
     static constexpr int kFar = 4096;
+    static constexpr size_t kSpread = 8;   // partners of one rotation
 };
 
 // A string on up to two qubits, as gates name it.
@@ -351,8 +476,9 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
     // a rotation exp(-i phi P) about an axis seen through the frame
     Rotations rots(out, op_gate.size() / 4 + 16);
     size_t emitted = 0;
-    auto emit = [&](const Pauli &p, double phi, int slot) {
+    auto emit = [&](const Pauli &p, double phi, int slot, bool phases = false) {
         PauliOp o;
+        o.phases = phases;
         o.x = p.x;
         o.z = p.z;
         o.slot = slot;
@@ -488,14 +614,14 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
         case QSIM_G_S: f.turn(one('Z', q0), 1); f.push(kind, q0, -1, 0.0); break;
         case QSIM_G_SDG: f.turn(one('Z', q0), 3); f.push(kind, q0, -1, 0.0); break;
         case QSIM_G_SX: f.turn(one('X', q0), 1); f.push(kind, q0, -1, 0.0); break;
-        case QSIM_G_T: emit(f.image(one('Z', q0)), M_PI / 8, -1); out->phase += M_PI / 8; break;
-        case QSIM_G_TDG: emit(f.image(one('Z', q0)), -M_PI / 8, -1); out->phase -= M_PI / 8; break;
+        case QSIM_G_T: emit(f.image(one('Z', q0)), M_PI / 8, -1, true); out->phase += M_PI / 8; break;
+        case QSIM_G_TDG: emit(f.image(one('Z', q0)), -M_PI / 8, -1, true); out->phase -= M_PI / 8; break;
         case QSIM_G_RX: rotation(one('X', q0), th); break;
         case QSIM_G_RY: rotation(one('Y', q0), th); break;
         case QSIM_G_RZ: rotation(one('Z', q0), th); break;
         case QSIM_G_RXX: rotation(two('X', q0, 'X', q1), th); break;
         case QSIM_G_RZZ: rotation(two('Z', q0, 'Z', q1), th); break;
-        case QSIM_G_U1: emit(f.image(one('Z', q0)), th / 2, -1); out->phase += th / 2; break;
+        case QSIM_G_U1: emit(f.image(one('Z', q0)), th / 2, -1, true); out->phase += th / 2; break;
         case QSIM_G_U2:
         case QSIM_G_U3: {
             // e^{i (ph + la) / 2} Rz(ph) Ry(t) Rz(la)
@@ -545,9 +671,9 @@ bool pauli_lower(int n, const qsim_gate *g, const std::vector<size_t> &op_gate, 
         }
         case QSIM_G_CU1:
             // exp(i theta (1 - Z_c)(1 - Z_t) / 4)
-            emit(f.image(one('Z', q0)), th / 4, -1);
-            emit(f.image(one('Z', q1)), th / 4, -1);
-            emit(f.image(two('Z', q0, 'Z', q1)), -th / 4, -1);
+            emit(f.image(one('Z', q0)), th / 4, -1, true);
+            emit(f.image(one('Z', q1)), th / 4, -1, true);
+            emit(f.image(two('Z', q0, 'Z', q1)), -th / 4, -1, true);
             out->phase += th / 4;
             break;
         default: return false;   // CH, CU3: no product of few rotations
