@@ -76,8 +76,8 @@ bool clash(const PauliOp &o, uint64_t x, uint64_t z) {
 // about the same two strings adds to it, or a rotation that takes one of them
 // away: half of it elsewhere would leave the other half's rounding errors where
 // both are the identity.  (Phases of U1, T and CU1 add up all the same: a QFT has a
-// rotation per controlled phase in place of two.)  `last` finds, by X mask (by string for a diagonal), the
-// latest rotation; `prev` the one before.
+// rotation per controlled phase in place of two.)  `table` finds the latest rotation
+// by X mask, a diagonal by its string; `prev` the one before.
 class Rotations {
 public:
     Rotations(PauliProgram *out, size_t most) : P(out), table(64) {
